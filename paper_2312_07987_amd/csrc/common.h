@@ -65,18 +65,18 @@ struct RouterSelect {
   float* gate;
   const void* x;                // bf16 [N][dm]
   const unsigned short* Wt;     // [side][H*E][dmp] router columns as vectors
-  double* Z;                    // [side][N][H*E] fp64 logits of the rechecked entries
   int N, kstep, H, E, k, dm, dmp;
 };
 
 // One segment of a concatenated reduction with per-row gates (segment mode 3): the segment's A columns start at
 // A (rows lda apart, shared by all segments), its B matrix at B (strides sbk / sbn shared), and row n of A
 // is scaled by gtab[n * gld + gcol] before it is multiplied (gcol < 0: not scaled).
+// klen != 0 (fp32 kernel only): the segment has its own length and its own row strides lda (A) and sbn (B).
 struct SegDesc {
   const void* A;
   const void* B;
   int gcol;
-  int pad_;
+  int klen, lda, sbn;
 };
 enum { MAX_SEGD = 40 };
 
@@ -124,6 +124,11 @@ struct RowGemmArgs {
   //     having gate 0, so that heads and experts are summed in one accumulator and the output is written once.
   const float* gtab;
   int gld;
+  // ... the fp32 kernel takes the gates from the top-k tables [head][token][gk] of `gheads` heads instead and keeps the
+  // tile's dense gates in LDS (column head * experts + expert)
+  const int* gidx;
+  const float* ggate;
+  int gk, gheads;
   SegDesc segd[MAX_SEGD];
 };
 
@@ -228,12 +233,11 @@ struct RouterArgs {
   const void* x;          // [N, dm]
   const void* W[2];       // per side [dm, HE]; W[1] == NULL -> one side only
   const float* b[2];      // per side [HE] or NULL
-  double* Z;              // [sides, N, HE] fp64 logits (scratch)
   int* idx;               // [sides, H, N, k]
   float* gate;            // [sides, H, N, k]
   int* perm;              // [sides, H, N*k]
   int* offsets;           // [sides, H, E+1]
-  int* blockcnt;          // [sides*H, nblk, E] scratch
+  int* blockcnt;          // [sides*H, router_count_blocks(N), E] scratch
   int N, dm, H, E, k, sides;
   int bf16;
   // if not NULL (and for as many sides), launch_router_hybrid also sorts the tokens by expert set,
@@ -251,6 +255,7 @@ bool router_hybrid_supported(const RouterArgs& a);
 void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s);
 void launch_dense_routing(int* idx, float* gate, int* perm, int* offsets, int N, int H, hipStream_t s);
 int router_blocks(int N);  // token blocks used by the histogram/scatter kernels
+int router_count_blocks(int N);   // token blocks of the fp64 router's expert counts
 // gtab[side][n][h*E+e] = gate of the selected experts, 0 elsewhere (idx, gate: [side][H][N][k], sides side_stride_in apart)
 void launch_gate_table(const int* idx, const float* gate, float* gtab, int N, int H, int E, int k, int sides, long side_stride_in,
                        hipStream_t s);
@@ -314,7 +319,9 @@ struct RouterBwdArgs {
   const float* gate;    // same
   const float* dgate;   // [2, H, N, k]
   void* dz;             // [N][ld]: side s owns columns s*side_stride .. +HE, the rest of its stride is zeroed
-  float* db[2];         // per side [HE] or NULL, atomic add (zeroed by caller)
+  float* db[2];         // per side [HE] or NULL: stored where one block holds all tokens (and not db_add), else added
+                        // atomically (zeroed by the caller)
+  int db_add;
   float* dbpart;        // if not NULL: no atomics; block b of (side, head) sh stores its E sums at
                         // dbpart[(sh * blocks + b) * E + e] and launch_router_wgrad_split adds them up
   int N, H, E, k, sides, shared;
@@ -339,6 +346,27 @@ void launch_simt_row_gemm(const RowGemmArgs& a, int bf16, hipStream_t s);
 void launch_simt_wgrad(const WgradArgs& a, int bf16, hipStream_t s);
 void launch_simt_attn_fwd(const AttnArgs& a, int bf16, hipStream_t s);
 void launch_simt_attn_bwd(const AttnBwdArgs& a, int bf16, hipStream_t s);
+
+// fp32 storage on the fp32 matrix instructions (mfma_f32.hip): any size and alignment
+bool f32_row_gemm_supported(const RowGemmArgs& a);
+void launch_f32_row_gemm(const RowGemmArgs& a, hipStream_t s);
+// One weight gradient of a list; f32_wgrad_plan fills everything but `w` (and chooses w.chunk, and may exchange the sides).
+// The result is stored (zeros for an empty group); problems of more than one chunk need partial_floats floats at w.partial.
+struct F32Wgrad {
+  WgradArgs w;
+  int nj, nch, slots, blocks, transposed;
+  int add;   // 1: added atomically to an output the caller has zeroed (problems that share an output)
+  size_t partial_floats;
+};
+enum { F32_WG_MAX = 6 };
+struct F32WgradList {
+  int n;
+  F32Wgrad p[F32_WG_MAX];
+};
+void f32_wgrad_plan(F32Wgrad& p);
+void launch_f32_wgrad(const F32WgradList& l, hipStream_t s);
+void launch_f32_attn_fwd(const AttnArgs& a, hipStream_t s);
+void launch_f32_attn_bwd(const AttnBwdArgs& a, hipStream_t s);
 
 // MFMA family (bf16 storage only).  *_supported() say whether a launch can be served.
 bool mfma_row_gemm_supported(const RowGemmArgs& a);

@@ -8,6 +8,7 @@
 #include <initializer_list>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/switchhead.h"
@@ -74,13 +75,14 @@ struct Layout {
   size_t pQ, pK;                                                   // per-slot query / key rows (expert Q/K only)
   size_t rope;                                                     // (cos, sin) table [T][dh/2] (rotary embedding only)
   size_t xq, accq;   // fewer queries than keys only: the query tokens' rows of x; their fp32 share of dx
-  size_t Z, blockcnt, acc32;                                       // forward scratch
+  size_t blockcnt, acc32;                                       // forward scratch
   size_t setid, gset, gsort, setexp, setperm, setoff, setcnt, yh;
   size_t gtab;                                                     // dense gate table [2][N][H*E] fp32 (gated-concatenation GEMMs)
   size_t wrt;                                                      // x^T dz of both routers [dm, dh] fp32 (fused with the Q/K weight gradient)
   size_t dR, wr3;                                                  // wide router dz rows [N, H*dh], routers packed [dm, dh]                 // expert-set path (bf16 only)
   size_t rh;                                                       // two-stage router scratch (bf16 only)
-  size_t wpart;                                                    // per-chunk weight-gradient partial sums (bf16 only)
+  size_t wpart;                                                    // per-chunk weight-gradient partial sums
+  size_t wpart_floats = 0;                                         // ... their room (fp32 storage)
   size_t u, dctx, dQ, dK, dV, delta, dgate, dz;                    // backward scratch
   size_t dst;                                                      // score gradient dS^T of the attention backward (0: recomputed)
 };
@@ -171,8 +173,7 @@ Layout make_layout(const sh_shape* s) {
     L.pQ = take(H * N * k * dh * esz, true);
     L.pK = take(H * N * k * dh * esz, true);
   }
-  L.Z = take(2 * N * H * E * 8);
-  L.blockcnt = take(2 * H * (size_t)router_blocks((int)N) * E * 4);
+  L.blockcnt = take(2 * H * (size_t)router_count_blocks((int)N) * E * 4);
   L.acc32 = take(N * dm * 4);
   L.u = take(H * N * k * dh * esz);
   L.dctx = take(N * H * dh * esz);
@@ -210,6 +211,31 @@ Layout make_layout(const sh_shape* s) {
     L.wpart = take(groups * ((N + cmin - 1) / cmin) * dm * dh * 4);
     size_t o7[7];
     L.rh = take(router_hybrid_bytes((int)N, (int)dm, (int)H, (int)E, o7));
+  }
+  if (s->dtype == SH_F32) {
+    // the weight gradients of one backward call share a launch: room for all of their chunks
+    const bool rect = s->T_q > 0 && s->T_q < s->T;
+    const size_t Nq = rect ? (size_t)s->B * s->T_q : N;
+    auto room = [&](bool gathered, size_t heads, size_t experts, size_t rows_per_expert, size_t groups_rows, size_t ka, size_t kb, size_t kb_store) {
+      F32Wgrad p{};
+      p.w.heads = (int)heads;
+      p.w.E = (int)experts;
+      p.w.M = (int)groups_rows;
+      p.w.max_group_rows = (int)rows_per_expert;
+      p.w.perm = gathered ? (const int*)1 : nullptr;   // (only tested)
+      p.w.Ka = (int)ka;
+      p.w.Kb = (int)kb;
+      p.w.kb_store = (int)kb_store;
+      f32_wgrad_plan(p);
+      L.wpart_floats += p.partial_floats;
+    };
+    room(true, H, E, Nq, Nq * k, dh, dm, 0);
+    room(true, H, E, N, N * k, dm, dh, 0);
+    room(false, H, 1, Nq, Nq, dm, dh, 0);
+    room(false, H, 1, N, N, dm, dh, 0);
+    room(false, 1, 1, N, N, dm, (H * E + 7) / 8 * 8, H * E);
+    room(false, 1, 1, Nq, Nq, dm, (H * E + 7) / 8 * 8, H * E);
+    L.wpart = take(L.wpart_floats * 4);
   }
   // The score gradient of the attention backward, [B][H][keys][queries] bf16: the dK / dV kernel leaves it for the
   // dQ product instead of that kernel recomputing scores and probabilities.  Quadratic in T, so only up to 1 GiB.
@@ -292,6 +318,7 @@ sh_status check_launch(const char* what) {
 }
 
 bool use_mfma(const Ctx& c) { return c.bf16 && c.aligned && g_family.load() == 0; }
+bool use_f32(const Ctx& c) { return !c.bf16 && g_family.load() == 0; }
 
 // the matrix-core kernels move 16-byte pieces: NULL counts as aligned
 bool all_aligned16(std::initializer_list<const void*> ps) {
@@ -303,8 +330,16 @@ bool all_aligned16(std::initializer_list<const void*> ps) {
 void row_gemm(const Ctx& c, const RowGemmArgs& a) {
   if (use_mfma(c) && mfma_row_gemm_supported(a))
     launch_mfma_row_gemm(a, c.st);
+  else if (use_f32(c) && f32_row_gemm_supported(a))
+    launch_f32_row_gemm(a, c.st);
   else
     launch_simt_row_gemm(a, c.bf16, c.st);
+}
+
+// clears the outputs of a weight gradient (one launch for both operand sets)
+void fill_wgrad(const Ctx& c, const WgradArgs& a) {
+  const size_t h1 = a.hsplit > 0 ? a.hsplit : a.heads, per = (size_t)a.E * a.Ka * (a.kb_store ? a.kb_store : a.Kb);
+  launch_zero4_f32(a.dW, h1 * per, a.hsplit > 0 ? a.dW2 : nullptr, a.hsplit > 0 ? (a.heads - h1) * per : 0, nullptr, 0, nullptr, 0, c.st);
 }
 
 // Weight gradient of one step.  MFMA family: per-chunk partial sums + a reduction (deterministic,
@@ -323,13 +358,19 @@ void wgrad(const Ctx& c, WgradArgs a, bool deterministic = true, bool zero = tru
       return;
     }
   }
-  // atomic paths add into zeroed outputs
-  const int h1 = a.hsplit > 0 ? a.hsplit : a.heads;
-  const size_t kb = a.kb_store ? a.kb_store : a.Kb;
-  if (zero) {
-    launch_fill_f32(a.dW, (size_t)h1 * a.E * a.Ka * kb, 0.f, c.st);
-    if (a.hsplit > 0) launch_fill_f32(a.dW2, (size_t)(a.heads - a.hsplit) * a.E * a.Ka * kb, 0.f, c.st);
+  if (use_f32(c)) {
+    F32WgradList l{};
+    l.n = 1;
+    l.p[0].w = a;
+    f32_wgrad_plan(l.p[0]);
+    // (sums of several calls, and shapes whose chunks exceed the scratch, are added atomically)
+    l.p[0].add = !zero || l.p[0].partial_floats > c.L.wpart_floats;
+    l.p[0].w.partial = c.p<float>(c.L.wpart);
+    if (l.p[0].add && zero) fill_wgrad(c, a);
+    return launch_f32_wgrad(l, c.st);
   }
+  // atomic paths add into zeroed outputs
+  if (zero) fill_wgrad(c, a);
   if (use_mfma(c) && mfma_wgrad_supported(a)) {
     launch_mfma_wgrad(a, c.st);
     return;
@@ -402,6 +443,10 @@ bool sets_usable(const Ctx& c) { return use_mfma(c) && set_tables(c); }
 // taken where that factor is at most 2 (and the shape fills the 256 x 256 tiles); else the expert-set path.
 bool gated_concat(const Ctx& c) { return use_mfma(c) && gated_shape(c.s); }
 
+// The same in fp32 (any token count): `segs` segments.  Its tile builds the dense gates from the top-k tables in LDS.  Against
+// expert-sorted rows added with fp32 atomics into a zeroed output it multiplies E / k times as much; see f32_concat's callers.
+bool f32_gated(const Ctx& c, int segs) { return use_f32(c) && segs <= MAX_SEGD && c.E <= 2 * c.k; }
+
 RowGemmArgs identity_rows(const Ctx& c, int heads, int side = 0) {
   RowGemmArgs a{};
   a.heads = heads;
@@ -409,6 +454,25 @@ RowGemmArgs identity_rows(const Ctx& c, int heads, int side = 0) {
   a.M = c.n(side);
   a.a_div = 1;
   a.c_div = 1;
+  return a;
+}
+
+RowGemmArgs f32_concat(const Ctx& c, int side, void* out) {
+  RowGemmArgs a = identity_rows(c, 1, side);
+  a.seg_mode = 3;
+  a.lda = (long)c.H * c.dh;
+  a.C = out;
+  a.ldc = c.dm;
+  a.K = c.dh;
+  a.Nc = c.dm;
+  a.mode = STORE_F32;
+  a.experts = c.E;
+  a.gheads = c.H;
+  a.gk = c.k;
+  if (!c.dense) {
+    a.gidx = c.idx(side);
+    a.ggate = c.gate(side);
+  }
   return a;
 }
 
@@ -565,12 +629,11 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
       ra.x = side ? xq : x;
       ra.W[0] = own ? W_D : W_S;
       ra.b[0] = own ? b_D : b_S;
-      ra.Z = c.p<double>(c.L.Z) + (size_t)side * N * H * E;
       ra.idx = c.idx(side);
       ra.gate = c.gate(side);
       ra.perm = c.perm(side);
       ra.offsets = c.offsets(side);
-      ra.blockcnt = c.p<int>(c.L.blockcnt) + (size_t)side * H * nblk * E;
+      ra.blockcnt = c.p<int>(c.L.blockcnt) + (size_t)side * H * router_count_blocks(N) * E;
       ra.N = n;
       ra.dm = dm;
       ra.H = H;
@@ -596,7 +659,6 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     ra.W[1] = W_D;
     ra.b[0] = b_S;
     ra.b[1] = b_D;
-    ra.Z = c.p<double>(c.L.Z);
     ra.idx = c.idx(0);
     ra.gate = c.gate(0);
     ra.perm = c.perm(0);
@@ -711,9 +773,9 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     a.K = dm;
     a.Nc = dh;
     a.mode = STORE_T;
-    if (!c.rect && use_mfma(c) && mfma_row_gemm_supported(a)) {
+    if (!c.rect && ((use_mfma(c) && mfma_row_gemm_supported(a)) || use_f32(c))) {
       prof_mark(c.st, "fwd.qk_proj");
-      launch_mfma_row_gemm(a, c.st);
+      row_gemm(c, a);
     } else {
       a.heads = H;
       a.hsplit = 0;
@@ -789,6 +851,8 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     a.Tq = c.Tq;
     if (use_mfma(c) && mfma_attn_supported(shape->T, dh))
       launch_mfma_attn_fwd(a, c.st);
+    else if (use_f32(c))
+      launch_f32_attn_fwd(a, c.st);
     else
       launch_simt_attn_fwd(a, c.bf16, c.st);
   }
@@ -821,6 +885,17 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
       launch_pp_row_gemm(a, c.st);
       y_done = true;
     }
+  }
+  if (f32_gated(c, H * E)) {
+    prof_mark(c.st, "fwd.o_experts");
+    RowGemmArgs a = f32_concat(c, 1, y);
+    a.sbk = dm;
+    a.sbn = 1;
+    a.nseg = H * E;
+    for (int s_ = 0; s_ < H * E; ++s_)
+      a.segd[s_] = {c.p<float>(c.L.ctx) + (size_t)(s_ / E) * dh, (const float*)W_O + (size_t)s_ * dh * dm, c.dense ? -1 : s_, 0, 0, 0};
+    launch_f32_row_gemm(a, c.st);
+    y_done = true;
   }
   // Expert-set path: per head one GEMM whose reduction runs over the
   // k gate-scaled copies of the token's read-out row, then the sum over heads.
@@ -875,7 +950,7 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     a.Nc = dm;
     a.mode = ATOMIC_F32;
     row_gemm(c, a);
-    prof_mark(c.st, "fwd.y_cast");
+    if (c.bf16) prof_mark(c.st, "fwd.y_cast");
     if (c.bf16) launch_cast_from_f32(acc, y, (size_t)c.Nq * dm, 1, c.st);
   }
   prof_mark(c.st, nullptr);
@@ -969,8 +1044,10 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     sa.dh = dh;
     launch_slot_combine(sa, c.bf16, c.st);
   }
-  {
-    prof_mark(c.st, "bwd.o_wgrad");
+  const int HE_ = H * E, HEp_ = (HE_ + 7) / 8 * 8;
+  // fp32: everything behind the attention backward in four launches (see the tail below)
+  const bool f32_tail = !c.qk_experts && f32_gated(c, HE_ + 2 * H + 2);
+  auto o_wgrad_args = [&] {
     WgradArgs w{};
     w.tag = TAG_O_WGRAD;
     w.perm = c.perm(1);
@@ -996,7 +1073,11 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     w.gate = c.gate(1);
     w.gate_hstride = (long)Nq * k;
     w.chunk = chunk;
-    wgrad(c, w);
+    return w;
+  };
+  if (!f32_tail) {
+    prof_mark(c.st, "bwd.o_wgrad");
+    wgrad(c, o_wgrad_args());
   }
 
   // attention
@@ -1023,7 +1104,10 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       launch_mfma_attn_bwd(a, c.st);   // marks its two kernels itself
     else {
       prof_mark(c.st, "bwd.attention");
-      launch_simt_attn_bwd(a, c.bf16, c.st);
+      if (use_f32(c))
+        launch_f32_attn_bwd(a, c.st);
+      else
+        launch_simt_attn_bwd(a, c.bf16, c.st);
     }
   }
 
@@ -1036,6 +1120,179 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     } else {
       launch_rope_apply(c.p<void>(c.L.dQ), c.p<void>(c.L.dK), c.p<float2>(c.L.rope), N, shape->T, 0, H, dh, 1, c.bf16, c.st);
     }
+  }
+
+  // gates' gradient of a projection P[n,h] = sum_j g[n,h,j] x[n] W[h,e_j] from the per-slot rows the forward pass kept, given dP
+  auto slot_dots = [&](int side, size_t dP, size_t slots, bool add) {
+    SlotArgs sa{};
+    sa.slots = c.p<void>(slots);
+    sa.gate = c.gate(side);
+    sa.other = c.p<void>(dP);
+    sa.dots = c.p<float>(c.L.dgate) + (size_t)side * H * N * k;
+    sa.dots_add = add;
+    sa.N = c.n(side);
+    sa.H = H;
+    sa.k = k;
+    sa.dh = dh;
+    launch_slot_combine(sa, c.bf16, c.st);
+  };
+  // the weight gradient of such a projection
+  auto proj_wgrad_args = [&](int side, size_t dP, float* dW) {
+    WgradArgs w{};
+    w.tag = TAG_V_WGRAD;
+    w.scale_b = 1;   // gate on the d_head-wide dP rows instead of the d_model-wide x rows
+    w.perm = c.perm(side);
+    w.offsets = c.offsets(side);
+    w.heads = H;
+    w.E = E;
+    w.M = c.n(side) * k;
+    w.max_group_rows = c.n(side);
+    w.a_div = k;
+    w.b_div = k;
+    w.A = side ? xq : x;
+    w.lda = dm;
+    w.a_hoff = 0;
+    w.Ka = dm;
+    w.Bm = c.p<void>(dP);
+    w.ldb = hd;
+    w.b_hoff = dh;
+    w.Kb = dh;
+    w.dW = dW;
+    w.w_hstride = (long)E * dm * dh;
+    w.w_estride = (long)dm * dh;
+    w.swa = dh;
+    w.gate = c.gate(side);
+    w.gate_hstride = (long)c.n(side) * k;
+    w.chunk = chunk;
+    return w;
+  };
+  // x^T dQ / x^T dK of one side's tokens (rows of the operands: that side's tokens)
+  auto dense_wgrad_args = [&](int side, size_t dP, float* dW) {
+    WgradArgs w{};
+    w.tag = TAG_QK_WGRAD;
+    w.heads = H;
+    w.E = 1;
+    w.M = c.n(side);
+    w.a_div = 1;
+    w.b_div = 1;
+    w.A = side ? xq : x;
+    w.lda = dm;
+    w.Ka = dm;
+    w.Bm = c.p<void>(dP);
+    w.ldb = hd;
+    w.b_hoff = dh;
+    w.Kb = dh;
+    w.dW = dW;
+    w.w_hstride = (long)dm * dh;
+    w.swa = dh;
+    w.chunk = chunk_dense;
+    return w;
+  };
+
+  if (f32_tail) {
+    // dz of the routers, then every weight gradient in one launch and dx as one GEMM over the H*E value experts (scaled by the
+    // token's gates), the 2H query / key matrices and the routers: no atomics, no zero fill and no accumulator passes over dx.
+    // (fewer queries than keys: the destination side's share, per query token, is a second GEMM added to its rows at the end)
+    if (!c.dense) {
+      prof_mark(c.st, "bwd.dgate_s");
+      slot_dots(0, c.L.dV, c.L.pV, false);
+    }
+    F32WgradList wl{};
+    auto add_wgrad = [&](const WgradArgs& w) {
+      F32Wgrad& p = wl.p[wl.n++];
+      p.w = w;
+      f32_wgrad_plan(p);
+    };
+    add_wgrad(o_wgrad_args());
+    add_wgrad(proj_wgrad_args(0, c.L.dV, dW_V));
+    add_wgrad(dense_wgrad_args(1, c.L.dQ, dW_Q));
+    add_wgrad(dense_wgrad_args(0, c.L.dK, dW_K));
+    // logit gradients: [tokens][sides][HEp], or one block per side where the sides have tokens of their own
+    const int sides = c.dense ? 0 : (c.rect || !c.shared) ? 2 : 1;
+    const int own = c.shared ? 1 : 2;   // routers with weights of their own
+    const long dz_ld = c.rect ? HEp_ : (long)sides * HEp_;
+    auto dz_of = [&](int side) { return c.p<float>(c.L.dz) + (c.rect ? (size_t)side * N * HEp_ : (size_t)side * HEp_); };
+    for (int sd = 0; sd < sides; ++sd) {
+      float* dW = sd < own && sd == 1 ? dW_D : dW_S;
+      if (!dW) continue;
+      WgradArgs w{};
+      w.heads = 1;
+      w.E = 1;
+      w.M = c.n(sd);
+      w.a_div = 1;
+      w.b_div = 1;
+      w.A = sd ? xq : x;
+      w.lda = dm;
+      w.Ka = dm;
+      w.Bm = dz_of(sd);
+      w.ldb = dz_ld;
+      w.Kb = HEp_;   // the padded columns are zero
+      w.kb_store = HE_;
+      w.swa = HE_;
+      w.dW = dW;
+      add_wgrad(w);
+      if (sides > own) wl.p[wl.n - 1].add = 1;   // both sides' tokens add into the shared router's gradient
+    }
+    float* part = c.p<float>(c.L.wpart);
+    for (int i = 0; i < wl.n; ++i) {
+      wl.p[i].w.partial = part;
+      if (!wl.p[i].add) part += wl.p[i].partial_floats;
+    }
+    // what is added to atomically: the bias gradients over more than one block of tokens, a router both sides' tokens share
+    const bool add_w = sides > own && dW_S;
+    if (!c.dense && (N > 256 || sides > own))
+      launch_zero4_f32(db_S, db_S ? (size_t)HE_ : 0, own == 2 ? db_D : nullptr, own == 2 && db_D ? (size_t)HE_ : 0,
+                       add_w ? dW_S : nullptr, add_w ? (size_t)dm * HE_ : 0, nullptr, 0, c.st);
+    if (!c.dense) {
+      prof_mark(c.st, "bwd.router");
+      for (int sd = 0; sd < (c.rect ? 2 : 1); ++sd) {
+        const bool second = sd == 1 && !c.shared;
+        RouterBwdArgs rb{};
+        rb.idx = c.idx(sd);
+        rb.gate = c.gate(sd);
+        rb.dgate = c.p<float>(c.L.dgate) + (size_t)sd * H * N * k;
+        rb.dz = dz_of(sd);
+        rb.db[0] = second ? db_D : db_S;
+        rb.db[1] = c.rect || c.shared ? nullptr : db_D;
+        rb.db_add = c.rect && c.shared;
+        rb.N = c.n(sd);
+        rb.H = H;
+        rb.E = E;
+        rb.k = k;
+        rb.sides = c.rect ? 1 : sides;
+        rb.shared = c.shared && !c.rect;
+        rb.ld = (int)dz_ld;
+        rb.side_stride = HEp_;
+        launch_router_bwd(rb, 0, c.st);
+      }
+    }
+    prof_mark(c.st, "bwd.wgrads");
+    launch_f32_wgrad(wl, c.st);
+    for (int side = c.rect ? 1 : 0; side >= 0; --side) {
+      // side 1 first (fewer queries than keys only): queries and destination router; side 0: values, keys, source router
+      prof_mark(c.st, side ? "bwd.q_dgrad" : "bwd.dx_gemm");
+      RowGemmArgs a = f32_concat(c, side, side ? (void*)c.p<float>(c.L.accq) : dx);
+      a.sbk = 1;
+      a.sbn = dh;
+      int n = 0;
+      auto seg = [&](const float* A, const void* B, size_t boff, int gcol) { a.segd[n++] = {A, (const float*)B + boff, gcol, 0, 0, 0}; };
+      if (side == 0) {
+        for (int s_ = 0; s_ < HE_; ++s_) seg(c.p<float>(c.L.dV) + (size_t)(s_ / E) * dh, W_V, (size_t)s_ * dm * dh, c.dense ? -1 : s_);
+        for (int h_ = 0; h_ < H; ++h_) seg(c.p<float>(c.L.dK) + (size_t)h_ * dh, W_K, (size_t)h_ * dm * dh, -1);
+      }
+      if (side == 1 || !c.rect)
+        for (int h_ = 0; h_ < H; ++h_) seg(c.p<float>(c.L.dQ) + (size_t)h_ * dh, W_Q, (size_t)h_ * dm * dh, -1);
+      for (int sd = 0; sd < sides; ++sd)
+        if (!c.rect || sd == side) a.segd[n++] = {dz_of(sd), sd == 1 && !c.shared ? W_D : W_S, -1, HE_, (int)dz_ld, HE_};
+      a.nseg = n;
+      launch_f32_row_gemm(a, c.st);
+    }
+    if (c.rect) {
+      prof_mark(c.st, "bwd.dx_query_rows");
+      launch_add_query_rows(dx, c.p<float>(c.L.accq), Nq, shape->T, c.Tq, dm, 0, c.st);
+    }
+    prof_mark(c.st, nullptr);
+    return check_launch("switchhead_backward");
   }
 
   // dense queries and keys: weight gradients, then dx = dQ W_Q^T + dK W_K^T.  With the MFMA
@@ -1080,17 +1337,9 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     if (!c.rect) {
       wgrad(c, w);
     } else {   // queries and keys come from different token sets: one launch each
-      w.heads = H;
-      w.hsplit = 0;
-      w.A = xq;
-      w.M = Nq;
-      wgrad(c, w);
+      wgrad(c, dense_wgrad_args(1, c.L.dQ, dW_Q));
       prof_mark(c.st, "bwd.qk_wgrad");
-      w.A = x;
-      w.M = N;
-      w.Bm = c.p<void>(c.L.dK);
-      w.dW = dW_K;
-      wgrad(c, w);
+      wgrad(c, dense_wgrad_args(0, c.L.dK, dW_K));
     }
   };
   // the query tokens' own share of dx (fewer queries than keys): fp32, added to their rows at the end
@@ -1274,53 +1523,16 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     run_qk_dgrad(false);
   }
 
-  // A projection P[n,h] = sum_j g[n,h,j] x[n] W[h,e_j] (values; queries and keys in the all-expert
-  // form) given dP: the gates' gradient <x W[h,e_j], dP> from the per-slot rows the forward pass
-  // kept, dW[h,e] = sum_n g x[n]^T dP[n,h], and the projection's share of dx.
+  // A projection P[n,h] = sum_j g[n,h,j] x[n] W[h,e_j] (values; queries and keys in the all-expert form) given dP: the
+  // gates' gradient, dW[h,e] = sum_n g x[n]^T dP[n,h], and the projection's share of dx.
   int yh_used = 0;   // bf16 partials of dx written so far (expert-set path)
   const bool sets_path = sets;
   auto expert_proj_bwd = [&](int side, const void* W, size_t dP, size_t slots, float* dW, bool dots_add,
                              const char* l_gate, const char* l_wgrad, const char* l_dgrad) {
     prof_mark(c.st, l_gate);
-    SlotArgs sa{};
-    sa.slots = c.p<void>(slots);
-    sa.gate = c.gate(side);
-    sa.other = c.p<void>(dP);
-    sa.dots = c.p<float>(c.L.dgate) + (size_t)side * H * N * k;
-    sa.dots_add = dots_add;
-    sa.N = c.n(side);
-    sa.H = H;
-    sa.k = k;
-    sa.dh = dh;
-    launch_slot_combine(sa, c.bf16, c.st);
+    slot_dots(side, dP, slots, dots_add);
     prof_mark(c.st, l_wgrad);
-    WgradArgs w{};
-    w.tag = TAG_V_WGRAD;
-    w.scale_b = 1;   // gate on the d_head-wide dP rows instead of the d_model-wide x rows
-    w.perm = c.perm(side);
-    w.offsets = c.offsets(side);
-    w.heads = H;
-    w.E = E;
-    w.M = c.n(side) * k;
-    w.max_group_rows = c.n(side);
-    w.a_div = k;
-    w.b_div = k;
-    w.A = side ? xq : x;
-    w.lda = dm;
-    w.a_hoff = 0;
-    w.Ka = dm;
-    w.Bm = c.p<void>(dP);
-    w.ldb = hd;
-    w.b_hoff = dh;
-    w.Kb = dh;
-    w.dW = dW;
-    w.w_hstride = (long)E * dm * dh;
-    w.w_estride = (long)dm * dh;
-    w.swa = dh;
-    w.gate = c.gate(side);
-    w.gate_hstride = (long)c.n(side) * k;
-    w.chunk = chunk;
-    wgrad(c, w);
+    wgrad(c, proj_wgrad_args(side, dP, dW));
     if (merged_dx) return;   // this projection's share of dx is part of the one GEMM that writes dx
     prof_mark(c.st, l_dgrad);
     const bool to_accq = c.rect && side == 1;   // rows of the query tokens: their own fp32 accumulator
@@ -1393,6 +1605,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       rb.k = k;
       rb.sides = 1;
       rb.shared = 0;
+      rb.db_add = c.shared;
       rb.ld = HEp;
       rb.side_stride = HEp;
       rb.pad_to = 0;

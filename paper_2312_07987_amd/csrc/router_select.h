@@ -18,7 +18,7 @@ namespace sh {
 // (every exact tie is), lane 0 evaluates the canonical sum itself and selects from that, so the indices
 // are those of the canonical logits in every case.
 __device__ __forceinline__ void recheck_entry(const unsigned short* __restrict__ xrow, const unsigned short* __restrict__ wt0,
-                                              const float* __restrict__ bh, double* __restrict__ zs, double* __restrict__ zout,
+                                              const float* __restrict__ bh, double* __restrict__ zs,
                                               int* __restrict__ idx_out, float* __restrict__ gate_out, int dm, int dmp, int E,
                                               int k, int lane, double reorder) {
   // eight experts at a time: the token's features are loaded once per slab and the eight columns'
@@ -74,7 +74,6 @@ __device__ __forceinline__ void recheck_entry(const unsigned short* __restrict__
         zs[e] = acc + (bh ? (double)bh[e] : 0.0);
       }
     }
-    for (int e = 0; e < E; ++e) zout[e] = zs[e];
     unsigned long long sel = 0ull;
     for (int j = 0; j < k; ++j) {
       int best = -1;
@@ -158,7 +157,7 @@ __device__ __forceinline__ void router_select_tile(const RouterSelect& r, int si
       // twice d_model * 2^-53 * |x| * max|w|, doubled again for the rounding of the norms themselves
       const double reorder = 4.0 * (double)r.dm * 1.1102230246251565e-16 * (double)sqrtf(rs[fl]) * (double)sqrtf(w2);
       recheck_entry((const unsigned short*)r.x + (long)n * r.dm, r.Wt + ((long)side * HE + h * E) * r.dmp, b ? b + h * E : nullptr,
-                    zs[wave], r.Z + ((long)side * N + n) * HE + (long)h * E, r.idx + o, r.gate + o, r.dm, r.dmp, E, k, lane, reorder);
+                    zs[wave], r.idx + o, r.gate + o, r.dm, r.dmp, E, k, lane, reorder);
     }
     __syncthreads();
     if (threadIdx.x == 0) *nflag = 0;

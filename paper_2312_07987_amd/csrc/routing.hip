@@ -2,102 +2,113 @@
 // and the expert-sorted permutation of the token->expert assignments (the "sorting and
 // top-k steps" of Sec. 3.6 "Shared Selection").
 //
-//   router_logits  z = x W (+ b) in fp64, summed over i = 0..d_model-1 in that order with
-//                  one accumulator per logit, so the selection is a fixed function of the
-//                  stored inputs (products of bf16/fp32 inputs are exact in fp64)
-//   topk_hist      per (side, head, token): k passes of "largest remaining logit, lowest
-//                  index on ties"; gate = sigmoid(logit); per-block expert histogram from
-//                  wave ballots
-//   scan           exclusive scan over (expert major, token block minor)
-//   scatter        stable placement: rank inside the block from ballots + popcounts, so
-//                  no atomics decide an order and the result is deterministic
+//   select    z = x W (+ b) in fp64, summed over i = 0..d_model-1 in that order with one
+//             accumulator per logit, so the selection is a fixed function of the stored inputs
+//             (products of bf16/fp32 inputs are exact in fp64); per (side, head, token) k passes of
+//             "largest remaining logit, lowest index on ties"; gate = sigmoid(logit); expert counts
+//             of the work-group's tokens
+//   scan      exclusive scan over (expert major, token block minor), done by every scatter block for
+//             itself where the table of counts is small
+//   scatter   stable placement: rank inside the block from ballots + popcounts, so
+//             no atomics decide an order and the result is deterministic
 #include "common.h"
 
 namespace sh {
 
-static constexpr int RT_TOK = 64;    // tokens per block of the logits kernel
-static constexpr int RT_COL = 64;    // logit columns per block
-static constexpr int RT_KC = 32;     // d_model chunk staged in LDS
-static constexpr int RB = 256;       // tokens per block of topk/scatter kernels
+static constexpr int RT_TOK = 32;    // tokens per block of the fp64 router
+static constexpr int RT_KC = 64;     // d_model chunk staged in LDS
+static constexpr int RB = 256;       // tokens per block of the scatter kernels
 
 int router_blocks(int N) { return (N + RB - 1) / RB; }
+int router_count_blocks(int N) { return (N + RT_TOK - 1) / RT_TOK; }
 
-template <typename T>
-__global__ __launch_bounds__(256) void router_logits_kernel(const T* __restrict__ x, const T* __restrict__ W0,
+// Logits, selection and expert counts in one launch.  A work-group takes 32 tokens of one side (and as many whole heads as
+// 64 logit columns hold): 8 threads per token, each with every eighth column, so a thread runs CPT fp64 chains over the
+// features.  x and W go through LDS as fp32 in slabs of RT_KC features, the next slab waits in registers.  Bound by the
+// latency of the slab loads and by the fp64 chains (one accumulator per logit, so a logit is d_model dependent FMAs); the
+// earlier form (64 tokens, 16 columns per thread, 32 features per barrier pair, selection and histogram in a second launch,
+// tables scanned in a third) took 156 us for 4096 tokens of d_model 412 with 2 x 10 columns, most of its threads on padding.
+template <typename T, int CPT>
+__global__ __launch_bounds__(256) void router_select_kernel(const T* __restrict__ x, const T* __restrict__ W0,
                                                             const T* __restrict__ W1, const float* __restrict__ b0,
-                                                            const float* __restrict__ b1, double* __restrict__ Z,
-                                                            int N, int dm, int HE) {
-  __shared__ double xs[RT_TOK][RT_KC + 1];
-  __shared__ double ws[RT_KC][RT_COL];
-  const int side = blockIdx.y;
+                                                            const float* __restrict__ b1, int* __restrict__ idx,
+                                                            float* __restrict__ gate, int* __restrict__ cnt, int N, int dm,
+                                                            int H, int E, int k, int hpb, int ncb) {
+  constexpr int NC = 8 * CPT;   // columns held in LDS
+  constexpr int LX = RT_KC + 1;
+  __shared__ float xs[RT_TOK * LX];
+  __shared__ float ws[RT_KC * NC];
+  __shared__ double z[RT_TOK][NC + 1];
+  __shared__ int cn[NC];
+  const int side = blockIdx.y, HE = H * E;
+  const int h0 = blockIdx.z * hpb, nh = min(hpb, H - h0), ncols = nh * E, col0 = h0 * E;
   const T* W = side ? W1 : W0;
   const float* b = side ? b1 : b0;
   const int tok0 = blockIdx.x * RT_TOK;
-  const int col0 = blockIdx.z * RT_COL;
-  const int tid = threadIdx.x;
-  const int tok = tid % RT_TOK;
-  const int cg = tid / RT_TOK;  // 0..3 -> 16 columns each
-
-  double acc[16];
+  const int tid = threadIdx.x, tok = tid & (RT_TOK - 1), cg = tid / RT_TOK;
+  constexpr int XN = RT_TOK * RT_KC / 256, WN = (RT_KC * NC + 255) / 256;
+  T rx[XN], rw[WN];
+  // (an index past the end loads element 0 and is replaced by zero in put(): no branch around a load)
+  auto fetch = [&](int k0) {
 #pragma unroll
-  for (int c = 0; c < 16; ++c) acc[c] = 0.0;
-
+    for (int i = 0; i < XN; ++i) {
+      const int t = tid + i * 256, n = tok0 + t / RT_KC, kk = k0 + t % RT_KC;
+      rx[i] = x[n < N && kk < dm ? (long)n * dm + kk : 0];
+    }
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+      const int t = tid + i * 256, kk = k0 + t / NC, c = t % NC;
+      rw[i] = W[kk < dm && c < ncols ? (long)kk * HE + col0 + c : 0];
+    }
+  };
+  auto put = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < XN; ++i) {
+      const int t = tid + i * 256, n = tok0 + t / RT_KC, kk = k0 + t % RT_KC;
+      xs[(t / RT_KC) * LX + t % RT_KC] = n < N && kk < dm ? ld(&rx[i], 0) : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+      const int t = tid + i * 256, kk = k0 + t / NC, c = t % NC;
+      if (t < RT_KC * NC) ws[t] = kk < dm && c < ncols ? ld(&rw[i], 0) : 0.f;
+    }
+  };
+  double acc[CPT];
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) acc[c] = 0.0;
+  fetch(0);
   for (int k0 = 0; k0 < dm; k0 += RT_KC) {
-    for (int t = tid; t < RT_TOK * RT_KC; t += 256) {
-      int r = t / RT_KC, i = t % RT_KC;
-      int n = tok0 + r, kk = k0 + i;
-      xs[r][i] = (n < N && kk < dm) ? (double)ld(x, (long)n * dm + kk) : 0.0;
-    }
-    for (int t = tid; t < RT_KC * RT_COL; t += 256) {
-      int i = t / RT_COL, c = t % RT_COL;
-      int kk = k0 + i, col = col0 + c;
-      ws[i][c] = (kk < dm && col < HE) ? (double)ld(W, (long)kk * HE + col) : 0.0;
-    }
+    put(k0);
     __syncthreads();
-    // strictly ascending i; the zero padding beyond d_model adds exact zeros
-#pragma unroll 4
+    if (k0 + RT_KC < dm) fetch(k0 + RT_KC);
+    // strictly ascending feature index; the zero padding beyond d_model adds exact zeros
+#pragma unroll 8
     for (int i = 0; i < RT_KC; ++i) {
-      double xv = xs[tok][i];
+      const double xv = (double)xs[tok * LX + i];
 #pragma unroll
-      for (int c = 0; c < 16; ++c) acc[c] = fma(xv, ws[i][cg * 16 + c], acc[c]);
+      for (int c = 0; c < CPT; ++c) acc[c] = fma(xv, (double)ws[i * NC + cg + 8 * c], acc[c]);
     }
     __syncthreads();
   }
-  int n = tok0 + tok;
-  if (n < N) {
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      int col = col0 + cg * 16 + c;
-      if (col < HE) {
-        double z = acc[c];
-        if (b) z += (double)b[col];
-        Z[((long)side * N + n) * HE + col] = z;
-      }
-    }
+  for (int c = 0; c < CPT; ++c) {
+    const int col = cg + 8 * c;
+    if (col < ncols) z[tok][col] = acc[c] + (b ? (double)b[col0 + col] : 0.0);
   }
-}
-
-__global__ __launch_bounds__(RB) void topk_hist_kernel(const double* __restrict__ Z, int* __restrict__ idx,
-                                                       float* __restrict__ gate, int* __restrict__ blockcnt, int N,
-                                                       int H, int E, int k, int nblk) {
-  __shared__ int cnt[64];
-  const int sh_ = blockIdx.y;  // side*H + h
-  const int side = sh_ / H, h = sh_ % H;
-  const int n = blockIdx.x * RB + threadIdx.x;
-  const bool valid = n < N;
-  if (threadIdx.x < 64) cnt[threadIdx.x] = 0;
+  if (tid < NC) cn[tid] = 0;
   __syncthreads();
-
-  unsigned long long sel = 0ull;
-  if (valid) {
-    const double* z = Z + ((long)side * N + n) * (long)(H * E) + (long)h * E;
-    long o = ((long)sh_ * N + n) * k;
+  for (int item = tid; item < RT_TOK * nh; item += 256) {
+    const int t = item % RT_TOK, h = item / RT_TOK, n = tok0 + t;
+    if (n >= N) continue;
+    const double* zt = &z[t][h * E];
+    unsigned long long sel = 0ull;
+    const long o = ((long)(side * H + h0 + h) * N + n) * k;
     for (int j = 0; j < k; ++j) {
       int best = -1;
       double bv = 0.0;
       for (int e = 0; e < E; ++e) {
         if ((sel >> e) & 1ull) continue;
-        double v = z[e];
+        const double v = zt[e];
         if (best < 0 || v > bv) {  // strict: the lower index keeps a tie
           best = e;
           bv = v;
@@ -106,15 +117,11 @@ __global__ __launch_bounds__(RB) void topk_hist_kernel(const double* __restrict_
       sel |= 1ull << best;
       idx[o + j] = best;
       gate[o + j] = (float)(1.0 / (1.0 + exp(-bv)));
+      atomicAdd(&cn[h * E + best], 1);
     }
   }
-  const int lane = threadIdx.x & 63;
-  for (int e = 0; e < E; ++e) {
-    unsigned long long bal = __ballot(valid && ((sel >> e) & 1ull));
-    if (lane == 0 && bal) atomicAdd(&cnt[e], __popcll(bal));
-  }
   __syncthreads();
-  if (threadIdx.x < E) blockcnt[((long)sh_ * nblk + blockIdx.x) * E + threadIdx.x] = cnt[threadIdx.x];
+  for (int c = tid; c < ncols; c += 256) cnt[((long)(side * H + h0 + c / E) * ncb + blockIdx.x) * E + c % E] = cn[c];
 }
 
 // One block per (side, head).  blockcnt[sh][blk][e] (counts) -> in place: first position of
@@ -177,8 +184,9 @@ __global__ __launch_bounds__(256) void scan2_kernel(int* __restrict__ blockcnt, 
 // cnt[sh][blk][bin] (for tables small enough that every block can read them whole): sbase[bin] = first
 // position of bin `bin` for token block blockIdx.x; token block 0 also writes offsets[sh][0..nbins].
 // One wave per bin, lanes over token blocks.  Called by all RB threads; ends with a barrier.
+// `per`: count blocks per scatter block (a count block holds RB / per tokens).
 __device__ __forceinline__ void block_bases(const int* __restrict__ cnt, int* __restrict__ offsets, int nbins, int nblk,
-                                            int* __restrict__ sbase /* LDS [2 * 128 + 1] */) {
+                                            int* __restrict__ sbase /* LDS [2 * 128 + 1] */, int per = 1) {
   const int sh_ = blockIdx.y, blk = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int* c = cnt + (long)sh_ * nblk * nbins;
@@ -188,7 +196,7 @@ __device__ __forceinline__ void block_bases(const int* __restrict__ cnt, int* __
     for (int b = lane; b < nblk; b += 64) {
       const int v = c[(long)b * nbins + e];
       all += v;
-      pre += b < blk ? v : 0;
+      pre += b < blk * per ? v : 0;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -220,7 +228,7 @@ __device__ __forceinline__ void block_bases(const int* __restrict__ cnt, int* __
 template <bool LOCAL = false>
 __device__ __forceinline__ void scatter_body(const int* __restrict__ idx, const int* __restrict__ base,
                                              int* __restrict__ perm, int N, int E, int k, int nblk,
-                                             const int* sbase = nullptr) {
+                                             const int* sbase = nullptr, int per = 1) {
   __shared__ int wcnt[RB / 64][64];
   const int sh_ = blockIdx.y;
   const int n = blockIdx.x * RB + threadIdx.x;
@@ -257,7 +265,7 @@ __device__ __forceinline__ void scatter_body(const int* __restrict__ idx, const 
         if constexpr (LOCAL)
           pos += sbase[e];
         else
-          pos += base[((long)sh_ * nblk + blockIdx.x) * E + e];
+          pos += base[((long)sh_ * nblk + (long)blockIdx.x * per) * E + e];
         for (int w = 0; w < wave; ++w) pos += wcnt[w][e];
         perm[(long)sh_ * N * k + pos] = n * k + j;
       }
@@ -265,8 +273,8 @@ __device__ __forceinline__ void scatter_body(const int* __restrict__ idx, const 
   }
 }
 __global__ __launch_bounds__(RB) void scatter_kernel(const int* __restrict__ idx, const int* __restrict__ base,
-                                                     int* __restrict__ perm, int N, int E, int k, int nblk) {
-  scatter_body(idx, base, perm, N, E, k, nblk);
+                                                     int* __restrict__ perm, int N, int E, int k, int nblk, int per) {
+  scatter_body(idx, base, perm, N, E, k, nblk, nullptr, per);
 }
 
 __global__ void dense_routing_kernel(int* idx, float* gate, int* perm, int* offsets, int N, int H) {
@@ -380,10 +388,10 @@ __global__ __launch_bounds__(RB) void hist_gate_table_kernel(const int* __restri
 // expert scatter whose blocks scan the (small) count table for themselves: one launch instead of scan + scatter
 __global__ __launch_bounds__(RB) void scan_scatter1_kernel(const int* __restrict__ idx, const int* __restrict__ cnt,
                                                            int* __restrict__ offsets, int* __restrict__ perm, int N, int E, int k,
-                                                           int nblk) {
+                                                           int ncb, int per) {
   __shared__ int sb[2 * 128 + 1];
-  block_bases(cnt, offsets, E, nblk, sb);
-  scatter_body<true>(idx, nullptr, perm, N, E, k, nblk, sb);
+  block_bases(cnt, offsets, E, ncb, sb, per);
+  scatter_body<true>(idx, nullptr, perm, N, E, k, 0, sb);
 }
 
 // Wp[side][i][c] = W_side[i][c] for c < HE, 0 for HE <= c < HEp (rows padded to 16 bytes)
@@ -449,20 +457,29 @@ bool router_hybrid_supported(const RouterArgs& a) {
   return a.bf16 && a.dm % 4 == 0 && ((uintptr_t)a.x % 16) == 0 && a.H * a.E <= 32;
 }
 
+template <typename T>
+static void launch_router_select(const RouterArgs& a, hipStream_t s) {
+  const int hpb = 64 / a.E < a.H ? 64 / a.E : a.H;   // whole heads per work-group
+  const int ncb = router_count_blocks(a.N), cpt = (hpb * a.E + 7) / 8;
+  const dim3 g(ncb, a.sides, (a.H + hpb - 1) / hpb);
+  auto kern = cpt <= 1 ? router_select_kernel<T, 1> : cpt <= 2 ? router_select_kernel<T, 2> : cpt <= 4 ? router_select_kernel<T, 4> : router_select_kernel<T, 8>;
+  kern<<<g, 256, 0, s>>>((const T*)a.x, (const T*)a.W[0], (const T*)a.W[1], a.b[0], a.b[1], a.idx, a.gate, a.blockcnt, a.N, a.dm,
+                         a.H, a.E, a.k, hpb, ncb);
+}
+
 void launch_router(const RouterArgs& a, hipStream_t s) {
-  const int HE = a.H * a.E;
-  dim3 g((a.N + RT_TOK - 1) / RT_TOK, a.sides, (HE + RT_COL - 1) / RT_COL);
   if (a.bf16)
-    router_logits_kernel<bf16_t><<<g, 256, 0, s>>>((const bf16_t*)a.x, (const bf16_t*)a.W[0], (const bf16_t*)a.W[1],
-                                                   a.b[0], a.b[1], a.Z, a.N, a.dm, HE);
+    launch_router_select<bf16_t>(a, s);
   else
-    router_logits_kernel<float><<<g, 256, 0, s>>>((const float*)a.x, (const float*)a.W[0], (const float*)a.W[1],
-                                                  a.b[0], a.b[1], a.Z, a.N, a.dm, HE);
-  const int nblk = router_blocks(a.N);
-  dim3 g2(nblk, a.sides * a.H);
-  topk_hist_kernel<<<g2, RB, 0, s>>>(a.Z, a.idx, a.gate, a.blockcnt, a.N, a.H, a.E, a.k, nblk);
-  scan_kernel<<<a.sides * a.H, 256, 0, s>>>(a.blockcnt, a.offsets, a.E, nblk);
-  scatter_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.perm, a.N, a.E, a.k, nblk);
+    launch_router_select<float>(a, s);
+  const int ncb = router_count_blocks(a.N), per = RB / RT_TOK;
+  const dim3 g2(router_blocks(a.N), a.sides * a.H);
+  if ((long)ncb * a.E <= 8192) {   // small tables: every scatter block scans the counts it needs itself
+    scan_scatter1_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.offsets, a.perm, a.N, a.E, a.k, ncb, per);
+    return;
+  }
+  scan_kernel<<<a.sides * a.H, 256, 0, s>>>(a.blockcnt, a.offsets, a.E, ncb);
+  scatter_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.perm, a.N, a.E, a.k, ncb, per);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -664,7 +681,6 @@ void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s) {
   g.rsel.gate = a.gate;
   g.rsel.x = a.x;
   g.rsel.Wt = Wt;
-  g.rsel.Z = a.Z;
   g.rsel.N = a.N;
   g.rsel.kstep = rg_kstep();
   g.rsel.H = a.H;
@@ -697,11 +713,11 @@ void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s) {
   else
     hist_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.N, a.E, a.k, nblk);
   if ((long)nblk * a.E <= 8192) {
-    scan_scatter1_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.offsets, a.perm, a.N, a.E, a.k, nblk);
+    scan_scatter1_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.offsets, a.perm, a.N, a.E, a.k, nblk, 1);
     return;
   }
   scan_kernel<<<a.sides * a.H, 256, 0, s>>>(a.blockcnt, a.offsets, a.E, nblk);
-  scatter_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.perm, a.N, a.E, a.k, nblk);
+  scatter_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.perm, a.N, a.E, a.k, nblk, 1);
 }
 
 }  // namespace sh

@@ -484,6 +484,8 @@ __global__ __launch_bounds__(256) void router_bwd_kernel(RouterBwdArgs a) {
     const float bs = ((wsum[0][threadIdx.x] + wsum[1][threadIdx.x]) + wsum[2][threadIdx.x]) + wsum[3][threadIdx.x];
     if (a.dbpart)
       a.dbpart[((long)sh_ * gridDim.x + blockIdx.x) * E + threadIdx.x] = bs;
+    else if (a.db[side] && gridDim.x == 1 && !a.db_add)
+      a.db[side][h * E + threadIdx.x] = bs;
     else if (a.db[side])
       atomicAdd(&a.db[side][h * E + threadIdx.x], bs);
   }

@@ -114,6 +114,21 @@ def test_fp32_ragged_everything(causal):
              seed=5)
 
 
+@pytest.mark.parametrize("over", [
+    dict(B=1, T=257, d_model=76, d_head=76),                     # one row past a chunk: partial sums, and past four 64-row tiles
+    dict(B=3, T=100, d_model=412, d_head=80, T_q=99),            # 80-wide tiles, queries packed, two token sets
+    dict(B=1, T=320, d_model=48, d_head=33, E=3, k=3),           # rows of no vector width
+    dict(B=2, T=97, d_model=64, d_head=130, E=7, k=2),           # experts over twice the active ones: the atomic path
+    dict(B=5, T=65, d_model=100, d_head=196, nheads=1, causal=0),
+    dict(B=1, T=31, d_model=64, d_head=16, nheads=9, E=4),       # more segments than one concatenated product takes
+])
+@pytest.mark.parametrize("shared", [False, True])
+def test_fp32_tile_edges(over, shared):
+    """The fp32 matrix-core kernels at the edges of their tiles (64 rows, 64 or 80 columns, 32 owned attention rows), chunks
+    and dispatch rules."""
+    run_case(dict(dict(name="edge32", dtype="f32", nheads=2, E=4, k=2, causal=1, bias0=0.0), **over), shared=shared, seed=31)
+
+
 def test_fp32_shared_selection_and_dense_mode():
     run_case(small("c0"), shared=True)
     run_case(dict(name="dense", dtype="f32", B=2, T=48, d_model=64, nheads=4, d_head=16, E=1, k=1, causal=1, bias0=0.0),
