@@ -53,6 +53,8 @@ def step_work(cfg):
         "bwd.o_dgrad": expert_q, "bwd.o_wgrad": expert_q, "bwd.v_wgrad": expert, "bwd.v_dgrad": expert,
         "bwd.q_wgrad": proj_q, "bwd.k_wgrad": proj, "bwd.qk_wgrad": proj + proj_q, "bwd.q_dgrad": proj_q, "bwd.k_dgrad": proj,
         "bwd.router_wgrad": router, "bwd.router_dgrad": router,
+        # every weight gradient in one launch
+        "bwd.wgrads": expert_q + expert + (expert_q + expert if cfg.get("qk_experts") else proj_q + proj) + router,
         # all of dx as one GEMM: the value experts' input gradient, the queries' and keys', the routers'
         "bwd.dx_gemm": expert + proj + proj_q + router,
         # query / key expert banks (all-expert form): each step has the shape of its value-expert twin
@@ -86,7 +88,8 @@ STEP_KERNEL = {
     "bwd.qk_dgrad": r"(pp_row_gemm_kernel<true, 6, 2>|mfma_row_gemm_kernel<.*, 6, 2(, \w+)?>)",
     "bwd.dx_gemm": r"pp_row_gemm_kernel<true, 6, 3>",
     "bwd.o_wgrad": r"mfma_wgrad_kernel<.*, 8, 7(, \w+)?>", "bwd.v_wgrad": r"mfma_wgrad_kernel<.*, 8, 8(, \w+)?>",
-    "bwd.qk_wgrad": r"mfma_wgrad_kernel<.*, 8, 9(, \w+)?>", "bwd.wgrad_reduce": r"wgrad_reduce_kernel",
+    "bwd.qk_wgrad": r"mfma_wgrad_kernel<.*, 8, 9(, \w+)?>", "bwd.wgrad_reduce": r"wgrad_(list_)?reduce_kernel",
+    "bwd.wgrads": r"mfma_wgrad_list_kernel",
     "fwd.attention": r"mfma_attn_fwd_kernel", "bwd.attention_dkv": r"mfma_attn_dkv(_ws)?_kernel",
     "bwd.attention_dq": r"mfma_attn_dq(_ds)?_kernel", "fwd.y_sum": r"sum_heads_kernel", "bwd.dx_cast": r"sum_heads_kernel",
     "fwd.v_combine": r"slot_combine", "bwd.dctx_combine": r"slot_combine", "bwd.dgate_s": r"slot_combine",

@@ -179,6 +179,40 @@ struct WgradArgs {
 };
 void launch_wgrad_reduce(const WgradArgs& a, hipStream_t s);
 
+// Every weight gradient of a backward pass as one launch (mfma_wgrad.hip).  wgrad_list_add turns a WgradArgs (one operand set, no
+// hsplit) into an item; groups with no rows get zeros, no output needs clearing.
+struct WgradItem {
+  const int* perm;
+  const int* offsets;
+  const float* gate;
+  long gate_hstride;
+  int heads, E, M, div;
+  const void* A;
+  long lda, a_hoff;
+  const void* B;
+  long ldb, b_hoff;
+  int Ka, Kb;
+  float* dW;
+  long w_hstride, w_estride;
+  float* dW2;
+  int swa, kb_store, col_split;   // as in WgradArgs
+  int wide, tj, ntile;            // output tiles of 128 x 256 (wide) or 256 x 128
+};
+enum { WGRAD_LIST_MAX = 6 };
+struct WgradList {
+  int n, items;
+  float* partial;   // wgrad_list_partial_floats() floats
+  // the routers' bias gradients from the block sums of launch_router_bwd (dbpart NULL: not wanted)
+  const float* dbpart;
+  float *db0, *db1;
+  int db_nblk, db_E, db_HE, db_sides;
+  WgradItem p[WGRAD_LIST_MAX];
+};
+void wgrad_list_add(WgradList& l, const WgradArgs& w);
+size_t wgrad_list_partial_floats(const WgradList& l);
+bool wgrad_list_supported(const WgradList& l);
+void launch_wgrad_list(const WgradList& l, hipStream_t s);
+
 // Finds the tile `tile` (of `bm` rows) among the E groups of one head.  Returns false when
 // `tile` lies beyond the last tile.  off points at the head's E+1 offsets.
 __device__ __forceinline__ bool find_tile(const int* off, int E, int bm, int tile, int& e, int& row0, int& rows) {

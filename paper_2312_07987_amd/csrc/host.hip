@@ -82,7 +82,7 @@ struct Layout {
   size_t dR, wr3;                                                  // wide router dz rows [N, H*dh], routers packed [dm, dh]                 // expert-set path (bf16 only)
   size_t rh;                                                       // two-stage router scratch (bf16 only)
   size_t wpart;                                                    // per-chunk weight-gradient partial sums
-  size_t wpart_floats = 0;                                         // ... their room (fp32 storage)
+  size_t wpart_floats = 0;                                         // ... their room
   size_t u, dctx, dQ, dK, dV, delta, dgate, dz;                    // backward scratch
   size_t dst;                                                      // score gradient dS^T of the attention backward (0: recomputed)
 };
@@ -137,6 +137,12 @@ bool gated_shape(const sh_shape* s) {
   const bool rect = s->T_q > 0 && s->T_q < s->T;
   return s->dtype == SH_BF16 && !rect && !s->qk_experts && s->d_head % 64 == 0 && s->d_model % 256 == 0 && N % 256 == 0 &&
          N >= 2048 && s->nheads * s->E + 2 * s->nheads + 1 <= MAX_SEGD && s->E <= 2 * s->k;
+}
+
+// Shapes whose weight gradients run as one launch (wgrad_list): output tiles of 128 x 256 features that are mostly filled, a lane
+// per (head, expert).  Below (narrow heads, narrow models) the launches of one problem each on 128 x 128 tiles stay.
+bool list_shape(const sh_shape* s) {
+  return s->dtype == SH_BF16 && s->d_model >= 256 && s->d_head >= 64 && s->nheads * s->E <= 64;
 }
 
 Layout make_layout(const sh_shape* s) {
@@ -204,11 +210,6 @@ Layout make_layout(const sh_shape* s) {
   L.rh = L.wpart = L.gtab = 0;
   if (s->dtype == SH_BF16) {
     L.gtab = take(2 * N * H * E * 4, true);
-    // groups x chunks-per-group x one expert matrix, fp32 (the dense Q/K pair counts as 2H groups)
-    const size_t groups = H * E > 2 * H + 1 ? H * E : 2 * H + 1;   // expert Q/K banks: H * E groups each, one at a time
-    const size_t ce = wgrad_chunk(H * N * k, dm, dh), cd = wgrad_chunk(2 * H * N, dm, dh);
-    const size_t cmin = ce < cd ? ce : cd;
-    L.wpart = take(groups * ((N + cmin - 1) / cmin) * dm * dh * 4);
     size_t o7[7];
     L.rh = take(router_hybrid_bytes((int)N, (int)dm, (int)H, (int)E, o7));
   }
@@ -253,6 +254,41 @@ Layout make_layout(const sh_shape* s) {
       else if (bytes <= ((size_t)1 << 30))
         L.dst = take(bytes);
     }
+  }
+  // The weight gradients' partial sums: room for the launches of one problem each, or for the launch of all problems (wgrad_list).
+  // A shape that fits into the built-in workspace with the former stays there: it keeps the launches of one problem each.
+  if (s->dtype == SH_BF16) {
+    // groups x chunks-per-group x one expert matrix, fp32 (the dense Q/K pair counts as 2H groups)
+    const size_t groups = H * E > 2 * H + 1 ? H * E : 2 * H + 1;   // expert Q/K banks: H * E groups each, one at a time
+    const size_t ce = wgrad_chunk(H * N * k, dm, dh), cd = wgrad_chunk(2 * H * N, dm, dh);
+    const size_t cmin = ce < cd ? ce : cd;
+    const size_t one = groups * ((N + cmin - 1) / cmin) * dm * dh;
+    L.wpart_floats = one;
+    if (list_shape(s) && off + align_up(one * 4) > (size_t)SWITCHHEAD_STATIC_WORKSPACE_BYTES) {
+      // (the routers with tables and weights of their own: the largest list the shape can have)
+      WgradList l{};
+      const bool rect = s->T_q > 0 && s->T_q < s->T;
+      const size_t Nq = rect ? (size_t)s->B * s->T_q : N, HEp = (H * E + 7) / 8 * 8;
+      auto add = [&](size_t heads, size_t experts, size_t rows, size_t ka, size_t kb) {
+        WgradArgs w{};
+        w.heads = (int)heads;
+        w.E = (int)experts;
+        w.M = (int)rows;
+        w.Ka = (int)ka;
+        w.Kb = (int)kb;
+        wgrad_list_add(l, w);
+      };
+      const size_t qe = s->qk_experts ? E : 1, qk = s->qk_experts ? k : 1;
+      add(H, E, Nq * k, dh, dm);
+      add(H, E, N * k, dm, dh);
+      add(H, qe, Nq * qk, dm, dh);
+      add(H, qe, N * qk, dm, dh);
+      add(1, 1, N, dm, rect ? HEp : 2 * HEp);
+      if (rect) add(1, 1, Nq, dm, HEp);
+      const size_t need = wgrad_list_partial_floats(l);
+      if (need > L.wpart_floats) L.wpart_floats = need;
+    }
+    L.wpart = take(L.wpart_floats * 4);
   }
   L.total = off;
   L.kept = kept;
@@ -1075,7 +1111,107 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     w.chunk = chunk;
     return w;
   };
-  if (!f32_tail) {
+  // the weight gradient of a projection P[n,h] = sum_j g[n,h,j] x[n] W[h,e_j] given dP
+  auto proj_wgrad_args = [&](int side, size_t dP, float* dW) {
+    WgradArgs w{};
+    w.tag = TAG_V_WGRAD;
+    w.scale_b = 1;   // gate on the d_head-wide dP rows instead of the d_model-wide x rows
+    w.perm = c.perm(side);
+    w.offsets = c.offsets(side);
+    w.heads = H;
+    w.E = E;
+    w.M = c.n(side) * k;
+    w.max_group_rows = c.n(side);
+    w.a_div = k;
+    w.b_div = k;
+    w.A = side ? xq : x;
+    w.lda = dm;
+    w.a_hoff = 0;
+    w.Ka = dm;
+    w.Bm = c.p<void>(dP);
+    w.ldb = hd;
+    w.b_hoff = dh;
+    w.Kb = dh;
+    w.dW = dW;
+    w.w_hstride = (long)E * dm * dh;
+    w.w_estride = (long)dm * dh;
+    w.swa = dh;
+    w.gate = c.gate(side);
+    w.gate_hstride = (long)c.n(side) * k;
+    w.chunk = chunk;
+    return w;
+  };
+  // x^T dQ / x^T dK of one side's tokens (rows of the operands: that side's tokens)
+  auto dense_wgrad_args = [&](int side, size_t dP, float* dW) {
+    WgradArgs w{};
+    w.tag = TAG_QK_WGRAD;
+    w.heads = H;
+    w.E = 1;
+    w.M = c.n(side);
+    w.a_div = 1;
+    w.b_div = 1;
+    w.A = side ? xq : x;
+    w.lda = dm;
+    w.Ka = dm;
+    w.Bm = c.p<void>(dP);
+    w.ldb = hd;
+    w.b_hoff = dh;
+    w.Kb = dh;
+    w.dW = dW;
+    w.w_hstride = (long)dm * dh;
+    w.swa = dh;
+    w.chunk = chunk_dense;
+    return w;
+  };
+
+  // bf16: every weight gradient in one launch at the end, where the shape and the pointers allow it.  The routers' dz, with the
+  // rows of both sides next to each other unless the sides have tokens of their own (then a shared router adds up both: not here).
+  const bool wide_dz = !c.dense && (c.shared ? 1 : 2) * HEp_ <= dh && (c.L.dR - c.L.dK) == (c.L.dK - c.L.dQ);
+  WgradList wl{};
+  bool use_list = use_mfma(c) && list_shape(shape);
+  bool list_router = use_list && !c.dense && !(c.rect && c.shared);
+  if (use_list) {
+    auto add_router = [&](int side, size_t dz, long ld, int cols, float* dW, float* dW2) {
+      WgradArgs w{};
+      w.heads = 1;
+      w.E = 1;
+      w.M = c.n(side);
+      w.a_div = 1;
+      w.b_div = 1;
+      w.A = side ? xq : x;
+      w.lda = dm;
+      w.Ka = dm;
+      w.Bm = c.p<void>(dz);
+      w.ldb = ld;
+      w.Kb = cols;         // the padded columns of dz are zero
+      w.kb_store = HE_;
+      w.swa = HE_;
+      w.dW = dW;
+      w.dW2 = dW2;
+      w.col_split = dW2 ? HEp_ : 0;
+      wgrad_list_add(wl, w);
+    };
+    if (list_router && c.rect) {
+      if (dW_S) add_router(0, c.L.dz, HEp_, HEp_, dW_S, nullptr);
+      if (dW_D) add_router(1, c.L.dz + (size_t)N * HEp_ * 2, HEp_, HEp_, dW_D, nullptr);
+    } else if (list_router) {
+      const size_t dz0 = wide_dz ? c.L.dR : c.L.dz;
+      const long ld = wide_dz ? hd : (c.shared ? 1 : 2) * HEp_;
+      float* second = c.shared ? nullptr : dW_D;
+      if (dW_S)
+        add_router(0, dz0, ld, second ? 2 * HEp_ : HEp_, dW_S, second);
+      else if (second)
+        add_router(0, dz0 + (size_t)HEp_ * 2, ld, HEp_, second, nullptr);
+    }
+    wgrad_list_add(wl, o_wgrad_args());
+    wgrad_list_add(wl, proj_wgrad_args(0, c.L.dV, dW_V));
+    wgrad_list_add(wl, c.qk_experts ? proj_wgrad_args(1, c.L.dQ, dW_Q) : dense_wgrad_args(1, c.L.dQ, dW_Q));
+    wgrad_list_add(wl, c.qk_experts ? proj_wgrad_args(0, c.L.dK, dW_K) : dense_wgrad_args(0, c.L.dK, dW_K));
+    wl.partial = c.p<float>(c.L.wpart);
+    use_list = wgrad_list_supported(wl) && wgrad_list_partial_floats(wl) <= c.L.wpart_floats;
+    list_router = list_router && use_list;
+  }
+  if (!f32_tail && !use_list) {
     prof_mark(c.st, "bwd.o_wgrad");
     wgrad(c, o_wgrad_args());
   }
@@ -1136,59 +1272,6 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     sa.dh = dh;
     launch_slot_combine(sa, c.bf16, c.st);
   };
-  // the weight gradient of such a projection
-  auto proj_wgrad_args = [&](int side, size_t dP, float* dW) {
-    WgradArgs w{};
-    w.tag = TAG_V_WGRAD;
-    w.scale_b = 1;   // gate on the d_head-wide dP rows instead of the d_model-wide x rows
-    w.perm = c.perm(side);
-    w.offsets = c.offsets(side);
-    w.heads = H;
-    w.E = E;
-    w.M = c.n(side) * k;
-    w.max_group_rows = c.n(side);
-    w.a_div = k;
-    w.b_div = k;
-    w.A = side ? xq : x;
-    w.lda = dm;
-    w.a_hoff = 0;
-    w.Ka = dm;
-    w.Bm = c.p<void>(dP);
-    w.ldb = hd;
-    w.b_hoff = dh;
-    w.Kb = dh;
-    w.dW = dW;
-    w.w_hstride = (long)E * dm * dh;
-    w.w_estride = (long)dm * dh;
-    w.swa = dh;
-    w.gate = c.gate(side);
-    w.gate_hstride = (long)c.n(side) * k;
-    w.chunk = chunk;
-    return w;
-  };
-  // x^T dQ / x^T dK of one side's tokens (rows of the operands: that side's tokens)
-  auto dense_wgrad_args = [&](int side, size_t dP, float* dW) {
-    WgradArgs w{};
-    w.tag = TAG_QK_WGRAD;
-    w.heads = H;
-    w.E = 1;
-    w.M = c.n(side);
-    w.a_div = 1;
-    w.b_div = 1;
-    w.A = side ? xq : x;
-    w.lda = dm;
-    w.Ka = dm;
-    w.Bm = c.p<void>(dP);
-    w.ldb = hd;
-    w.b_hoff = dh;
-    w.Kb = dh;
-    w.dW = dW;
-    w.w_hstride = (long)dm * dh;
-    w.swa = dh;
-    w.chunk = chunk_dense;
-    return w;
-  };
-
   if (f32_tail) {
     // dz of the routers, then every weight gradient in one launch and dx as one GEMM over the H*E value experts (scaled by the
     // token's gates), the 2H query / key matrices and the routers: no atomics, no zero fill and no accumulator passes over dx.
@@ -1197,9 +1280,9 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       prof_mark(c.st, "bwd.dgate_s");
       slot_dots(0, c.L.dV, c.L.pV, false);
     }
-    F32WgradList wl{};
+    F32WgradList fl{};
     auto add_wgrad = [&](const WgradArgs& w) {
-      F32Wgrad& p = wl.p[wl.n++];
+      F32Wgrad& p = fl.p[fl.n++];
       p.w = w;
       f32_wgrad_plan(p);
     };
@@ -1231,12 +1314,12 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       w.swa = HE_;
       w.dW = dW;
       add_wgrad(w);
-      if (sides > own) wl.p[wl.n - 1].add = 1;   // both sides' tokens add into the shared router's gradient
+      if (sides > own) fl.p[fl.n - 1].add = 1;   // both sides' tokens add into the shared router's gradient
     }
     float* part = c.p<float>(c.L.wpart);
-    for (int i = 0; i < wl.n; ++i) {
-      wl.p[i].w.partial = part;
-      if (!wl.p[i].add) part += wl.p[i].partial_floats;
+    for (int i = 0; i < fl.n; ++i) {
+      fl.p[i].w.partial = part;
+      if (!fl.p[i].add) part += fl.p[i].partial_floats;
     }
     // what is added to atomically: the bias gradients over more than one block of tokens, a router both sides' tokens share
     const bool add_w = sides > own && dW_S;
@@ -1267,7 +1350,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       }
     }
     prof_mark(c.st, "bwd.wgrads");
-    launch_f32_wgrad(wl, c.st);
+    launch_f32_wgrad(fl, c.st);
     for (int side = c.rect ? 1 : 0; side >= 0; --side) {
       // side 1 first (fewer queries than keys only): queries and destination router; side 0: values, keys, source router
       prof_mark(c.st, side ? "bwd.q_dgrad" : "bwd.dx_gemm");
@@ -1395,8 +1478,6 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
   // dx += dQ W_Q^T + dK W_K^T (one GEMM over the 2H concatenated segments).  Where the routers' dz fits
   // into rows of the same shape it rides along as one more segment (dz_S W_S^T + dz_D W_D^T), and the
   // launch moves behind the router backward kernel.
-  const int HE_r = H * E, HEp_r = (HE_r + 7) / 8 * 8, sides_r = c.shared ? 1 : 2;
-  const bool wide_dz = !c.dense && sides_r * HEp_r <= dh && (c.L.dR - c.L.dK) == (c.L.dK - c.L.dQ);
   // All of dx as ONE token-ordered GEMM (gated concatenation, see gated_concat): the value experts' input gradient
   // over all E experts of every head with the source side's dense gates, the 2H query / key segments and, where
   // the routers' dz rows have the shape of a dQ row, the routers' segment; dx is written once, in bf16.
@@ -1441,13 +1522,13 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
   // the routers' weight gradients ride along with the Q/K weight gradient under the same conditions,
   // if the three-set launch is one the matrix-core kernel takes (it has no other implementation)
   bool fuse_router_w = false;
-  if (fuse_router && dW_S && (c.shared || dW_D)) {
+  if (!use_list && fuse_router && dW_S && (c.shared || dW_D)) {
     WgradArgs probe = qk_wgrad_args(true);
     probe.partial = c.p<float>(c.L.wpart);
     probe.max_chunks = (probe.M + probe.chunk - 1) / probe.chunk;
     fuse_router_w = mfma_wgrad_supported(probe);
   }
-  if (!c.qk_experts && !fuse_router_w) run_qk_wgrad(false);
+  if (!use_list && !c.qk_experts && !fuse_router_w) run_qk_wgrad(false);
   auto run_qk_dgrad = [&](bool with_router) {
     RowGemmArgs a = identity_rows(c, 1);
     a.tag = TAG_QK_DGRAD;
@@ -1531,8 +1612,10 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
                              const char* l_gate, const char* l_wgrad, const char* l_dgrad) {
     prof_mark(c.st, l_gate);
     slot_dots(side, dP, slots, dots_add);
-    prof_mark(c.st, l_wgrad);
-    wgrad(c, proj_wgrad_args(side, dP, dW));
+    if (!use_list) {
+      prof_mark(c.st, l_wgrad);
+      wgrad(c, proj_wgrad_args(side, dP, dW));
+    }
     if (merged_dx) return;   // this projection's share of dx is part of the one GEMM that writes dx
     prof_mark(c.st, l_dgrad);
     const bool to_accq = c.rect && side == 1;   // rows of the query tokens: their own fp32 accumulator
@@ -1610,7 +1693,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       rb.side_stride = HEp;
       rb.pad_to = 0;
       launch_router_bwd(rb, c.bf16, c.st);
-      if (dW) {
+      if (dW && !list_router) {
         prof_mark(c.st, "bwd.router_wgrad");
         WgradArgs w{};
         w.heads = 1;
@@ -1680,13 +1763,16 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     float* dWs[2] = {dW_S, c.shared ? nullptr : dW_D};
     float* dbs[2] = {db_S, c.shared ? nullptr : db_D};
     // the small outputs that are accumulated with atomics are cleared by one launch
-    const bool both_w = sides == 2 && dWs[0] && dWs[1] && !fuse_router_w;
+    const bool both_w = sides == 2 && dWs[0] && dWs[1] && !fuse_router_w && !list_router;
     // fused weight gradient: the bias gradients go through per-block sums that the split kernel adds up
     // (no atomics, nothing to clear); the dz region proper is free then (the rows sit in dR)
     const size_t esz_r = c.bf16 ? 2 : 4;
     const int rblk = router_bwd_blocks(N);
-    const bool db_partial = fuse_router_w && wide_dz && (dbs[0] || dbs[1]) &&
-                            (size_t)sides * H * rblk * E * 4 <= (size_t)N * 2 * ((H * E + 7) / 8 * 8) * esz_r;
+    // (with the one launch of all weight gradients its reduction adds them up; the place of x^T dz is free then)
+    const size_t db_bytes = (size_t)sides * H * rblk * E * 4;
+    const bool db_partial = (dbs[0] || dbs[1]) && (list_router ? db_bytes <= (size_t)dm * dh * 4
+                                                               : fuse_router_w && wide_dz && db_bytes <= (size_t)N * 2 * ((H * E + 7) / 8 * 8) * esz_r);
+    float* dbpart = db_partial ? c.p<float>(list_router ? c.L.wrt : c.L.dz) : nullptr;
     if (!db_partial)
       launch_zero4_f32(dbs[0], dbs[0] ? (size_t)HE : 0, dbs[1], dbs[1] ? (size_t)HE : 0, both_w ? dWs[0] : nullptr,
                        both_w ? (size_t)dm * HE : 0, both_w ? dWs[1] : nullptr, both_w ? (size_t)dm * HE : 0, c.st);
@@ -1697,7 +1783,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     rb.dz = c.p<void>(wide_dz ? c.L.dR : c.L.dz);
     rb.db[0] = dbs[0];
     rb.db[1] = dbs[1];
-    rb.dbpart = db_partial ? c.p<float>(c.L.dz) : nullptr;
+    rb.dbpart = dbpart;
     rb.N = N;
     rb.H = H;
     rb.E = E;
@@ -1728,8 +1814,15 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     if (fuse_router_w) {
       run_qk_wgrad(true);
       prof_mark(c.st, "bwd.router_wsplit");
-      launch_router_wgrad_split(c.p<float>(c.L.wrt), dWs[0], dWs[1], dm, dh, HE, HEp, db_partial ? c.p<float>(c.L.dz) : nullptr,
-                                rblk, E, dbs[0], dbs[1], c.st);
+      launch_router_wgrad_split(c.p<float>(c.L.wrt), dWs[0], dWs[1], dm, dh, HE, HEp, dbpart, rblk, E, dbs[0], dbs[1], c.st);
+    } else if (list_router) {
+      wl.dbpart = dbpart;
+      wl.db0 = dbs[0];
+      wl.db1 = dbs[1];
+      wl.db_nblk = rblk;
+      wl.db_E = E;
+      wl.db_HE = HE;
+      wl.db_sides = sides;
     } else
     // dW_S / dW_D = x^T dz: one launch for both sides when both are wanted
     {
@@ -1842,6 +1935,10 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
   if (c.rect) {
     prof_mark(c.st, "bwd.dx_query_rows");
     launch_add_query_rows(dx, accq, Nq, shape->T, c.Tq, dm, c.bf16, c.st);
+  }
+  if (use_list) {
+    prof_mark(c.st, "bwd.wgrads");
+    launch_wgrad_list(wl, c.st);   // marks its reduction itself
   }
   prof_mark(c.st, nullptr);
   return check_launch("switchhead_backward");

@@ -129,6 +129,26 @@ def test_fp32_tile_edges(over, shared):
     run_case(dict(dict(name="edge32", dtype="f32", nheads=2, E=4, k=2, causal=1, bias0=0.0), **over), shared=shared, seed=31)
 
 
+@pytest.mark.parametrize("over, shared", [
+    (dict(B=5, T=261, d_model=412, nheads=2, d_head=76, E=5, k=3), False),              # 8-byte pieces, ragged in both features
+    (dict(B=3, T=701, d_model=1024, nheads=4, d_head=128, E=5, k=3), True),             # a last unit of a few rows, one router
+    (dict(B=2, T=800, d_model=1024, nheads=4, d_head=128, E=8, k=2, qk_experts=1), False),   # more items than fit at once
+    (dict(B=2, T=900, d_model=300, nheads=2, d_head=168, E=4, k=2, T_q=333), False),    # both tile shapes partly filled, two token sets
+    (dict(B=2, T=900, d_model=256, nheads=1, d_head=256, E=3, k=2, T_q=450), True),     # a shared router over two token sets
+    (dict(B=1, T=1031, d_model=512, nheads=4, d_head=64, E=16, k=1), False),            # 64 groups
+])
+def test_bf16_weight_gradient_list(over, shared):
+    """All weight gradients in one launch: part and tile edges, and an expert nobody chooses (its gradient is zero)."""
+    def shun(t):
+        for side in ("b_S", "b_D"):
+            if t.get("W_" + side[2]) is not None:
+                b = np.zeros(cfg["nheads"] * cfg["E"], np.float32)
+                b[1::cfg["E"]] = -30.0
+                t[side] = b
+    cfg = dict(dict(name="wgrads", dtype="bf16", causal=1, bias0=0.0), **over)
+    run_case(cfg, shared=shared, seed=47, mutate=shun)
+
+
 def test_fp32_shared_selection_and_dense_mode():
     run_case(small("c0"), shared=True)
     run_case(dict(name="dense", dtype="f32", B=2, T=48, d_model=64, nheads=4, d_head=16, E=1, k=1, causal=1, bias0=0.0),
