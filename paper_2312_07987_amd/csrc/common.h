@@ -78,7 +78,7 @@ struct SegDesc {
   int gcol;
   int klen, lda, sbn;
 };
-enum { MAX_SEGD = 40 };
+enum { MAX_SEGD = 64, F32_MAX_SEGD = 40 };   // (the fp32 kernel keeps a tile's dense gates in LDS, that many columns wide)
 
 struct RowGemmArgs {
   const int* perm;
@@ -118,12 +118,15 @@ struct RowGemmArgs {
   const float* segate;
   int seg_split;
   long a_sstride, a_wstride, b_sstride;
-  //  3  gated concatenation (token-ordered rows, M a multiple of 256): nseg segments of length K described by
+  //  3  gated concatenation (token-ordered rows): nseg segments of length K described by
   //     segd[]; the expert projections whose experts sit on the reduction side (Sec. 2.2, the y equation, and
   //     the value experts' input gradient) run over ALL experts of every head this way, an unselected expert
   //     having gate 0, so that heads and experts are summed in one accumulator and the output is written once.
+  //     seg_q > 0 (bf16 kernel): row n is position n % seq_T of a sequence, and the segments from seg_q on belong to its last seq_Tq
+  //     positions alone; their A rows and gates are numbered by query (sequence * seq_Tq + position - (seq_T - seq_Tq)).
   const float* gtab;
   int gld;
+  int seg_q, seq_T, seq_Tq;
   // ... the fp32 kernel takes the gates from the top-k tables [head][token][gk] of `gheads` heads instead and keeps the
   // tile's dense gates in LDS (column head * experts + expert)
   const int* gidx;

@@ -133,10 +133,23 @@ sh_status check_shape(const sh_shape* s) {
 // Shapes whose output experts and input gradient run as gated concatenation (see gated_concat below): a property
 // of the shape alone, so that the workspace layout and both passes agree on it.  Such shapes have no expert-set tables.
 bool gated_shape(const sh_shape* s) {
-  const long long N = (long long)s->B * s->T;
+  const long N = (long)s->B * s->T, H = s->nheads, E = s->E, k = s->k, HEp = (H * E + 7) / 8 * 8;
   const bool rect = s->T_q > 0 && s->T_q < s->T;
-  return s->dtype == SH_BF16 && !rect && !s->qk_experts && s->d_head % 64 == 0 && s->d_model % 256 == 0 && N % 256 == 0 &&
-         N >= 2048 && s->nheads * s->E + 2 * s->nheads + 1 <= MAX_SEGD && s->E <= 2 * s->k;
+  const long Nq = rect ? (long)s->B * s->T_q : N;
+  // segments of dx: value experts, queries and keys (or their experts), routers
+  const long qk = s->qk_experts ? 2 * H * E : 2 * H, dx_segs = H * E + qk + (rect ? 2 : 1);
+  if (s->dtype != SH_BF16 || s->d_head % 64 != 0 || s->d_model % 256 != 0 || N < 2048 || Nq < 2048 || dx_segs > MAX_SEGD || E > 2 * k) return false;
+  // (two token sets: the routers' dz rows of both sides lie next to each other in rows of H * d_head)
+  if (rect && (H < 2 || HEp > s->d_head)) return false;
+  // One work-group per CU: a launch costs whole rounds of 256 tiles times its segments (4.4 us a round and segment of 128, measured at
+  // 256 tiles).  The expert-set path costs its selected segments, partial sums and their addition per tile (11.8 us for 256
+  // tiles), so it is the better one where the last round is mostly empty.  A training step over B x 512 tokens of d_model
+  // 1024, 4 heads of 128, 3 of 5 experts: B = 4 479 us gated, 338 by sets; B = 8 468 and 402; the lines meet near B = 18.
+  const long cols = s->d_model / 256;
+  auto rounds = [&](long rows) { return ((rows + 255) / 256 * cols + 255) / 256; };
+  const long gated = rounds(Nq) * H * E + rounds(N) * dx_segs;
+  const long sets = (Nq * H * k + N * (H * k + (s->qk_experts ? 2 * H * k : 2 * H) + 1)) * cols / 256;
+  return gated * 256 * 44 <= sets * 118;
 }
 
 // Shapes whose weight gradients run as one launch (wgrad_list): output tiles of 128 x 256 features that are mostly filled, a lane
@@ -476,12 +489,12 @@ bool sets_usable(const Ctx& c) { return use_mfma(c) && set_tables(c); }
 // gradient) run as ONE token-ordered GEMM over all E experts of every head, an unselected expert having gate 0:
 // heads and experts are then summed inside the accumulator and y / dx are written once, instead of one bf16
 // partial per head that another kernel adds up.  It multiplies E/k times the selected experts' work, so it is
-// taken where that factor is at most 2 (and the shape fills the 256 x 256 tiles); else the expert-set path.
+// taken where that factor is at most 2 (and the shape fills the 256 x 256 tiles, see gated_shape); else the expert-set path.
 bool gated_concat(const Ctx& c) { return use_mfma(c) && gated_shape(c.s); }
 
 // The same in fp32 (any token count): `segs` segments.  Its tile builds the dense gates from the top-k tables in LDS.  Against
 // expert-sorted rows added with fp32 atomics into a zeroed output it multiplies E / k times as much; see f32_concat's callers.
-bool f32_gated(const Ctx& c, int segs) { return use_f32(c) && segs <= MAX_SEGD && c.E <= 2 * c.k; }
+bool f32_gated(const Ctx& c, int segs) { return use_f32(c) && segs <= F32_MAX_SEGD && c.E <= 2 * c.k; }
 
 RowGemmArgs identity_rows(const Ctx& c, int heads, int side = 0) {
   RowGemmArgs a{};
@@ -602,9 +615,11 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
   const bool tables = set_tables(c);
   const bool sets = sets_usable(c);
   const bool gated = gated_concat(c);
+  // (like the set tables, the gate table is there for a backward call under either kernel family)
+  const bool gate_table = gated_shape(shape) && !c.dense;
   bool gtab_done = false;
   // the tables a path uses must have a place in the workspace layout (offset 0 is the top-k indices)
-  if ((tables && (c.L.setperm == 0 || c.L.setid == 0 || c.L.gsort == 0)) || (gated && c.L.gtab == 0) || (sets && c.L.yh == 0))
+  if ((tables && (c.L.setperm == 0 || c.L.setid == 0 || c.L.gsort == 0)) || ((gated || gate_table) && c.L.gtab == 0) || (sets && c.L.yh == 0))
     return fail(SH_ERR_UNSUPPORTED, "switchhead_forward: internal error, the workspace layout lacks a table this shape's path uses");
   bool sets_sorted = false;
   SetSortArgs sa{};
@@ -661,6 +676,7 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
         continue;
       }
       const bool own = side == 1 && !c.shared;   // the destination side's own router
+      float* gtab_side = c.p<float>(c.L.gtab) + (size_t)side * N * H * E;
       RouterArgs ra{};
       ra.x = side ? xq : x;
       ra.W[0] = own ? W_D : W_S;
@@ -679,11 +695,14 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
       ra.bf16 = c.bf16;
       if (use_mfma(c) && router_hybrid_supported(ra)) {
         if (tables) ra.sets = &s1;
+        if (gate_table) ra.gtab = gtab_side;
         launch_router_hybrid(ra, c.p<char>(c.L.rh), c.st);
       } else {
         launch_router(ra, c.st);
         if (tables) launch_set_sort(s1, c.st);
+        if (gate_table) launch_gate_table(c.idx(side), c.gate(side), gtab_side, n, H, E, k, 1, 0, c.st);
       }
+      gtab_done = true;
     }
     sets_sorted = true;
   } else if (c.dense) {
@@ -711,7 +730,7 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
       if (tables && !c.shared) {   // both sorts in the same launches
         ra.sets = &sa;
         sets_sorted = true;
-      } else if (gated && !c.shared && !c.dense) {   // the dense gate table rides along the histogram pass
+      } else if (gate_table && !c.shared) {   // the dense gate table rides along the histogram pass
         ra.gtab = c.p<float>(c.L.gtab);
         gtab_done = true;
       }
@@ -749,7 +768,7 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     launch_set_sort(sa, c.st);
   }
 
-  if (gated && !c.dense && !gtab_done) {
+  if (gate_table && !gtab_done) {
     prof_mark(c.st, "fwd.gate_table");
     launch_gate_table(c.idx(0), c.gate(0), c.p<float>(c.L.gtab), N, H, E, k, 2, (long)H * N * k, c.st);
   }
@@ -1164,9 +1183,57 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     return w;
   };
 
+  const bool wide_dz = !c.dense && (c.shared ? 1 : 2) * HEp_ <= dh && (c.L.dR - c.L.dK) == (c.L.dK - c.L.dQ);
+  // All of dx as ONE token-ordered GEMM (gated concatenation, see gated_concat): the value experts' input gradient over all E experts
+  // of every head with the source side's dense gates, the query and key segments (likewise over their experts in the
+  // all-expert form) and, where the routers' dz rows have the shape of a dQ row, the routers' segment; dx is written once, in
+  // bf16.  Fewer queries than keys: the destination side's segments (queries, its router) come last and count for the query rows.
+  auto merged_dx_args = [&](bool with_router) {
+    RowGemmArgs a = identity_rows(c, 1);
+    a.tag = TAG_QK_DGRAD;
+    a.seg_mode = 3;
+    a.lda = hd;
+    a.sbk = 1;
+    a.sbn = dh;
+    a.C = dx;
+    a.ldc = dm;
+    a.K = dh;
+    a.Nc = dm;
+    a.mode = STORE_T;
+    a.gtab = c.dense ? nullptr : c.p<float>(c.L.gtab);   // [source side | destination side]
+    a.gld = H * E;
+    int n = 0;
+    auto seg = [&](const void* A, const void* B, int gcol) {
+      if (n < MAX_SEGD) a.segd[n] = {A, B, gcol, 0, 0, 0};
+      ++n;
+    };
+    auto projection = [&](size_t dP, const void* W, bool experts, int side) {
+      const int per = experts ? E : 1;
+      for (int s_ = 0; s_ < H * per; ++s_)
+        seg(c.p<bf16_t>(dP) + (size_t)(s_ / per) * dh, (const bf16_t*)W + (size_t)s_ * dm * dh, experts && !c.dense ? side * N * H * E + s_ : -1);
+    };
+    projection(c.L.dV, W_V, true, 0);
+    projection(c.L.dK, W_K, c.qk_experts, 0);
+    if (with_router) seg(c.p<bf16_t>(c.L.dR), c.p<bf16_t>(c.L.wr3), -1);
+    if (c.rect) {
+      a.seg_q = n;
+      a.seq_T = shape->T;
+      a.seq_Tq = c.Tq;
+    }
+    projection(c.L.dQ, W_Q, c.qk_experts, 1);
+    if (with_router && c.rect) seg(c.p<bf16_t>(c.L.dR) + dh, c.p<bf16_t>(c.L.wrt), -1);
+    a.nseg = n;
+    return a;
+  };
+  // (dz rows of one side: HEp columns; of both sides next to each other: wide_dz.  Two token sets: one behind the other in dR's rows)
+  const bool wide_rect = c.rect && !c.dense && HEp_ <= dh && H >= 2 && (c.L.dR - c.L.dK) == (c.L.dK - c.L.dQ);
+  const bool merged_dx = gated_concat(c) && (c.dense || (c.rect ? wide_rect : wide_dz)) && pp_row_gemm_supported(merged_dx_args(!c.dense));
   // bf16: every weight gradient in one launch at the end, where the shape and the pointers allow it.  The routers' dz, with the
   // rows of both sides next to each other unless the sides have tokens of their own (then a shared router adds up both: not here).
-  const bool wide_dz = !c.dense && (c.shared ? 1 : 2) * HEp_ <= dh && (c.L.dR - c.L.dK) == (c.L.dK - c.L.dQ);
+  // two token sets: where each side's dz rows lie
+  const bool rect_wide = c.rect && merged_dx && !c.dense;
+  auto rect_dz = [&](int side) { return rect_wide ? c.L.dR + (size_t)side * dh * 2 : c.L.dz + (size_t)side * N * HEp_ * (c.bf16 ? 2 : 4); };
+  const long rect_ld = rect_wide ? hd : HEp_;
   WgradList wl{};
   bool use_list = use_mfma(c) && list_shape(shape);
   bool list_router = use_list && !c.dense && !(c.rect && c.shared);
@@ -1192,8 +1259,8 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       wgrad_list_add(wl, w);
     };
     if (list_router && c.rect) {
-      if (dW_S) add_router(0, c.L.dz, HEp_, HEp_, dW_S, nullptr);
-      if (dW_D) add_router(1, c.L.dz + (size_t)N * HEp_ * 2, HEp_, HEp_, dW_D, nullptr);
+      if (dW_S) add_router(0, rect_dz(0), rect_ld, HEp_, dW_S, nullptr);
+      if (dW_D) add_router(1, rect_dz(1), rect_ld, HEp_, dW_D, nullptr);
     } else if (list_router) {
       const size_t dz0 = wide_dz ? c.L.dR : c.L.dz;
       const long ld = wide_dz ? hd : (c.shared ? 1 : 2) * HEp_;
@@ -1428,7 +1495,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
   // the query tokens' own share of dx (fewer queries than keys): fp32, added to their rows at the end
   float* accq = c.rect ? c.p<float>(c.L.accq) : nullptr;
   bool accq_set = false;
-  if (c.rect && !c.qk_experts) {
+  if (c.rect && !c.qk_experts && !merged_dx) {
     // dQ W_Q^T as one GEMM over the H concatenated head segments that overwrites the accumulator
     RowGemmArgs a = identity_rows(c, 1, 1);
     a.tag = TAG_QK_DGRAD;
@@ -1453,7 +1520,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       accq_set = true;
     }
   }
-  if (c.rect && !accq_set) {
+  if (c.rect && !accq_set && !merged_dx) {
     prof_mark(c.st, "bwd.dx_zero");
     launch_fill_f32(accq, (size_t)Nq * dm, 0.f, c.st);
     if (!c.qk_experts) {
@@ -1478,51 +1545,12 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
   // dx += dQ W_Q^T + dK W_K^T (one GEMM over the 2H concatenated segments).  Where the routers' dz fits
   // into rows of the same shape it rides along as one more segment (dz_S W_S^T + dz_D W_D^T), and the
   // launch moves behind the router backward kernel.
-  // All of dx as ONE token-ordered GEMM (gated concatenation, see gated_concat): the value experts' input gradient
-  // over all E experts of every head with the source side's dense gates, the 2H query / key segments and, where
-  // the routers' dz rows have the shape of a dQ row, the routers' segment; dx is written once, in bf16.
-  auto merged_dx_args = [&](bool with_router) {
-    RowGemmArgs a = identity_rows(c, 1);
-    a.tag = TAG_QK_DGRAD;
-    a.seg_mode = 3;
-    a.lda = hd;
-    a.sbk = 1;
-    a.sbn = dh;
-    a.C = dx;
-    a.ldc = dm;
-    a.K = dh;
-    a.Nc = dm;
-    a.mode = STORE_T;
-    a.gtab = c.dense ? nullptr : c.p<float>(c.L.gtab);   // the source side's gates
-    a.gld = H * E;
-    int n = 0;
-    for (int s_ = 0; s_ < H * E && n < MAX_SEGD; ++s_, ++n) {
-      a.segd[n].A = c.p<bf16_t>(c.L.dV) + (size_t)(s_ / E) * dh;
-      a.segd[n].B = (const bf16_t*)W_V + (size_t)s_ * dm * dh;
-      a.segd[n].gcol = c.dense ? -1 : s_;
-    }
-    for (int which = 0; which < 2; ++which)
-      for (int h_ = 0; h_ < H && n < MAX_SEGD; ++h_, ++n) {
-        a.segd[n].A = c.p<bf16_t>(which ? c.L.dK : c.L.dQ) + (size_t)h_ * dh;
-        a.segd[n].B = (const bf16_t*)(which ? W_K : W_Q) + (size_t)h_ * dm * dh;
-        a.segd[n].gcol = -1;
-      }
-    if (with_router && n < MAX_SEGD) {
-      a.segd[n].A = c.p<bf16_t>(c.L.dR);
-      a.segd[n].B = c.p<bf16_t>(c.L.wr3);
-      a.segd[n].gcol = -1;
-      ++n;
-    }
-    a.nseg = n;
-    return a;
-  };
-  const bool merged_dx = gated_concat(c) && (c.dense || wide_dz) && pp_row_gemm_supported(merged_dx_args(!c.dense));
-  const bool fuse_router = wide_dz && (sets || merged_dx) && c.bf16 && use_mfma(c) && !c.qk_experts && !c.rect;
+  const bool fuse_router = wide_dz && use_mfma(c) && !c.rect && (merged_dx || (sets && !c.qk_experts));
   bool router_fused = false;
   // the routers' weight gradients ride along with the Q/K weight gradient under the same conditions,
   // if the three-set launch is one the matrix-core kernel takes (it has no other implementation)
   bool fuse_router_w = false;
-  if (!use_list && fuse_router && dW_S && (c.shared || dW_D)) {
+  if (!use_list && fuse_router && !c.qk_experts && dW_S && (c.shared || dW_D)) {
     WgradArgs probe = qk_wgrad_args(true);
     probe.partial = c.p<float>(c.L.wpart);
     probe.max_chunks = (probe.M + probe.chunk - 1) / probe.chunk;
@@ -1595,7 +1623,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     }
   };
   if (c.qk_experts) {
-    if (!sets) {   // the expert input gradients below add into the accumulator
+    if (!sets && !merged_dx) {   // the expert input gradients below add into the accumulator
       prof_mark(c.st, "bwd.dx_zero");
       launch_fill_f32(dxacc, (size_t)N * dm, 0.f, c.st);
       acc_written = true;
@@ -1675,7 +1703,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       const bool own = side == 1 && !c.shared;
       const void* W = own ? W_D : W_S;
       float* dW = own ? dW_D : dW_S;
-      char* dzs = c.p<char>(c.L.dz) + (size_t)side * N * HEp * esz;
+      char* dzs = c.p<char>(rect_dz(side));
       RouterBwdArgs rb{};
       rb.idx = c.idx(side);
       rb.gate = c.gate(side);
@@ -1689,9 +1717,15 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       rb.sides = 1;
       rb.shared = 0;
       rb.db_add = c.shared;
-      rb.ld = HEp;
+      rb.ld = (int)rect_ld;
       rb.side_stride = HEp;
-      rb.pad_to = 0;
+      rb.pad_to = rect_wide ? dh : 0;
+      if (rect_wide) {   // the packed router for the dx GEMM rides along
+        rb.W[0] = W;
+        rb.wide_out = c.p<void>(side ? c.L.wrt : c.L.wr3);
+        rb.dm = dm;
+        rb.wide_width = dh;
+      }
       launch_router_bwd(rb, c.bf16, c.st);
       if (dW && !list_router) {
         prof_mark(c.st, "bwd.router_wgrad");
@@ -1705,7 +1739,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
         w.lda = dm;
         w.Ka = dm;
         w.Bm = dzs;
-        w.ldb = HEp;
+        w.ldb = rect_ld;
         w.Kb = HEp;
         w.kb_store = HE;
         w.swa = HE;
@@ -1713,6 +1747,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
         w.dW = dW;
         wgrad(c, w, false, /*zero=*/!(c.shared && side == 1));   // shared selection: both sides add into dW_S
       }
+      if (merged_dx) continue;
       prof_mark(c.st, "bwd.router_dgrad");
       RowGemmArgs a = identity_rows(c, 1, side);
       a.A = dzs;
@@ -1921,9 +1956,9 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       }
     }
   }
-  if (merged_dx && c.dense) {
+  if (merged_dx && (c.dense || c.rect)) {
     prof_mark(c.st, "bwd.dx_gemm");
-    launch_pp_row_gemm(merged_dx_args(false), c.st);
+    launch_pp_row_gemm(merged_dx_args(!c.dense), c.st);
   }
   if (!merged_dx) prof_mark(c.st, "bwd.dx_cast");
   if (merged_dx) {
@@ -1932,7 +1967,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
                      yh_taken() + (router_partial ? 1 : 0), c.st);
   else if (c.bf16)
     launch_cast_from_f32(dxacc, dx, (size_t)N * dm, 1, c.st);
-  if (c.rect) {
+  if (c.rect && !merged_dx) {
     prof_mark(c.st, "bwd.dx_query_rows");
     launch_add_query_rows(dx, accq, Nq, shape->T, c.Tq, dm, c.bf16, c.st);
   }

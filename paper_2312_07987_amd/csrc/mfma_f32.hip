@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
   __shared__ __attribute__((aligned(16))) float Bs_[2][BNT ? BN * FLDA : FBK * (BN + 4)];
   __shared__ int ids[FBM];
   __shared__ float gsc[FBM];
-  __shared__ float gts[SEG ? FBM * MAX_SEGD : 1];   // the tile's dense gates, [row][head * experts + expert]
+  __shared__ float gts[SEG ? FBM * F32_MAX_SEGD : 1];   // the tile's dense gates, [row][head * experts + expert]
 
   const int h = blockIdx.z, n0 = blockIdx.y * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -79,12 +79,12 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
   if constexpr (SEG) {
     if (a.gidx) {
       const int HE = a.gheads * a.experts;
-      for (int t = tid; t < FBM * HE; t += 256) gts[(t / HE) * MAX_SEGD + t % HE] = 0.f;
+      for (int t = tid; t < FBM * HE; t += 256) gts[(t / HE) * F32_MAX_SEGD + t % HE] = 0.f;
       __syncthreads();
       for (int t = tid; t < rows * a.gheads * a.gk; t += 256) {
         const int j = t % a.gk, row = t / a.gk % rows, hd = t / (a.gk * rows);
         const long o = ((long)hd * a.M + row0 + row) * a.gk + j;
-        gts[row * MAX_SEGD + hd * a.experts + a.gidx[o]] = a.ggate[o];
+        gts[row * F32_MAX_SEGD + hd * a.experts + a.gidx[o]] = a.ggate[o];
       }
     }
   }
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
       const int c = tid + i * 256, kk = st.k0 + (c % A_CPR) * VEC;
       vec_t v = st.ra[i];
       if constexpr (SEG) {
-        if (st.gcol >= 0) v *= gts[c / A_CPR * MAX_SEGD + st.gcol];
+        if (st.gcol >= 0) v *= gts[c / A_CPR * F32_MAX_SEGD + st.gcol];
       }
       if constexpr (VEC == 4) {
 #pragma unroll
@@ -263,8 +263,8 @@ static bool f32_vec4(const RowGemmArgs& a) {
 bool f32_row_gemm_supported(const RowGemmArgs& a) {
   if (a.sbk != 1 && a.sbn != 1) return false;
   if (a.seg_mode != 0 && a.seg_mode != 3) return false;
-  if (a.seg_mode == 3 && (a.nseg < 1 || a.nseg > MAX_SEGD || a.heads != 1 || a.perm || a.a_div != 1)) return false;
-  if (a.seg_mode == 3 && a.gidx && a.gheads * a.experts > MAX_SEGD) return false;
+  if (a.seg_mode == 3 && (a.nseg < 1 || a.nseg > F32_MAX_SEGD || a.heads != 1 || a.perm || a.a_div != 1)) return false;
+  if (a.seg_mode == 3 && a.gidx && a.gheads * a.experts > F32_MAX_SEGD) return false;
   return a.E <= 128;   // the tile lookup covers 128 groups
 }
 

@@ -37,6 +37,8 @@ struct PpCfg {
 static_assert(PpCfg::BN * PpCfg::LDB_NT == PpCfg::BK * PpCfg::LDB_NN, "both B layouts fill the same area");
 
 // PAIR: the tile's 256 columns are two adjacent heads of 128 columns each (dense queries / keys)
+// SEG 4 is segment mode 3 with segments of the query rows (seg_q): a tile that holds no query row leaves them out, in a mixed tile the
+// other rows count as zeros there.
 template <bool BNT, int TAG, int SEG>
 __global__ __launch_bounds__(512, 1) void pp_row_gemm_kernel(RowGemmArgs a) {
   constexpr int BM = PpCfg::BM, BN = PpCfg::BN, BK = PpCfg::BK;
@@ -103,8 +105,12 @@ __global__ __launch_bounds__(512, 1) void pp_row_gemm_kernel(RowGemmArgs a) {
   const unsigned short* A = (const unsigned short*)a.A;
   const unsigned short* B0 = (const unsigned short*)(second ? a.B2 : a.B) + (SEG ? 0 : (long)hh * a.b_hstride);
   const int n0 = ct * BN;
+  constexpr bool CAT = SEG == 3 || SEG == 4;
   const int nks = a.K / BK;            // K steps per segment
-  const int nk = nks * nseg;
+  int nk = nks * nseg;
+  if constexpr (SEG == 4) {
+    if (row0 % a.seq_T + rows - 1 < a.seq_T - a.seq_Tq) nk = nks * a.seg_q;   // (a tile that reaches into the next sequence holds this one's last rows)
+  }
 
   // ---- load plan: 4 A pieces and 4 B pieces of 16 bytes per thread and K step ------------
   // A: piece i is row (tid / 8) + 64 i, k piece tid % 8; rows past the tile's end repeat its first row
@@ -141,7 +147,7 @@ __global__ __launch_bounds__(512, 1) void pp_row_gemm_kernel(RowGemmArgs a) {
   auto a_base = [&](int it) -> const unsigned short* {
     const int seg = SEG ? it / nks : 0, k0 = (SEG ? it % nks : it) * BK;
     if constexpr (SEG == 2) return A + (long)(seg / a.seg_split) * a.a_wstride + (long)(seg % a.seg_split) * a.a_sstride + k0;
-    if constexpr (SEG == 3) return (const unsigned short*)a.segd[seg].A + k0;
+    if constexpr (CAT) return (const unsigned short*)a.segd[seg].A + k0;
     return A + k0;
   };
   auto b_base = [&](int it) -> const unsigned short* {
@@ -156,21 +162,37 @@ __global__ __launch_bounds__(512, 1) void pp_row_gemm_kernel(RowGemmArgs a) {
       const int which = seg / a.seg_split;
       Bp = (const unsigned short*)(which == 0 ? a.B : which == 1 ? a.B2 : a.B3) + (long)(seg % a.seg_split) * a.b_sstride;
     }
-    if constexpr (SEG == 3) Bp = (const unsigned short*)a.segd[seg].B;
+    if constexpr (CAT) Bp = (const unsigned short*)a.segd[seg].B;
     return BNT ? Bp + k0 : Bp + (long)k0 * a.sbk;
   };
-  // SEG 3: the gates of the step's segment for the thread's four rows travel with the A pieces
-  const unsigned g_voff = SEG == 3 ? (unsigned)(((long)(row0 + (tid >> 3)) * a.gld) * 4) : 0u;
+  // SEG 3, 4: the gates of the step's segment for the thread's four rows travel with the A pieces (byte offsets like the rows')
+  unsigned g_voff[4] = {0, 0, 0, 0}, q_voff[4] = {0, 0, 0, 0}, gq_voff[4] = {0, 0, 0, 0};
+  unsigned is_q = 0;   // SEG 4: which of the thread's rows are query rows
+  if constexpr (CAT) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int id = min(row0 + (tid >> 3) + 64 * i, a.M - 1);
+      g_voff[i] = (unsigned)id * (unsigned)(a.gld * 4);
+      if constexpr (SEG == 4) {
+        const int bq = id / a.seq_T, q = id % a.seq_T - (a.seq_T - a.seq_Tq);
+        const unsigned qrow = (unsigned)(bq * a.seq_Tq + max(q, 0));
+        is_q |= q >= 0 ? 1u << i : 0u;
+        q_voff[i] = (unsigned)(((long)qrow * a.lda + (tid & 7) * 8) * 2);
+        gq_voff[i] = qrow * (unsigned)(a.gld * 4);
+      }
+    }
+  }
   auto load_a = [&](u32x4 (&ra)[4], float (&rg)[4], int it) {
     const char* p = (const char*)a_base(it);
+    const bool qs = SEG == 4 && it / nks >= a.seg_q;   // uniform
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ra[i] = *(const u32x4*)(p + a_voff[i]);
-    if constexpr (SEG == 3) {
+    for (int i = 0; i < 4; ++i) ra[i] = *(const u32x4*)(p + (qs ? q_voff[i] : a_voff[i]));
+    if constexpr (CAT) {
       const int gcol = a.segd[it / nks].gcol;
       if (gcol >= 0) {
         const char* gp = (const char*)(a.gtab + gcol);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rg[i] = *(const float*)(gp + (long)i * 64 * a.gld * 4 + g_voff);
+        for (int i = 0; i < 4; ++i) rg[i] = *(const float*)(gp + (qs ? gq_voff[i] : g_voff[i]));
       } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) rg[i] = 1.f;
@@ -190,7 +212,9 @@ __global__ __launch_bounds__(512, 1) void pp_row_gemm_kernel(RowGemmArgs a) {
       u32x4 v = ra[i];
       // expert sets: the row's gate for this segment's expert, applied on the way into LDS
       if constexpr (SEG == 1) v = scale_chunk4(v, gsc[((tid >> 3) + 64 * i) * 8 + seg]);
-      if constexpr (SEG == 3) v = scale_chunk4(v, rg[i]);
+      if constexpr (CAT) v = scale_chunk4(v, rg[i]);
+      // (zeros by selection: the stand-in row of a position that is no query may hold anything)
+      if constexpr (SEG == 4) v = it / nks >= a.seg_q && !((is_q >> i) & 1u) ? (u32x4)(0u) : v;
       *(u32x4*)(&As[a_lds0 + i * 64 * LDA]) = v;
     }
   };
@@ -340,9 +364,13 @@ bool pp_row_gemm_supported(const RowGemmArgs& a) {
          a.nseg <= 3 * a.seg_split && (a.nseg <= 2 * a.seg_split || (a.B3 && pp_aligned(a.B3))) && a.heads == 1 && a.E == 1;
   }
   if (a.seg_mode == 3) {
-    ok = ok && a.nseg >= 1 && a.nseg <= MAX_SEGD && a.heads == 1 && a.E == 1 && a.M % 256 == 0 && a.hsplit == 0;
+    ok = ok && a.nseg >= 1 && a.nseg <= MAX_SEGD && a.heads == 1 && a.E == 1 && a.hsplit == 0 &&
+         (long)a.M * a.gld * 4 < (1l << 32);
+    // (two tables at most: one per routing side, M rows apart)
+    const long gmax = 2l * a.M * a.gld;
+    if (a.seg_q) ok = ok && a.seg_q > 0 && a.seg_q < a.nseg && a.seq_Tq > 0 && a.seq_Tq < a.seq_T && a.M % a.seq_T == 0;
     for (int p = 0; ok && p < a.nseg; ++p)
-      ok = a.segd[p].A && a.segd[p].B && pp_aligned(a.segd[p].A) && pp_aligned(a.segd[p].B) && (a.segd[p].gcol < 0 || (a.gtab && a.segd[p].gcol < a.gld));
+      ok = a.segd[p].A && a.segd[p].B && pp_aligned(a.segd[p].A) && pp_aligned(a.segd[p].B) && (a.segd[p].gcol < 0 || (a.gtab && a.segd[p].gcol < gmax));
   }
   if (a.seg_mode == 1) {
     ok = ok && a.nseg >= 1 && a.nseg <= 8 && a.E <= 128 && a.perm && a.segate && a.set_experts;
@@ -394,7 +422,7 @@ void launch_pp_row_gemm(const RowGemmArgs& a, hipStream_t s) {
     case TAG_V_DGRAD * 4 + 1: return launch_pp<true, TAG_V_DGRAD, 1>(a, s);
     case TAG_QK_DGRAD * 4 + 2: return launch_pp<true, TAG_QK_DGRAD, 2>(a, s);
     case TAG_O_EXPERTS * 4 + 3: return launch_pp<false, TAG_O_EXPERTS, 3>(a, s);
-    case TAG_QK_DGRAD * 4 + 3: return launch_pp<true, TAG_QK_DGRAD, 3>(a, s);
+    case TAG_QK_DGRAD * 4 + 3: return a.seg_q ? launch_pp<true, TAG_QK_DGRAD, 4>(a, s) : launch_pp<true, TAG_QK_DGRAD, 3>(a, s);
     default: return;
   }
 }

@@ -149,6 +149,20 @@ def test_bf16_weight_gradient_list(over, shared):
     run_case(cfg, shared=shared, seed=47, mutate=shun)
 
 
+@pytest.mark.parametrize("over, shared", [
+    (dict(B=5, T=1161), False),                       # a last tile of 173 rows
+    (dict(B=5, T=1160, T_q=1000), False),             # tiles with query rows of two sequences, query rows beside cached ones
+    (dict(B=3, T=2600, T_q=1300), True),              # tiles without any query row, one router over two token sets
+    (dict(B=5, T=1161, qk_experts=1), False),         # queries and keys over their experts, gates of either side
+    (dict(B=6, T=1000, T_q=961, qk_experts=1), True),
+])
+def test_bf16_gated_concatenation_forms(over, shared):
+    """One product for y and one for dx over every (head, expert): token counts that are no multiple of the tile, two token sets,
+    expert queries and keys."""
+    cfg = dict(dict(name="gated", dtype="bf16", d_model=2048, nheads=2, d_head=64, E=3, k=2, causal=1, bias0=0.0), **over)
+    run_case(cfg, shared=shared, seed=53)
+
+
 def test_fp32_shared_selection_and_dense_mode():
     run_case(small("c0"), shared=True)
     run_case(dict(name="dense", dtype="f32", B=2, T=48, d_model=64, nheads=4, d_head=16, E=1, k=1, causal=1, bias0=0.0),
