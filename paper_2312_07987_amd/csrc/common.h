@@ -66,6 +66,10 @@ struct RouterSelect {
   const void* x;                // bf16 [N][dm]
   const unsigned short* Wt;     // [side][H*E][dmp] router columns as vectors
   int N, kstep, H, E, k, dm, dmp;
+  // fewer queries than keys: side 1 routes the Nq rows of xq (0: the rows of x); its tables follow those of H * N tokens
+  const void* xq;
+  int Nq;
+  int shared;   // side 1 uses side 0's columns
 };
 
 // One segment of a concatenated reduction with per-row gates (segment mode 3): the segment's A columns start at
@@ -283,14 +287,29 @@ struct RouterArgs {
   // if not NULL (launch_router_hybrid without `sets`, both sides routed on the same N tokens): the dense gate table
   // [sides][N][H*E] is written along the histogram pass
   float* gtab;
+  // launch_router_hybrid with sides == 2: side 1 routes the Nq rows of xq instead (0: the same tokens).  Every side-1 table then starts
+  // where it would with N tokens.  shared: with the weights and the bias of side 0.
+  const void* xq;
+  int Nq, shared;
 };
 void launch_router(const RouterArgs& a, hipStream_t s);
+// Up to eight pieces of 4-byte elements copied by one launch (the destination side's tables where one selection serves both sides)
+struct CopyList {
+  int n;
+  const void* src[8];
+  void* dst[8];
+  size_t count[8];
+};
+void launch_copy_list(const CopyList& l, hipStream_t s);
 // bf16 storage: fp32 matrix-core logits with an fp64 re-evaluation of every decision that
 // is not provably safe (see routing.hip).  `scratch` needs router_hybrid_bytes() bytes.
 size_t router_hybrid_bytes(int N, int dm, int H, int E, size_t* off7);
 bool router_hybrid_supported(const RouterArgs& a);
 void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s);
-void launch_dense_routing(int* idx, float* gate, int* perm, int* offsets, int N, int H, hipStream_t s);
+// Dense attention: every token takes "expert" 0 with gate 1, on both sides (n0 and n1 tokens, the second side's tables behind those of
+// H * n0 tokens).  t (or NULL): the set tables to fill as well.
+void launch_dense_routing(int* idx, float* gate, int* perm, int* offsets, int n0, int n1, int H, const SetSortArgs* t, hipStream_t s);
+bool router_sides_supported(const RouterArgs& a);   // launch_router_hybrid takes the two token sets of `a` in one go
 int router_blocks(int N);  // token blocks used by the histogram/scatter kernels
 int router_count_blocks(int N);   // token blocks of the fp64 router's expert counts
 // gtab[side][n][h*E+e] = gate of the selected experts, 0 elsewhere (idx, gate: [side][H][N][k], sides side_stride_in apart)

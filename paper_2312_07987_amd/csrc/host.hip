@@ -653,7 +653,37 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
                          c.st) != hipSuccess)
       return fail(SH_ERR_HIP, "switchhead_forward: copy of the query rows failed");
     const int nblk = router_blocks(N), ns = count_sets(E, k);
-    for (int side = 0; side < 2; ++side) {
+    // (matrix-core router: both sides share its launches)
+    RouterArgs rs{};
+    rs.x = x;
+    rs.xq = xq;
+    rs.Nq = c.Nq;
+    rs.shared = c.shared;
+    rs.W[0] = W_S;
+    rs.W[1] = W_D;
+    rs.b[0] = b_S;
+    rs.b[1] = c.shared ? b_S : b_D;
+    rs.idx = c.idx(0);
+    rs.gate = c.gate(0);
+    rs.perm = c.perm(0);
+    rs.offsets = c.offsets(0);
+    rs.blockcnt = c.p<int>(c.L.blockcnt);
+    rs.N = N;
+    rs.dm = dm;
+    rs.H = H;
+    rs.E = E;
+    rs.k = k;
+    rs.sides = 2;
+    rs.bf16 = c.bf16;
+    if (tables) rs.sets = &sa;
+    if (gate_table) rs.gtab = c.p<float>(c.L.gtab);
+    const bool together = !c.dense && use_mfma(c) && router_sides_supported(rs);
+    if (together) {
+      launch_router_hybrid(rs, c.p<char>(c.L.rh), c.st);
+      gtab_done = true;
+    }
+    if (c.dense) launch_dense_routing(c.idx(0), c.gate(0), c.perm(0), c.offsets(0), N, c.Nq, H, tables ? &sa : nullptr, c.st);
+    for (int side = 0; side < (together || c.dense ? 0 : 2); ++side) {
       const int n = c.n(side);
       // this side's expert-set tables (the set sort of each side runs on its own tokens)
       SetSortArgs s1 = sa;
@@ -668,12 +698,6 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
         s1.blockcnt = sa.blockcnt + (size_t)side * H * nblk * ns;
         s1.N = n;
         s1.sides = 1;
-      }
-      if (c.dense) {
-        // (dense attention has one expert set, but the kernels of the set path still read its tables)
-        launch_dense_routing(c.idx(side), c.gate(side), c.perm(side), c.offsets(side), n, H, c.st);
-        if (tables) launch_set_sort(s1, c.st);
-        continue;
       }
       const bool own = side == 1 && !c.shared;   // the destination side's own router
       float* gtab_side = c.p<float>(c.L.gtab) + (size_t)side * N * H * E;
@@ -706,7 +730,9 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     }
     sets_sorted = true;
   } else if (c.dense) {
-    launch_dense_routing(c.idx(0), c.gate(0), c.perm(0), c.offsets(0), N, H, c.st);
+    // (dense attention has one expert set, but the kernels of the set path still read its tables)
+    launch_dense_routing(c.idx(0), c.gate(0), c.perm(0), c.offsets(0), N, N, H, tables ? &sa : nullptr, c.st);
+    sets_sorted = true;
   } else {
     RouterArgs ra{};
     ra.x = x;
@@ -727,7 +753,8 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     ra.sides = c.shared ? 1 : 2;
     ra.bf16 = c.bf16;
     if (use_mfma(c) && router_hybrid_supported(ra)) {
-      if (tables && !c.shared) {   // both sorts in the same launches
+      if (tables) {   // both sorts in the same launches
+        sa.sides = ra.sides;
         ra.sets = &sa;
         sets_sorted = true;
       } else if (gate_table && !c.shared) {   // the dense gate table rides along the histogram pass
@@ -739,13 +766,26 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
       launch_router(ra, c.st);
     }
   }
-  if ((c.dense || c.shared) && !c.rect) {
+  if (c.shared && !c.rect) {
     // one selection serves both sides: the destination tables repeat the source tables
-    const size_t n1 = (size_t)H * N * k * 4;
-    (void)hipMemcpyAsync(c.idx(1), c.idx(0), n1, hipMemcpyDeviceToDevice, c.st);
-    (void)hipMemcpyAsync(c.gate(1), c.gate(0), n1, hipMemcpyDeviceToDevice, c.st);
-    (void)hipMemcpyAsync(c.perm(1), c.perm(0), n1, hipMemcpyDeviceToDevice, c.st);
-    (void)hipMemcpyAsync(c.offsets(1), c.offsets(0), (size_t)H * (E + 1) * 4, hipMemcpyDeviceToDevice, c.st);
+    CopyList l{};
+    auto add = [&](const void* src, void* dst, size_t count) {
+      l.src[l.n] = src;
+      l.dst[l.n] = dst;
+      l.count[l.n++] = count;
+    };
+    const size_t n1 = (size_t)H * N * k;
+    add(c.idx(0), c.idx(1), n1);
+    add(c.gate(0), c.gate(1), n1);
+    add(c.perm(0), c.perm(1), n1);
+    add(c.offsets(0), c.offsets(1), (size_t)H * (E + 1));
+    if (tables && sets_sorted) {
+      const size_t ns = count_sets(E, k);
+      add(sa.gsort, sa.gsort + n1, n1);
+      add(sa.setperm, sa.setperm + (size_t)H * N, (size_t)H * N);
+      add(sa.setoff, sa.setoff + H * (ns + 1), H * (ns + 1));
+    }
+    launch_copy_list(l, c.st);
   }
 
   if (tables && !sets_sorted) {

@@ -85,9 +85,10 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
       if (row0 >= end) return;
       rows = end - row0 < BM ? end - row0 : BM;
     } else {
+      const int M = TAG == TAG_ROUTER && h == 1 && a.rsel.Nq > 0 ? a.rsel.Nq : a.M;
       row0 = w * BM;
-      if (row0 >= a.M) return;
-      rows = a.M - row0 < BM ? a.M - row0 : BM;
+      if (row0 >= M) return;
+      rows = M - row0 < BM ? M - row0 : BM;
     }
   }
   const bool second = a.hsplit > 0 && h >= a.hsplit;
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
   }
   __syncthreads();
 
-  const unsigned short* A = (const unsigned short*)a.A;
+  const unsigned short* A = (const unsigned short*)(TAG == TAG_ROUTER && h == 1 && a.rsel.Nq > 0 ? a.rsel.xq : a.A);
   const unsigned short* Bbase = (const unsigned short*)(second ? a.B2 : a.B);
   const unsigned short* B = Bbase + (SEG ? 0 : (long)hh * a.b_hstride + (long)e * a.b_estride);
   const int n0 = ct * BN;

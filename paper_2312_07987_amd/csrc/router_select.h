@@ -102,7 +102,12 @@ __device__ __forceinline__ void recheck_entry(const unsigned short* __restrict__
 //   zs, flist, nflag: LDS scratch (4 x 64 doubles, 256 ints, 1 int; nflag = 0 on entry)
 __device__ __forceinline__ void router_select_tile(const RouterSelect& r, int side, const double* zt, int HEp, const float* rs,
                                                    const int* ids, int rows, double (*zs)[64], int* flist, int* nflag) {
-  const int H = r.H, E = r.E, k = r.k, N = r.N;
+  const int H = r.H, E = r.E, k = r.k;
+  const bool own = side && r.Nq > 0;             // side 1 with tokens of its own
+  const int N = own ? r.Nq : r.N;
+  const long out0 = (long)side * H * r.N;
+  const void* x = own ? r.xq : r.x;
+  const int wside = r.shared ? 0 : side;         // whose columns
   const float* b = r.b[side];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int item0 = 0; item0 < rows * H; item0 += 256) {
@@ -110,13 +115,13 @@ __device__ __forceinline__ void router_select_tile(const RouterSelect& r, int si
     const int nl = item / H, h = item % H;
     const int n = item < rows * H ? ids[nl] : -1;
     if (n >= 0) {
-      const int sh_ = side * H + h;
+      const int sh_ = wside * H + h;
       const double* z = zt + nl * HEp + h * E;
       float w2 = 0.f;   // largest squared column norm of this head's router
       for (int e = 0; e < E; ++e) w2 = fmaxf(w2, r.wnorm2[(long)sh_ * E + e]);
       const double bound0 = 4.0 * (double)r.kstep * 5.9604645e-8 * (double)(sqrtf(rs[nl]) * 1.0001f) * (double)(sqrtf(w2) * 1.0001f);
       unsigned long long sel = 0ull;
-      const long o = ((long)sh_ * N + n) * k;
+      const long o = (out0 + (long)h * N + n) * k;
       double prev = 0.0, bprev = 0.0;
       bool flag = false;
       const int passes = k < E ? k + 1 : k;
@@ -150,13 +155,13 @@ __device__ __forceinline__ void router_select_tile(const RouterSelect& r, int si
     for (int f = wave; f < nf; f += 4) {
       const int it = flist[f];
       const int fl = it / H, h = it % H, n = ids[fl];
-      const int sh_ = side * H + h;
-      const long o = ((long)sh_ * N + n) * k;
+      const int sh_ = wside * H + h;
+      const long o = (out0 + (long)h * N + n) * k;
       float w2 = 0.f;
       for (int e = 0; e < E; ++e) w2 = fmaxf(w2, r.wnorm2[(long)sh_ * E + e]);
       // twice d_model * 2^-53 * |x| * max|w|, doubled again for the rounding of the norms themselves
       const double reorder = 4.0 * (double)r.dm * 1.1102230246251565e-16 * (double)sqrtf(rs[fl]) * (double)sqrtf(w2);
-      recheck_entry((const unsigned short*)r.x + (long)n * r.dm, r.Wt + ((long)side * HE + h * E) * r.dmp, b ? b + h * E : nullptr,
+      recheck_entry((const unsigned short*)x + (long)n * r.dm, r.Wt + ((long)wside * HE + h * E) * r.dmp, b ? b + h * E : nullptr,
                     zs[wave], r.idx + o, r.gate + o, r.dm, r.dmp, E, k, lane, reorder);
     }
     __syncthreads();

@@ -277,18 +277,45 @@ __global__ __launch_bounds__(RB) void scatter_kernel(const int* __restrict__ idx
   scatter_body(idx, base, perm, N, E, k, nblk, nullptr, per);
 }
 
-__global__ void dense_routing_kernel(int* idx, float* gate, int* perm, int* offsets, int N, int H) {
-  long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  long tot = (long)H * N;
-  if (i < tot) {
-    idx[i] = 0;
-    gate[i] = 1.0f;
-    perm[i] = (int)(i % N);
+__global__ void dense_routing_kernel(int* idx, float* gate, int* perm, int* offsets, int n0, int n1, int H, int* setperm, float* gsort,
+                                     int* setoff, int* setexp) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int side = blockIdx.y, N = side ? n1 : n0;
+  const long at = (long)side * H * n0 + i;
+  if (i < (long)H * N) {
+    const int n = (int)(i % N);
+    idx[at] = 0;
+    gate[at] = 1.0f;
+    perm[at] = n;
+    if (setperm) {
+      setperm[at] = n;
+      gsort[at] = 1.0f;
+    }
   }
   if (i < H) {
-    offsets[2 * i] = 0;
-    offsets[2 * i + 1] = N;
+    const long o = (side * (long)H + i) * 2;
+    offsets[o] = 0;
+    offsets[o + 1] = N;
+    if (setperm) {
+      setoff[o] = 0;
+      setoff[o + 1] = N;
+    }
   }
+  if (setperm && i == 0) setexp[0] = 0;
+}
+
+__global__ __launch_bounds__(256) void copy_list_kernel(CopyList l) {
+  const unsigned* src = (const unsigned*)l.src[blockIdx.y];
+  unsigned* dst = (unsigned*)l.dst[blockIdx.y];
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < l.count[blockIdx.y]; i += (size_t)gridDim.x * 256) dst[i] = src[i];
+}
+
+void launch_copy_list(const CopyList& l, hipStream_t s) {
+  size_t mx = 0;
+  for (int i = 0; i < l.n; ++i) mx = l.count[i] > mx ? l.count[i] : mx;
+  if (!mx) return;
+  const size_t b = (mx + 255) / 256;
+  copy_list_kernel<<<dim3((unsigned)(b < 256 ? b : 256), l.n), 256, 0, s>>>(l);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -637,9 +664,49 @@ void launch_set_sort(const SetSortArgs& a, hipStream_t s) {
   set_scatter_kernel<<<g, RB, 0, s>>>(a.setid, a.blockcnt, a.setperm, a.gset, a.gsort, a.N, a.k, a.nsets, nblk);
 }
 
-void launch_dense_routing(int* idx, float* gate, int* perm, int* offsets, int N, int H, hipStream_t s) {
-  long tot = (long)H * N;
-  dense_routing_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>(idx, gate, perm, offsets, N, H);
+void launch_dense_routing(int* idx, float* gate, int* perm, int* offsets, int n0, int n1, int H, const SetSortArgs* t, hipStream_t s) {
+  const long tot = (long)H * (n0 > n1 ? n0 : n1);
+  dense_routing_kernel<<<dim3((unsigned)((tot + 255) / 256), 2), 256, 0, s>>>(idx, gate, perm, offsets, n0, n1, H, t ? t->setperm : nullptr,
+                                                                              t ? t->gsort : nullptr, t ? t->setoff : nullptr, t ? t->setexp : nullptr);
+}
+
+// Both sides' sorts where the sides have tokens of their own (fewer queries than keys): the passes above with the side as a grid
+// dimension.  One side after the other is two chains of four launches that wait for memory most of the time (eight sequences of
+// 1000 keys and one query: 94 us for both sides, a third of the call).
+struct SidesArgs {
+  const int* idx;
+  const float* gate;
+  int *blockcnt, *perm, *offsets;
+  float* gtab;
+  SetSortArgs t;   // t.setid NULL: no set tables
+  int N[2], nblk[2], H, E, k;
+};
+__global__ __launch_bounds__(RB) void hist_sides_kernel(SidesArgs a) {
+  const int side = blockIdx.z, N = a.N[side], nblk = a.nblk[side];
+  if ((int)blockIdx.x >= nblk) return;
+  const long at = (long)side * a.H * a.N[0], cat = (long)side * a.H * a.nblk[0];
+  hist_body(a.idx + at * a.k, a.blockcnt + cat * a.E, N, a.E, a.k, nblk);
+  if (a.t.setid)
+    set_hist_body(a.idx + at * a.k, a.gate + at * a.k, a.t.setid + at, a.t.gset + at * a.k, a.t.setexp, a.t.blockcnt + cat * a.t.nsets, N, a.k,
+                  a.E, a.t.nsets, nblk);
+  if (a.gtab) gate_row_body(a.idx + at * a.k, a.gate + at * a.k, a.gtab + at * a.E, N, a.H, a.E, a.k);
+}
+__global__ __launch_bounds__(RB) void scan_scatter_sides_kernel(SidesArgs a) {
+  __shared__ int sb[2][2 * 128 + 1];
+  const int side = blockIdx.z, N = a.N[side], nblk = a.nblk[side];
+  if ((int)blockIdx.x >= nblk) return;
+  const long at = (long)side * a.H * a.N[0], cat = (long)side * a.H * a.nblk[0];
+  block_bases(a.blockcnt + cat * a.E, a.offsets + (long)side * a.H * (a.E + 1), a.E, nblk, sb[0]);
+  if (a.t.setid) block_bases(a.t.blockcnt + cat * a.t.nsets, a.t.setoff + (long)side * a.H * (a.t.nsets + 1), a.t.nsets, nblk, sb[1]);
+  scatter_body<true>(a.idx + at * a.k, nullptr, a.perm + at * a.k, N, a.E, a.k, nblk, sb[0]);
+  if (!a.t.setid) return;
+  __syncthreads();
+  set_scatter_body<true>(a.t.setid + at, nullptr, a.t.setperm + at, a.t.gset + at * a.k, a.t.gsort + at * a.k, N, a.k, a.t.nsets, nblk, sb[1]);
+}
+
+bool router_sides_supported(const RouterArgs& a) {
+  const long nblk = router_blocks(a.N), bins = a.sets && a.sets->nsets > a.E ? a.sets->nsets : a.E;
+  return router_hybrid_supported(a) && ((uintptr_t)a.xq % 16) == 0 && nblk * bins <= 8192;   // (small tables, as below)
 }
 
 void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s) {
@@ -653,7 +720,7 @@ void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s) {
 
   // per (side, head): largest column norm, columns copied out as vectors and
   // into the padded matrix the GEMM reads
-  router_prep_kernel<<<a.sides * a.H * a.E, 256, 0, s>>>((const bf16_t*)a.W[0], (const bf16_t*)a.W[1], wmax, Wt,
+  router_prep_kernel<<<(a.shared ? 1 : a.sides) * a.H * a.E, 256, 0, s>>>((const bf16_t*)a.W[0], (const bf16_t*)a.W[1], wmax, Wt,
                                                    (unsigned short*)Wp, a.dm, dmp, a.H, a.E, HEp);
   // stage 1: z32 = x W on the matrix cores, fp32 accumulation, both sides in one launch; the selection
   // (and the fp64 recheck of its doubtful entries) is that kernel's epilogue
@@ -666,7 +733,7 @@ void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s) {
   g.A = a.x;
   g.lda = a.dm;
   g.B = Wp;
-  g.b_hstride = (long)a.dm * HEp;
+  g.b_hstride = a.shared ? 0 : (long)a.dm * HEp;
   g.sbk = HEp;
   g.sbn = 1;
   g.C = nullptr;   // nothing is stored: the selection consumes the logits inside the kernel
@@ -688,7 +755,31 @@ void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s) {
   g.rsel.k = a.k;
   g.rsel.dm = a.dm;
   g.rsel.dmp = dmp;
+  g.rsel.xq = a.xq;
+  g.rsel.Nq = a.Nq;
+  g.rsel.shared = a.shared;
   launch_mfma_row_gemm(g, s);
+  if (a.Nq > 0) {
+    SidesArgs d{};
+    d.idx = a.idx;
+    d.gate = a.gate;
+    d.blockcnt = a.blockcnt;
+    d.perm = a.perm;
+    d.offsets = a.offsets;
+    d.gtab = a.gtab;
+    if (a.sets) d.t = *a.sets;
+    d.N[0] = a.N;
+    d.N[1] = a.Nq;
+    d.nblk[0] = router_blocks(a.N);
+    d.nblk[1] = router_blocks(a.Nq);
+    d.H = a.H;
+    d.E = a.E;
+    d.k = a.k;
+    const dim3 gs(d.nblk[0], a.H, 2);
+    hist_sides_kernel<<<gs, RB, 0, s>>>(d);
+    scan_scatter_sides_kernel<<<gs, RB, 0, s>>>(d);
+    return;
+  }
 
   const int nblk = router_blocks(a.N);
   dim3 g2(nblk, a.sides * a.H);

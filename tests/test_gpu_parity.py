@@ -163,6 +163,20 @@ def test_bf16_gated_concatenation_forms(over, shared):
     run_case(cfg, shared=shared, seed=53)
 
 
+@pytest.mark.parametrize("over, how", [
+    (dict(T=520, T_q=1), "own"),                      # three blocks of source tokens, one of destination tokens
+    (dict(T=257, T_q=256), "shared"),
+    (dict(T=300, T_q=7, E=8, k=2), "own"),
+    (dict(T=300), "shared"),                          # one selection: all of the destination side's tables are copies
+    (dict(T=300, T_q=44, E=1, k=1), "dense"),
+    (dict(T=300, E=1, k=1), "dense"),
+])
+def test_bf16_routing_tables_of_both_sides(over, how):
+    """Both sides' selections and sorts in shared launches, tables copied or filled directly."""
+    cfg = dict(dict(name="sides", dtype="bf16", B=2, d_model=128, nheads=3, d_head=32, E=4, k=2, causal=1, bias0=0.0), **over)
+    run_case(cfg, shared=how == "shared", dense=how == "dense", seed=59)
+
+
 def test_fp32_shared_selection_and_dense_mode():
     run_case(small("c0"), shared=True)
     run_case(dict(name="dense", dtype="f32", B=2, T=48, d_model=64, nheads=4, d_head=16, E=1, k=1, causal=1, bias0=0.0),
