@@ -431,6 +431,9 @@ void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s);
 // 256 x 256 tiles, eight waves in two alternating groups (mfma_pp.hip); launch_mfma_row_gemm routes to it
 bool pp_row_gemm_supported(const RowGemmArgs& a);
 void launch_pp_row_gemm(const RowGemmArgs& a, hipStream_t s);
+// 32 x 32 tiles for launches of a few rows (mfma_skinny.hip); launch_mfma_row_gemm routes to it
+bool skinny_row_gemm_supported(const RowGemmArgs& a);
+void launch_skinny_row_gemm(const RowGemmArgs& a, hipStream_t s);
 bool mfma_wgrad_supported(const WgradArgs& a);
 void launch_mfma_wgrad(const WgradArgs& a, hipStream_t s);
 bool mfma_attn_supported(int T, int dh);

@@ -512,6 +512,7 @@ static void launch_generic(const RowGemmArgs& a, hipStream_t s) {
 void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.Nc <= 0) return;
   if (pp_row_gemm_supported(a)) return launch_pp_row_gemm(a, s);
+  if (skinny_row_gemm_supported(a)) return launch_skinny_row_gemm(a, s);
   const int vec = row_gemm_vec(a);
   const bool nt = a.sbk == 1;
   if (vec == 8) {

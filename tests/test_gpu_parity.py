@@ -177,6 +177,18 @@ def test_bf16_routing_tables_of_both_sides(over, how):
     run_case(cfg, shared=how == "shared", dense=how == "dense", seed=59)
 
 
+@pytest.mark.parametrize("over", [
+    dict(T=33, d_model=1024, d_head=128),                        # one row past a tile
+    dict(T=65, d_model=1000, d_head=72, E=5, k=3),               # a reduction that no wave's share divides, a last tile of 8 columns
+    dict(T=70, d_model=2056, d_head=40, qk_experts=1),           # more than one trip per wave
+    dict(T=40, d_model=24, d_head=8),                            # waves without any share
+    dict(T=300, d_model=264, d_head=64, T_q=3, causal=0),        # three query rows per sequence
+])
+def test_bf16_projections_of_a_few_rows(over):
+    """The 32 x 32 tiles of short calls at the edges of their rows, columns and shares of the reduction."""
+    run_case(dict(dict(name="few", dtype="bf16", B=1, nheads=2, E=4, k=2, causal=1, bias0=0.0), **over), seed=61)
+
+
 def test_fp32_shared_selection_and_dense_mode():
     run_case(small("c0"), shared=True)
     run_case(dict(name="dense", dtype="f32", B=2, T=48, d_model=64, nheads=4, d_head=16, E=1, k=1, causal=1, bias0=0.0),
