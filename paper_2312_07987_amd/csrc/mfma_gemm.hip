@@ -49,6 +49,8 @@ typedef TileCfg<4, 1, 1, 3, 64, 1> CfgN96;      // 128 x 96, wave tile 32 x 96: 
                                                 // waste a fifth of a 96-wide tile instead of two fifths of a 128-wide one
 typedef TileCfg<2, 2, 1, 1, 64, 1> CfgRouter;   // 64 x 64: the router logits have <= 32 columns and want many work-groups (a K step of
                                                 // 256, four times the bytes per load round trip but one work-group per CU: 35 -> 50 us at c2)
+typedef TileCfg<2, 2, 1, 1, 64, 4> CfgRouterDeep;   // the same for launches of at most one work-group per CU: four K steps per trip to memory
+                                                    // (a K loop of d_model 1024 is sixteen trips otherwise: a 100-token call 92 -> 89.6 us)
 typedef TileCfg<2, 2, 2, 4, 64, 1, 2> CfgWide;     // 128 x 256, wave tile 64 x 128, two work-groups per CU
 typedef TileCfg<2, 2, 4, 2, 64, 1, 2> CfgMed;   // 256 x 128, wave tile 128 x 64, two work-groups per CU
 
@@ -294,6 +296,46 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
         __syncthreads();
       }
     }
+  } else if constexpr (Cfg::STAGES == 4) {
+    // four K steps travel together; loads without conditions (clamped, what must not count is zeroed on its way into LDS)
+    static_assert(SEG == 0 && !BNT, "the router's launch");
+    chunk_t da[4][A_N], db[4][B_N];
+    auto load4 = [&](int it) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k0 = (it + u) * BK;
+#pragma unroll
+        for (int i = 0; i < A_N; ++i) da[u][i] = *(const chunk_t*)(A + (a_off[i] >= 0 ? a_off[i] : 0l) + min(k0, K - VEC - a_kc[i]));
+#pragma unroll
+        for (int i = 0; i < B_N; ++i) db[u][i] = *(const chunk_t*)(B + (b_ok[i] ? b_off[i] : (long)b_kc[i] * a.sbk) + (long)min(k0, K - 1 - b_kc[i]) * a.sbk);
+      }
+    };
+    auto store4 = [&](int it) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        unsigned short* As = smem + u * Cfg::STAGE_ELEMS;
+        unsigned short* Bs = As + Cfg::A_ELEMS;
+        const int k0 = (it + u) * BK;
+#pragma unroll
+        for (int i = 0; i < A_N; ++i) {
+          const chunk_t v = a_off[i] >= 0 && k0 + a_kc[i] < K ? da[u][i] : zero_chunk<VEC>();
+          *(chunk_t*)(&As[a_lds[i]]) = v;
+          if constexpr (TAG == TAG_ROUTER) sumsq[i] += chunk_sumsq(v);
+        }
+#pragma unroll
+        for (int i = 0; i < B_N; ++i) *(chunk_t*)(&Bs[b_lds[i]]) = b_ok[i] && k0 + b_kc[i] < K ? db[u][i] : zero_chunk<VEC>();
+      }
+    };
+    load4(0);
+    for (int kt = 0; kt < nk; kt += 4) {
+      store4(kt);
+      __syncthreads();
+      if (kt + 4 < nk) load4(kt + 4);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (active) compute(u);   // (steps past the last are zeros)
+      __syncthreads();
+    }
   } else {
     // two LDS stages: K step kt is multiplied from stage kt&1 while step kt+2 travels
     // global -> registers; it is written into the stage just consumed
@@ -509,6 +551,15 @@ static void launch_generic(const RowGemmArgs& a, hipStream_t s) {
     launch_generic_cfg<CfgSmall, VEC, BNT>(a, s);
 }
 
+template <int VEC>
+static void launch_router_logits(const RowGemmArgs& a, hipStream_t s) {
+  const long rows = a.rsel.Nq > 0 && a.heads == 2 ? (a.M + 63) / 64 + (a.rsel.Nq + 63) / 64 : (long)a.heads * ((a.M + 63) / 64);
+  if (rows <= 256 && a.K >= 64)   // at most one tile per CU: nothing else hides the trips to memory
+    launch_cfg<CfgRouterDeep, VEC, false, TAG_ROUTER, 0>(a, s);
+  else
+    launch_cfg<CfgRouter, VEC, false, TAG_ROUTER, 0>(a, s);
+}
+
 void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.Nc <= 0) return;
   if (pp_row_gemm_supported(a)) return launch_pp_row_gemm(a, s);
@@ -532,14 +583,14 @@ void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s) {
         case TAG_V_EXPERTS * 4 + 0: return launch_tagged<false, TAG_V_EXPERTS, 0>(a, s);
         case TAG_O_EXPERTS * 4 + 0: return launch_tagged<false, TAG_O_EXPERTS, 0>(a, s);
         case TAG_O_EXPERTS * 4 + 1: return launch_tagged<false, TAG_O_EXPERTS, 1>(a, s);
-        case TAG_ROUTER * 4 + 0: return launch_cfg<CfgRouter, 8, false, TAG_ROUTER, 0>(a, s);
+        case TAG_ROUTER * 4 + 0: return launch_router_logits<8>(a, s);
         default: return launch_generic<8, false>(a, s);
       }
     }
   }
   if (nt)
     return launch_generic<4, true>(a, s);
-  if (a.tag == TAG_ROUTER) return launch_cfg<CfgRouter, 4, false, TAG_ROUTER, 0>(a, s);
+  if (a.tag == TAG_ROUTER) return launch_router_logits<4>(a, s);
   return launch_generic<4, false>(a, s);
 }
 
