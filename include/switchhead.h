@@ -192,6 +192,8 @@ sh_status switchhead_forward_static(const sh_shape* shape,
  *            dW_S, dW_D, db_S, db_D may be NULL when not wanted; dW_D/db_D are ignored
  *            with shared selection (dW_S then holds the sum of both sides) and all four
  *            are ignored in dense mode.
+ *            dx may be the same buffer as dy where their shapes agree (square attention): dy is
+ *            read to the end before dx is written.  Other outputs must not overlap inputs.
  * Determinism: with bf16 storage and the matrix-core kernels, dW_Q, dW_K, dW_V, dW_O are
  * sums of per-chunk partial results added in a fixed order (bit-identical from run to run),
  * and so are the router gradients dW_S, dW_D, db_S, db_D where they ride along the query/key

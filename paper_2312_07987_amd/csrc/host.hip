@@ -1318,6 +1318,15 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
     use_list = wgrad_list_supported(wl) && wgrad_list_partial_floats(wl) <= c.L.wpart_floats;
     list_router = list_router && use_list;
   }
+  // The list reads dy, so it runs before the launch that writes dx: dx may lie where dy lies.  (It needs the routers' dz and
+  // nothing of dx; bf16 sums of dx that several launches share are kept in the workspace until the last of them.)
+  bool list_done = false;
+  auto run_list = [&] {
+    if (!use_list || list_done) return;
+    list_done = true;
+    prof_mark(c.st, "bwd.wgrads");
+    launch_wgrad_list(wl, c.st);   // marks its reduction itself
+  };
   if (!f32_tail && !use_list) {
     prof_mark(c.st, "bwd.o_wgrad");
     wgrad(c, o_wgrad_args());
@@ -1877,9 +1886,19 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       rb.wide_width = dh;
     }
     launch_router_bwd(rb, c.bf16, c.st);
+    if (list_router) {
+      wl.dbpart = dbpart;
+      wl.db0 = dbs[0];
+      wl.db1 = dbs[1];
+      wl.db_nblk = rblk;
+      wl.db_E = E;
+      wl.db_HE = HE;
+      wl.db_sides = sides;
+    }
     const size_t esz = c.bf16 ? 2 : 4;
     const char* dz0 = c.p<char>(wide_dz ? c.L.dR : c.L.dz);
     if (fuse_router && merged_dx) {
+      run_list();
       prof_mark(c.st, "bwd.dx_gemm");
       launch_pp_row_gemm(merged_dx_args(true), c.st);
       router_fused = true;
@@ -1890,17 +1909,8 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       run_qk_wgrad(true);
       prof_mark(c.st, "bwd.router_wsplit");
       launch_router_wgrad_split(c.p<float>(c.L.wrt), dWs[0], dWs[1], dm, dh, HE, HEp, dbpart, rblk, E, dbs[0], dbs[1], c.st);
-    } else if (list_router) {
-      wl.dbpart = dbpart;
-      wl.db0 = dbs[0];
-      wl.db1 = dbs[1];
-      wl.db_nblk = rblk;
-      wl.db_E = E;
-      wl.db_HE = HE;
-      wl.db_sides = sides;
-    } else
-    // dW_S / dW_D = x^T dz: one launch for both sides when both are wanted
-    {
+    } else if (!list_router) {
+      // dW_S / dW_D = x^T dz: one launch for both sides when both are wanted
       WgradArgs w{};
       w.E = 1;
       w.M = N;
@@ -1996,6 +2006,7 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       }
     }
   }
+  run_list();
   if (merged_dx && (c.dense || c.rect)) {
     prof_mark(c.st, "bwd.dx_gemm");
     launch_pp_row_gemm(merged_dx_args(!c.dense), c.st);
@@ -2010,10 +2021,6 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
   if (c.rect && !merged_dx) {
     prof_mark(c.st, "bwd.dx_query_rows");
     launch_add_query_rows(dx, accq, Nq, shape->T, c.Tq, dm, c.bf16, c.st);
-  }
-  if (use_list) {
-    prof_mark(c.st, "bwd.wgrads");
-    launch_wgrad_list(wl, c.st);   // marks its reduction itself
   }
   prof_mark(c.st, nullptr);
   return check_launch("switchhead_backward");
