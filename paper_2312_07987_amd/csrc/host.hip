@@ -141,10 +141,14 @@ bool gated_shape(const sh_shape* s) {
   if (s->dtype != SH_BF16 || s->d_head % 64 != 0 || s->d_model % 256 != 0 || N < 2048 || Nq < 2048 || dx_segs > MAX_SEGD || E > 2 * k) return false;
   // (two token sets: the routers' dz rows of both sides lie next to each other in rows of H * d_head)
   if (rect && (H < 2 || HEp > s->d_head)) return false;
+  // Whole tiles, dense queries and keys, at most 40 segments: y and dx are one fp32 accumulator rounded once, whatever it costs (the sets
+  // below would be faster up to about 9000 tokens, but round a partial sum of every head to bf16).
+  if (!rect && !s->qk_experts && N % 256 == 0 && dx_segs <= 40) return true;
   // One work-group per CU: a launch costs whole rounds of 256 tiles times its segments (4.4 us a round and segment of 128, measured at
   // 256 tiles).  The expert-set path costs its selected segments, partial sums and their addition per tile (11.8 us for 256
   // tiles), so it is the better one where the last round is mostly empty.  A training step over B x 512 tokens of d_model
-  // 1024, 4 heads of 128, 3 of 5 experts: B = 4 479 us gated, 338 by sets; B = 8 468 and 402; the lines meet near B = 18.
+  // 1024, 4 heads of 128, 3 of 5 experts: B = 4 479 us gated, 338 by sets; B = 8 468 and 402; the lines meet near B = 18.  The forms
+  // that come this far have bf16 partials of the heads by sets and one accumulator here: either is good enough, so the faster one.
   const long cols = s->d_model / 256;
   auto rounds = [&](long rows) { return ((rows + 255) / 256 * cols + 255) / 256; };
   const long gated = rounds(Nq) * H * E + rounds(N) * dx_segs;

@@ -43,3 +43,35 @@ def test_dx_in_the_place_of_dy(over, dense):
         # (the same launches on the same values: what is not equal bit for bit was added atomically, in another order)
         e = nerr(runs[1][n], ref)
         assert e < 1e-5, (n, e)
+
+
+@pytest.mark.parametrize("B", [4, 16])
+@pytest.mark.parametrize("what", ["y", "dx"])
+def test_heads_are_summed_in_fp32(B, what):
+    """B x 512 tokens (whole 256-row tiles): y and dx are one fp32 accumulator over the heads, rounded once.  Two heads with the same
+    router, queries, keys and (for y) values, whose output (for dx: value) experts are opposite up to one sixteenth: the sum is a
+    sixteenth of what each head adds, so partial sums rounded to bf16 (2^-9 of a head's share each) would show as 2^-5 of the
+    result, twice the bar and more; the accumulator leaves the rounding of the operands, which the two heads have in common."""
+    cfg = _cfg(B=B, T=512, d_model=1024, nheads=2, d_head=128, E=5, k=3)
+    t = make_inputs(cfg, seed=103)
+    for n in ("W_S", "W_D"):
+        t[n][:, cfg["E"]:] = t[n][:, :cfg["E"]]
+    for n in ("W_Q", "W_K", "W_V", "W_O"):
+        t[n][1] = t[n][0]
+    other = "W_O" if what == "y" else "W_V"
+    if what == "dx":   # the shares of the queries, keys and routers have nothing to cancel: keep them small
+        for n in ("W_Q", "W_K", "W_S", "W_D"):
+            t[n] = round_to_bf16(t[n] * np.float32(2.0 ** -8))
+    noise = np.random.default_rng(5).standard_normal(t[other][1].shape).astype(np.float32) * np.std(t[other][0]) / 16
+    t[other][1] = round_to_bf16(noise - t[other][0])
+    layer = _layer(cfg, t)
+    layer.forward()
+    layer.backward()
+    f = orc.forward(t["x"], t["W_Q"], t["W_K"], t["W_V"], t["W_O"], t["W_S"], t["W_D"], t["b_S"], t["b_D"], k=cfg["k"], causal=True)
+    got, ref = layer.outputs(), f["y"]
+    if what == "dx":
+        got = layer.grads()["dx"]
+        ref = orc.backward(t["x"], t["W_Q"], t["W_K"], t["W_V"], t["W_O"], t["W_S"], t["W_D"], f, t["dy"])["dx"]
+    e = float(np.sqrt(np.sum((got - ref) ** 2) / np.sum(ref ** 2)))
+    print("  %s relative error %.3e" % (what, e), flush=True)
+    assert e < 1e-2
