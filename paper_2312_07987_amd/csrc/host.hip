@@ -144,6 +144,9 @@ bool gated_shape(const sh_shape* s) {
   // Whole tiles, dense queries and keys, at most 40 segments: y and dx are one fp32 accumulator rounded once, whatever it costs (the sets
   // below would be faster up to about 9000 tokens, but round a partial sum of every head to bf16).
   if (!rect && !s->qk_experts && N % 256 == 0 && dx_segs <= 40) return true;
+  // The other forms only where the backward pass can make dx one product as well: a row of d_head holds both routers' dz.  Without it dx
+  // would be fp32 atomics and passes over an accumulator, and there are no set tables to fall back on.
+  if (!rect && 2 * HEp > s->d_head) return false;
   // One work-group per CU: a launch costs whole rounds of 256 tiles times its segments (4.4 us a round and segment of 128, measured at
   // 256 tiles).  The expert-set path costs its selected segments, partial sums and their addition per tile (11.8 us for 256
   // tiles), so it is the better one where the last round is mostly empty.  A training step over B x 512 tokens of d_model

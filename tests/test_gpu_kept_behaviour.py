@@ -14,6 +14,18 @@ def _cfg(**over):
     return dict(dict(name="kept", dtype="bf16", causal=1, bias0=0.0, qk_experts=0), **over)
 
 
+def _steps(layer):
+    """Labels of the steps that a forward and a backward call run."""
+    from paper_2312_07987_amd import binding
+    binding.switchhead_profile_enable(1)
+    try:
+        layer.forward()
+        layer.backward()
+        return set(binding.switchhead_profile_read())
+    finally:
+        binding.switchhead_profile_enable(0)
+
+
 def _layer(cfg, t, dense=False):
     from paper_2312_07987_amd.runner import DeviceLayer
     print("case", cfg, flush=True)
@@ -75,3 +87,18 @@ def test_heads_are_summed_in_fp32(B, what):
     e = float(np.sqrt(np.sum((got - ref) ** 2) / np.sum(ref ** 2)))
     print("  %s relative error %.3e" % (what, e), flush=True)
     assert e < 1e-2
+
+
+@pytest.mark.parametrize("nheads, E, k", [(8, 5, 3), (4, 9, 5)])
+def test_many_narrow_heads_keep_the_expert_sets(nheads, E, k):
+    """Two routers whose logits do not fit into one row of d_head (2 * 40 columns, heads of 64): dx cannot be one product over
+    every (head, expert), so both passes run by expert sets, with sums in a fixed order and no accumulator to clear."""
+    cfg = _cfg(B=10, T=520, d_model=2048, nheads=nheads, d_head=64, E=E, k=k)
+    run_case(cfg, seed=107)
+    layer = _layer(cfg, make_inputs(cfg, seed=107))
+    steps = _steps(layer)
+    assert "fwd.y_sum" in steps and not steps & {"fwd.y_zero", "fwd.y_cast", "bwd.dx_zero"}, steps
+    first = layer.dx.clone()
+    layer.dx.zero_()
+    layer.backward()
+    assert bool((layer.dx == first).all())
