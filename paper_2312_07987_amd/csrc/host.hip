@@ -147,6 +147,9 @@ bool gated_shape(const sh_shape* s) {
   // The other forms only where the backward pass can make dx one product as well: a row of d_head holds both routers' dz.  Without it dx
   // would be fp32 atomics and passes over an accumulator, and there are no set tables to fall back on.
   if (!rect && 2 * HEp > s->d_head) return false;
+  // The gates scale an operand that is then rounded to bf16.  That is what the sets do as well; but query experts over two token sets, and
+  // everything where there are too many sets, multiply an fp32 result by the gate, and keep doing so.
+  if ((rect && s->qk_experts) || count_sets(s->E, s->k) > MAX_SETS) return false;
   // One work-group per CU: a launch costs whole rounds of 256 tiles times its segments (4.4 us a round and segment of 128, measured at
   // 256 tiles).  The expert-set path costs its selected segments, partial sums and their addition per tile (11.8 us for 256
   // tiles), so it is the better one where the last round is mostly empty.  A training step over B x 512 tokens of d_model

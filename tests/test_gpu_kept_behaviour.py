@@ -102,3 +102,16 @@ def test_many_narrow_heads_keep_the_expert_sets(nheads, E, k):
     layer.dx.zero_()
     layer.backward()
     assert bool((layer.dx == first).all())
+
+
+@pytest.mark.parametrize("over, steps", [
+    (dict(B=6, T=1000, T_q=961, d_model=2048, nheads=2, d_head=64, E=3, k=2, qk_experts=1), {"bwd.q_dgrad_e"}),
+    (dict(B=6, T=1000, d_model=2048, nheads=4, d_head=128, E=10, k=5), {"fwd.y_cast", "bwd.v_dgrad"}),   # 252 sets
+])
+def test_gates_scale_fp32_results_where_they_did(over, steps):
+    """Query experts over two token sets, and shapes with more expert sets than the tables hold: the gate multiplies the fp32 result of
+    a product, not an operand that is rounded to bf16 afterwards."""
+    cfg = _cfg(**over)
+    run_case(cfg, seed=109)
+    got = _steps(_layer(cfg, make_inputs(cfg, seed=109)))
+    assert steps <= got and "bwd.dx_gemm" not in got, got
