@@ -147,6 +147,8 @@ bool gated_shape(const sh_shape* s) {
   // The other forms only where the backward pass can make dx one product as well: a row of d_head holds both routers' dz.  Without it dx
   // would be fp32 atomics and passes over an accumulator, and there are no set tables to fall back on.
   if (!rect && 2 * HEp > s->d_head) return false;
+  // ... and every operand and gate table lies below 4 GiB, as the products' 32-bit offsets need.
+  if ((N + 1) * H * s->d_head * 2 >= (1l << 32) || N * H * E * 4 >= (1l << 32)) return false;
   // The gates scale an operand that is then rounded to bf16.  That is what the sets do as well; but query experts over two token sets, and
   // everything where there are too many sets, multiply an fp32 result by the gate, and keep doing so.
   if ((rect && s->qk_experts) || count_sets(s->E, s->k) > MAX_SETS) return false;

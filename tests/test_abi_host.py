@@ -74,6 +74,17 @@ def test_workspace_split_and_score_gradient_scratch(lib):
     assert f32[0] == f32[1]
 
 
+def test_operands_past_32_bit_offsets_keep_the_expert_sets(lib):
+    """The gated concatenation's products address their operands by 32-bit byte offsets.  A shape whose rows of all heads pass
+    4 GiB has the expert-set tables in its workspace instead (kept: a permutation, and the gates of k slots, per head and side)."""
+    def kept_per_token(B, d_head):
+        s = binding.make_shape(B, 4097, 1024, 4, d_head, 3, 2, 1, "bf16")
+        return binding.switchhead_workspace_parts(s)[0] / (B * 4097)
+    tables = 2 * 4 * (4 + 2 * 4)
+    assert abs(kept_per_token(1025, 128) - kept_per_token(1023, 128) - tables) < 1   # 4 GiB = 4194304 rows of 4 x 128
+    assert abs(kept_per_token(1025, 64) - kept_per_token(1023, 64)) < 1
+
+
 def test_forward_rejects_bad_arguments_without_launching(lib):
     s = binding.make_shape(2, 64, 64, 2, 32, 4, 2, 1, "f32")
     fake = ctypes.c_void_p(256)          # never dereferenced: every check below fails first
