@@ -239,7 +239,9 @@ Layout make_layout(const sh_shape* s) {
     L.rh = take(router_hybrid_bytes((int)N, (int)dm, (int)H, (int)E, o7));
   }
   if (s->dtype == SH_F32) {
-    // the weight gradients of one backward call share a launch: room for all of their chunks
+    // The weight gradients of one backward call share a launch: room for the partial sums of all their chunks, unless that would push a
+    // shape out of the built-in workspace (a forward call never uses it) or add more than the rest of the workspace, as long
+    // layers of many experts and few tokens do.  Without room the chunks are added atomically to outputs cleared first.
     const bool rect = s->T_q > 0 && s->T_q < s->T;
     const size_t Nq = rect ? (size_t)s->B * s->T_q : N;
     auto room = [&](bool gathered, size_t heads, size_t experts, size_t rows_per_expert, size_t groups_rows, size_t ka, size_t kb, size_t kb_store) {
@@ -261,6 +263,8 @@ Layout make_layout(const sh_shape* s) {
     room(false, H, 1, N, N, dm, dh, 0);
     room(false, 1, 1, N, N, dm, (H * E + 7) / 8 * 8, H * E);
     room(false, 1, 1, Nq, Nq, dm, (H * E + 7) / 8 * 8, H * E);
+    const size_t bytes = align_up(L.wpart_floats * 4), built_in = SWITCHHEAD_STATIC_WORKSPACE_BYTES;
+    if (bytes > off || (off <= built_in && off + bytes > built_in)) L.wpart_floats = 0;
     L.wpart = take(L.wpart_floats * 4);
   }
   // The score gradient of the attention backward, [B][H][keys][queries] bf16: the dK / dV kernel leaves it for the
@@ -1444,16 +1448,34 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       add_wgrad(w);
       if (sides > own) fl.p[fl.n - 1].add = 1;   // both sides' tokens add into the shared router's gradient
     }
-    float* part = c.p<float>(c.L.wpart);
-    for (int i = 0; i < fl.n; ++i) {
-      fl.p[i].w.partial = part;
-      if (!fl.p[i].add) part += fl.p[i].partial_floats;
+    // what is added to atomically is cleared first: the bias gradients over more than one block of tokens, a router both sides' tokens
+    // share, weight gradients of several chunks that have no room for partial sums
+    float* out[F32_WG_MAX + 2];
+    size_t len[F32_WG_MAX + 2];
+    int nz = 0;
+    auto zero = [&](float* p, size_t n) {
+      if (p) out[nz] = p, len[nz++] = n;
+    };
+    if (!c.dense && (N > 256 || sides > own)) {
+      zero(db_S, HE_);
+      if (own == 2) zero(db_D, HE_);
     }
-    // what is added to atomically: the bias gradients over more than one block of tokens, a router both sides' tokens share
-    const bool add_w = sides > own && dW_S;
-    if (!c.dense && (N > 256 || sides > own))
-      launch_zero4_f32(db_S, db_S ? (size_t)HE_ : 0, own == 2 ? db_D : nullptr, own == 2 && db_D ? (size_t)HE_ : 0,
-                       add_w ? dW_S : nullptr, add_w ? (size_t)dm * HE_ : 0, nullptr, 0, c.st);
+    float *part = c.p<float>(c.L.wpart), *end = part + c.L.wpart_floats;
+    bool dW_S_cleared = false;
+    for (int i = 0; i < fl.n; ++i) {
+      F32Wgrad& p = fl.p[i];
+      p.w.partial = part;
+      if (p.partial_floats > (size_t)(end - part)) p.add = 1;
+      if (!p.add) {
+        part += p.partial_floats;
+      } else if (p.w.dW != dW_S || !dW_S_cleared) {   // (a shared router's gradient is two problems of one output)
+        dW_S_cleared = dW_S_cleared || p.w.dW == dW_S;
+        zero(p.w.dW, (size_t)p.w.heads * p.w.E * p.w.Ka * (p.w.kb_store ? p.w.kb_store : p.w.Kb));
+      }
+    }
+    for (int i = nz; i < F32_WG_MAX + 2; ++i) out[i] = nullptr, len[i] = 0;
+    for (int i = 0; i < nz; i += 4)
+      launch_zero4_f32(out[i], len[i], out[i + 1], len[i + 1], out[i + 2], len[i + 2], out[i + 3], len[i + 3], c.st);
     if (!c.dense) {
       prof_mark(c.st, "bwd.router");
       for (int sd = 0; sd < (c.rect ? 2 : 1); ++sd) {

@@ -85,6 +85,25 @@ def test_operands_past_32_bit_offsets_keep_the_expert_sets(lib):
     assert abs(kept_per_token(1025, 64) - kept_per_token(1023, 64)) < 1
 
 
+@pytest.mark.parametrize("B, T, layer", [
+    (4, 256, (412, 2, 76, 5, 3)), (1, 700, (412, 2, 76, 5, 3)), (1, 1024, (412, 2, 76, 5, 3)),
+    (1, 257, (1024, 4, 128, 5, 3)), (1, 300, (1024, 4, 128, 5, 3)),
+    (2, 154, (2048, 5, 64, 3, 3)), (45, 6, (2048, 3, 256, 7, 1)),
+])
+def test_fp32_scratch_of_backward_leaves_forward_its_built_in_workspace(lib, B, T, layer):
+    """Room for the weight gradients' partial sums must not push a shape out of the built-in workspace: these fit by what else
+    their layout holds (5.5 to 15 MiB)."""
+    assert 0 < binding.switchhead_workspace_bytes(binding.make_shape(B, T, *layer, 1, "f32")) <= binding.STATIC_WORKSPACE_BYTES
+
+
+def test_fp32_partial_sums_at_most_double_the_workspace(lib):
+    """Many experts, few tokens: the partial sums would be the gradients of every expert (430 MiB instead of 12)."""
+    s = binding.make_shape(3, 94, 2048, 5, 76, 63, 2, 1, "f32", qk_experts=1)
+    assert binding.switchhead_workspace_bytes(s) < 26 << 20
+    s = binding.make_shape(16, 256, 412, 2, 76, 5, 3, 1, "f32")   # a training batch keeps them (44 + 35 MiB)
+    assert binding.switchhead_workspace_bytes(s) > 70 << 20
+
+
 def test_forward_rejects_bad_arguments_without_launching(lib):
     s = binding.make_shape(2, 64, 64, 2, 32, 4, 2, 1, "f32")
     fake = ctypes.c_void_p(256)          # never dereferenced: every check below fails first
