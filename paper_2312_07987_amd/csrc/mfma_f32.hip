@@ -57,6 +57,7 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
   __shared__ int ids[FBM];
   __shared__ float gsc[FBM];
   __shared__ float gts[SEG ? FBM * F32_MAX_SEGD : 1];   // the tile's dense gates, [row][head * experts + expert]
+  __shared__ int again;                                 // SEG: an element of the tile is NaN
 
   const int h = blockIdx.z, n0 = blockIdx.y * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -77,6 +78,7 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
     gsc[tid] = a.gate ? a.gate[(long)h * a.gate_hstride + id] : 1.f;
   }
   if constexpr (SEG) {
+    if (tid == 0) again = 0;
     if (a.gidx) {
       const int HE = a.gheads * a.experts;
       for (int t = tid; t < FBM * HE; t += 256) gts[(t / HE) * F32_MAX_SEGD + t % HE] = 0.f;
@@ -242,6 +244,35 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
         atomicAdd(crow + n, acc[j][v] * sc);
       else
         crow[n] = acc[j][v] * sc;
+    }
+  }
+  if constexpr (SEG) {
+    // An expert that a token did not select is multiplied by zero, which must not let its infinities and NaNs through: elements that
+    // came out as NaN are computed once more from the selected experts alone, up to the first NaN that is really theirs.
+    bool nan = false;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) nan |= acc[j][v] != acc[j][v];
+    if (__ballot(nan) && lane == 0) again = 1;
+    __syncthreads();
+    if (!again) return;
+    for (int t = tid; t < rows * BN; t += 256) {
+      const int row = t / BN, n = n0 + t % BN;
+      if (n >= Nc) continue;
+      float* o = C + (long)(row0 + row) * a.ldc + n;
+      if (*o == *o) continue;
+      float s = 0.f;
+      for (int q = 0; q < nseg && s == s; ++q) {
+        const SegDesc& d = a.segd[q];
+        const float gt = d.gcol >= 0 ? gts[row * F32_MAX_SEGD + d.gcol] : 1.f;
+        if (gt == 0.f) continue;
+        const int K = d.klen ? d.klen : a.K;
+        const float* Ap = (const float*)d.A + (long)(row0 + row) * (d.klen ? d.lda : a.lda);
+        const float* Bp = (const float*)d.B + (BNT ? (long)n * (d.klen ? d.sbn : a.sbn) : (long)n);
+        for (int k = 0; k < K; ++k) s = fmaf(Ap[k] * gt, Bp[BNT ? (long)k : (long)k * a.sbk], s);
+      }
+      *o = s;
     }
   }
 }

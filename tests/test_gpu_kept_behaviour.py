@@ -145,3 +145,50 @@ def test_fp32_weight_gradients_without_room_for_partial_sums(over, shared):
     for n, v in layer.grads().items():
         if v is not None:
             assert nerr(v, first[n]) < 1e-5, n
+
+
+def _poison_one(t, n, h, e, i, j):
+    t[n] = t[n].copy()
+    t[n][h, e, i, j] = np.inf
+    t[n][h, e, i + 1, j + 2] = np.nan
+
+
+@pytest.mark.parametrize("over, shared", [
+    (dict(dtype="f32", B=2, T=70, d_model=50, nheads=2, d_head=20, E=4, k=2), False),
+    (dict(dtype="f32", B=2, T=70, d_model=412, nheads=2, d_head=76, E=5, k=3, T_q=41), False),
+])
+def test_experts_that_a_token_did_not_select_do_not_reach_it(over, shared):
+    """Infinities and NaNs in experts nobody selects leave no trace; in an output expert they reach only the tokens that
+    selected it."""
+    cfg = _cfg(**over)
+    t = make_inputs(cfg, seed=127, shared_router=shared)
+    HE, E = cfg["nheads"] * cfg["E"], cfg["E"]
+    t["b_S"] = np.zeros(HE, np.float32)
+    t["b_S"][E + 1] = -40.0                       # head 1, expert 1: nobody
+    t["b_D"] = None if shared else t["b_S"].copy()
+    layer = _layer(cfg, t)
+    layer.forward()
+    layer.backward()
+    y, g = layer.outputs(), layer.grads()
+    bad = dict(t)
+    for n in ("W_V", "W_O") + (("W_Q", "W_K") if cfg["qk_experts"] else ()):
+        _poison_one(bad, n, 1, 1, 3, 5)
+    layer = _layer(cfg, bad)
+    layer.forward()
+    layer.backward()
+    bar = 1e-5 if cfg["dtype"] == "f32" else 4e-3   # (elements summed in another order: bf16 results may move by one rounding, 2^-8)
+    assert nerr(layer.outputs(), y) < bar
+    for n, v in layer.grads().items():
+        if v is not None:
+            assert np.isfinite(v).all() and nerr(v, g[n]) < bar, n
+    _poison_one(bad, "W_O", 0, 2, 4, 7)           # head 0, expert 2: some
+    layer = _layer(cfg, bad)
+    layer.forward()
+    got, r = layer.outputs().reshape(-1, cfg["d_model"]), layer.routing()
+    sel = (r["idx_D"] if "idx_D" in r else r["idx"][1])[0]
+    hit = (sel == 2).any(-1)
+    assert 0 < hit.sum() < hit.size
+    want = y.reshape(-1, cfg["d_model"])
+    assert nerr(got[~hit], want[~hit]) < bar
+    ok = np.isfinite(got[hit])
+    assert not ok[:, [7, 9]].any() and np.delete(ok, [7, 9], 1).all()
