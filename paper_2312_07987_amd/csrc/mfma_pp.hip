@@ -328,6 +328,44 @@ __global__ __launch_bounds__(512, 1) void pp_row_gemm_kernel(RowGemmArgs a) {
         *(uint4*)((unsigned short*)Cb + crow + n0 + wn + cc) = *(const uint4*)(&Cs[lr * LDC + cc]);
       }
     }
+    if constexpr (CAT) {
+      // An expert that a token did not select is multiplied by zero, which must not let its infinities and NaNs through: elements that
+      // came out as NaN are computed once more from the selected experts alone, up to the first NaN that is really theirs.  (Every
+      // wave looks at its own part of the tile: the sum of its accumulators, NaN if one of them is.)
+      float t4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 16; ++q) t4[q & 3] += acc[i][j][q];
+      const float tsum = (t4[0] + t4[1]) + (t4[2] + t4[3]);
+      if (!__ballot(tsum != tsum)) return;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // the stores above, by other lanes of this wave
+      for (int t = lane; t < 128 * 64; t += 64) {
+        const int id = row0 + wm + t / 64, n = n0 + wn + t % 64;
+        if (id >= row0 + rows) break;
+        unsigned short* o = (unsigned short*)Cb + (long)id * a.ldc + n;
+        if ((*o & 0x7fff) <= 0x7f80) continue;
+        float s = 0.f;
+        for (int p = 0; p < nseg && s == s; ++p) {
+          const SegDesc& d = a.segd[p];
+          long row = id;
+          if (SEG == 4 && p >= a.seg_q) {
+            const int q = id % a.seq_T - (a.seq_T - a.seq_Tq);
+            if (q < 0) continue;
+            row = (long)(id / a.seq_T) * a.seq_Tq + q;
+          }
+          const float gt = d.gcol >= 0 ? a.gtab[d.gcol + row * a.gld] : 1.f;
+          if (gt == 0.f) continue;
+          const unsigned short* Ap = (const unsigned short*)d.A + row * a.lda;
+          const unsigned short* Bp = (const unsigned short*)d.B + (BNT ? (long)n * a.sbn : (long)n);
+          for (int k = 0; k < a.K; ++k)
+            s = fmaf(bf16_to_f32(f32_to_bf16(bf16_to_f32(Ap[k]) * gt)), bf16_to_f32(Bp[BNT ? (long)k : (long)k * a.sbk]), s);
+        }
+        *o = f32_to_bf16(s);
+      }
+    }
     return;
   }
   // fp32 output

@@ -156,6 +156,9 @@ def _poison_one(t, n, h, e, i, j):
 @pytest.mark.parametrize("over, shared", [
     (dict(dtype="f32", B=2, T=70, d_model=50, nheads=2, d_head=20, E=4, k=2), False),
     (dict(dtype="f32", B=2, T=70, d_model=412, nheads=2, d_head=76, E=5, k=3, T_q=41), False),
+    (dict(B=5, T=1161, d_model=2048, nheads=2, d_head=64, E=3, k=2), False),             # a last tile of 173 rows
+    (dict(B=5, T=1160, T_q=1000, d_model=2048, nheads=2, d_head=64, E=3, k=2), True),    # two token sets
+    (dict(B=5, T=1161, d_model=2048, nheads=2, d_head=64, E=3, k=2, qk_experts=1), False),
 ])
 def test_experts_that_a_token_did_not_select_do_not_reach_it(over, shared):
     """Infinities and NaNs in experts nobody selects leave no trace; in an output expert they reach only the tokens that
