@@ -180,11 +180,22 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
       }
       *(vec_t*)&As_[stage][(c / A_CPR) * FLDA + (c % A_CPR) * VEC] = v;
     }
-    // (what B holds past the end of the reduction is a repeat that meets a zero of A)
 #pragma unroll
     for (int i = 0; i < B_N; ++i) {
       const int c = tid + i * 256;
       if (B_TOT % 256 == 0 || c < B_TOT) *(vec_t*)&Bs_[stage][(c / B_CPR) * LDB + (c % B_CPR) * VEC] = st.rb[i];
+    }
+    // What B holds past the end of the reduction is a repeat; it becomes zero as well (an infinity times the zero of A is NaN).  A
+    // thread's own pieces, after they are stored: selecting on the way, as A does, costs every step.  (SEG computes NaNs again.)
+    if (!SEG && st.k0 + FBK > st.K) {   // uniform
+#pragma unroll
+      for (int i = 0; i < B_N; ++i) {
+        const int c = tid + i * 256;
+        if (B_TOT % 256 != 0 && c >= B_TOT) continue;
+#pragma unroll
+        for (int t = 0; t < VEC; ++t)
+          if (st.k0 + (BNT ? (c % B_CPR) * VEC + t : c / B_CPR) >= st.K) Bs_[stage][(c / B_CPR) * LDB + (c % B_CPR) * VEC + t] = 0.f;
+      }
     }
   };
 
@@ -401,7 +412,7 @@ __device__ __forceinline__ void f32_wgrad_body(const F32Wgrad& p, int blk, float
       st.rb[i] = *(const vec_t*)(Bm + (long)ids_b[rr] * a.ldb + (f < a.Kb ? f : 0));
     }
   };
-  // the gate goes to one side, rows past the chunk become zeros on the other (features past the end reach only results
+  // the gate goes to one side, rows past the chunk become zeros on both (features past the end reach only results
   // that are not stored)
   auto store = [&](const Step& st, int stage, int r0) {
 #pragma unroll
@@ -415,6 +426,14 @@ __device__ __forceinline__ void f32_wgrad_body(const F32Wgrad& p, int blk, float
     for (int i = 0; i < B_N; ++i) {
       const int c = tid + i * 256;
       if (B_TOT % 256 == 0 || c < B_TOT) *(vec_t*)&Bs[stage * 32 * LDB + (c / B_CPR) * LDB + (c % B_CPR) * VEC] = st.rb[i];
+    }
+    if (r0 + 32 > rows) {   // uniform; a thread's own pieces, as in the row GEMM
+#pragma unroll
+      for (int i = 0; i < B_N; ++i) {
+        const int c = tid + i * 256;
+        if ((B_TOT % 256 == 0 || c < B_TOT) && r0 + c / B_CPR >= rows)
+          *(vec_t*)&Bs[stage * 32 * LDB + (c / B_CPR) * LDB + (c % B_CPR) * VEC] = vec_t{};
+      }
     }
   };
   f32x4 acc[NJ];

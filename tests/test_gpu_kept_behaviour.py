@@ -195,3 +195,27 @@ def test_experts_that_a_token_did_not_select_do_not_reach_it(over, shared):
     assert nerr(got[~hit], want[~hit]) < bar
     ok = np.isfinite(got[hit])
     assert not ok[:, [7, 9]].any() and np.delete(ok, [7, 9], 1).all()
+
+
+@pytest.mark.parametrize("d_model, d_head", [(50, 20), (76, 36), (33, 17)])
+def test_fp32_infinities_past_the_end_of_a_reduction(d_model, d_head):
+    """The row that fills up the last step of a reduction is a repeat; an infinity in it stays an infinity of its own place."""
+    cfg = _cfg(dtype="f32", B=1, T=45, d_model=d_model, nheads=2, d_head=d_head, E=4, k=2)
+    t = make_inputs(cfg, seed=131)
+    t["W_K"][0, 0, 3] = np.inf            # the first of d_model reduction indices
+    layer = _layer(cfg, t)
+    layer.forward()
+    assert np.array_equal(layer.intermediates()["K"][:, 0, 3], np.where(t["x"][0, :, 0] > 0, np.inf, -np.inf))
+    t = make_inputs(cfg, seed=131)
+    t["dy"][0, -1, 5] = np.inf            # the last token: the last row of every group it belongs to
+    layer = _layer(cfg, t)
+    layer.forward()
+    layer.backward()
+    got, inter, r = layer.grads()["dW_O"], layer.intermediates(), layer.routing()
+    for h in range(cfg["nheads"]):
+        for e in range(cfg["E"]):
+            col = got[h, e, :, 5]
+            if e in r["idx"][1][h, -1]:
+                assert np.array_equal(col, np.where(inter["ctx"][-1, h] > 0, np.inf, -np.inf)), (h, e)
+            else:
+                assert np.isfinite(col).all(), (h, e)
