@@ -599,7 +599,8 @@ __host__ __device__ constexpr int f32_attn_kt() {
 }
 
 // NROWS rows of dh floats on their way into LDS [row][DH + 4]: load() requests them (16-byte rows: v4), store() writes them;
-// columns past dh zero, rows past `valid` repeat the last valid one (what they meet is a probability of exactly zero)
+// columns past dh and rows outside lo .. hi - 1 zero.  Rows that no owned row sees stay out that way: a probability of zero
+// would turn an infinity or a NaN of theirs into a NaN.
 template <int DH, int NROWS>
 struct F32Tile {
   static constexpr int LD = DH + 4, CPR = DH / 4, N = NROWS * CPR / 256;
@@ -616,17 +617,24 @@ struct F32Tile {
       v[i] = *(const f32x4*)(s + (long)min(c / CPR, valid_rows - 1) * rs + (d < dh ? d : 0));
     }
   }
-  __device__ __forceinline__ void store(float* dst, long rs, int dh, bool v4, int tid) const {
+  __device__ __forceinline__ void store(float* dst, long rs, int dh, bool v4, int tid, int lo, int hi) const {
     if (v4) {
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const int c = tid + i * 256, d = (c % CPR) * 4;
         *(f32x4*)&dst[(c / CPR) * LD + d] = d < dh ? v[i] : f32x4{};
       }
+      if (lo > 0 || hi < NROWS) {   // uniform; a thread's own pieces
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const int c = tid + i * 256, row = c / CPR;
+          if (row < lo || row >= hi) *(f32x4*)&dst[row * LD + (c % CPR) * 4] = f32x4{};
+        }
+      }
     } else {
       for (int c = tid; c < NROWS * DH; c += 256) {
         const int row = c / DH, d = c % DH;
-        dst[row * LD + d] = d < dh ? src[(long)min(row, valid - 1) * rs + d] : 0.f;
+        dst[row * LD + d] = d < dh && row >= lo && row < hi ? src[(long)min(row, valid - 1) * rs + d] : 0.f;
       }
     }
   }
@@ -715,8 +723,8 @@ __global__ __launch_bounds__(256) void f32_attn_fwd_kernel(AttnArgs a, int v4) {
   const int last = a.causal ? min(T - 1, q + off) : T - 1;   // this lane's last visible key
   for (int k0 = 0; k0 < kend; k0 += KT) {
     __syncthreads();
-    tk.store(Ks, rs, dh, v4, tid);
-    tv.store(Vs, rs, dh, v4, tid);
+    tk.store(Ks, rs, dh, v4, tid, 0, kend - k0);
+    tv.store(Vs, rs, dh, v4, tid, 0, kend - k0);
     __syncthreads();
     if (k0 + KT < kend) {
       tk.load(K + (long)(k0 + KT) * rs, rs, T - k0 - KT, dh, v4, tid);
@@ -808,8 +816,8 @@ __global__ __launch_bounds__(256) void f32_attn_bwd_kernel(AttnBwdArgs a, int v4
     const int last = a.causal ? min(T - 1, q + off) : T - 1;
     for (int k0 = 0; k0 < kend; k0 += KT) {
       __syncthreads();
-      ta.store(t0, rs, dh, v4, tid);
-      tb.store(t1, rs, dh, v4, tid);
+      ta.store(t0, rs, dh, v4, tid, 0, kend - k0);
+      tb.store(t1, rs, dh, v4, tid, 0, kend - k0);
       __syncthreads();
       if (k0 + KT < kend) {
         ta.load(K + (long)(k0 + KT) * rs, rs, T - k0 - KT, dh, v4, tid);
@@ -821,8 +829,8 @@ __global__ __launch_bounds__(256) void f32_attn_bwd_kernel(AttnBwdArgs a, int v4
         const f32x4 dp = f32_dot_block<NC>(t1, LD, kb * 16 + r, g, gf);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const float p = k0 + kb * 16 + 4 * g + v <= last ? __builtin_amdgcn_exp2f(fmaf(s[v], sc, -L)) : 0.f;
-          s[v] = p * (dp[v] - D);
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[v], sc, -L));
+          s[v] = k0 + kb * 16 + 4 * g + v <= last ? p * (dp[v] - D) : 0.f;
         }
         f32_acc_block<NC>(acc, t0, LD, kb * 16, r, g, s);
       }
@@ -842,7 +850,7 @@ __global__ __launch_bounds__(256) void f32_attn_bwd_kernel(AttnBwdArgs a, int v4
   f32_row_frags<NC>(vf, V + (long)u * rs, g, dh, u < T);
 #pragma unroll
   for (int c = 0; c < NC; ++c) ak[c] = av[c] = f32x4{};
-  const int qbeg = a.causal ? (max(u0 - off, 0) / KT) * KT : 0;
+  const int qfirst = a.causal ? max(u0 - off, 0) : 0, qbeg = qfirst / KT * KT;   // the first query that sees an owned key
   float nl = 0.f, nd = 0.f;
   auto request = [&](int qt) {
     ta.load(Q + (long)qt * rs, rs, Tq - qt, dh, v4, tid);
@@ -854,8 +862,8 @@ __global__ __launch_bounds__(256) void f32_attn_bwd_kernel(AttnBwdArgs a, int v4
   if (qbeg < Tq) request(qbeg);
   for (int qt = qbeg; qt < Tq; qt += KT) {
     __syncthreads();
-    ta.store(t0, rs, dh, v4, tid);
-    tb.store(t1, rs, dh, v4, tid);
+    ta.store(t0, rs, dh, v4, tid, qfirst - qt, Tq - qt);
+    tb.store(t1, rs, dh, v4, tid, qfirst - qt, Tq - qt);
     if (tid < KT) {
       ls[tid] = nl * 1.44269504088896340736f;
       dl[tid] = nd;
@@ -872,7 +880,7 @@ __global__ __launch_bounds__(256) void f32_attn_bwd_kernel(AttnBwdArgs a, int v4
         const bool vis = q < Tq && u < T && (!a.causal || u <= q + off);
         const float p = vis ? __builtin_amdgcn_exp2f(fmaf(s[v], sc, -ls[ql])) : 0.f;
         s[v] = p;
-        dp[v] = p * (dp[v] - dl[ql]);
+        dp[v] = vis ? p * (dp[v] - dl[ql]) : 0.f;
       }
       f32_acc_block<NC>(av, t1, LD, qb * 16, r, g, s);
       f32_acc_block<NC>(ak, t0, LD, qb * 16, r, g, dp);

@@ -219,3 +219,31 @@ def test_fp32_infinities_past_the_end_of_a_reduction(d_model, d_head):
                 assert np.array_equal(col, np.where(inter["ctx"][-1, h] > 0, np.inf, -np.inf)), (h, e)
             else:
                 assert np.isfinite(col).all(), (h, e)
+
+
+@pytest.mark.parametrize("d_head", [20, 21, 76])
+def test_fp32_causal_queries_do_not_meet_what_lies_far_behind_them(d_head):
+    """NaNs and infinities in later tokens: under the causal mask the queries of earlier blocks of 32, and the keys and values
+    that only later queries with bad gradients do not see, keep their results."""
+    cfg = _cfg(dtype="f32", B=1, T=150, d_model=64, nheads=2, d_head=d_head, E=4, k=2)
+    t = make_inputs(cfg, seed=137)
+    base = _layer(cfg, t)
+    base.forward()
+    base.backward()
+    y, g, want = base.outputs(), base.grads(), base.intermediates()
+    for first in (32, 100):                                # the first bad token; its block of 32 starts at `clean`
+        clean = first // 32 * 32
+        bad = dict(t, x=t["x"].copy())
+        bad["x"][0, first:] = np.inf
+        bad["x"][0, first + 1::2] = np.nan
+        layer = _layer(cfg, bad)
+        layer.forward()
+        assert nerr(layer.outputs()[:, :clean], y[:, :clean]) < 1e-6
+        assert nerr(layer.intermediates()["ctx"][:clean], want["ctx"][:clean]) < 1e-6
+    # queries before an owned block of keys never see it: their gradients must not reach it
+    bad = dict(t, dy=t["dy"].copy())
+    bad["dy"][0, :10] = np.nan
+    layer = _layer(cfg, bad)
+    layer.forward()
+    layer.backward()
+    assert nerr(layer.grads()["dx"][:, 32:], g["dx"][:, 32:]) < 1e-5
