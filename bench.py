@@ -86,7 +86,7 @@ STEP_KERNEL = {
     "bwd.o_dgrad": r"mfma_row_gemm_kernel<.*, 4, 0(, \w+)?>",
     "bwd.v_dgrad": r"(pp_row_gemm_kernel<true, 5, 1>|mfma_row_gemm_kernel<.*, 5, 1(, \w+)?>)",
     "bwd.qk_dgrad": r"(pp_row_gemm_kernel<true, 6, 2>|mfma_row_gemm_kernel<.*, 6, 2(, \w+)?>)",
-    "bwd.dx_gemm": r"pp_row_gemm_kernel<true, 6, 3>",
+    "bwd.dx_gemm": r"pp_row_gemm_kernel<true, 6, [34]>",
     "bwd.o_wgrad": r"mfma_wgrad_kernel<.*, 8, 7(, \w+)?>", "bwd.v_wgrad": r"mfma_wgrad_kernel<.*, 8, 8(, \w+)?>",
     "bwd.qk_wgrad": r"mfma_wgrad_kernel<.*, 8, 9(, \w+)?>", "bwd.wgrad_reduce": r"wgrad_(list_)?reduce_kernel",
     "bwd.wgrads": r"mfma_wgrad_list_kernel",
@@ -171,7 +171,7 @@ def roofline_of(cfg, per_step):
     dom = max(per_step, key=per_step.get)
     if dom in flops:
         ach = flops[dom] / (per_step[dom] * 1e-3) / 1e12
-        mfma = cfg["dtype"] == "bf16"   # fp32 storage runs the plain fp32 kernels: vector ALU, not MFMA
+        mfma = cfg["dtype"] == "bf16"   # (the fp32 matrix instructions have the rate of the vector ALU)
         peak = PEAK_BF16_TFLOPS if mfma else PEAK_FP32_VEC_TFLOPS
         roof = {"bound": "mfma" if mfma else "alu", "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak}
     elif dom in alu:

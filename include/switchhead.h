@@ -194,13 +194,23 @@ sh_status switchhead_forward_static(const sh_shape* shape,
  *            are ignored in dense mode.
  *            dx may be the same buffer as dy where their shapes agree (square attention): dy is
  *            read to the end before dx is written.  Other outputs must not overlap inputs.
- * Determinism: with bf16 storage and the matrix-core kernels, dW_Q, dW_K, dW_V, dW_O are
- * sums of per-chunk partial results added in a fixed order (bit-identical from run to run),
- * and so are the router gradients dW_S, dW_D, db_S, db_D where they ride along the query/key
- * weight-gradient launch (square attention, dense queries and keys, 2 * nheads * E, each side
- * rounded up to a multiple of 8, not above d_head).  Otherwise the router gradients, and every
- * weight gradient of the plain fp32 kernels, are accumulated with fp32 atomic adds over token
- * chunks, so their last bits may differ from run to run.
+ * Determinism: where several work-groups share a sum, their parts are added in a fixed order or with fp32 atomic adds, whose
+ * last bits may differ from run to run.  Bit-identical from run to run are
+ *   - bf16 storage on the matrix-core kernels, d_model and d_head multiples of 8:
+ *       y, dx                   where there are at most 128 sets of k experts (dx not with qk_experts and T_q < T together);
+ *       dW_Q, dW_K, dW_V, dW_O  always;
+ *       dW_S, dW_D              where all weight gradients share one launch (d_model >= 256, d_head >= 64, nheads * E <= 64, a
+ *                               workspace above SWITCHHEAD_STATIC_WORKSPACE_BYTES), but not with shared selection and
+ *                               T_q < T together;
+ *       db_S, db_D              under the conditions of dW_S and dW_D, square attention;
+ *   - fp32 storage:
+ *       y                       E <= 2k and nheads * E <= 40;
+ *       dx                      E <= 2k, nheads * (E + 2) <= 38, dense queries and keys;
+ *       all dW                  calls of at most 256 tokens, or whose workspace has room for partial sums (it has not where they would
+ *                               more than double it or move the shape out of SWITCHHEAD_STATIC_WORKSPACE_BYTES); dW_S not
+ *                               with shared selection and T_q < T together;
+ *       db_S, db_D              calls of at most 256 tokens, not with shared selection and T_q < T together.
+ * Elsewhere, and on the plain kernels, the last bits of some of them may differ.
  */
 sh_status switchhead_backward(const sh_shape* shape,
                               const void* x, const void* W_Q, const void* W_K,

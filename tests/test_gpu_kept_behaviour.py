@@ -247,3 +247,45 @@ def test_fp32_causal_queries_do_not_meet_what_lies_far_behind_them(d_head):
     layer.forward()
     layer.backward()
     assert nerr(layer.grads()["dx"][:, 32:], g["dx"][:, 32:]) < 1e-5
+
+
+def test_fp32_sort_tables_too_large_for_the_in_block_scan():
+    """The fp64 router's scan and scatter over a count table of 32-token blocks: 130 blocks of 64 experts."""
+    run_case(_cfg(dtype="f32", B=41, T=101, d_model=16, nheads=1, d_head=8, E=64, k=2), seed=139)
+
+
+def test_bf16_two_token_sets_with_sort_tables_too_large_for_shared_launches():
+    """67 token blocks of 126 expert sets: each side is routed and sorted in launches of its own."""
+    run_case(_cfg(B=34, T=501, T_q=20, d_model=64, nheads=1, d_head=32, E=9, k=4), seed=149)
+
+
+@pytest.mark.parametrize("over, atomic", [
+    (dict(dtype="f32", B=16, T=256, d_model=412, nheads=2, d_head=76, E=5, k=3), ("db_S", "db_D")),   # several chunks, their partial sums in order
+    (dict(B=4, T=700, T_q=350, d_model=1024, nheads=4, d_head=128, E=5, k=3), ("db_S", "db_D")),      # two token sets, all weight gradients in one launch
+    (dict(B=9, T=300, d_model=1024, nheads=4, d_head=128, E=5, k=3), ()),
+    (dict(B=9, T=300, d_model=1024, nheads=4, d_head=128, E=5, k=3, qk_experts=1), ()),
+    (dict(dtype="f32", B=2, T=100, d_model=412, nheads=2, d_head=76, E=5, k=3, T_q=60), ()),        # at most 256 tokens
+])
+def test_gradients_repeat_bit_for_bit(over, atomic):
+    """What the header promises to repeat; `atomic` are the ones it does not."""
+    cfg = _cfg(**over)
+    layer = _layer(cfg, make_inputs(cfg, seed=151))
+    layer.forward()
+    y = layer.outputs()
+    layer.backward()
+    first = layer.grads()
+    for _ in range(3):
+        layer.forward()
+        layer.backward()
+        assert np.array_equal(layer.outputs(), y)
+        for n, v in layer.grads().items():
+            if v is not None and n not in atomic:
+                assert np.array_equal(v, first[n]), n
+
+
+@pytest.mark.parametrize("over", [dict(T=1161), dict(T=1160, T_q=1000), dict(T=1161, qk_experts=1)])
+def test_gated_forms_are_taken(over):
+    """The shapes that the parity test of the gated concatenation relies on do run it, in both passes."""
+    cfg = _cfg(**dict(dict(B=5, d_model=2048, nheads=2, d_head=64, E=3, k=2), **over))
+    steps = _steps(_layer(cfg, make_inputs(cfg, seed=157)))
+    assert "bwd.dx_gemm" in steps and not steps & {"fwd.y_sum", "fwd.y_zero"}, steps

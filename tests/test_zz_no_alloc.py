@@ -18,7 +18,7 @@ def test_static_workspace_forward_matches_the_caller_workspace_forward():
     cases.append((c, 7))
     c = config("c2"); c.update(B=2, T=96, d_model=256, nheads=2)            # smaller, same kernels
     cases.append((c, 8))
-    cases.append((config("c0"), 9))                                         # fp32 storage, plain kernels
+    cases.append((config("c0"), 9))                                         # fp32 storage
     for cfg, seed in cases:
         print("case", cfg, flush=True)
         t = make_inputs(cfg, seed=seed)
@@ -31,7 +31,7 @@ def test_static_workspace_forward_matches_the_caller_workspace_forward():
         got = layer.outputs()
         if cfg["dtype"] == "bf16":
             assert np.array_equal(got, ref)      # this path adds its partial sums in a fixed order
-        else:                                    # fp32 storage sums heads and slots with atomic adds
+        else:                                    # fp32 storage may add with atomics
             assert np.max(np.abs(got - ref)) <= 1e-4 * np.max(np.abs(ref))
     # a shape that does not fit is refused, nothing is launched and y stays as it was
     big = config("c2")
