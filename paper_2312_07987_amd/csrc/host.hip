@@ -149,9 +149,11 @@ bool gated_shape(const sh_shape* s) {
   if (!rect && 2 * HEp > s->d_head) return false;
   // ... and every operand and gate table lies below 4 GiB, as the products' 32-bit offsets need.
   if ((N + 1) * H * s->d_head * 2 >= (1l << 32) || N * H * E * 4 >= (1l << 32)) return false;
-  // The gates scale an operand that is then rounded to bf16.  That is what the sets do as well; but query experts over two token sets, and
-  // everything where there are too many sets, multiply an fp32 result by the gate, and keep doing so.
-  if ((rect && s->qk_experts) || count_sets(s->E, s->k) > MAX_SETS) return false;
+  // The gates scale an operand that is then rounded to bf16, as they do in the sets.  Where there are too many sets they multiply an
+  // fp32 result of expert-sorted rows, and keep doing so: relative error of y against fp64 4.03e-3 that way, 4.35e-3 gated (4 heads of 128,
+  // 5 of 10 experts).  (Query experts over two token sets are sorted rows as well, but the bf16 partials of the other projections
+  // outweigh that: query rows of dx 6.19e-3 by sets and sorted rows, 6.00e-3 gated at d_model 2048, 2 heads of 64, 2 of 3 experts.)
+  if (count_sets(s->E, s->k) > MAX_SETS) return false;
   // One work-group per CU: a launch costs whole rounds of 256 tiles times its segments (4.4 us a round and segment of 128, measured at
   // 256 tiles).  The expert-set path costs its selected segments, partial sums and their addition per tile (11.8 us for 256
   // tiles), so it is the better one where the last round is mostly empty.  A training step over B x 512 tokens of d_model

@@ -158,7 +158,7 @@ def test_bf16_weight_gradient_list(over, shared):
 ])
 def test_bf16_gated_concatenation_forms(over, shared):
     """One product for y and one for dx over every (head, expert): token counts that are no multiple of the tile, two token sets,
-    expert queries and keys.  (Both of the last together keep the gates on fp32 results, on other products.)"""
+    expert queries and keys."""
     cfg = dict(dict(name="gated", dtype="bf16", d_model=2048, nheads=2, d_head=64, E=3, k=2, causal=1, bias0=0.0), **over)
     run_case(cfg, shared=shared, seed=53)
 
