@@ -972,9 +972,15 @@ template <int DH>
 static void launch_dh(const AttnArgs* f, const AttnBwdArgs* bw, hipStream_t s) {
   if (f) {
     dim3 g((((f->Tq > 0 ? f->Tq : f->T) + 127) / 128) * f->H * f->B);
-    // long sequences: two wave groups per work-group split the key tiles of a query tile between them; so do launches of at most one
-    // work-group per CU from 256 keys on, where the second group has the rest of the CU to itself (8 x 1000 keys, one query: 31.6 -> 27.9 us; 9 x 701: 26.5 -> 24.4)
-    const bool split = DH <= 128 && DH >= 64 && (f->T >= 1024 || (f->T >= 256 && g.x <= 256));
+    // Long sequences: two wave groups per work-group split the key tiles of a query tile between them; so do launches of at most one
+    // work-group per CU from 256 keys on, where the second group has the rest of the CU to itself.  One group / two, us: heads of 64 over
+    // 256 keys 13.2 / 12.3 with 256 work-groups, 13.6 / 16.4 with 320; of 96 over 256 keys 15.5 / 14.1 with 128.  Heads wider than 96
+    // gain later: of 128 over 256 keys 15.5 / 16.1 with 128 work-groups, over 320 15.2 / 15.0 with 48, over 384 21.3 / 21.7 with 252, over
+    // 512 23.0 / 22.5 with 256; and not with a few queries per sequence in more than 128 (one query, 320 keys 15.8 / 16.7 and
+    // 640 keys 23.6 / 24.1 with 240, but 22.2 / 20.8 with 32).
+    const int queries = f->Tq > 0 ? f->Tq : f->T;
+    const int keys_from = DH > 96 ? 320 : 256, groups_to = DH > 96 && (f->T < 512 || queries < 128) ? 128 : 256;
+    const bool split = DH <= 128 && DH >= 64 && (f->T >= 1024 || (f->T >= keys_from && (int)g.x <= groups_to));
     if constexpr (DH <= 128 && DH >= 64) {
       if (split) {
         if (attn_vec(f->dh) == 8)

@@ -5,8 +5,9 @@
 // reduction indices (32 x 256 of A straight into operand fragments, 256 x 32 of B) before it waits: one round trip per 1024.  The four
 // partial sums meet in LDS and are added in wave order.
 // 100 rows of d_model 1024, 4 heads of 128 (events around each): queries and keys 21 -> 10 us, value experts (5 experts, 3 active)
-// 22 -> 15; the whole call 110 -> 92.  The line: 768 tiles are three for each CU, two of them resident; a 128 x 128 launch of that size
-// (48 tiles) still takes its sixteen trips.
+// 22 -> 15; the whole call 110 -> 92.  The line, on its safe side: 768 tiles are three for each CU, two of them resident.  A launch of 128 x 128
+// tiles takes its sixteen trips whatever its size; in us, those / these: 608 tiles 21.7 / 15.2 and 800 21.5 / 17.9 (queries and
+// keys, whole tiles), 680 22.3 / 20.6, 928 23.3 / 23.5, 980 22.5 / 22.0, 1280 22.2 / 26.6 (value experts, partly filled).
 #include "common.h"
 #include "mfma_util.h"
 
