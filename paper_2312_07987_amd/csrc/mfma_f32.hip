@@ -695,13 +695,14 @@ __device__ __forceinline__ void f32_unpark(f32x4 (&acc)[NC], const float* park, 
 }
 
 template <int DH>
-__global__ __launch_bounds__(256) void f32_attn_fwd_kernel(AttnArgs a, int v4) {
+__global__ __launch_bounds__(256) void f32_attn_fwd_kernel(AttnArgs a, int v4, int rank0) {
   constexpr int KT = f32_attn_kt<DH>(), LD = DH + 4, NC = DH / 16, NB = KT / 32;   // NB: the wave's blocks of a tile
   extern __shared__ __attribute__((aligned(16))) float fl[];
   float *Ks = fl, *Vs = fl + KT * LD;
   const int T = a.T, dh = a.dh, Tq = a.Tq > 0 ? a.Tq : T, off = T - Tq;
-  const int nt = (Tq + 31) / 32, P = a.B * a.H;
-  const int tile = nt - 1 - (int)(blockIdx.x / P), pair = blockIdx.x % P;   // under a causal mask the long tiles come first
+  const int nt = (Tq + 31) / 32, pair = blockIdx.y * gridDim.x + blockIdx.x;
+  if (pair >= a.B * a.H) return;
+  const int tile = nt - 1 - rank0 - (int)blockIdx.z;   // under a causal mask the long tiles come first
   const int b = pair / a.H, h = pair % a.H;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
   const int kb0 = (wave >> 1) * NB;
@@ -784,13 +785,13 @@ __global__ __launch_bounds__(256) void f32_attn_fwd_kernel(AttnArgs a, int v4) {
 
 // Backward, one launch: the first blocks own 32 queries each (dQ), the rest 32 keys (dK, dV); neither needs the other.
 template <int DH>
-__global__ __launch_bounds__(256) void f32_attn_bwd_kernel(AttnBwdArgs a, int v4) {
+__global__ __launch_bounds__(256) void f32_attn_bwd_kernel(AttnBwdArgs a, int v4, int rank0) {
   constexpr int KT = f32_attn_kt<DH>(), LD = DH + 4, NC = DH / 16, NB = KT / 32;
   extern __shared__ __attribute__((aligned(16))) float fl[];
   float *t0 = fl, *t1 = fl + KT * LD, *ls = t1 + KT * LD, *dl = ls + KT;
   const int T = a.T, dh = a.dh, Tq = a.Tq > 0 ? a.Tq : T, off = T - Tq;
-  const int P = a.B * a.H, nq = (Tq + 31) / 32;
-  const int rank = blockIdx.x / P, pair = blockIdx.x % P;
+  const int nq = (Tq + 31) / 32, rank = rank0 + (int)blockIdx.z, pair = blockIdx.y * gridDim.x + blockIdx.x;
+  if (pair >= a.B * a.H) return;
   const int b = pair / a.H, h = pair % a.H;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
   const int b0 = (wave >> 1) * NB, own = (wave & 1) * 16 + r;
@@ -905,16 +906,18 @@ static void launch_f32_attn_dh(const AttnArgs* f, const AttnBwdArgs* bw, hipStre
   constexpr int KT = f32_attn_kt<DH>();
   const size_t lds = sizeof(float) * (size_t)(2 * KT * (DH + 4) + 2 * KT);
   auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  const int B = f ? f->B : bw->B, H = f ? f->H : bw->H, T = f ? f->T : bw->T, tq = f ? f->Tq : bw->Tq, Tq = tq > 0 ? tq : T;
+  const int ranks = (Tq + 31) / 32 + (f ? 0 : (T + 31) / 32);
+  // a dimension of the grid holds less than 2^32 threads, y and z at most 65535 blocks; any B, H and T get through
+  const unsigned P = (unsigned)B * (unsigned)H, px = P < (1u << 22) ? P : 1u << 22, py = (P + px - 1) / px;
   if (f) {
-    const int Tq = f->Tq > 0 ? f->Tq : f->T;
     const int v4 = f->dh % 4 == 0 && al(f->K) && al(f->V);
     if (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)f32_attn_fwd_kernel<DH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    f32_attn_fwd_kernel<DH><<<(unsigned)(((Tq + 31) / 32) * f->B * f->H), 256, lds, s>>>(*f, v4);
+    for (int r0 = 0; r0 < ranks; r0 += 65535) f32_attn_fwd_kernel<DH><<<dim3(px, py, min(ranks - r0, 65535)), 256, lds, s>>>(*f, v4, r0);
   } else {
-    const int Tq = bw->Tq > 0 ? bw->Tq : bw->T;
     const int v4 = bw->dh % 4 == 0 && al(bw->K) && al(bw->V) && al(bw->Q) && al(bw->dO);
     if (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)f32_attn_bwd_kernel<DH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    f32_attn_bwd_kernel<DH><<<(unsigned)(((Tq + 31) / 32 + (bw->T + 31) / 32) * bw->B * bw->H), 256, lds, s>>>(*bw, v4);
+    for (int r0 = 0; r0 < ranks; r0 += 65535) f32_attn_bwd_kernel<DH><<<dim3(px, py, min(ranks - r0, 65535)), 256, lds, s>>>(*bw, v4, r0);
   }
 }
 

@@ -256,3 +256,20 @@ def test_gated_forms_are_taken(over):
     cfg = _cfg(**dict(dict(B=5, d_model=2048, nheads=2, d_head=64, E=3, k=2), **over))
     steps = _steps(_layer(cfg, make_inputs(cfg, seed=157)))
     assert "bwd.dx_gemm" in steps and not steps & {"fwd.y_sum", "fwd.y_zero"}, steps
+
+
+def test_fp32_more_sequences_and_heads_than_one_grid_dimension_holds():
+    """65535 sequences of one token with 260 heads: 17 million (sequence, head) pairs of 256 threads pass 2^32.  With a single key the
+    read-out is the value row, and queries and keys get no gradient."""
+    import torch
+    cfg = _cfg(dtype="f32", B=65535, T=1, d_model=4, nheads=260, d_head=4, E=1, k=1)
+    layer = _layer(cfg, make_inputs(cfg, seed=163), dense=True)
+    layer.forward()
+    layer.backward()
+    V, ctx = (torch.empty((65535, 260, 4), device=layer.dev) for _ in range(2))
+    from paper_2312_07987_amd import binding
+    binding.switchhead_get_intermediates(layer.shape, layer.ws, None, None, V, ctx, None)
+    assert bool((ctx - V).abs().max() <= 1e-6 * V.abs().max())
+    assert float(layer.dW["W_Q"].abs().max()) < 1e-3 and float(layer.dW["W_K"].abs().max()) < 1e-3
+    want = torch.einsum("nhd,nm->hdm", V.double(), layer.dy[:, 0].double())
+    assert float((layer.dW["W_O"][:, 0].double() - want).abs().max()) < 1e-4 * float(want.abs().max())
