@@ -202,7 +202,8 @@ sh_status switchhead_forward_static(const sh_shape* shape,
  *       dW_S, dW_D              where all weight gradients share one launch (d_model >= 256, d_head >= 64, nheads * E <= 64, a
  *                               workspace above SWITCHHEAD_STATIC_WORKSPACE_BYTES), but not with shared selection and
  *                               T_q < T together;
- *       db_S, db_D              under the conditions of dW_S and dW_D, square attention;
+ *       db_S, db_D              under the conditions of dW_S and dW_D, square attention, routers * nheads * E * tokens / 256 not
+ *                               above d_model * d_head;
  *   - fp32 storage:
  *       y                       E <= 2k and nheads * E <= 40;
  *       dx                      E <= 2k, nheads * (E + 2) <= 38, dense queries and keys;
