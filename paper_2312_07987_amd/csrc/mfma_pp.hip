@@ -360,8 +360,18 @@ __global__ __launch_bounds__(512, 1) void pp_row_gemm_kernel(RowGemmArgs a) {
           if (gt == 0.f) continue;
           const unsigned short* Ap = (const unsigned short*)d.A + row * a.lda;
           const unsigned short* Bp = (const unsigned short*)d.B + (BNT ? (long)n * a.sbn : (long)n);
-          for (int k = 0; k < a.K; ++k)
-            s = fmaf(bf16_to_f32(f32_to_bf16(bf16_to_f32(Ap[k]) * gt)), bf16_to_f32(Bp[BNT ? (long)k : (long)k * a.sbk]), s);
+          for (int k = 0; k < a.K && s == s; k += 8) {   // (rows start at multiples of 16 bytes)
+            unsigned short av[8], bv[8];
+            *(uint4*)av = *(const uint4*)(Ap + k);
+            if constexpr (BNT) {
+              *(uint4*)bv = *(const uint4*)(Bp + k);
+            } else {
+#pragma unroll
+              for (int u = 0; u < 8; ++u) bv[u] = Bp[(long)(k + u) * a.sbk];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s = fmaf(bf16_to_f32(f32_to_bf16(bf16_to_f32(av[u]) * gt)), bf16_to_f32(bv[u]), s);
+          }
         }
         *o = f32_to_bf16(s);
       }
