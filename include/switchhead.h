@@ -207,8 +207,8 @@ sh_status switchhead_forward_static(const sh_shape* shape,
  *   - fp32 storage:
  *       y                       E <= 2k and nheads * E <= 40;
  *       dx                      E <= 2k, nheads * (E + 2) <= 38, dense queries and keys;
- *       all dW                  calls of at most 256 tokens, or whose workspace has room for partial sums (it has not where they would
- *                               more than double it or move the shape out of SWITCHHEAD_STATIC_WORKSPACE_BYTES); dW_S not
+ *       all dW                  calls of at most 256 tokens, or whose workspace has room for all partial sums (it has not where they
+ *                               would double it or move the shape out of SWITCHHEAD_STATIC_WORKSPACE_BYTES); dW_S not
  *                               with shared selection and T_q < T together;
  *       db_S, db_D              calls of at most 256 tokens, not with shared selection and T_q < T together.
  * Elsewhere, and on the plain kernels, the last bits of some of them may differ.

@@ -207,8 +207,11 @@ Layout make_layout(const sh_shape* s) {
     L.pK = take(H * N * k * dh * esz, true);
   }
   L.blockcnt = take(2 * H * (size_t)router_count_blocks((int)N) * E * 4);
-  L.acc32 = take(N * dm * 4);
-  L.u = take(H * N * k * dh * esz);
+  L.acc32 = L.u = 0;
+  if (s->dtype == SH_BF16) {   // (fp32 storage accumulates in y and dx themselves; u: see below)
+    L.acc32 = take(N * dm * 4);
+    L.u = take(H * N * k * dh * esz);
+  }
   L.dctx = take(N * H * dh * esz);
   L.dQ = take(N * H * dh * esz);
   L.dK = take(N * H * dh * esz);
@@ -241,9 +244,10 @@ Layout make_layout(const sh_shape* s) {
     L.rh = take(router_hybrid_bytes((int)N, (int)dm, (int)H, (int)E, o7));
   }
   if (s->dtype == SH_F32) {
-    // The weight gradients of one backward call share a launch: room for the partial sums of all their chunks, unless that would push a
-    // shape out of the built-in workspace (a forward call never uses it) or add more than the rest of the workspace, as long
-    // layers of many experts and few tokens do.  Without room the chunks are added atomically to outputs cleared first.
+    // The weight gradients of one backward call share a launch: room for the partial sums of their chunks, as far as it neither pushes
+    // a shape out of the built-in workspace (a forward call never uses it) nor doubles the workspace, as long layers of
+    // many experts and few tokens would.  Gradients that find no room are added atomically to outputs cleared first.
+    // The partial sums begin over u, the per-slot rows of the output experts' dgrad, which are consumed before the first of them.
     const bool rect = s->T_q > 0 && s->T_q < s->T;
     const size_t Nq = rect ? (size_t)s->B * s->T_q : N;
     auto room = [&](bool gathered, size_t heads, size_t experts, size_t rows_per_expert, size_t groups_rows, size_t ka, size_t kb, size_t kb_store) {
@@ -265,9 +269,10 @@ Layout make_layout(const sh_shape* s) {
     room(false, H, 1, N, N, dm, dh, 0);
     room(false, 1, 1, N, N, dm, (H * E + 7) / 8 * 8, H * E);
     room(false, 1, 1, Nq, Nq, dm, (H * E + 7) / 8 * 8, H * E);
-    const size_t bytes = align_up(L.wpart_floats * 4), built_in = SWITCHHEAD_STATIC_WORKSPACE_BYTES;
-    if (bytes > off || (off <= built_in && off + bytes > built_in)) L.wpart_floats = 0;
-    L.wpart = take(L.wpart_floats * 4);
+    const size_t u_bytes = align_up(H * N * k * dh * esz), with_u = off + u_bytes, built_in = SWITCHHEAD_STATIC_WORKSPACE_BYTES;
+    const size_t extra = with_u <= built_in && built_in - with_u < with_u ? built_in - with_u : with_u;
+    if (align_up(L.wpart_floats * 4) > u_bytes + extra) L.wpart_floats = (u_bytes + extra) / 4;
+    L.u = L.wpart = take(L.wpart_floats * 4 > u_bytes ? L.wpart_floats * 4 : u_bytes);
   }
   // The score gradient of the attention backward, [B][H][keys][queries] bf16: the dK / dV kernel leaves it for the
   // dQ product instead of that kernel recomputing scores and probabilities.  Quadratic in T, so only up to 1 GiB.

@@ -100,8 +100,8 @@ def test_fp32_partial_sums_at_most_double_the_workspace(lib):
     """Many experts, few tokens: the partial sums would be the gradients of every expert (430 MiB instead of 12)."""
     s = binding.make_shape(3, 94, 2048, 5, 76, 63, 2, 1, "f32", qk_experts=1)
     assert binding.switchhead_workspace_bytes(s) < 26 << 20
-    s = binding.make_shape(16, 256, 412, 2, 76, 5, 3, 1, "f32")   # a training batch keeps them (44 + 35 MiB)
-    assert binding.switchhead_workspace_bytes(s) > 70 << 20
+    s = binding.make_shape(16, 256, 412, 2, 76, 5, 3, 1, "f32")   # a training batch keeps them (35 of 65 MiB)
+    assert binding.switchhead_workspace_bytes(s) > 60 << 20
 
 
 def test_forward_rejects_bad_arguments_without_launching(lib):
