@@ -44,7 +44,7 @@ __device__ __forceinline__ void st(bf16_t* p, long i, float v) { p[i].v = f32_to
 //   A[arow*lda + h*a_hoff + k],  B[h*b_hstride + e*b_estride + k*sbk + n*sbn],
 //   C[crow*ldc + h*c_hoff + n]
 // ----------------------------------------------------------------------------------------
-enum { STORE_T = 0, STORE_F32 = 1, ATOMIC_F32 = 2, STORE_F64 = 3 };
+enum { STORE_T = 0, STORE_F32 = 1, ATOMIC_F32 = 2 };
 
 // Which step of the layer a launch serves.  The MFMA kernels are instantiated once per tag so
 // that a profiler shows one kernel name per step; the arithmetic is the same for every tag.
@@ -52,24 +52,7 @@ enum {
   TAG_GENERIC = 0,
   TAG_QK_PROJ, TAG_V_EXPERTS, TAG_O_EXPERTS,   // forward row GEMMs
   TAG_O_DGRAD, TAG_V_DGRAD, TAG_QK_DGRAD,      // backward row GEMMs
-  TAG_O_WGRAD, TAG_V_WGRAD, TAG_QK_WGRAD,      // weight gradients
-  TAG_ROUTER                                   // router logits: fp32 partial sums of 64 terms, added up in fp64
-};
-
-// Epilogue of the router logits GEMM (TAG_ROUTER): the selection of Sec. 2.2's router equations on the
-// tile's logits, see router_select.h.  Launch head h is router side h.
-struct RouterSelect {
-  const float* b[2];            // logit bias per side or NULL
-  const float* wnorm2;          // [side][H*E] squared column norms
-  int* idx;                     // [side][H][N][k]
-  float* gate;
-  const void* x;                // bf16 [N][dm]
-  const unsigned short* Wt;     // [side][H*E][dmp] router columns as vectors
-  int N, kstep, H, E, k, dm, dmp;
-  // fewer queries than keys: side 1 routes the Nq rows of xq (0: the rows of x); its tables follow those of H * N tokens
-  const void* xq;
-  int Nq;
-  int shared;   // side 1 uses side 0's columns
+  TAG_O_WGRAD, TAG_V_WGRAD, TAG_QK_WGRAD       // weight gradients
 };
 
 // One segment of a concatenated reduction with per-row gates (segment mode 3): the segment's A columns start at
@@ -117,8 +100,6 @@ struct RowGemmArgs {
   //     against (B, B2 or B3 for p/seg_split = 0, 1, 2) + (p%seg_split)*b_sstride.
   int seg_mode, nseg, experts;
   const int* set_experts;
-  // TAG_ROUTER only: the selection that consumes the logits in the kernel's epilogue (C is not written)
-  RouterSelect rsel;
   const float* segate;
   int seg_split;
   long a_sstride, a_wstride, b_sstride;
@@ -278,19 +259,19 @@ struct RouterArgs {
   float* gate;            // [sides, H, N, k]
   int* perm;              // [sides, H, N*k]
   int* offsets;           // [sides, H, E+1]
-  int* blockcnt;          // [sides*H, router_count_blocks(N), E] scratch
+  int* blockcnt;          // [sides*H, E, router_count_blocks(N)] scratch
   int N, dm, H, E, k, sides;
   int bf16;
   // if not NULL (and for as many sides), launch_router_hybrid also sorts the tokens by expert set,
   // sharing the passes of the expert sort; the caller then skips launch_set_sort
   const SetSortArgs* sets;
-  // if not NULL (launch_router_hybrid without `sets`, both sides routed on the same N tokens): the dense gate table
-  // [sides][N][H*E] is written along the histogram pass
+  int* setcnt;            // [sides*H, nsets, router_count_blocks(N)] scratch for that
+  // if not NULL (launch_router_hybrid): the dense gate table [sides][N][H*E] is written as well
   float* gtab;
-  // launch_router_hybrid with sides == 2: side 1 routes the Nq rows of xq instead (0: the same tokens).  Every side-1 table then starts
-  // where it would with N tokens.  shared: with the weights and the bias of side 0.
-  const void* xq;
-  int Nq, shared;
+  // launch_router_hybrid with sides == 2 and Nq > 0: side 1 routes the last Tq of every T rows of x, Nq in all, and copies them
+  // to xq.  Every side-1 table then starts where it would with N tokens.  shared: with the weights of side 0.
+  void* xq;
+  int Nq, shared, T, Tq;
 };
 void launch_router(const RouterArgs& a, hipStream_t s);
 // Up to eight pieces of 4-byte elements copied by one launch (the destination side's tables where one selection serves both sides)
@@ -302,16 +283,14 @@ struct CopyList {
 };
 void launch_copy_list(const CopyList& l, hipStream_t s);
 // bf16 storage: fp32 matrix-core logits with an fp64 re-evaluation of every decision that
-// is not provably safe (see routing.hip).  `scratch` needs router_hybrid_bytes() bytes.
-size_t router_hybrid_bytes(int N, int dm, int H, int E, size_t* off7);
+// is not provably safe (see routing.hip).
 bool router_hybrid_supported(const RouterArgs& a);
-void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s);
+void launch_router_hybrid(const RouterArgs& a, hipStream_t s);
 // Dense attention: every token takes "expert" 0 with gate 1, on both sides (n0 and n1 tokens, the second side's tables behind those of
 // H * n0 tokens).  t (or NULL): the set tables to fill as well.
 void launch_dense_routing(int* idx, float* gate, int* perm, int* offsets, int n0, int n1, int H, const SetSortArgs* t, hipStream_t s);
-bool router_sides_supported(const RouterArgs& a);   // launch_router_hybrid takes the two token sets of `a` in one go
-int router_blocks(int N);  // token blocks used by the histogram/scatter kernels
-int router_count_blocks(int N);   // token blocks of the fp64 router's expert counts
+int router_blocks(int N);  // token blocks used by the set histogram and the scatter kernels
+int router_count_blocks(int N);   // token blocks of the routers' counts
 // gtab[side][n][h*E+e] = gate of the selected experts, 0 elsewhere (idx, gate: [side][H][N][k], sides side_stride_in apart)
 void launch_gate_table(const int* idx, const float* gate, float* gtab, int N, int H, int E, int k, int sides, long side_stride_in,
                        hipStream_t s);
@@ -326,7 +305,7 @@ struct SetSortArgs {
   int* setexp;         // [nsets, 8] the ascending experts of every set
   int* setperm;        // [sides, H, N] token ids sorted by set id (stable)
   int* setoff;         // [sides, H, nsets+1]
-  int* blockcnt;       // [sides*H, nblk, nsets] scratch
+  int* blockcnt;       // [sides*H, nsets, nblk] scratch
   int N, H, k, E, nsets, sides;
 };
 void launch_set_sort(const SetSortArgs& a, hipStream_t s);
@@ -426,7 +405,6 @@ void launch_f32_attn_bwd(const AttnBwdArgs& a, hipStream_t s);
 
 // MFMA family (bf16 storage only).  *_supported() say whether a launch can be served.
 bool mfma_row_gemm_supported(const RowGemmArgs& a);
-int rg_kstep();  // terms summed in fp32 by one K step of the row GEMM
 void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s);
 // 256 x 256 tiles, eight waves in two alternating groups (mfma_pp.hip); launch_mfma_row_gemm routes to it
 bool pp_row_gemm_supported(const RowGemmArgs& a);

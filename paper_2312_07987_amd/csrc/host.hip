@@ -80,7 +80,7 @@ struct Layout {
   size_t gtab;                                                     // dense gate table [2][N][H*E] fp32 (gated-concatenation GEMMs)
   size_t wrt;                                                      // x^T dz of both routers [dm, dh] fp32 (fused with the Q/K weight gradient)
   size_t dR, wr3;                                                  // wide router dz rows [N, H*dh], routers packed [dm, dh]                 // expert-set path (bf16 only)
-  size_t rh;                                                       // two-stage router scratch (bf16 only)
+  size_t rh, rh_bytes;                                             // routers packed for the backward pass; counts of the set sort (bf16 only)
   size_t wpart;                                                    // per-chunk weight-gradient partial sums
   size_t wpart_floats = 0;                                         // ... their room
   size_t u, dctx, dQ, dK, dV, delta, dgate, dz;                    // backward scratch
@@ -237,11 +237,12 @@ Layout make_layout(const sh_shape* s) {
   } else {
     L.setid = L.gset = L.gsort = L.setexp = L.setperm = L.setoff = L.setcnt = L.yh = 0;
   }
-  L.rh = L.wpart = L.gtab = 0;
+  L.rh = L.rh_bytes = L.wpart = L.gtab = 0;
   if (s->dtype == SH_BF16) {
     L.gtab = take(2 * N * H * E * 4, true);
-    size_t o7[7];
-    L.rh = take(router_hybrid_bytes((int)N, (int)dm, (int)H, (int)E, o7));
+    // both routers padded to HEp columns, and as much again in whole slabs of 1024 features (what callers' workspaces are sized for)
+    L.rh_bytes = align_up(2 * dm * ((H * E + 7) / 8 * 8) * 2) + align_up(2 * H * E * 4) + align_up(2 * H * E * ((dm + 1023) / 1024 * 1024) * 2);
+    L.rh = take(L.rh_bytes);
   }
   if (s->dtype == SH_F32) {
     // The weight gradients of one backward call share a launch: room for the partial sums of their chunks, as far as it neither pushes
@@ -668,24 +669,28 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     sa.nsets = count_sets(E, k);
     sa.sides = 2;
   }
+  // The two-stage router counts its tokens per set in blocks of 32.  The counts live until the scatter: in the scratch of the packed routers
+  // or, longer tables, where queries, keys, values, read-outs and value slots are written later (36 bytes or more per token and head
+  // of four or more columns, for at most 32 bytes of counts).
+  int* const setcnt = [&] {
+    const size_t need = tables ? (size_t)2 * H * router_count_blocks(N) * count_sets(E, k) * 4 : 0;
+    return need <= c.L.rh_bytes ? c.p<int>(c.L.rh) : need <= c.L.pV + (size_t)H * N * k * dh * 2 - c.L.Q ? c.p<int>(c.L.Q) : nullptr;
+  }();
   prof_mark(c.st, "fwd.router");
   const void* xq = x;   // the destination (query) tokens' rows of x
   if (c.rect) {
     // Fewer queries than keys: the query tokens' rows (the last T_q of every sequence) are copied into
     // one block, and each side is routed on its own tokens.  Shared selection evaluates the one router
     // on the query rows again, which gives the source side's numbers for those tokens.
+    // (the matrix-core router takes both sides in one launch and copies the rows as it reads them)
     const size_t esz = c.bf16 ? 2 : 4, rowb = (size_t)dm * esz;
     xq = c.p<void>(c.L.xq);
-    if (hipMemcpy2DAsync(c.p<void>(c.L.xq), (size_t)c.Tq * rowb, (const char*)x + (size_t)(shape->T - c.Tq) * rowb,
-                         (size_t)shape->T * rowb, (size_t)c.Tq * rowb, (size_t)shape->B, hipMemcpyDeviceToDevice,
-                         c.st) != hipSuccess)
-      return fail(SH_ERR_HIP, "switchhead_forward: copy of the query rows failed");
-    const int nblk = router_blocks(N), ns = count_sets(E, k);
-    // (matrix-core router: both sides share its launches)
     RouterArgs rs{};
     rs.x = x;
-    rs.xq = xq;
+    rs.xq = c.p<void>(c.L.xq);
     rs.Nq = c.Nq;
+    rs.T = shape->T;
+    rs.Tq = c.Tq;
     rs.shared = c.shared;
     rs.W[0] = W_S;
     rs.W[1] = W_D;
@@ -704,10 +709,16 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     rs.sides = 2;
     rs.bf16 = c.bf16;
     if (tables) rs.sets = &sa;
+    rs.setcnt = setcnt;
     if (gate_table) rs.gtab = c.p<float>(c.L.gtab);
-    const bool together = !c.dense && use_mfma(c) && router_sides_supported(rs);
+    const bool together = !c.dense && use_mfma(c) && router_hybrid_supported(rs) && setcnt;
+    if (!together && hipMemcpy2DAsync(c.p<void>(c.L.xq), (size_t)c.Tq * rowb, (const char*)x + (size_t)(shape->T - c.Tq) * rowb,
+                         (size_t)shape->T * rowb, (size_t)c.Tq * rowb, (size_t)shape->B, hipMemcpyDeviceToDevice,
+                         c.st) != hipSuccess)
+      return fail(SH_ERR_HIP, "switchhead_forward: copy of the query rows failed");
+    const int nblk = router_blocks(N), ns = count_sets(E, k);
     if (together) {
-      launch_router_hybrid(rs, c.p<char>(c.L.rh), c.st);
+      launch_router_hybrid(rs, c.st);
       gtab_done = true;
     }
     if (c.dense) launch_dense_routing(c.idx(0), c.gate(0), c.perm(0), c.offsets(0), N, c.Nq, H, tables ? &sa : nullptr, c.st);
@@ -745,15 +756,9 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
       ra.k = k;
       ra.sides = 1;
       ra.bf16 = c.bf16;
-      if (use_mfma(c) && router_hybrid_supported(ra)) {
-        if (tables) ra.sets = &s1;
-        if (gate_table) ra.gtab = gtab_side;
-        launch_router_hybrid(ra, c.p<char>(c.L.rh), c.st);
-      } else {
-        launch_router(ra, c.st);
-        if (tables) launch_set_sort(s1, c.st);
-        if (gate_table) launch_gate_table(c.idx(side), c.gate(side), gtab_side, n, H, E, k, 1, 0, c.st);
-      }
+      launch_router(ra, c.st);
+      if (tables) launch_set_sort(s1, c.st);
+      if (gate_table) launch_gate_table(c.idx(side), c.gate(side), gtab_side, n, H, E, k, 1, 0, c.st);
       gtab_done = true;
     }
     sets_sorted = true;
@@ -780,16 +785,17 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     ra.k = k;
     ra.sides = c.shared ? 1 : 2;
     ra.bf16 = c.bf16;
-    if (use_mfma(c) && router_hybrid_supported(ra)) {
+    if (use_mfma(c) && router_hybrid_supported(ra) && setcnt) {
       if (tables) {   // both sorts in the same launches
         sa.sides = ra.sides;
         ra.sets = &sa;
+        ra.setcnt = setcnt;
         sets_sorted = true;
-      } else if (gate_table && !c.shared) {   // the dense gate table rides along the histogram pass
+      } else if (gate_table && !c.shared) {   // the router writes the dense gate table itself
         ra.gtab = c.p<float>(c.L.gtab);
         gtab_done = true;
       }
-      launch_router_hybrid(ra, c.p<char>(c.L.rh), c.st);
+      launch_router_hybrid(ra, c.st);
     } else {
       launch_router(ra, c.st);
     }

@@ -9,7 +9,6 @@
 //   D: register q (0..15) holds D[8*(q/4) + 4g + q%4][col r]
 #include "common.h"
 #include "mfma_util.h"
-#include "router_select.h"
 #include <cstdlib>
 
 namespace sh {
@@ -47,10 +46,6 @@ typedef TileCfg<2, 2, 2, 2, 80, 1> CfgSmall80;  // the same with an 80-wide K st
                                                 // or 80) then takes one step per segment instead of one and a mostly empty second
 typedef TileCfg<4, 1, 1, 3, 64, 1> CfgN96;      // 128 x 96, wave tile 32 x 96: outputs 65..96 wide (head widths 76, 80, 96)
                                                 // waste a fifth of a 96-wide tile instead of two fifths of a 128-wide one
-typedef TileCfg<2, 2, 1, 1, 64, 1> CfgRouter;   // 64 x 64: the router logits have <= 32 columns and want many work-groups (a K step of
-                                                // 256, four times the bytes per load round trip but one work-group per CU: 35 -> 50 us at c2)
-typedef TileCfg<2, 2, 1, 1, 64, 4> CfgRouterDeep;   // the same for launches of at most one work-group per CU: four K steps per trip to memory
-                                                    // (a K loop of d_model 1024 is sixteen trips otherwise: a 100-token call 92 -> 89.6 us)
 typedef TileCfg<2, 2, 2, 4, 64, 1, 2> CfgWide;     // 128 x 256, wave tile 64 x 128, two work-groups per CU
 typedef TileCfg<2, 2, 4, 2, 64, 1, 2> CfgMed;   // 256 x 128, wave tile 128 x 64, two work-groups per CU
 
@@ -87,10 +82,9 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
       if (row0 >= end) return;
       rows = end - row0 < BM ? end - row0 : BM;
     } else {
-      const int M = TAG == TAG_ROUTER && h == 1 && a.rsel.Nq > 0 ? a.rsel.Nq : a.M;
       row0 = w * BM;
-      if (row0 >= M) return;
-      rows = M - row0 < BM ? M - row0 : BM;
+      if (row0 >= a.M) return;
+      rows = a.M - row0 < BM ? a.M - row0 : BM;
     }
   }
   const bool second = a.hsplit > 0 && h >= a.hsplit;
@@ -136,7 +130,7 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
   }
   __syncthreads();
 
-  const unsigned short* A = (const unsigned short*)(TAG == TAG_ROUTER && h == 1 && a.rsel.Nq > 0 ? a.rsel.xq : a.A);
+  const unsigned short* A = (const unsigned short*)a.A;
   const unsigned short* Bbase = (const unsigned short*)(second ? a.B2 : a.B);
   const unsigned short* B = Bbase + (SEG ? 0 : (long)hh * a.b_hstride + (long)e * a.b_estride);
   const int n0 = ct * BN;
@@ -182,7 +176,6 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
 
   chunk_t ra[A_N], rb[B_N];
   const int nks = (K + BK - 1) / BK;   // K steps per segment
-  float sumsq[TAG == TAG_ROUTER ? A_N : 1] = {};
   int staged_seg = 0;   // segment of the K step that sits in ra / rb
   auto load_global = [&](int it) {
     const int seg = SEG ? it / nks : 0;
@@ -221,7 +214,6 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
       // flight while the previous step is multiplied
       if constexpr (SEG == 1) ra[i] = scale_chunk(ra[i], gsc[(a_lds[i] / LDA) * 8 + staged_seg]);
       *(chunk_t*)(&As[a_lds[i]]) = ra[i];
-      if constexpr (TAG == TAG_ROUTER) sumsq[i] += chunk_sumsq(ra[i]);   // row norms ride along (see epilogue)
     }
 #pragma unroll
     for (int i = 0; i < B_N; ++i) *(chunk_t*)(&Bs[b_lds[i]]) = rb[i];
@@ -236,16 +228,6 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-
-  constexpr bool ACC64 = TAG == TAG_ROUTER;
-  const bool active = !ACC64 || n0 + wn < Nc;   // router: at most 32 columns, held by the waves with wn == 0
-  double acc64[ACC64 ? MI : 1][16];
-  if constexpr (ACC64) {
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc64[i][q] = 0.0;
-  }
 
   auto compute = [&](int stage) {
     const unsigned short* As = smem + stage * Cfg::STAGE_ELEMS;
@@ -265,128 +247,26 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-          if (!ACC64 || j == 0) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-      if constexpr (ACC64) {
-        // router logits: the fp32 accumulator only ever holds the sum of 64 terms
-        if ((kk & 63) == 48) {
-#pragma unroll
-          for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-              acc64[i][q] += (double)acc[i][0][q];
-              acc[i][0][q] = 0.f;
-            }
-        }
-      }
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
     }
   };
 
   const int nk = nks * nseg;
-  if constexpr (Cfg::STAGES == 1) {
-    load_global(0);
-    store_lds(0);
+  load_global(0);
+  store_lds(0);
+  __syncthreads();
+  for (int kt = 0; kt < nk; ++kt) {
+    if (kt + 1 < nk) load_global(kt + 1);
+    compute(0);
     __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt + 1 < nk) load_global(kt + 1);
-      if (active) compute(0);
-      __syncthreads();
-      if (kt + 1 < nk) {
-        store_lds(0);
-        __syncthreads();
-      }
-    }
-  } else if constexpr (Cfg::STAGES == 4) {
-    // four K steps travel together; loads without conditions (clamped, what must not count is zeroed on its way into LDS)
-    static_assert(SEG == 0 && !BNT, "the router's launch");
-    chunk_t da[4][A_N], db[4][B_N];
-    auto load4 = [&](int it) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k0 = (it + u) * BK;
-#pragma unroll
-        for (int i = 0; i < A_N; ++i) da[u][i] = *(const chunk_t*)(A + (a_off[i] >= 0 ? a_off[i] : 0l) + min(k0, K - VEC - a_kc[i]));
-#pragma unroll
-        for (int i = 0; i < B_N; ++i) db[u][i] = *(const chunk_t*)(B + (b_ok[i] ? b_off[i] : (long)b_kc[i] * a.sbk) + (long)min(k0, K - 1 - b_kc[i]) * a.sbk);
-      }
-    };
-    auto store4 = [&](int it) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        unsigned short* As = smem + u * Cfg::STAGE_ELEMS;
-        unsigned short* Bs = As + Cfg::A_ELEMS;
-        const int k0 = (it + u) * BK;
-#pragma unroll
-        for (int i = 0; i < A_N; ++i) {
-          const chunk_t v = a_off[i] >= 0 && k0 + a_kc[i] < K ? da[u][i] : zero_chunk<VEC>();
-          *(chunk_t*)(&As[a_lds[i]]) = v;
-          if constexpr (TAG == TAG_ROUTER) sumsq[i] += chunk_sumsq(v);
-        }
-#pragma unroll
-        for (int i = 0; i < B_N; ++i) *(chunk_t*)(&Bs[b_lds[i]]) = b_ok[i] && k0 + b_kc[i] < K ? db[u][i] : zero_chunk<VEC>();
-      }
-    };
-    load4(0);
-    for (int kt = 0; kt < nk; kt += 4) {
-      store4(kt);
-      __syncthreads();
-      if (kt + 4 < nk) load4(kt + 4);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (active) compute(u);   // (steps past the last are zeros)
+    if (kt + 1 < nk) {
+      store_lds(0);
       __syncthreads();
     }
-  } else {
-    // two LDS stages: K step kt is multiplied from stage kt&1 while step kt+2 travels
-    // global -> registers; it is written into the stage just consumed
-    load_global(0);
-    store_lds(0);
-    if (nk > 1) {
-      load_global(1);
-      store_lds(1);
-    }
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt + 2 < nk) load_global(kt + 2);
-      compute(kt & 1);
-      __syncthreads();
-      if (kt + 2 < nk) store_lds(kt & 1);
-    }
-    __syncthreads();
   }
 
   // ---- epilogue -------------------------------------------------------------------------
   char* Cb = (char*)(second ? a.C2 : a.C);
-  if constexpr (ACC64) {
-    // Router: the tile's logits never leave the CU.  They go to LDS (the operand tiles are dead) next to
-    // the rows' sums of squares (the error bound needs |x_n|, and every chunk of the A rows went through
-    // this block's registers: 8 threads share a row), and the selection runs on them right here.
-    static_assert(BM * 32 * 8 + BM * 4 + 4 * 64 * 8 + 256 * 4 + 16 <= Cfg::STAGES * Cfg::STAGE_ELEMS * 2, "router epilogue needs the LDS");
-    double* zt = (double*)smem;                  // [BM][Nc], Nc <= 32
-    double(*zs)[64] = (double(*)[64])(zt + BM * 32);
-    float* rs = (float*)(zs + 4);
-    int* flist = (int*)(rs + BM);
-    int* nflag = flist + 256;
-    __syncthreads();
-    for (int t = tid; t < BM; t += 256) rs[t] = 0.f;
-    if (tid == 0) *nflag = 0;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < A_N; ++i) atomicAdd(&rs[a_lds[i] / LDA], sumsq[i]);
-    if (active) {
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const int row = wm + i * 32 + 8 * (q >> 2) + 4 * g + (q & 3);
-          const int n = n0 + wn + r;
-          if (n < Nc) zt[row * Nc + n] = acc64[i][q];
-        }
-    }
-    __syncthreads();
-    router_select_tile(a.rsel, h, zt, Nc, rs, ids, BM, zs, flist, nflag);
-    return;
-  }
   if (a.mode == STORE_T) {   // the host checks Nc % VEC == 0 for this mode
     // bf16 output: each wave stages 32 rows of its tile in LDS (the operand tiles are dead: the
     // main loop ends with a barrier), then stores them as 16-byte (8-byte) pieces along the rows.  The
@@ -443,8 +323,6 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
   }
 }
 
-int rg_kstep() { return 64; }   // terms the router logits GEMM sums in fp32 before it flushes to fp64
-
 static bool aligned_to(const void* p, size_t b) { return ((uintptr_t)p % b) == 0; }
 
 // vector width (bf16 elements) all loads of a row GEMM can use, 0 if none
@@ -470,9 +348,6 @@ static int row_gemm_vec(const RowGemmArgs& a) {
 
 bool mfma_row_gemm_supported(const RowGemmArgs& a) {
   if (a.seg_mode == 1 && (a.nseg < 1 || a.nseg > 8 || a.E > 128)) return false;   // the tile lookup covers 128 groups
-  if (a.tag == TAG_ROUTER && (a.Nc > 32 || a.mode != STORE_F64 || a.seg_mode != 0 || a.perm || a.E != 1 || a.hsplit != 0 ||
-                              a.a_div != 1 || a.Nc < a.rsel.H * a.rsel.E))
-    return false;
   // row ids stay below M; the multiply-high division needs id * divisor < 2^32
   if ((long)a.M * (a.a_div > a.c_div ? a.a_div : a.c_div) >= (1L << 32)) return false;
   return row_gemm_vec(a) != 0;
@@ -505,7 +380,7 @@ static void launch_cfg(const RowGemmArgs& a, hipStream_t s) {
 enum { SHAPE_SMALL, SHAPE_WIDE, SHAPE_MED };
 static int pick_shape(const RowGemmArgs& a) {
   const int group_rows = a.perm ? a.max_group_rows : a.M;
-  if (a.tag == TAG_ROUTER || a.tag == TAG_GENERIC) return SHAPE_SMALL;
+  if (a.tag == TAG_GENERIC) return SHAPE_SMALL;
   // measured on MI355X: the 256 x 128 tile with two work-groups per CU wins where the rows are
   // dense (its operand traffic per flop is 25 % lower); expert-gathered rows do better with
   // the small tile (more work-groups in flight per CU)
@@ -551,15 +426,6 @@ static void launch_generic(const RowGemmArgs& a, hipStream_t s) {
     launch_generic_cfg<CfgSmall, VEC, BNT>(a, s);
 }
 
-template <int VEC>
-static void launch_router_logits(const RowGemmArgs& a, hipStream_t s) {
-  const long rows = a.rsel.Nq > 0 && a.heads == 2 ? (a.M + 63) / 64 + (a.rsel.Nq + 63) / 64 : (long)a.heads * ((a.M + 63) / 64);
-  if (rows <= 256 && a.K >= 64)   // at most one tile per CU: nothing else hides the trips to memory
-    launch_cfg<CfgRouterDeep, VEC, false, TAG_ROUTER, 0>(a, s);
-  else
-    launch_cfg<CfgRouter, VEC, false, TAG_ROUTER, 0>(a, s);
-}
-
 void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.Nc <= 0) return;
   if (pp_row_gemm_supported(a)) return launch_pp_row_gemm(a, s);
@@ -583,14 +449,12 @@ void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s) {
         case TAG_V_EXPERTS * 4 + 0: return launch_tagged<false, TAG_V_EXPERTS, 0>(a, s);
         case TAG_O_EXPERTS * 4 + 0: return launch_tagged<false, TAG_O_EXPERTS, 0>(a, s);
         case TAG_O_EXPERTS * 4 + 1: return launch_tagged<false, TAG_O_EXPERTS, 1>(a, s);
-        case TAG_ROUTER * 4 + 0: return launch_router_logits<8>(a, s);
         default: return launch_generic<8, false>(a, s);
       }
     }
   }
   if (nt)
     return launch_generic<4, true>(a, s);
-  if (a.tag == TAG_ROUTER) return launch_router_logits<4>(a, s);
   return launch_generic<4, false>(a, s);
 }
 

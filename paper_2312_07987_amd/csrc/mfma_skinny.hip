@@ -17,10 +17,6 @@ namespace {
 constexpr int SK_T = 32;      // tile rows and columns
 constexpr int SK_KW = 256;    // reduction indices a wave holds at a time
 constexpr int SK_MAX_TILES = 768;
-__device__ __forceinline__ void wave_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 }  // namespace
 
 __global__ __launch_bounds__(256, 2) void skinny_row_gemm_kernel(RowGemmArgs a) {
@@ -104,7 +100,7 @@ static bool sk_aligned(const void* p) { return ((uintptr_t)p % 16) == 0; }
 // A launch of at most SK_MAX_TILES tiles of 32 x 32 (expected: a sorted group's rows are counted together), three for each CU; 16-byte
 // pieces of A and B, whole pieces of 8 columns.
 bool skinny_row_gemm_supported(const RowGemmArgs& a) {
-  if (a.seg_mode != 0 || a.gate || a.mode != STORE_T || a.sbn != 1 || a.sbk < a.Nc || a.tag == TAG_ROUTER) return false;
+  if (a.seg_mode != 0 || a.gate || a.mode != STORE_T || a.sbn != 1 || a.sbk < a.Nc) return false;
   if (a.M < 1 || a.K < 8 || a.K % 8 != 0 || a.Nc < 8 || a.Nc % 8 != 0) return false;
   if (!sk_aligned(a.A) || !sk_aligned(a.B) || !sk_aligned(a.C) || (a.hsplit > 0 && !(sk_aligned(a.B2) && sk_aligned(a.C2)))) return false;
   if (a.lda % 8 || a.a_hoff % 8 || a.sbk % 8 || a.b_hstride % 8 || a.b_estride % 8 || a.ldc % 4 || a.c_hoff % 4) return false;

@@ -12,6 +12,7 @@ namespace sh {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
@@ -38,6 +39,12 @@ __device__ __forceinline__ bf16x8 frag_transposed(const unsigned short* tile, in
   return u.v;
 }
 
+// orders a wave's LDS operations on an area of its own (the hardware keeps their order; this keeps the compiler from changing it)
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 template <int VEC>
 struct Chunk;
 template <>
@@ -48,19 +55,6 @@ template <>
 struct Chunk<4> {
   typedef uint2 type;
 };
-
-__device__ __forceinline__ float chunk_sumsq(uint4 v) {
-  const unsigned w[4] = {v.x, v.y, v.z, v.w};
-  float s = 0.f;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const float lo = __uint_as_float(w[u] << 16), hi = __uint_as_float(w[u] & 0xffff0000u);
-    s = fmaf(lo, lo, s);
-    s = fmaf(hi, hi, s);
-  }
-  return s;
-}
-__device__ __forceinline__ float chunk_sumsq(uint2 v) { return chunk_sumsq(make_uint4(v.x, v.y, 0, 0)); }
 
 template <int VEC>
 __device__ __forceinline__ typename Chunk<VEC>::type zero_chunk() {

@@ -8,14 +8,15 @@
 //             "largest remaining logit, lowest index on ties"; gate = sigmoid(logit); expert counts
 //             of the work-group's tokens
 //   scan      exclusive scan over (expert major, token block minor), done by every scatter block for
-//             itself where the table of counts is small
+//             itself where the table of counts is small; counts are [side, head][bin][token block]
 //   scatter   stable placement: rank inside the block from ballots + popcounts, so
 //             no atomics decide an order and the result is deterministic
 #include "common.h"
+#include "mfma_util.h"
 
 namespace sh {
 
-static constexpr int RT_TOK = 32;    // tokens per block of the fp64 router
+static constexpr int RT_TOK = 32;    // tokens per work-group of either router, and per block of counts
 static constexpr int RT_KC = 64;     // d_model chunk staged in LDS
 static constexpr int RB = 256;       // tokens per block of the scatter kernels
 
@@ -121,19 +122,17 @@ __global__ __launch_bounds__(256) void router_select_kernel(const T* __restrict_
     }
   }
   __syncthreads();
-  for (int c = tid; c < ncols; c += 256) cnt[((long)(side * H + h0 + c / E) * ncb + blockIdx.x) * E + c % E] = cn[c];
+  for (int c = tid; c < ncols; c += 256) cnt[((long)(side * H + h0) * E + c) * ncb + blockIdx.x] = cn[c];
 }
 
-// One block per (side, head).  blockcnt[sh][blk][e] (counts) -> in place: first position of
+// One block per (side, head).  blockcnt[sh][e][blk] (counts) -> in place: first position of
 // bin e for token block blk; offsets[sh][0..E].  One wave per bin, lanes over token blocks.
 __device__ __forceinline__ void scan_body(int* __restrict__ blockcnt, int* __restrict__ offsets, int E, int nblk) {
   __shared__ int tot[129];
-  const int sh_ = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int* c = blockcnt + (long)sh_ * nblk * E;
   for (int e = wave; e < E; e += 4) {
     int sum = 0;
-    for (int b = lane; b < nblk; b += 64) sum += c[(long)b * E + e];
+    for (int b = lane; b < nblk; b += 64) sum += blockcnt[(long)e * nblk + b];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
     if (lane == 0) tot[e] = sum;
@@ -149,132 +148,103 @@ __device__ __forceinline__ void scan_body(int* __restrict__ blockcnt, int* __res
     tot[E] = run;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i <= E; i += 256) offsets[(long)sh_ * (E + 1) + i] = tot[i];
+  for (int i = threadIdx.x; i <= E; i += 256) offsets[i] = tot[i];
   for (int e = wave; e < E; e += 4) {
     int run = tot[e];
     for (int b0 = 0; b0 < nblk; b0 += 64) {
       const int b = b0 + lane;
-      const int v = b < nblk ? c[(long)b * E + e] : 0;
+      const int v = b < nblk ? blockcnt[(long)e * nblk + b] : 0;
       int inc = v;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
         int u = __shfl_up(inc, o, 64);
         if (lane >= o) inc += u;
       }
-      if (b < nblk) c[(long)b * E + e] = run + inc - v;
+      if (b < nblk) blockcnt[(long)e * nblk + b] = run + inc - v;
       run += __shfl(inc, 63, 64);
     }
   }
 }
-__global__ __launch_bounds__(256) void scan_kernel(int* __restrict__ blockcnt, int* __restrict__ offsets, int E,
-                                                   int nblk) {
-  scan_body(blockcnt, offsets, E, nblk);
-}
-// the expert table (blockIdx.y == 0) and the set table (blockIdx.y == 1) in one launch
-__global__ __launch_bounds__(256) void scan2_kernel(int* __restrict__ blockcnt, int* __restrict__ offsets, int E,
-                                                    int* __restrict__ setcnt, int* __restrict__ setoff, int nsets,
-                                                    int nblk) {
-  if (blockIdx.y == 0)
-    scan_body(blockcnt, offsets, E, nblk);
-  else
-    scan_body(setcnt, setoff, nsets, nblk);
+
+// sum over the 16 lanes of a row (rotations inside the row)
+__device__ __forceinline__ int row_sum(int v) {
+  v += __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, false);
+  v += __builtin_amdgcn_mov_dpp(v, 0x124, 0xf, 0xf, false);
+  v += __builtin_amdgcn_mov_dpp(v, 0x122, 0xf, 0xf, false);
+  return v + __builtin_amdgcn_mov_dpp(v, 0x121, 0xf, 0xf, false);
 }
 
 // What scan_body would leave for this token block, computed by the block itself from the raw counts
-// cnt[sh][blk][bin] (for tables small enough that every block can read them whole): sbase[bin] = first
-// position of bin `bin` for token block blockIdx.x; token block 0 also writes offsets[sh][0..nbins].
-// One wave per bin, lanes over token blocks.  Called by all RB threads; ends with a barrier.
-// `per`: count blocks per scatter block (a count block holds RB / per tokens).
-__device__ __forceinline__ void block_bases(const int* __restrict__ cnt, int* __restrict__ offsets, int nbins, int nblk,
-                                            int* __restrict__ sbase /* LDS [2 * 128 + 1] */, int per = 1) {
-  const int sh_ = blockIdx.y, blk = blockIdx.x;
+// cnt[bin][count block] (for tables small enough that every block can read them whole): sbase[bin] = first
+// position of bin `bin` for token block blockIdx.x, which holds the count blocks from blockIdx.x * per on; token block 0
+// also writes offsets[0..nbins].  16 lanes per bin, sixteen loads in flight.  Called by all RB threads; ends with a barrier.
+__device__ __forceinline__ void block_bases(const int* __restrict__ cnt, int* __restrict__ offsets, int nbins, int ncb, int per,
+                                            int* __restrict__ sbase /* LDS [2 * 128 + 1] */) {
+  const int first = blockIdx.x * per;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int* c = cnt + (long)sh_ * nblk * nbins;
   int* tot = sbase + 128;
-  for (int e = wave; e < nbins; e += RB / 64) {
+  for (int e0 = 0; e0 < nbins; e0 += RB / 16) {
+    const int e = e0 + (threadIdx.x >> 4);
+    const int* c = cnt + (long)min(e, nbins - 1) * ncb;
     int all = 0, pre = 0;
-    for (int b = lane; b < nblk; b += 64) {
-      const int v = c[(long)b * nbins + e];
-      all += v;
-      pre += b < blk * per ? v : 0;
-    }
+    for (int b0 = lane & 15; b0 - (lane & 15) < ncb; b0 += 256) {
+      int v[16];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      all += __shfl_xor(all, o, 64);
-      pre += __shfl_xor(pre, o, 64);
+      for (int u = 0; u < 16; ++u) v[u] = c[min(b0 + 16 * u, ncb - 1)];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int b = b0 + 16 * u;
+        all += b < ncb ? v[u] : 0;
+        pre += b < first ? v[u] : 0;   // (first < ncb)
+      }
     }
-    if (lane == 0) {
+    all = row_sum(all);
+    pre = row_sum(pre);
+    if ((lane & 15) == 0 && e < nbins) {
       tot[e] = all;
       sbase[e] = pre;
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int i = 0; i < nbins; ++i) {
-      const int t = tot[i];
-      tot[i] = run;
-      sbase[i] += run;
-      run += t;
-    }
-    tot[nbins] = run;
-  }
-  __syncthreads();
-  if (blk == 0)
-    for (int i = threadIdx.x; i <= nbins; i += RB) offsets[(long)sh_ * (nbins + 1) + i] = tot[i];
-}
-
-// LOCAL: the block's bases are in LDS (sbase, from block_bases) instead of the scanned table `base`
-template <bool LOCAL = false>
-__device__ __forceinline__ void scatter_body(const int* __restrict__ idx, const int* __restrict__ base,
-                                             int* __restrict__ perm, int N, int E, int k, int nblk,
-                                             const int* sbase = nullptr, int per = 1) {
-  __shared__ int wcnt[RB / 64][64];
-  const int sh_ = blockIdx.y;
-  const int n = blockIdx.x * RB + threadIdx.x;
-  const bool valid = n < N;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-
-  int ej[8], rk[8];
-  unsigned long long sel = 0ull;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    ej[j] = -1;
-    rk[j] = 0;
-    if (valid && j < k) {
-      ej[j] = idx[((long)sh_ * N + n) * k + j];
-      sel |= 1ull << ej[j];
-    }
-  }
-  const unsigned long long lt = (1ull << lane) - 1ull;
-  for (int e = 0; e < E; ++e) {
-    unsigned long long bal = __ballot(valid && ((sel >> e) & 1ull));
-    int r = __popcll(bal & lt);
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (ej[j] == e) rk[j] = r;
-    if (lane == 0) wcnt[wave][e] = __popcll(bal);
-  }
-  __syncthreads();
-  if (valid) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (j < k) {
-        int e = ej[j];
-        int pos = rk[j];
-        if constexpr (LOCAL)
-          pos += sbase[e];
-        else
-          pos += base[((long)sh_ * nblk + (long)blockIdx.x * per) * E + e];
-        for (int w = 0; w < wave; ++w) pos += wcnt[w][e];
-        perm[(long)sh_ * N * k + pos] = n * k + j;
+  if (wave == 0) {   // exclusive sum over the bins (at most 128)
+    const int v0 = lane < nbins ? tot[lane] : 0, v1 = lane + 64 < nbins ? tot[lane + 64] : 0;
+    int p0 = v0, p1 = v1;
+    for (int o = 1; o < 64 && o < nbins; o <<= 1) {
+      const int u0 = __shfl_up(p0, o, 64), u1 = __shfl_up(p1, o, 64);
+      if (lane >= o) {
+        p0 += u0;
+        p1 += u1;
       }
     }
+    const int first_half = __shfl(p0, min(nbins, 64) - 1, 64);
+    p1 += first_half;
+    const int sum = nbins > 64 ? __shfl(p1, nbins - 65, 64) : first_half;
+    if (lane < nbins) sbase[lane] += p0 - v0;
+    if (lane + 64 < nbins) sbase[lane + 64] += p1 - v1;
+    if (blockIdx.x == 0) {
+      if (lane < nbins) offsets[lane] = p0 - v0;
+      if (lane + 64 < nbins) offsets[lane + 64] = p1 - v1;
+      if (lane == 0) offsets[nbins] = sum;
+    }
   }
+  __syncthreads();
 }
-__global__ __launch_bounds__(RB) void scatter_kernel(const int* __restrict__ idx, const int* __restrict__ base,
-                                                     int* __restrict__ perm, int N, int E, int k, int nblk, int per) {
-  scatter_body(idx, base, perm, N, E, k, nblk, nullptr, per);
+
+// The waves' counts of a token block become their first positions.  base[e * stride]: the block's.  Called by all threads; barriers
+// on both sides.
+template <int BINS>
+__device__ __forceinline__ void wave_bases(int (&wcnt)[RB / 64][BINS], const int* base, long stride, int nbins) {
+  __syncthreads();
+  for (int e = threadIdx.x; e < nbins; e += RB) {
+    int run = base[e * stride];
+#pragma unroll
+    for (int w = 0; w < RB / 64; ++w) {
+      const int v = wcnt[w][e];
+      wcnt[w][e] = run;
+      run += v;
+    }
+  }
+  __syncthreads();
 }
 
 __global__ void dense_routing_kernel(int* idx, float* gate, int* perm, int* offsets, int n0, int n1, int H, int* setperm, float* gsort,
@@ -319,106 +289,578 @@ void launch_copy_list(const CopyList& l, hipStream_t s) {
 }
 
 // ----------------------------------------------------------------------------------------
-// Two-stage router for bf16 storage.  Stage 1 takes the logits from a matrix-core GEMM whose
-// fp32 accumulator only ever holds the sum of one K step (KS = 64 exact bf16 x bf16 products)
-// and is added to an fp64 accumulator after every step.  Their distance from the canonical
-// fp64 logits is bounded by
-//   bound = 4 * KS * 2^-24 * |x_n|_2 * max_c |W[:,c]|_2  (+ 1e-13 relative for the fp64 adds),
-// a Cauchy-Schwarz bound on sum_i |x_i w_i| times the fp32 error of a KS-term sum, with a
-// factor 4 of slack for the adder tree of the matrix core.  If every gap between consecutive sorted
-// logits down to the (k+1)-th exceeds 2*bound, the ordered top-k list is provably the one
-// the fp64 logits give, and it is written directly.  Otherwise stage 2 (same kernel, one wave per
-// such (token, side, head)) re-evaluates its E logits in fp64 and selects from those.  Stage 2 adds
-// the products in a fixed blocked order (16 per lane, then a butterfly over the lanes), which
-// differs from the sequential fp64 sum by a few ulp of fp64 -- twelve orders of magnitude below
-// the fp32-level gaps that send an entry here -- and gives bit-identical sums for identical
-// columns, so ties still resolve to the lower index.
+// Two-stage router for bf16 storage, one launch: logits on the matrix cores, selection, fp64 recheck of doubtful decisions,
+// block counts of both sorts, dense gate rows.
+//
+// Stage 1: a matrix instruction sums 32 exact bf16 x bf16 products in fp32, the two results of a K step of 64 are added in fp32, the K
+// steps in fp64.  The distance from the canonical fp64 logit is bounded by
+//   bound = 4 * KS * 2^-24 * |x_n|_2 * max_c |W[:,c]|_2  (+ 1e-13 relative for the fp64 adds),  KS = 33,
+// a Cauchy-Schwarz bound on sum_i |x_i w_i| times the fp32 error of a 32-term sum and one addition, with a factor 4 of slack for the
+// adder tree of the matrix core.  If every gap between consecutive sorted logits down to the (k+1)-th exceeds 2*bound, the ordered
+// top-k list is provably the one the fp64 logits give.  Otherwise (a fraction of a percent, and every exact tie) stage 2
+// re-evaluates the E logits in fp64 and selects from those.
+//
+// Stage 2 adds the products in a fixed blocked order (a lane takes a feature of each K step, then a butterfly, then the waves), the same
+// for identical columns.  That is not the canonical order (one accumulator, i = 0 .. d_model-1 ascending, bias last), but both are fp64
+// sums of the same exact products, so each lies within d_model * 2^-53 * sum|x_i w_i| of the true value and the two differ by
+// at most twice that.  `reorder` is an upper bound of that difference (Cauchy-Schwarz, with slack): logits of the head that
+// the blocked sum puts further apart are ordered the same way by the canonical sum.  If some pair is closer (every
+// exact tie is), the canonical sums themselves are evaluated, an expert per lane, and the selection is made from them: the indices
+// are those of the canonical logits in every case.
+//
+// A work-group takes 32 tokens of one side, its eight waves every eighth K step of 64.  A wave asks for everything it needs of S
+// steps before it waits: its tokens' features go straight into operand fragments (16 rows of 64 contiguous bytes an instruction),
+// the router's rows, contiguous in memory, through the wave's own corner of LDS, from where transposing reads make the other
+// operand.  The norms of the bound are summed from the fragments (two products an instruction), the K steps' sums meet in LDS.
+// Bound by one trip to memory and the chain of short steps behind it (25000 cycles for a tile, two or four tiles on a CU at a time), for many
+// tokens by those tiles' vector instructions.  Router and sorts, us, against four launches (router packed and copied out as columns;
+// logits on 64 x 64 tiles of the row GEMM, 20 of 64 columns used, and a recheck of one entry per wave; histogram; scan and scatter):
+// d_model 1024, 2 x 20 columns, 100 tokens 46 -> 17, 6300 tokens 57 -> 31, 16384 tokens 56 -> 43; d_model 412, 2 x 10 columns, 16384
+// tokens 48 -> 31; 2 x 32 columns, 16384 tokens 63 -> 60; 8000 cached and 8 query rows, with the copy of the latter, 57 -> 24.
 // ----------------------------------------------------------------------------------------
-// Per (side, head, expert) work-group: the squared norm of that router column (the error bound takes
-// the largest of a head's), the column copied out as a contiguous
-// vector Wt[side][h*E + e][dmp] (zero padded to dmp, a multiple of 1024) for the fp64 recheck and into
-// the padded matrix Wp[side][i][HEp] the logits GEMM reads (the last column also zeroes the padding).
-__global__ __launch_bounds__(256) void router_prep_kernel(const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1,
-                                                          float* __restrict__ wnorm2, unsigned short* __restrict__ Wt, unsigned short* __restrict__ Wp,
-                                                          int dm, int dmp, int H, int E, int HEp) {
-  __shared__ float red[4];
-  const int HE = H * E;
-  const int side = blockIdx.x / HE, col = blockIdx.x % HE;   // col = h*E + e
-  const unsigned short* W = (const unsigned short*)(side ? W1 : W0);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned short* wp = Wp + (long)side * dm * HEp;
-  if (col == HE - 1)
-    for (int t = threadIdx.x; t < dm * (HEp - HE); t += 256) wp[(long)(t / (HEp - HE)) * HEp + HE + t % (HEp - HE)] = 0;
-  float s = 0.f;
-  unsigned short* wt = Wt + ((long)side * HE + col) * dmp;
-  for (int i = threadIdx.x; i < dmp; i += 256) {
-    unsigned short v = 0;
-    if (i < dm) {
-      v = W[(long)i * HE + col];
-      wp[(long)i * HEp + col] = v;
+struct RouterTileArgs {
+  const unsigned short* x;
+  const unsigned short* W[2];
+  const float* b[2];
+  int* idx;          // [side][H][N][k]
+  float* gate;
+  int* cnt;          // [side][H][E][count block]
+  float* gtab;       // [side][N[0]][H*E] or NULL
+  int* setid;        // NULL: no set tables
+  float* gset;
+  int* setexp;
+  int* setcnt;       // [side][H][nsets][count block]
+  unsigned short* xq;   // side 1's rows of x, packed, are written here (NULL: the sides share their tokens)
+  int N[2], ncb[2], sides;
+  int dm, H, E, k, nsets;
+  int T, Tq;         // side 1 with tokens of its own: the last Tq of every T rows of x
+};
+
+constexpr int binom(int n, int r) {   // n < 64, results below 2^31 / n as far as they are used
+  if (r < 0 || r > n) return 0;
+  int v = 1;
+  for (int i = 1; i <= r; ++i) v = v * (n - r + i) / i;
+  return v;
+}
+struct BinomTable {
+  int v[32][8];   // v[e][p] = C(e, p + 1)
+  constexpr BinomTable() : v() {
+    for (int e = 0; e < 32; ++e)
+      for (int p = 0; p < 8; ++p) v[e][p] = binom(e, p + 1);
+  }
+};
+__device__ const BinomTable binom_table = BinomTable();
+
+// the ascending experts of every set (combinadic unranking), for the kernels that follow
+__device__ __forceinline__ void write_set_experts(int* __restrict__ setexp, int nsets, int E, int k) {
+  if ((int)threadIdx.x >= nsets) return;
+  int rank = threadIdx.x;
+  for (int p = k - 1; p >= 0; --p) {
+    int x = p;
+    while (x + 1 < E && binom(x + 1, p + 1) <= rank) ++x;
+    rank -= binom(x, p + 1);
+    setexp[threadIdx.x * 8 + p] = x;
+  }
+}
+
+// sum of the squares of two bf16, added to s
+__device__ __forceinline__ float sumsq2(unsigned w, float s) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  const bf16x2_t v = __builtin_bit_cast(bf16x2_t, w);
+  return __builtin_amdgcn_fdot2_f32_bf16(v, v, s, false);
+}
+
+__device__ __forceinline__ double bf16_to_f64(unsigned short v) { return (double)__uint_as_float((unsigned)v << 16); }
+
+// k passes of "largest remaining logit, the lowest index on ties"
+__device__ __forceinline__ void select_serial(const double* z, unsigned char* sel_out, int E, int k) {
+  unsigned sel = 0;
+  for (int j = 0; j < k; ++j) {
+    int best = -1;
+    double bv = 0.0;
+    for (int e = 0; e < E; ++e) {
+      if ((sel >> e) & 1u) continue;
+      const double v = z[e];
+      if (best < 0 || v > bv) {
+        best = e;
+        bv = v;
+      }
     }
-    wt[i] = v;
-    const float f = __uint_as_float((unsigned)v << 16);
-    s = fmaf(f, f, s);
+    sel |= 1u << best;
+    sel_out[j] = (unsigned char)best;
+  }
+}
+
+// The selection of one (token, head) from its fp64 logits z[0..E-1], by one wave.  xrow: the token's features; w: the head's first
+// column (rows HE apart).
+__device__ __forceinline__ void recheck_select(const unsigned short* __restrict__ xrow, const unsigned short* __restrict__ w, const float* __restrict__ bh,
+                                               double* z, unsigned char* sel_out, int dm, int HE, int E, int k, int lane, double reorder) {
+  bool close = false;
+  if (E <= 8) {   // a lane per pair; the rank of an expert is the number of those that go before it
+    const int e = lane >> 3, f = lane & 7;
+    const double ze = z[min(e, E - 1)], zf = z[min(f, E - 1)];
+    const bool pair = e < E && f < E && e != f;
+    close = pair && !(fabs(ze - zf) > reorder);
+    const unsigned long long before = __ballot(pair && zf > ze);
+    if (!__ballot(close)) {
+      const int rank = __popcll((before >> (8 * (lane & 7))) & 0xffull);
+      if (lane < E && rank < k) sel_out[rank] = (unsigned char)lane;
+      return;
+    }
+  } else if (lane < E) {
+    for (int f = 0; f < lane; ++f) close = close || !(fabs(z[lane] - z[f]) > reorder);
+  }
+  if (__ballot(close)) {   // the canonical sums, an expert per lane
+    const int e = min(lane, E - 1);
+    double acc = 0.0;
+    for (int i0 = 0; i0 < dm; i0 += 16) {
+      unsigned short xv[16], wv[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const unsigned i = min(i0 + j, dm - 1);
+        xv[j] = xrow[i];
+        wv[j] = w[i * (unsigned)HE + e];
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const double next = fma(bf16_to_f64(xv[j]), bf16_to_f64(wv[j]), acc);
+        acc = i0 + j < dm ? next : acc;
+      }
+    }
+    wave_order();
+    if (lane < E) z[lane] = acc + (bh ? (double)bh[lane] : 0.0);
+    wave_order();
+  }
+  if (lane == 0) select_serial(z, sel_out, E, k);
+}
+
+// VEC: bf16 elements of x per load (d_model a multiple of 8 or of 4).  S: K steps of a wave per trip (2: one trip, d_model at most 1024).  P: 8-byte pieces of a K step's
+// router rows per lane (16 * H*E pieces).  CB: blocks of 16 logit columns.
+template <int VEC, int S, int P, int CB>
+__global__ __launch_bounds__(512, 4) void router_tile_kernel(RouterTileArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ int bt[32 * 8];            // binom_table
+  __shared__ int cn[32], cns[384];      // counts of the tile's tokens per (head, expert) and per (head, set); H*E <= 32, at most 128 sets a head
+  __shared__ unsigned char sidx[1024];  // [head][token][k] selected experts
+  __shared__ float gd[RT_TOK * 32];     // [token][H*E] dense gates
+  __shared__ unsigned short flist[1024];
+  __shared__ float rsp[8][32], wsp[8][32], rs[32], w2[32];
+  __shared__ double part[2][8][8];
+  __shared__ int nflag;
+  const int H = a.H, E = a.E, k = a.k, HE = H * E, dm = a.dm;
+  int side, tile;
+  if (a.xq) {   // two token sets: the tiles of one behind those of the other
+    side = (int)blockIdx.x >= a.ncb[0];
+    tile = (int)blockIdx.x - (side ? a.ncb[0] : 0);
+  } else if (a.sides == 2) {   // both sides' tiles of the same tokens run on the same XCD (work-groups are dealt round-robin)
+    side = ((int)blockIdx.x >> 3) & 1;
+    tile = ((int)blockIdx.x >> 4) * 8 + ((int)blockIdx.x & 7);
+  } else {
+    side = 0;
+    tile = blockIdx.x;
+  }
+  if (blockIdx.x == gridDim.x - 1) {   // one work-group more, for the table that no tile owns
+    if (a.setid) write_set_experts(a.setexp, a.nsets, E, k);
+    return;
+  }
+  if (tile >= a.ncb[side]) return;
+  const int N = a.N[side], tok0 = tile * RT_TOK;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+  const bool own = side && a.xq;
+  auto row_of = [&](int n) { return own ? (long)(n / a.Tq) * a.T + (a.T - a.Tq) + n % a.Tq : (long)n; };
+  // a row past the end repeats the last one; nothing of it is kept
+  const unsigned short* xp[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) xp[i] = a.x + row_of(min(tok0 + 16 * i + r, N - 1)) * dm;
+  const unsigned short* W = a.W[side];
+  const int total = dm * HE;
+
+  const int ZS = HE | 1;   // row stride of the sums: odd, so that a column's rows lie in different banks
+  // the wave's corner of LDS: its router rows of a K step, [column block][64][16], then its sums, [K step][32 tokens][ZS]
+  const int corner = max(CB * 64 * 16 * 2, (S * 32 * ZS * 4 + 15) / 16 * 16);
+  unsigned short* wl = (unsigned short*)(lds + wave * corner);
+  float xs[2] = {0.f, 0.f}, ws[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) ws[c] = 0.f;
+  double z[2] = {0.0, 0.0};   // the logits of token tid % 32, columns tid / 32 and 16 more
+  // where a lane's pieces go: their first element's row and column
+  const unsigned inv = div_magic(HE);
+  int krc[P];   // row * 32 + column
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const int row = div_by(4 * (lane + 64 * i), inv);
+    krc[i] = row * 32 + 4 * (lane + 64 * i) - row * HE;
+  }
+  // a K step's router rows into the wave's corner of LDS (the area is the wave's own, and a wave's LDS operations keep their order)
+  auto stage = [&](unsigned short* dst, const uint2 (&v)[P]) {
+    auto at = [&](int row, int c) { return dst + ((c >> 4) * 64 + row) * 16 + (c & 15); };
+    wave_order();
+    if (HE % 4 == 0) {
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        if (lane + 64 * i < 16 * HE) *(uint2*)at(krc[i] >> 5, krc[i] & 31) = v[i];
+    } else if (HE % 2 == 0) {
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        if (lane + 64 * i < 16 * HE) {
+          int at0 = krc[i];
+          asm("" : "+v"(at0));   // (or the compiler computes this layout's addresses ahead of the loop in every layout)
+          const int row = at0 >> 5, c = at0 & 31;
+          const bool next = c + 2 >= HE;
+          *(unsigned*)at(row, c) = v[i].x;
+          *(unsigned*)at(row + next, c + 2 - (next ? HE : 0)) = v[i].y;
+        }
+    } else {
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        if (lane + 64 * i < 16 * HE) {
+          const unsigned short u[4] = {(unsigned short)v[i].x, (unsigned short)(v[i].x >> 16), (unsigned short)v[i].y, (unsigned short)(v[i].y >> 16)};
+          int at0 = krc[i];
+          asm("" : "+v"(at0));
+          int row = at0 >> 5, c = at0 & 31;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            *at(row, c) = u[t];
+            if (++c == HE) ++row, c = 0;
+          }
+        }
+    }
+    wave_order();
+  };
+  for (int kb = 0; kb < dm; kb += 512 * S) {
+    uint2 wv[S][P], xa[S][2][2][2];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int k0 = kb + (s * 8 + wave) * 64;
+#pragma unroll
+      for (int i = 0; i < P; ++i) wv[s][i] = *(const uint2*)(W + min(k0 * HE + 4 * (lane + 64 * i), total - 4));
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int kk = k0 + 32 * j + 8 * g;
+          if constexpr (VEC == 8) {
+            const uint4 v = *(const uint4*)(xp[i] + min(kk, dm - 8));
+            xa[s][i][j][0] = make_uint2(v.x, v.y);
+            xa[s][i][j][1] = make_uint2(v.z, v.w);
+          } else {
+            xa[s][i][j][0] = *(const uint2*)(xp[i] + min(kk, dm - 4));
+            xa[s][i][j][1] = *(const uint2*)(xp[i] + min(kk + 4, dm - 4));
+          }
+        }
+    }
+    if (kb == 0 && tid < 256) bt[tid] = (&binom_table.v[0][0])[tid];
+    f32x4 sum[S][2][CB];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int k0 = kb + (s * 8 + wave) * 64;
+      if (k0 + 64 > dm) {       // (uniform in the wave) what lies past the last feature counts as zero on both sides
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+          if (k0 * HE + 4 * (lane + 64 * i) >= total) wv[s][i] = make_uint2(0, 0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int kk = k0 + 32 * j + 8 * g;
+            if (kk >= dm) xa[s][i][j][0] = make_uint2(0, 0);
+            if (kk + 4 >= dm) xa[s][i][j][1] = make_uint2(0, 0);
+          }
+      }
+      stage(wl, wv[s]);
+      if (own) {   // the packed copy of the query tokens' rows
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int kk = k0 + 32 * j + 8 * g;
+            unsigned short* q = a.xq + (long)(tok0 + 16 * i + r) * dm + kk;
+            if (tok0 + 16 * i + r < N && kk < dm) *(uint2*)q = xa[s][i][j][0];
+            if (tok0 + 16 * i + r < N && kk + 4 < dm) *(uint2*)(q + 4) = xa[s][i][j][1];
+          }
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        // (columns past the last hold whatever LDS held: they only reach results that are never read)
+        bf16x8 fb[CB], fa[2];
+#pragma unroll
+        for (int c = 0; c < CB; ++c) {
+          const unsigned short* p = wl + (c * 64 + 32 * j + 8 * g + (r >> 2)) * 16 + (r & 3) * 4;
+          union {
+            s16x4 h[2];
+            bf16x8 v;
+            uint4 w;
+          } u;
+          u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, p));
+          u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, p + 4 * 16));
+          fb[c] = u.v;
+          ws[c] = sumsq2(u.w.x, sumsq2(u.w.y, sumsq2(u.w.z, sumsq2(u.w.w, ws[c]))));
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint2 lo = xa[s][i][j][0], hi = xa[s][i][j][1];
+          xs[i] = sumsq2(lo.x, sumsq2(lo.y, sumsq2(hi.x, sumsq2(hi.y, xs[i]))));
+          fa[i] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int c = 0; c < CB; ++c) {
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            const f32x4 m = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[c], zero, 0, 0, 0);
+            sum[s][i][c] = j ? sum[s][i][c] + m : m;
+          }
+      }
+    }
+    wave_order();
+    float* part = (float*)wl;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int c = 0; c < CB; ++c)
+        if (16 * c + r < HE)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) part[(s * 32 + 16 * i + 4 * g + q) * ZS + 16 * c + r] = sum[s][i][c][q];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if ((tid >> 5) + 16 * u < HE) {
+        const float* p = (const float*)lds + (tid & 31) * ZS + (tid >> 5) + 16 * u;
+#pragma unroll
+        for (int w = 0; w < 8; ++w)
+#pragma unroll
+          for (int s = 0; s < S; ++s) z[u] += (double)p[w * (corner / 4) + s * 32 * ZS];
+      }
+    if constexpr (S == 2) break;   // the host's promise: dm <= 1024 (a loop that the compiler sees costs 100 spilled registers)
+    if (kb + 512 * S < dm) __syncthreads();
+  }
+
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    xs[i] += __shfl_xor(xs[i], 16, 64);
+    xs[i] += __shfl_xor(xs[i], 32, 64);
+    if (g == 0) rsp[wave][16 * i + r] = xs[i];
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (lane == 0) red[wave] = s;
+  for (int c = 0; c < CB; ++c) {
+    ws[c] += __shfl_xor(ws[c], 16, 64);
+    ws[c] += __shfl_xor(ws[c], 32, 64);
+    if (g == 0) wsp[wave][16 * c + r] = ws[c];
+  }
+  if (tid < 32) cn[tid] = 0;
+  if (tid == 0) nflag = 0;
+  for (int t = tid; t < RT_TOK * HE; t += 512) gd[t] = 0.f;
+  if (a.setid)
+    for (int t = tid; t < H * a.nsets; t += 512) cns[t] = 0;
   __syncthreads();
-  if (threadIdx.x == 0) wnorm2[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-}
-
-__device__ __forceinline__ void hist_body(const int* __restrict__ idx, int* __restrict__ blockcnt, int N, int E, int k,
-                                          int nblk) {
-  __shared__ int cnt[64];
-  const int sh_ = blockIdx.y;
-  const int n = blockIdx.x * RB + threadIdx.x;
-  if (threadIdx.x < 64) cnt[threadIdx.x] = 0;
-  __syncthreads();
-  unsigned long long sel = 0ull;
-  if (n < N)
-    for (int j = 0; j < k; ++j) sel |= 1ull << idx[((long)sh_ * N + n) * k + j];
-  const int lane = threadIdx.x & 63;
-  for (int e = 0; e < E; ++e) {
-    unsigned long long bal = __ballot((sel >> e) & 1ull);
-    if (lane == 0 && bal) atomicAdd(&cnt[e], __popcll(bal));
+  double* zp = (double*)lds;   // logits [32 tokens][ZS]
+  const float* b = a.b[side];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int c = (tid >> 5) + 16 * u;
+    if (c < HE) zp[(tid & 31) * ZS + c] = z[u] + (b ? (double)b[c] : 0.0);
+  }
+  if (tid < 32) {
+    float v = rsp[0][tid];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) v += rsp[w][tid];
+    rs[tid] = v;
+  } else if (tid >= 64 && tid < 64 + HE) {   // squared column norms
+    float v = wsp[0][tid - 64];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) v += wsp[w][tid - 64];
+    w2[tid - 64] = v;
   }
   __syncthreads();
-  if (threadIdx.x < E) blockcnt[((long)sh_ * nblk + blockIdx.x) * E + threadIdx.x] = cnt[threadIdx.x];
-}
-__global__ __launch_bounds__(RB) void hist_kernel(const int* __restrict__ idx, int* __restrict__ blockcnt, int N, int E,
-                                                  int k, int nblk) {
-  hist_body(idx, blockcnt, N, E, k, nblk);
-}
 
-// The expert histogram, and along the same pass over the top-k tables the dense gate rows of the
-// gated-concatenation GEMMs: gtab[sh / H][n][(sh % H) * E + e] = the token's gate of expert e, 0 if not selected.
-__device__ __forceinline__ void gate_row_body(const int* __restrict__ idx, const float* __restrict__ gate,
-                                              float* __restrict__ gtab, int N, int H, int E, int k) {
-  const int sh_ = blockIdx.y, n = blockIdx.x * RB + threadIdx.x;
-  if (n >= N) return;
-  float* out = gtab + ((long)(sh_ / H) * N + n) * (H * E) + (long)(sh_ % H) * E;
-  const long o = ((long)sh_ * N + n) * k;
-  for (int e = 0; e < E; ++e) {
-    float g = 0.f;
-    for (int j = 0; j < k; ++j) g = idx[o + j] == e ? gate[o + j] : g;
-    out[e] = g;
+  // ---- first-stage selection, an item per (head, token) ----------------------------------
+  const int items = RT_TOK * H;
+  for (int it = tid; it < items; it += 512) {
+    const int h = it / RT_TOK, t = it % RT_TOK;
+    if (tok0 + t >= N) continue;
+    const double* zi = zp + t * ZS + h * E;
+    float wn = 0.f;   // largest squared column norm of the head
+    for (int e = 0; e < E; ++e) {
+      const float v = w2[h * E + e];
+      wn = v > wn || v != v ? v : wn;   // (a NaN stays: nothing of that head counts as decided)
+    }
+    const double bound0 = 4.0 * 33 * 5.9604645e-8 * (double)(sqrtf(rs[t]) * 1.0001f) * (double)(sqrtf(wn) * 1.0001f);
+    bool flag = false;
+    if (E <= 8) {
+      // every pair in registers; decided: no other logit close to a selected one
+      double v[8];
+      int rank[8], near[8];
+      double top = 0.0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[e] = zi[min(e, E - 1)];
+        top = fmax(top, fabs(v[e]));
+        rank[e] = near[e] = 0;
+      }
+      const double gap = 2.0 * (bound0 + 1e-13 * (top + 1.0));
+#pragma unroll
+      for (int e = 1; e < 8; ++e)
+        if (e < E) {
+#pragma unroll
+          for (int f = 0; f < e; ++f) {
+            const double d = v[e] - v[f];
+            const int c = !(fabs(d) > gap), later = d > 0.0;   // (a NaN counts as close)
+            rank[f] += later;
+            rank[e] += 1 - later;
+            near[e] |= c;
+            near[f] |= c;
+          }
+        }
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (e < E && rank[e] < k) {
+          sidx[it * k + rank[e]] = (unsigned char)e;
+          flag = flag || near[e];
+        }
+    } else {
+      unsigned sel = 0;
+      double prev = 0.0, bprev = 0.0;
+      const int passes = k < E ? k + 1 : k;
+      for (int j = 0; j < passes; ++j) {
+        int best = -1;
+        double bv = 0.0;
+        for (int e = 0; e < E; ++e) {
+          if ((sel >> e) & 1u) continue;
+          const double v = zi[e];
+          if (best < 0 || v > bv) {
+            best = e;
+            bv = v;
+          }
+        }
+        const double bb = bound0 + 1e-13 * (fabs(bv) + 1.0);
+        if (j > 0 && !(prev - bv > bprev + bb)) flag = true;
+        prev = bv;
+        bprev = bb;
+        sel |= 1u << best;
+        if (j < k) sidx[it * k + j] = (unsigned char)best;
+      }
+    }
+    if (flag) flist[atomicAdd(&nflag, 1)] = (unsigned short)it;
   }
-}
-__global__ __launch_bounds__(RB) void hist_gate_table_kernel(const int* __restrict__ idx, const float* __restrict__ gate,
-                                                             int* __restrict__ blockcnt, float* __restrict__ gtab, int N, int H,
-                                                             int E, int k, int nblk) {
-  hist_body(idx, blockcnt, N, E, k, nblk);
-  gate_row_body(idx, gate, gtab, N, H, E, k);
-}
+  __syncthreads();
+  const int nf = nflag;
+  if (nf) {
+    // Second stage: the waves share an entry's K steps, the next wave in turn adds up their parts and selects while the others
+    // go on (two sets of parts, one barrier each).
+    unsigned short* w2l = (unsigned short*)(zp + (32 * ZS + 1) / 2 * 2) + wave * (CB * 64 * 16);   // behind the logits
+    int buf = 0;
+    for (int f = 0; f < nf; ++f) {
+      const int it = flist[f], h = it / RT_TOK, t = it % RT_TOK;
+      const unsigned short* xrow = a.x + row_of(tok0 + t) * dm;
+      double* zi = zp + t * ZS + h * E;
+      for (int e0 = 0; e0 < E; e0 += 8, buf ^= 1) {
+        double acc[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc[u] = 0.0;
+        for (int kb = wave * 64; kb < dm; kb += 1024) {
+          uint2 wv[2][P];
+          unsigned short xv[2];
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const int k0 = kb + 512 * s;
+#pragma unroll
+            for (int i = 0; i < P; ++i) wv[s][i] = *(const uint2*)(W + min(k0 * HE + 4 * (lane + 64 * i), total - 4));
+            xv[s] = xrow[min(k0 + lane, dm - 1)];
+          }
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            stage(w2l, wv[s]);
+            if (kb + 512 * s + lane < dm) {
+#pragma unroll
+              for (int u = 0; u < 8; ++u)
+                if (e0 + u < E) {
+                  const int c = h * E + e0 + u;
+                  acc[u] = fma(bf16_to_f64(xv[s]), bf16_to_f64(w2l[((c >> 4) * 64 + lane) * 16 + (c & 15)]), acc[u]);
+                }
+            }
+          }
+        }
+        // Sum over the lanes, half of the values handed to the other half of the lanes at each of the first steps: the tree over
+        // the lanes is the same for every value, whichever lanes end up with it.
+        int u0 = 0, d = 32;
+#pragma unroll
+        for (int nv = 8; nv > 1; nv >>= 1, d >>= 1) {
+          const bool hi = lane & d;
+          u0 = 2 * u0 + hi;
+#pragma unroll
+          for (int i = 0; i < nv / 2; ++i) {
+            const double keep = hi ? acc[i + nv / 2] : acc[i], give = hi ? acc[i] : acc[i + nv / 2];
+            acc[i] = keep + __shfl_xor(give, d, 64);
+          }
+        }
+#pragma unroll
+        for (int o = 4; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
+        if ((lane & 7) == 0) part[buf][wave][u0] = acc[0];
+        __syncthreads();
+        if (wave == f % 8) {
+          if (lane < 8 && e0 + lane < E) {
+            double v = part[buf][0][lane];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) v += part[buf][w][lane];
+            zi[e0 + lane] = v + (b ? (double)b[h * E + e0 + lane] : 0.0);
+          }
+          if (e0 + 8 >= E) {
+            wave_order();
+            // twice d_model * 2^-53 * |x| * max|w|, doubled again for the rounding of the norms themselves
+            float wn = 0.f;
+            for (int e = 0; e < E; ++e) wn = fmaxf(wn, w2[h * E + e]);
+            const double reorder = 4.0 * (double)dm * 1.1102230246251565e-16 * (double)sqrtf(rs[t]) * (double)sqrtf(wn);
+            recheck_select(xrow, W + h * E, b ? b + h * E : nullptr, zi, sidx + it * k, dm, HE, E, k, lane, reorder);
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
 
-// expert scatter whose blocks scan the (small) count table for themselves: one launch instead of scan + scatter
-__global__ __launch_bounds__(RB) void scan_scatter1_kernel(const int* __restrict__ idx, const int* __restrict__ cnt,
-                                                           int* __restrict__ offsets, int* __restrict__ perm, int N, int E, int k,
-                                                           int ncb, int per) {
-  __shared__ int sb[2 * 128 + 1];
-  block_bases(cnt, offsets, E, ncb, sb, per);
-  scatter_body<true>(idx, nullptr, perm, N, E, k, 0, sb);
+  // ---- gates, tables, counts ---------------------------------------------------------------
+  const long out0 = (long)side * H * a.N[0];
+  for (int u = tid; u < items * k; u += 512) {
+    const int it = u / k, h = it / RT_TOK, t = it % RT_TOK;
+    if (tok0 + t >= N) continue;
+    const int c = h * E + sidx[u];
+    const float gv = (float)(1.0 / (1.0 + exp(-zp[t * ZS + c])));
+    gd[t * HE + c] = gv;
+    const long o = (out0 + (long)h * N + tok0) * k + (u - h * RT_TOK * k);
+    a.idx[o] = c - h * E;
+    a.gate[o] = gv;
+    atomicAdd(&cn[c], 1);
+  }
+  __syncthreads();
+  if (a.setid) {
+    for (int it = tid; it < items; it += 512) {
+      const int h = it / RT_TOK, t = it % RT_TOK;
+      if (tok0 + t >= N) continue;
+      unsigned sel = 0;
+      for (int j = 0; j < k; ++j) sel |= 1u << sidx[it * k + j];
+      const long o = out0 + (long)h * N + tok0 + t;
+      int sid = 0;
+      for (int p = 0; p < k; ++p) {   // ascending experts
+        const int e = __builtin_ctz(sel);
+        sel &= sel - 1;
+        sid += bt[e * 8 + p];
+        a.gset[o * k + p] = gd[t * HE + h * E + e];
+      }
+      a.setid[o] = sid;
+      atomicAdd(&cns[h * a.nsets + sid], 1);
+    }
+    __syncthreads();
+    for (int c = tid; c < H * a.nsets; c += 512) a.setcnt[(long)side * H * a.nsets * a.ncb[0] + (long)c * a.ncb[side] + tile] = cns[c];
+  }
+  // (side 1's counts start where they would with N[0] tokens)
+  for (int c = tid; c < HE; c += 512) a.cnt[(long)side * HE * a.ncb[0] + (long)c * a.ncb[side] + tile] = cn[c];
+  if (a.gtab) {
+    float* out = a.gtab + ((long)side * a.N[0] + tok0) * HE;
+    const int cnt = min(RT_TOK, N - tok0) * HE;
+    for (int u = tid; u < cnt; u += 512) out[u] = gd[u];
+  }
 }
 
 // Wp[side][i][c] = W_side[i][c] for c < HE, 0 for HE <= c < HEp (rows padded to 16 bytes)
@@ -443,23 +885,6 @@ void launch_pack_router(const void* W0, const void* W1, void* Wp, int dm, int HE
   pack_router_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, s>>>((const bf16_t*)W0, (const bf16_t*)W1, (bf16_t*)Wp, dm, HE, HEp, sides);
 }
 
-size_t router_hybrid_bytes(int N, int dm, int H, int E, size_t* off) {
-  const size_t HEp = ((size_t)H * E + 7) / 8 * 8;
-  size_t o = 0;
-  auto take = [&](size_t b) {
-    size_t r = o;
-    o += (b + 255) & ~(size_t)255;
-    return r;
-  };
-  off[0] = take(2 * (size_t)dm * HEp * 2);   // Wp
-  off[1] = off[2] = 0;                       // (unused: the stage-1 logits and the row norms stay on the CU)
-  (void)N;
-  off[3] = take(2 * (size_t)H * E * 4);      // squared column norms
-  off[4] = off[5] = 0;                       // (unused)
-  off[6] = take(2 * (size_t)H * E * (((size_t)dm + 1023) / 1024 * 1024) * 2);   // Wt: router columns as vectors
-  return o;
-}
-
 // Dense gate table for the gated-concatenation GEMMs: gtab[side][n][h*E + e] = the gate of expert e of head h
 // for token n if the token selected it (Sec. 2.2: e in E^h), else 0.  One thread per (side, head, token).
 __global__ __launch_bounds__(256) void gate_table_kernel(const int* __restrict__ idx, const float* __restrict__ gate,
@@ -481,7 +906,8 @@ void launch_gate_table(const int* idx, const float* gate, float* gtab, int N, in
 }
 
 bool router_hybrid_supported(const RouterArgs& a) {
-  return a.bf16 && a.dm % 4 == 0 && ((uintptr_t)a.x % 16) == 0 && a.H * a.E <= 32;
+  return a.bf16 && a.dm % 4 == 0 && ((uintptr_t)a.x % 16) == 0 && ((uintptr_t)a.W[0] % 8) == 0 && ((uintptr_t)a.W[1] % 8) == 0 && a.H * a.E <= 32 &&
+         (long)a.dm * a.H * a.E < (1l << 30);
 }
 
 template <typename T>
@@ -494,55 +920,25 @@ static void launch_router_select(const RouterArgs& a, hipStream_t s) {
                          a.H, a.E, a.k, hpb, ncb);
 }
 
-void launch_router(const RouterArgs& a, hipStream_t s) {
-  if (a.bf16)
-    launch_router_select<bf16_t>(a, s);
-  else
-    launch_router_select<float>(a, s);
-  const int ncb = router_count_blocks(a.N), per = RB / RT_TOK;
-  const dim3 g2(router_blocks(a.N), a.sides * a.H);
-  if ((long)ncb * a.E <= 8192) {   // small tables: every scatter block scans the counts it needs itself
-    scan_scatter1_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.offsets, a.perm, a.N, a.E, a.k, ncb, per);
-    return;
-  }
-  scan_kernel<<<a.sides * a.H, 256, 0, s>>>(a.blockcnt, a.offsets, a.E, ncb);
-  scatter_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.perm, a.N, a.E, a.k, ncb, per);
-}
-
 // ----------------------------------------------------------------------------------------
 // Expert-SET sorting.  A token's k experts of one head form one of C(E,k) sets; tokens that
 // share a set share all k weight matrices, so the k gate-weighted products of Sec. 2.2's
 // output equation can be summed inside one matrix-core accumulator.  Set id = rank of the
 // ascending combination (combinatorial number system), tokens are counting-sorted by it.
 // ----------------------------------------------------------------------------------------
-__device__ __forceinline__ int binom(int n, int r) {
-  if (r < 0 || r > n) return 0;
-  long v = 1;
-  for (int i = 1; i <= r; ++i) v = v * (n - r + i) / i;
-  return (int)v;
-}
-
-__device__ __forceinline__ void set_hist_body(const int* __restrict__ idx, const float* __restrict__ gate,
-                                              int* __restrict__ setid, float* __restrict__ gset,
-                                              int* __restrict__ setexp, int* __restrict__ blockcnt, int N, int k, int E,
-                                              int nsets, int nblk) {
+// Set ids, gates in ascending-expert order and counts from the top-k tables (routers other than the two-stage one, which
+// writes them itself)
+__global__ __launch_bounds__(RB) void set_hist_kernel(const int* __restrict__ idx, const float* __restrict__ gate,
+                                                      int* __restrict__ setid, float* __restrict__ gset,
+                                                      int* __restrict__ setexp, int* __restrict__ blockcnt, int N, int k,
+                                                      int E, int nsets, int nblk) {
   __shared__ int cnt[128];
   const int sh_ = blockIdx.y;
   const int n = blockIdx.x * RB + threadIdx.x;
   const bool valid = n < N;
   if (threadIdx.x < 128) cnt[threadIdx.x] = 0;
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < nsets) {
-    // the table set id -> ascending experts (combinadic unranking), for the GEMMs that follow
-    int rank = threadIdx.x;
-    for (int p = k - 1; p >= 0; --p) {
-      int x = p;
-      while (x + 1 < E && binom(x + 1, p + 1) <= rank) ++x;
-      rank -= binom(x, p + 1);
-      setexp[threadIdx.x * 8 + p] = x;
-    }
-  }
+  if (blockIdx.x == 0 && blockIdx.y == 0) write_set_experts(setexp, nsets, E, k);
   __syncthreads();
-  int sid = -1;
   if (valid) {
     int e[8];
     float g[8];
@@ -565,7 +961,7 @@ __device__ __forceinline__ void set_hist_body(const int* __restrict__ idx, const
           g[j] = g[j + 1];
           g[j + 1] = tg;
         }
-    sid = 0;
+    int sid = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       if (j < k) {
@@ -573,95 +969,155 @@ __device__ __forceinline__ void set_hist_body(const int* __restrict__ idx, const
         gset[o + j] = g[j];
       }
     setid[(long)sh_ * N + n] = sid;
-  }
-  const int lane = threadIdx.x & 63;
-  for (int s = 0; s < nsets; ++s) {
-    unsigned long long bal = __ballot(sid == s);
-    if (lane == 0 && bal) atomicAdd(&cnt[s], __popcll(bal));
+    atomicAdd(&cnt[sid], 1);
   }
   __syncthreads();
-  if (threadIdx.x < nsets) blockcnt[((long)sh_ * nblk + blockIdx.x) * nsets + threadIdx.x] = cnt[threadIdx.x];
-}
-__global__ __launch_bounds__(RB) void set_hist_kernel(const int* __restrict__ idx, const float* __restrict__ gate,
-                                                      int* __restrict__ setid, float* __restrict__ gset,
-                                                      int* __restrict__ setexp, int* __restrict__ blockcnt, int N, int k,
-                                                      int E, int nsets, int nblk) {
-  set_hist_body(idx, gate, setid, gset, setexp, blockcnt, N, k, E, nsets, nblk);
-}
-// both histograms of a forward pass in one launch
-__global__ __launch_bounds__(RB) void hist2_kernel(const int* __restrict__ idx, const float* __restrict__ gate,
-                                                   int* __restrict__ blockcnt, int* __restrict__ setid,
-                                                   float* __restrict__ gset, int* __restrict__ setexp,
-                                                   int* __restrict__ setcnt, int N, int k, int E, int nsets, int nblk) {
-  hist_body(idx, blockcnt, N, E, k, nblk);
-  set_hist_body(idx, gate, setid, gset, setexp, setcnt, N, k, E, nsets, nblk);
+  if (threadIdx.x < nsets) blockcnt[((long)sh_ * nsets + threadIdx.x) * nblk + blockIdx.x] = cnt[threadIdx.x];
 }
 
-template <bool LOCAL = false>
-__device__ __forceinline__ void set_scatter_body(const int* __restrict__ setid, const int* __restrict__ base,
-                                                 int* __restrict__ setperm, const float* __restrict__ gset,
-                                                 float* __restrict__ gsort, int N, int k, int nsets, int nblk,
-                                                 const int* sbase = nullptr) {
+// The sorts of up to two sides (with tokens of their own or the same ones) from the tables and counts the routers leave: side s's
+// tables start where they would if side 0 had N[0] tokens before them.  The expert sort and the set sort of a side have blocks of their own.
+struct SortArgs {
+  const int* idx;
+  int *cnt, *perm, *offsets;   // cnt: [side][H][E][ncb]
+  SetSortArgs t;               // t.setid NULL: no set tables; t.blockcnt: [side][H][nsets][ncb]
+  int N[2], ncb[2], H, E, k, sides;
+  int per;                     // count blocks per block of RB tokens
+  int experts;                 // 0: the sets alone
+};
+// LOCAL: the block finds its first positions from the raw counts, else they are in the tables already (scan_kernel).  Everything a
+// block reads is requested before it waits: one trip to memory.
+template <bool LOCAL>
+__device__ __forceinline__ void sort_body(const SortArgs& a) {
+  __shared__ int sb[2 * 128 + 1];
   __shared__ int wcnt[RB / 64][128];
-  const int sh_ = blockIdx.y;
-  const int n = blockIdx.x * RB + threadIdx.x;
+  const int side = blockIdx.z % a.sides, sets = (int)blockIdx.z >= a.sides || !a.experts;
+  const int h = blockIdx.y, N = a.N[side], ncb = a.ncb[side], first = blockIdx.x * a.per, k = a.k;
+  if (first >= ncb) return;
+  const long at = (long)side * a.H * a.N[0] + (long)h * N, sh_ = side * a.H + h;
+  const int nbins = sets ? a.t.nsets : a.E;
+  int* c = (sets ? a.t.blockcnt : a.cnt) + ((long)side * a.H * a.ncb[0] + (long)h * ncb) * nbins;
+  int* offsets = sets ? a.t.setoff + sh_ * (nbins + 1) : a.offsets + sh_ * (nbins + 1);
+  const int n = blockIdx.x * RB + threadIdx.x, nc = min(n, N - 1);
+  const bool valid = n < N;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sid = n < N ? setid[(long)sh_ * N + n] : -1;
   const unsigned long long lt = (1ull << lane) - 1ull;
-  int rk = 0;
-  for (int s = 0; s < nsets; ++s) {
-    unsigned long long bal = __ballot(sid == s);
-    if (sid == s) rk = __popcll(bal & lt);
-    if (lane == 0) wcnt[wave][s] = __popcll(bal);
+  if (sets) {
+    const int sid = a.t.setid[at + nc];
+    float gv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) gv[j] = a.t.gset[(at + nc) * k + min(j, k - 1)];
+    for (int t = threadIdx.x; t < RB / 64 * 128; t += RB) (&wcnt[0][0])[t] = 0;
+    if constexpr (LOCAL) block_bases(c, offsets, nbins, ncb, a.per, sb);
+    // the rank among the wave's tokens of the same set: the lanes whose set id agrees with one's own in every bit
+    unsigned long long same = __ballot(valid);
+    for (int bit = 0; (1 << bit) < nbins; ++bit) {
+      const unsigned long long bal = __ballot((sid >> bit) & 1);
+      same &= (sid >> bit) & 1 ? bal : ~bal;
+    }
+    const int rk = __popcll(same & lt);
+    if constexpr (!LOCAL) __syncthreads();
+    if (valid && rk == 0) wcnt[wave][sid] = __popcll(same);
+    wave_bases(wcnt, LOCAL ? sb : c + first, LOCAL ? 1 : ncb, nbins);
+    if (!valid) return;
+    const int pos = rk + wcnt[wave][sid];
+    a.t.setperm[at + pos] = n;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j < k) a.t.gsort[(at + pos) * k + j] = gv[j];
+    return;
   }
-  __syncthreads();
-  if (sid < 0) return;
-  int pos = rk;
-  if constexpr (LOCAL)
-    pos += sbase[sid];
+  int ej[8], rk[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ej[j] = a.idx[(at + nc) * k + min(j, k - 1)];
+  if constexpr (LOCAL) block_bases(c, offsets, nbins, ncb, a.per, sb);
+  unsigned long long sel = 0ull;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (!valid || j >= k) ej[j] = -1;
+    rk[j] = 0;
+    if (ej[j] >= 0) sel |= 1ull << ej[j];
+  }
+  for (int e = 0; e < nbins; ++e) {
+    const unsigned long long bal = __ballot((sel >> e) & 1ull);
+    const int r = __popcll(bal & lt);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (ej[j] == e) rk[j] = r;
+    if (lane == 0) wcnt[wave][e] = __popcll(bal);
+  }
+  wave_bases(wcnt, LOCAL ? sb : c + first, LOCAL ? 1 : ncb, nbins);
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (ej[j] >= 0) a.perm[at * k + rk[j] + wcnt[wave][ej[j]]] = n * k + j;
+}
+__global__ __launch_bounds__(RB) void scan_scatter_kernel(SortArgs a) { sort_body<true>(a); }
+__global__ __launch_bounds__(RB) void scatter_kernel(SortArgs a) { sort_body<false>(a); }
+// one block per (side, head) and table
+__global__ __launch_bounds__(256) void scan_kernel(SortArgs a) {
+  const int side = blockIdx.y, h = blockIdx.x, ncb = a.ncb[side], sets = blockIdx.z || !a.experts;
+  const long cat = (long)side * a.H * a.ncb[0] + (long)h * ncb, sh_ = side * a.H + h;
+  if (sets)
+    scan_body(a.t.blockcnt + cat * a.t.nsets, a.t.setoff + sh_ * (a.t.nsets + 1), a.t.nsets, ncb);
   else
-    pos += base[((long)sh_ * nblk + blockIdx.x) * nsets + sid];
-  for (int w = 0; w < wave; ++w) pos += wcnt[w][sid];
-  setperm[(long)sh_ * N + pos] = n;
-  for (int j = 0; j < k; ++j) gsort[((long)sh_ * N + pos) * k + j] = gset[((long)sh_ * N + n) * k + j];
+    scan_body(a.cnt + cat * a.E, a.offsets + sh_ * (a.E + 1), a.E, ncb);
 }
-__global__ __launch_bounds__(RB) void set_scatter_kernel(const int* __restrict__ setid, const int* __restrict__ base,
-                                                         int* __restrict__ setperm, const float* __restrict__ gset,
-                                                         float* __restrict__ gsort, int N, int k, int nsets, int nblk) {
-  set_scatter_body(setid, base, setperm, gset, gsort, N, k, nsets, nblk);
+
+// Tables of up to SCAN_MAX counts per (side, head) are scanned by every scatter block for itself, one launch instead of two.
+static void launch_sort(const SortArgs& a, hipStream_t s) {
+  constexpr long SCAN_MAX = 32768;
+  const int nmax = a.sides > 1 && a.N[1] > a.N[0] ? a.N[1] : a.N[0];
+  const int tables = (a.experts ? 1 : 0) + (a.t.setid ? 1 : 0);
+  const dim3 g(router_blocks(nmax), a.H, a.sides * tables);
+  const long bins = a.t.setid && a.t.nsets > a.E ? a.t.nsets : a.E;
+  if (a.ncb[0] * bins <= SCAN_MAX) {
+    scan_scatter_kernel<<<g, RB, 0, s>>>(a);
+    return;
+  }
+  scan_kernel<<<dim3(a.H, a.sides, tables), 256, 0, s>>>(a);
+  scatter_kernel<<<g, RB, 0, s>>>(a);
 }
-// both scatters of a forward pass in one launch (the set scatter last: it may leave early)
-__global__ __launch_bounds__(RB) void scatter2_kernel(const int* __restrict__ idx, const int* __restrict__ base,
-                                                      int* __restrict__ perm, const int* __restrict__ setid,
-                                                      const int* __restrict__ setbase, int* __restrict__ setperm,
-                                                      const float* __restrict__ gset, float* __restrict__ gsort, int N, int E,
-                                                      int k, int nsets, int nblk) {
-  scatter_body(idx, base, perm, N, E, k, nblk);
-  __syncthreads();
-  set_scatter_body(setid, setbase, setperm, gset, gsort, N, k, nsets, nblk);
+
+static SortArgs sort_args(const RouterArgs& a) {
+  SortArgs d{};
+  d.idx = a.idx;
+  d.cnt = a.blockcnt;
+  d.perm = a.perm;
+  d.offsets = a.offsets;
+  d.N[0] = a.N;
+  d.N[1] = a.Nq > 0 ? a.Nq : a.N;
+  for (int i = 0; i < 2; ++i) d.ncb[i] = router_count_blocks(d.N[i]);
+  d.H = a.H;
+  d.E = a.E;
+  d.k = a.k;
+  d.sides = a.sides;
+  d.per = RB / RT_TOK;
+  d.experts = 1;
+  return d;
 }
-// the same with the scans done by every block for itself (small tables): `cnt` and `setcnt` hold the raw
-// per-block counts, the offsets tables are written here
-__global__ __launch_bounds__(RB) void scan_scatter2_kernel(const int* __restrict__ idx, const int* __restrict__ cnt,
-                                                           int* __restrict__ offsets, int* __restrict__ perm,
-                                                           const int* __restrict__ setid, const int* __restrict__ setcnt,
-                                                           int* __restrict__ setoff, int* __restrict__ setperm,
-                                                           const float* __restrict__ gset, float* __restrict__ gsort, int N,
-                                                           int E, int k, int nsets, int nblk) {
-  __shared__ int sb[2][2 * 128 + 1];
-  block_bases(cnt, offsets, E, nblk, sb[0]);
-  block_bases(setcnt, setoff, nsets, nblk, sb[1]);
-  scatter_body<true>(idx, nullptr, perm, N, E, k, nblk, sb[0]);
-  __syncthreads();
-  set_scatter_body<true>(setid, nullptr, setperm, gset, gsort, N, k, nsets, nblk, sb[1]);
+
+void launch_router(const RouterArgs& a, hipStream_t s) {
+  if (a.bf16)
+    launch_router_select<bf16_t>(a, s);
+  else
+    launch_router_select<float>(a, s);
+  launch_sort(sort_args(a), s);
 }
 
 void launch_set_sort(const SetSortArgs& a, hipStream_t s) {
   const int nblk = router_blocks(a.N);
   dim3 g(nblk, a.sides * a.H);
   set_hist_kernel<<<g, RB, 0, s>>>(a.idx, a.gate, a.setid, a.gset, a.setexp, a.blockcnt, a.N, a.k, a.E, a.nsets, nblk);
-  scan_kernel<<<a.sides * a.H, 256, 0, s>>>(a.blockcnt, a.setoff, a.nsets, nblk);
-  set_scatter_kernel<<<g, RB, 0, s>>>(a.setid, a.blockcnt, a.setperm, a.gset, a.gsort, a.N, a.k, a.nsets, nblk);
+  SortArgs d{};
+  d.t = a;
+  d.N[0] = d.N[1] = a.N;
+  d.ncb[0] = d.ncb[1] = nblk;
+  d.H = a.H;
+  d.E = a.E;
+  d.k = a.k;
+  d.sides = a.sides;
+  d.per = 1;
+  launch_sort(d, s);
 }
 
 void launch_dense_routing(int* idx, float* gate, int* perm, int* offsets, int n0, int n1, int H, const SetSortArgs* t, hipStream_t s) {
@@ -670,145 +1126,70 @@ void launch_dense_routing(int* idx, float* gate, int* perm, int* offsets, int n0
                                                                               t ? t->gsort : nullptr, t ? t->setoff : nullptr, t ? t->setexp : nullptr);
 }
 
-// Both sides' sorts where the sides have tokens of their own (fewer queries than keys): the passes above with the side as a grid
-// dimension.  One side after the other is two chains of four launches that wait for memory most of the time (eight sequences of
-// 1000 keys and one query: 94 us for both sides, a third of the call).
-struct SidesArgs {
-  const int* idx;
-  const float* gate;
-  int *blockcnt, *perm, *offsets;
-  float* gtab;
-  SetSortArgs t;   // t.setid NULL: no set tables
-  int N[2], nblk[2], H, E, k;
-};
-__global__ __launch_bounds__(RB) void hist_sides_kernel(SidesArgs a) {
-  const int side = blockIdx.z, N = a.N[side], nblk = a.nblk[side];
-  if ((int)blockIdx.x >= nblk) return;
-  const long at = (long)side * a.H * a.N[0], cat = (long)side * a.H * a.nblk[0];
-  hist_body(a.idx + at * a.k, a.blockcnt + cat * a.E, N, a.E, a.k, nblk);
-  if (a.t.setid)
-    set_hist_body(a.idx + at * a.k, a.gate + at * a.k, a.t.setid + at, a.t.gset + at * a.k, a.t.setexp, a.t.blockcnt + cat * a.t.nsets, N, a.k,
-                  a.E, a.t.nsets, nblk);
-  if (a.gtab) gate_row_body(a.idx + at * a.k, a.gate + at * a.k, a.gtab + at * a.E, N, a.H, a.E, a.k);
-}
-__global__ __launch_bounds__(RB) void scan_scatter_sides_kernel(SidesArgs a) {
-  __shared__ int sb[2][2 * 128 + 1];
-  const int side = blockIdx.z, N = a.N[side], nblk = a.nblk[side];
-  if ((int)blockIdx.x >= nblk) return;
-  const long at = (long)side * a.H * a.N[0], cat = (long)side * a.H * a.nblk[0];
-  block_bases(a.blockcnt + cat * a.E, a.offsets + (long)side * a.H * (a.E + 1), a.E, nblk, sb[0]);
-  if (a.t.setid) block_bases(a.t.blockcnt + cat * a.t.nsets, a.t.setoff + (long)side * a.H * (a.t.nsets + 1), a.t.nsets, nblk, sb[1]);
-  scatter_body<true>(a.idx + at * a.k, nullptr, a.perm + at * a.k, N, a.E, a.k, nblk, sb[0]);
-  if (!a.t.setid) return;
-  __syncthreads();
-  set_scatter_body<true>(a.t.setid + at, nullptr, a.t.setperm + at, a.t.gset + at * a.k, a.t.gsort + at * a.k, N, a.k, a.t.nsets, nblk, sb[1]);
-}
-
-bool router_sides_supported(const RouterArgs& a) {
-  const long nblk = router_blocks(a.N), bins = a.sets && a.sets->nsets > a.E ? a.sets->nsets : a.E;
-  return router_hybrid_supported(a) && ((uintptr_t)a.xq % 16) == 0 && nblk * bins <= 8192;   // (small tables, as below)
-}
-
-void launch_router_hybrid(const RouterArgs& a, char* scratch, hipStream_t s) {
-  size_t off[7];
-  router_hybrid_bytes(a.N, a.dm, a.H, a.E, off);
-  const int HE = a.H * a.E, HEp = (HE + 7) / 8 * 8;
-  bf16_t* Wp = (bf16_t*)(scratch + off[0]);
-  float* wmax = (float*)(scratch + off[3]);
-  unsigned short* Wt = (unsigned short*)(scratch + off[6]);
-  const int dmp = (a.dm + 1023) / 1024 * 1024;
-
-  // per (side, head): largest column norm, columns copied out as vectors and
-  // into the padded matrix the GEMM reads
-  router_prep_kernel<<<(a.shared ? 1 : a.sides) * a.H * a.E, 256, 0, s>>>((const bf16_t*)a.W[0], (const bf16_t*)a.W[1], wmax, Wt,
-                                                   (unsigned short*)Wp, a.dm, dmp, a.H, a.E, HEp);
-  // stage 1: z32 = x W on the matrix cores, fp32 accumulation, both sides in one launch; the selection
-  // (and the fp64 recheck of its doubtful entries) is that kernel's epilogue
-  RowGemmArgs g{};
-  g.heads = a.sides;
-  g.E = 1;
-  g.M = a.N;
-  g.a_div = 1;
-  g.c_div = 1;
-  g.A = a.x;
-  g.lda = a.dm;
-  g.B = Wp;
-  g.b_hstride = a.shared ? 0 : (long)a.dm * HEp;
-  g.sbk = HEp;
-  g.sbn = 1;
-  g.C = nullptr;   // nothing is stored: the selection consumes the logits inside the kernel
-  g.K = a.dm;
-  g.Nc = HEp;
-  g.mode = STORE_F64;
-  g.tag = TAG_ROUTER;
-  g.rsel.b[0] = a.b[0];
-  g.rsel.b[1] = a.b[1];
-  g.rsel.wnorm2 = wmax;
-  g.rsel.idx = a.idx;
-  g.rsel.gate = a.gate;
-  g.rsel.x = a.x;
-  g.rsel.Wt = Wt;
-  g.rsel.N = a.N;
-  g.rsel.kstep = rg_kstep();
-  g.rsel.H = a.H;
-  g.rsel.E = a.E;
-  g.rsel.k = a.k;
-  g.rsel.dm = a.dm;
-  g.rsel.dmp = dmp;
-  g.rsel.xq = a.xq;
-  g.rsel.Nq = a.Nq;
-  g.rsel.shared = a.shared;
-  launch_mfma_row_gemm(g, s);
-  if (a.Nq > 0) {
-    SidesArgs d{};
-    d.idx = a.idx;
-    d.gate = a.gate;
-    d.blockcnt = a.blockcnt;
-    d.perm = a.perm;
-    d.offsets = a.offsets;
-    d.gtab = a.gtab;
-    if (a.sets) d.t = *a.sets;
-    d.N[0] = a.N;
-    d.N[1] = a.Nq;
-    d.nblk[0] = router_blocks(a.N);
-    d.nblk[1] = router_blocks(a.Nq);
-    d.H = a.H;
-    d.E = a.E;
-    d.k = a.k;
-    const dim3 gs(d.nblk[0], a.H, 2);
-    hist_sides_kernel<<<gs, RB, 0, s>>>(d);
-    scan_scatter_sides_kernel<<<gs, RB, 0, s>>>(d);
-    return;
-  }
-
-  const int nblk = router_blocks(a.N);
-  dim3 g2(nblk, a.sides * a.H);
-  if (a.sets && a.sets->sides == a.sides) {
-    // the expert sort and the expert-set sort share their passes over the top-k tables
-    const SetSortArgs& t = *a.sets;
-    hist2_kernel<<<g2, RB, 0, s>>>(a.idx, a.gate, a.blockcnt, t.setid, t.gset, t.setexp, t.blockcnt, a.N, a.k, a.E, t.nsets,
-                                   nblk);
-    if ((long)nblk * (a.E > t.nsets ? a.E : t.nsets) <= 8192) {
-      // small tables: every scatter block scans the counts it needs itself, one launch less
-      scan_scatter2_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.offsets, a.perm, t.setid, t.blockcnt, t.setoff, t.setperm,
-                                             t.gset, t.gsort, a.N, a.E, a.k, t.nsets, nblk);
-      return;
+template <int VEC, int S, int P, int CB>
+static void launch_router_tiles(const RouterTileArgs& t, int blocks, hipStream_t s) {
+  const size_t ZS = (t.H * t.E) | 1, wl = CB * 64 * 16 * 2, sums = (S * 32 * ZS * 4 + 15) / 16 * 16;
+  const size_t first = 8 * (wl > sums ? wl : sums), second = (32 * ZS + 1) / 2 * 2 * 8 + 8 * wl;   // (the logits, then the second stage's router rows)
+  const size_t lds = first > second ? first : second;   // at most 68 KB
+  auto kern = router_tile_kernel<VEC, S, P, CB>;
+  if (lds > 48 * 1024) {   // (with the static part beyond 64 KB)
+    static bool raised = false;   // per instantiation
+    if (!raised) {
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 68 * 1024);
+      raised = true;
     }
-    scan2_kernel<<<dim3(a.sides * a.H, 2), 256, 0, s>>>(a.blockcnt, a.offsets, a.E, t.blockcnt, t.setoff, t.nsets, nblk);
-    scatter2_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.perm, t.setid, t.blockcnt, t.setperm, t.gset, t.gsort, a.N, a.E,
-                                      a.k, t.nsets, nblk);
-    return;
   }
-  if (a.gtab)
-    hist_gate_table_kernel<<<g2, RB, 0, s>>>(a.idx, a.gate, a.blockcnt, a.gtab, a.N, a.H, a.E, a.k, nblk);
+  kern<<<blocks + 1, 512, lds, s>>>(t);
+}
+template <int VEC, int S>
+static void launch_router_tiles(const RouterTileArgs& t, int blocks, hipStream_t s) {
+  const int HE = t.H * t.E;
+  if (HE <= 12) return launch_router_tiles<VEC, S, 3, 1>(t, blocks, s);
+  if (HE <= 16) return launch_router_tiles<VEC, S, 4, 1>(t, blocks, s);
+  if (HE <= 20) return launch_router_tiles<VEC, S, 5, 2>(t, blocks, s);
+  launch_router_tiles<VEC, 1, 8, 2>(t, blocks, s);   // (two would need the LDS of two work-groups)
+}
+
+void launch_router_hybrid(const RouterArgs& a, hipStream_t s) {
+  RouterTileArgs t{};
+  t.x = (const unsigned short*)a.x;
+  SortArgs d = sort_args(a);
+  for (int i = 0; i < 2; ++i) {
+    t.W[i] = (const unsigned short*)a.W[a.shared ? 0 : i];
+    t.b[i] = a.b[i];
+    t.N[i] = d.N[i];
+    t.ncb[i] = d.ncb[i];
+  }
+  t.idx = a.idx;
+  t.gate = a.gate;
+  t.cnt = a.blockcnt;
+  t.gtab = a.gtab;
+  if (a.sets) {
+    d.t = *a.sets;
+    d.t.blockcnt = a.setcnt;
+    t.setid = a.sets->setid;
+    t.gset = a.sets->gset;
+    t.setexp = a.sets->setexp;
+    t.setcnt = a.setcnt;
+    t.nsets = a.sets->nsets;
+  }
+  t.sides = a.sides;
+  t.dm = a.dm;
+  t.H = a.H;
+  t.E = a.E;
+  t.k = a.k;
+  if (a.Nq > 0) {
+    t.xq = (unsigned short*)a.xq;
+    t.T = a.T;
+    t.Tq = a.Tq;
+  }
+  const int blocks = a.Nq > 0 ? t.ncb[0] + t.ncb[1] : a.sides == 2 ? (t.ncb[0] + 7) / 8 * 16 : t.ncb[0];
+  const bool two = a.dm > 512 && a.dm <= 1024;
+  if (a.dm % 8 == 0)
+    two ? launch_router_tiles<8, 2>(t, blocks, s) : launch_router_tiles<8, 1>(t, blocks, s);
   else
-    hist_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.N, a.E, a.k, nblk);
-  if ((long)nblk * a.E <= 8192) {
-    scan_scatter1_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.offsets, a.perm, a.N, a.E, a.k, nblk, 1);
-    return;
-  }
-  scan_kernel<<<a.sides * a.H, 256, 0, s>>>(a.blockcnt, a.offsets, a.E, nblk);
-  scatter_kernel<<<g2, RB, 0, s>>>(a.idx, a.blockcnt, a.perm, a.N, a.E, a.k, nblk, 1);
+    two ? launch_router_tiles<4, 2>(t, blocks, s) : launch_router_tiles<4, 1>(t, blocks, s);
+  launch_sort(d, s);
 }
 
 }  // namespace sh
