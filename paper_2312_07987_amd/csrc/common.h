@@ -58,7 +58,8 @@ enum {
 // One segment of a concatenated reduction with per-row gates (segment mode 3): the segment's A columns start at
 // A (rows lda apart, shared by all segments), its B matrix at B (strides sbk / sbn shared), and row n of A
 // is scaled by gtab[n * gld + gcol] before it is multiplied (gcol < 0: not scaled).
-// klen != 0 (fp32 kernel only): the segment has its own length and its own row strides lda (A) and sbn (B).
+// klen != 0 (fp32 kernels only; the last seg_own segments, all of one length): the segment has its own length and its own row
+// strides lda (A) and sbn (B).
 struct SegDesc {
   const void* A;
   const void* B;
@@ -117,6 +118,7 @@ struct RowGemmArgs {
   const int* gidx;
   const float* ggate;
   int gk, gheads;
+  int seg_own;
   SegDesc segd[MAX_SEGD];
 };
 

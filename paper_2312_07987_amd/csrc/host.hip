@@ -1537,7 +1537,10 @@ sh_status switchhead_backward(const sh_shape* shape, const void* x, const void* 
       if (side == 1 || !c.rect)
         for (int h_ = 0; h_ < H; ++h_) seg(c.p<float>(c.L.dQ) + (size_t)h_ * dh, W_Q, (size_t)h_ * dm * dh, -1);
       for (int sd = 0; sd < sides; ++sd)
-        if (!c.rect || sd == side) a.segd[n++] = {dz_of(sd), sd == 1 && !c.shared ? W_D : W_S, -1, HE_, (int)dz_ld, HE_};
+        if (!c.rect || sd == side) {
+          a.segd[n++] = {dz_of(sd), sd == 1 && !c.shared ? W_D : W_S, -1, HE_, (int)dz_ld, HE_};
+          ++a.seg_own;
+        }
       a.nseg = n;
       launch_f32_row_gemm(a, c.st);
     }

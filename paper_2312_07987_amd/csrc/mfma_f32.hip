@@ -14,7 +14,7 @@
 // Measured for a training step of the 47M-parameter layer (d_model 412, 2 heads of 76, 5 experts, 3 active) over 16 x 256 tokens:
 // 2263 us on the vector kernels of simt.hip, 398 us here; value experts 110 -> 27 us (63 TFLOP/s: 390 tiles for 256 CUs, a second
 // tile on half of them), output experts with their zero fill 188 -> 45, weight gradients 550 -> 89, attention forward 188 -> 17
-// and backward 391 -> 37.  A toy layer (128 tokens, d_model 64) is launches and latency: 415 -> 90 us.
+// and backward 391 -> 37.  A toy layer (128 tokens, d_model 64) is launches and latency: 415 -> 70 us.
 #include "common.h"
 #include "mfma_util.h"
 
@@ -46,6 +46,22 @@ struct FVec<1> {
 // VEC: floats per global load (1 where a row is no multiple of 16 bytes).
 // ----------------------------------------------------------------------------------------
 static constexpr int FBM = 64, FBK = 32, FLDA = FBK + 4;   // row stride 36 words: the 16 rows of a 16-byte read hit 64 banks
+
+// SEG: one output element from the segments whose gate is not zero, up to the first NaN
+template <bool BNT>
+__device__ __forceinline__ float f32_selected_sum(const RowGemmArgs& a, const float* gates, int row, int n) {
+  float s = 0.f;
+  for (int q = 0; q < a.nseg && s == s; ++q) {
+    const SegDesc& d = a.segd[q];
+    const float gt = d.gcol >= 0 ? gates[d.gcol] : 1.f;
+    if (gt == 0.f) continue;
+    const int K = d.klen ? d.klen : a.K;
+    const float* Ap = (const float*)d.A + (long)row * (d.klen ? d.lda : a.lda);
+    const float* Bp = (const float*)d.B + (BNT ? (long)n * (d.klen ? d.sbn : a.sbn) : (long)n);
+    for (int k = 0; k < K; ++k) s = fmaf(Ap[k] * gt, Bp[BNT ? (long)k : (long)k * a.sbk], s);
+  }
+  return s;
+}
 
 template <int NJ, int VEC, bool BNT, bool SEG>
 __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
@@ -273,19 +289,148 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
       if (n >= Nc) continue;
       float* o = C + (long)(row0 + row) * a.ldc + n;
       if (*o == *o) continue;
-      float s = 0.f;
-      for (int q = 0; q < nseg && s == s; ++q) {
-        const SegDesc& d = a.segd[q];
-        const float gt = d.gcol >= 0 ? gts[row * F32_MAX_SEGD + d.gcol] : 1.f;
-        if (gt == 0.f) continue;
-        const int K = d.klen ? d.klen : a.K;
-        const float* Ap = (const float*)d.A + (long)(row0 + row) * (d.klen ? d.lda : a.lda);
-        const float* Bp = (const float*)d.B + (BNT ? (long)n * (d.klen ? d.sbn : a.sbn) : (long)n);
-        for (int k = 0; k < K; ++k) s = fmaf(Ap[k] * gt, Bp[BNT ? (long)k : (long)k * a.sbk], s);
-      }
-      *o = s;
+      *o = f32_selected_sum<BNT>(a, gts + row * F32_MAX_SEGD, row0 + row, n);
     }
   }
+}
+
+// ----------------------------------------------------------------------------------------
+// The same products for launches of few tiles: 16 x 32 tiles, the reduction split over eight waves.  A 64 x 64 tile keeps one CU's matrix
+// pipe for 1024 cycles per 32 reduction indices, so a launch of a few of them takes its whole reduction times that while most
+// of the chip is idle.  Here a wave takes every eighth piece of 16 indices, its operands come straight from memory in fragment order, four
+// pieces a trip, and the partial sums meet in LDS and are added in wave order.
+// The line, launches of 128 tiles of 64 rows: a training step with the small tiles up to 0 / 32 / 128 / 256 of them, us: toy layer (d_model 64, 2
+// heads of 32) over 128 tokens 91 / 71 / 70 / 70; 47M layer over 128 tokens 212 / 121 / 121 / 121, 512 tokens 235 / 224 / 160 / 159, 2048 tokens
+// 268 / 268 / 264 / 296; 262M layer over 128 tokens 468 / 303 / 272 / 272, 512 tokens 549 / 549 / 483 / 498.
+// ----------------------------------------------------------------------------------------
+static constexpr int F32_SMALL_TILES = 128;
+static constexpr int FSM_M = 16, FSM_N = 32, FSM_W = 8, FSM_U = 4;
+
+template <int VEC, bool BNT, bool SEG>
+__global__ __launch_bounds__(64 * FSM_W) void f32_small_gemm_kernel(RowGemmArgs a) {
+  __shared__ float part[FSM_W][FSM_M][FSM_N + 1];
+  __shared__ int ids[FSM_M];
+  __shared__ float gsc[FSM_M];
+  __shared__ float gts[SEG ? FSM_M * F32_MAX_SEGD : 1];   // the tile's dense gates, [row][head * experts + expert]
+  __shared__ SegDesc descs[SEG ? F32_MAX_SEGD : 1];
+  const int h = blockIdx.z, n0 = blockIdx.y * FSM_N;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 15, g = lane >> 4;
+  int e = 0, row0, rows;
+  if (a.perm) {
+    if (!find_tile_wave(a.offsets + (long)h * (a.E + 1), a.E, FSM_M, blockIdx.x, lane, e, row0, rows)) return;
+  } else {
+    row0 = blockIdx.x * FSM_M;
+    rows = a.M - row0 < FSM_M ? a.M - row0 : FSM_M;
+  }
+  const bool second = a.hsplit > 0 && h >= a.hsplit;
+  const int hh = second ? h - a.hsplit : h;
+  // (a row past the end repeats the last one; nothing of it is stored)
+  const int id = a.perm ? a.perm[(long)h * a.M + row0 + min(r, rows - 1)] : row0 + min(r, rows - 1);
+  if (tid < FSM_M) {
+    ids[tid] = id;
+    gsc[tid] = a.gate ? a.gate[(long)h * a.gate_hstride + id] : 1.f;
+  }
+  if constexpr (SEG) {
+    if (tid < a.nseg) descs[tid] = a.segd[tid];
+    if (a.gidx) {
+      for (int t = tid; t < FSM_M * F32_MAX_SEGD; t += 64 * FSM_W) gts[t] = 0.f;
+      __syncthreads();
+      for (int t = tid; t < FSM_M * a.gheads * a.gk; t += 64 * FSM_W) {
+        const int row = t % FSM_M, hd = t / FSM_M / a.gk, j = t / FSM_M % a.gk;
+        if (row < rows) {
+          const long o = ((long)hd * a.M + row0 + row) * a.gk + j;
+          gts[row * F32_MAX_SEGD + hd * a.experts + a.gidx[o]] = a.ggate[o];
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  const float* A = (const float*)a.A + (long)hh * a.a_hoff;
+  const float* B = (const float*)(second ? a.B2 : a.B) + (long)hh * a.b_hstride + (long)e * a.b_estride;
+  const int nseg = SEG ? a.nseg : 1, regular = SEG ? nseg - a.seg_own : 1, Nc = a.Nc;
+  const int cps = (a.K + 15) / 16, cps_own = SEG ? (descs[nseg - 1].klen + 15) / 16 : 0;   // pieces of a segment
+  const unsigned inv = div_magic(cps);
+  const int pieces = regular * cps + (nseg - regular) * cps_own;
+  const long arow = id / a.a_div;
+  f32x4 acc[2] = {f32x4{}, f32x4{}};
+  for (int c0 = wave; c0 < pieces; c0 += FSM_W * FSM_U) {
+    f32x4 fa[FSM_U], fb[FSM_U][2];
+#pragma unroll
+    for (int u = 0; u < FSM_U; ++u) {
+      const int c = min(c0 + u * FSM_W, pieces - 1);   // (a piece past the last: loaded, not used)
+      const float *Ap = A, *Bp = B;
+      int lda = (int)a.lda, sbn = a.sbn, K = a.K, k0 = c * 16, gcol = -1;
+      bool own = false;
+      if constexpr (SEG) {
+        const int c1 = c - regular * cps;
+        const int seg = c1 < 0 ? div_by(c, inv) : regular + (cps_own > 1 ? c1 / cps_own : c1);
+        k0 = (c1 < 0 ? c - seg * cps : c1 - (seg - regular) * cps_own) * 16;
+        const SegDesc d = descs[seg];
+        Ap = (const float*)d.A;
+        Bp = (const float*)d.B;
+        gcol = d.gcol;
+        if (d.klen) K = d.klen, lda = d.lda, sbn = d.sbn, own = true;
+      }
+      const int kk = k0 + 4 * g;
+      auto quad = [&](const float* row, bool vec) {   // row[kk .. kk + 3], zeros from K on
+        f32x4 v;
+        if (VEC == 4 && vec) {
+          v = *(const f32x4*)(row + (kk < K ? kk : 0));
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v[t] = row[kk + t < K ? kk + t : 0];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = kk + t < K ? v[t] : 0.f;
+        return v;
+      };
+      fa[u] = quad(Ap + arow * lda, true);
+      if (SEG && gcol >= 0) fa[u] *= gts[r * F32_MAX_SEGD + gcol];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + 16 * j + r, nn = n < Nc ? n : 0;   // (a column past the last repeats the first; not stored)
+        if constexpr (BNT) {
+          fb[u][j] = quad(Bp + (long)nn * sbn, !own);
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float v = Bp[(long)(kk + t < K ? kk + t : 0) * a.sbk + nn];
+            fb[u][j][t] = kk + t < K ? v : 0.f;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < FSM_U; ++u)
+      if (c0 + u * FSM_W < pieces) {   // uniform in the wave
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[j] = mfma_16x16x4(fa[u][t], fb[u][j][t], acc[j]);
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[wave][4 * g + v][16 * j + r] = acc[j][v];
+  __syncthreads();
+  const int row = tid / FSM_N, n = n0 + tid % FSM_N;   // an output element per thread
+  if (row >= rows || n >= Nc) return;
+  float s = part[0][row][tid % FSM_N];
+#pragma unroll
+  for (int w = 1; w < FSM_W; ++w) s += part[w][row][tid % FSM_N];
+  if constexpr (SEG) {
+    // (zero times an infinity or NaN of an expert that the token did not select: once more from the selected experts alone, as above)
+    if (s != s) s = f32_selected_sum<BNT>(a, gts + row * F32_MAX_SEGD, row0 + row, n);
+  }
+  s *= gsc[row];
+  float* C = (float*)(second ? a.C2 : a.C) + (long)hh * a.c_hoff + (long)(ids[row] / a.c_div) * a.ldc + n;
+  if (a.mode == ATOMIC_F32)
+    atomicAdd(C, s);
+  else
+    *C = s;
 }
 
 // 16-byte loads of both operands are possible
@@ -332,9 +477,21 @@ static int f32_nj(int cols) {
   return w5 < w4 ? 5 : 4;
 }
 
+template <int VEC>
+static void launch_f32_small(const RowGemmArgs& a, hipStream_t s) {
+  const dim3 g((a.M + FSM_M - 1) / FSM_M + (a.perm ? a.E : 0), (a.Nc + FSM_N - 1) / FSM_N, a.heads);
+  if (a.seg_mode == 3)
+    a.sbk == 1 ? f32_small_gemm_kernel<VEC, true, true><<<g, 64 * FSM_W, 0, s>>>(a) : f32_small_gemm_kernel<VEC, false, true><<<g, 64 * FSM_W, 0, s>>>(a);
+  else
+    a.sbk == 1 ? f32_small_gemm_kernel<VEC, true, false><<<g, 64 * FSM_W, 0, s>>>(a) : f32_small_gemm_kernel<VEC, false, false><<<g, 64 * FSM_W, 0, s>>>(a);
+}
+
 void launch_f32_row_gemm(const RowGemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.Nc <= 0) return;
   const bool v4 = f32_vec4(a);
+  const int nj = f32_nj(a.Nc);
+  const long tiles = (long)((a.M + FBM - 1) / FBM + (a.perm ? a.E / 2 : 0)) * ((a.Nc + 16 * nj - 1) / (16 * nj)) * a.heads;
+  if (tiles <= F32_SMALL_TILES) return v4 ? launch_f32_small<4>(a, s) : launch_f32_small<1>(a, s);
   switch (f32_nj(a.Nc) * 2 + (v4 ? 1 : 0)) {
     case 5: return launch_f32_rg<2, 4>(a, s);
     case 4: return launch_f32_rg<2, 1>(a, s);
