@@ -113,7 +113,7 @@ struct RowGemmArgs {
   const float* gtab;
   int gld;
   int seg_q, seq_T, seq_Tq;
-  // ... the fp32 kernel takes the gates from the top-k tables [head][token][gk] of `gheads` heads instead and keeps the
+  // ... the fp32 kernels and the bf16 one for a few rows take the gates from the top-k tables [head][token][gk] of `gheads` heads instead and keeps the
   // tile's dense gates in LDS (column head * experts + expert)
   const int* gidx;
   const float* ggate;
@@ -414,6 +414,9 @@ void launch_pp_row_gemm(const RowGemmArgs& a, hipStream_t s);
 // 32 x 32 tiles for launches of a few rows (mfma_skinny.hip); launch_mfma_row_gemm routes to it
 bool skinny_row_gemm_supported(const RowGemmArgs& a);
 void launch_skinny_row_gemm(const RowGemmArgs& a, hipStream_t s);
+// ... and segment mode 3 with the gates from the top-k tables
+bool skinny_concat_supported(const RowGemmArgs& a);
+void launch_skinny_concat(const RowGemmArgs& a, hipStream_t s);
 bool mfma_wgrad_supported(const WgradArgs& a);
 void launch_mfma_wgrad(const WgradArgs& a, hipStream_t s);
 bool mfma_attn_supported(int T, int dh);

@@ -1026,6 +1026,22 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     launch_f32_row_gemm(a, c.st);
     y_done = true;
   }
+  // A few rows: the same sum on small tiles, gates from the top-k tables
+  if (!y_done && use_mfma(c) && H * E <= MAX_SEGD) {
+    RowGemmArgs a = f32_concat(c, 1, y);
+    a.tag = TAG_O_EXPERTS;
+    a.mode = STORE_T;
+    a.sbk = dm;
+    a.sbn = 1;
+    a.nseg = H * E;
+    for (int s_ = 0; s_ < H * E; ++s_)
+      a.segd[s_] = {c.p<bf16_t>(c.L.ctx) + (size_t)(s_ / E) * dh, (const bf16_t*)W_O + (size_t)s_ * dh * dm, c.dense ? -1 : s_, 0, 0, 0};
+    if (skinny_concat_supported(a)) {
+      prof_mark(c.st, "fwd.o_experts");
+      launch_skinny_concat(a, c.st);
+      y_done = true;
+    }
+  }
   // Expert-set path: per head one GEMM whose reduction runs over the
   // k gate-scaled copies of the token's read-out row, then the sum over heads.
   if (y_done) {

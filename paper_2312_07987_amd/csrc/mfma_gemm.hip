@@ -380,7 +380,7 @@ static void launch_cfg(const RowGemmArgs& a, hipStream_t s) {
 enum { SHAPE_SMALL, SHAPE_WIDE, SHAPE_MED };
 static int pick_shape(const RowGemmArgs& a) {
   const int group_rows = a.perm ? a.max_group_rows : a.M;
-  if (a.tag == TAG_GENERIC) return SHAPE_SMALL;
+  if (a.tag == TAG_GENERIC || (a.seg_mode != 1 && !a.perm && pp_row_gemm_supported(a))) return SHAPE_SMALL;   // (supported: too few tiles)
   // measured on MI355X: the 256 x 128 tile with two work-groups per CU wins where the rows are
   // dense (its operand traffic per flop is 25 % lower); expert-gathered rows do better with
   // the small tile (more work-groups in flight per CU)
@@ -426,9 +426,18 @@ static void launch_generic(const RowGemmArgs& a, hipStream_t s) {
     launch_generic_cfg<CfgSmall, VEC, BNT>(a, s);
 }
 
+// At most 128 tiles of 256 x 256: their 512 tiles of 128 x 128 (two for each CU) are faster than one work-group on every other CU.  Dense
+// queries and keys / their input gradient, d_model 1024, 4 heads of 128, us, 256 x 256 and 128 x 128 tiles: 3000 tokens 29.4 and 22.5 /
+// 34.4 and 25.5, 6000 tokens 30.4 and 27.9 / 36.1 and 30.7, 8000 tokens (128 tiles) 31.5 and 28.9 / 38.2 and 33.4, 9000 tokens 32.3 and
+// 37.1 / 38.1 and 41.0.
+static bool pp_few_tiles(const RowGemmArgs& a) {
+  const long cols = a.Nc < 256 ? a.heads / 2 : (long)a.heads * (a.Nc / 256);
+  return (a.M + 255) / 256 * cols <= 128;
+}
+
 void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.Nc <= 0) return;
-  if (pp_row_gemm_supported(a)) return launch_pp_row_gemm(a, s);
+  if (pp_row_gemm_supported(a) && !(a.seg_mode != 1 && pp_few_tiles(a))) return launch_pp_row_gemm(a, s);
   if (skinny_row_gemm_supported(a)) return launch_skinny_row_gemm(a, s);
   const int vec = row_gemm_vec(a);
   const bool nt = a.sbk == 1;

@@ -95,6 +95,117 @@ __global__ __launch_bounds__(256, 2) void skinny_row_gemm_kernel(RowGemmArgs a) 
   *(uint2*)C = make_uint2(pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w));
 }
 
+// ----------------------------------------------------------------------------------------
+// Output experts of calls of a few rows: y[n] = sum over every (head, expert) segment of gate * ctx[n, h] W_O[h, e] in one accumulator
+// (segment mode 3, gates from the top-k tables, 0 for an expert that a token did not select).  32 x 32 tiles, token-ordered rows, the
+// reduction shared out among the waves in pieces of a head and 64 indices.  By expert sets the same
+// call was a launch of 128 x 128 tiles over the k selected experts of each head, a bf16 partial sum per head, and another launch to add
+// them.
+// ----------------------------------------------------------------------------------------
+template <int VEC>
+__device__ __forceinline__ uint4 sk_load8(const unsigned short* row, int k, int end) {   // row[k .. k + 7], zeros from `end` on (end >= VEC)
+  if constexpr (VEC == 8) {
+    const uint4 v = *(const uint4*)(row + min(k, end - 8));
+    return k < end ? v : make_uint4(0, 0, 0, 0);
+  } else {
+    const uint2 lo = *(const uint2*)(row + min(k, end - 4)), hi = *(const uint2*)(row + min(k + 4, end - 4));
+    return make_uint4(k < end ? lo.x : 0, k < end ? lo.y : 0, k + 4 < end ? hi.x : 0, k + 4 < end ? hi.y : 0);
+  }
+}
+
+template <int VEC>
+__global__ __launch_bounds__(512, 1) void skinny_concat_kernel(RowGemmArgs a) {
+  constexpr int W = 8, UK = 64, EB = 5;
+  __shared__ __attribute__((aligned(16))) unsigned short bs[W][UK * SK_T];   // then the partial sums [W][32][32] fp32
+  __shared__ float gts[SK_T * MAX_SEGD];   // the tile's dense gates [row][head * experts + expert]
+  __shared__ SegDesc descs[MAX_SEGD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 31, g = lane >> 5;
+  const int row0 = blockIdx.x * SK_T, n0 = blockIdx.y * SK_T;
+  const int rows = min(a.M - row0, SK_T);
+  if (tid < a.nseg) descs[tid] = a.segd[tid];
+  for (int t = tid; t < SK_T * MAX_SEGD; t += 512) gts[t] = 0.f;
+  __syncthreads();
+  if (a.gidx) {
+    for (int t = tid; t < SK_T * a.gheads * a.gk; t += 512) {
+      const int row = t % SK_T, j = t / SK_T % a.gk, h = t / SK_T / a.gk;
+      if (row < rows) {
+        const long o = ((long)h * a.M + row0 + row) * a.gk + j;
+        gts[row * MAX_SEGD + h * a.experts + a.gidx[o]] = a.ggate[o];
+      }
+    }
+    __syncthreads();
+  }
+  // A wave's item: a head, 64 of its reduction indices, up to EB of its experts (fewer where there would be idle waves).  The head's
+  // read-out is loaded once for its experts; everything of an item is requested before the wave waits.
+  const int H = a.gheads, E = a.experts, ups = (a.K + UK - 1) / UK;
+  int split = max((E + EB - 1) / EB, min(E, W / (H * ups)));
+  const int eb = (E + split - 1) / split;
+  split = (E + eb - 1) / eb;
+  const long arow = (long)(row0 + min(r, rows - 1)) * a.lda;   // (a row past the end repeats the last one; not stored)
+  f32x16 acc;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) acc[q] = 0.f;
+  for (int it = wave; it < H * ups * split; it += W) {
+    const int h = it / (ups * split), k0 = it / split % ups * UK, e0 = it % split * eb, ne = min(eb, E - e0);
+    const unsigned short* Ap = (const unsigned short*)descs[h * E].A + arow;
+    uint4 rb[EB][4], fa[4];
+#pragma unroll
+    for (int u = 0; u < EB; ++u)
+      if (u < ne) {   // uniform
+        const unsigned short* Bp = (const unsigned short*)descs[h * E + e0 + u].B;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rb[u][i] = sk_load8<VEC>(Bp + (long)min(k0 + (lane >> 2) + 16 * i, a.K - 1) * a.sbk, n0 + (lane & 3) * 8, a.Nc);
+      }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fa[i] = sk_load8<VEC>(Ap, k0 + 16 * i + 8 * g, a.K);
+#pragma unroll
+    for (int u = 0; u < EB; ++u)
+      if (u < ne) {
+        const int gcol = descs[h * E + e0 + u].gcol;
+        const float gt = gcol >= 0 ? gts[r * MAX_SEGD + gcol] : 1.f;
+        wave_order();   // (the area is the wave's own and a wave's LDS operations keep their order)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *(uint4*)(&bs[wave][((lane >> 2) + 16 * i) * SK_T + (lane & 3) * 8]) = k0 + (lane >> 2) + 16 * i < a.K ? rb[u][i] : make_uint4(0, 0, 0, 0);
+        wave_order();
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (k0 + 16 * i < a.K) {   // uniform
+            const uint4 f = gcol >= 0 ? scale_chunk(fa[i], gt) : fa[i];
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f), frag_transposed(bs[wave], SK_T, 16 * i + 8 * g, 0, lane), acc, 0, 0, 0);
+          }
+      }
+  }
+  __syncthreads();
+  float* part = (float*)&bs[0][0];   // [W][32][32]
+#pragma unroll
+  for (int q = 0; q < 16; ++q) part[(wave * SK_T + 8 * (q >> 2) + 4 * g + (q & 3)) * SK_T + r] = acc[q];
+  __syncthreads();
+  const int row = tid >> 4, c = (tid & 15) * 2, n = n0 + c;
+  if (row >= rows || n >= a.Nc) return;
+  float s[2] = {0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const float2 v = *(const float2*)(&part[(w * SK_T + row) * SK_T + c]);
+    s[0] = w ? s[0] + v.x : v.x;
+    s[1] = w ? s[1] + v.y : v.y;
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (s[u] != s[u]) {
+      // (zero times an infinity or NaN of an expert that the token did not select: once more from the selected experts alone)
+      s[u] = 0.f;
+      for (int p = 0; p < a.nseg && s[u] == s[u]; ++p) {
+        const float gt = descs[p].gcol >= 0 ? gts[row * MAX_SEGD + descs[p].gcol] : 1.f;
+        if (gt == 0.f) continue;
+        const unsigned short *Ap = (const unsigned short*)descs[p].A + (long)(row0 + row) * a.lda, *Bp = (const unsigned short*)descs[p].B + n + u;
+        for (int k = 0; k < a.K; ++k) s[u] = fmaf(bf16_to_f32(f32_to_bf16(bf16_to_f32(Ap[k]) * gt)), bf16_to_f32(Bp[(long)k * a.sbk]), s[u]);
+      }
+    }
+  *(unsigned*)((unsigned short*)a.C + (long)(row0 + row) * a.ldc + n) = pack_bf16x2(s[0], s[1]);
+}
+
 static bool sk_aligned(const void* p) { return ((uintptr_t)p % 16) == 0; }
 
 // A launch of at most SK_MAX_TILES tiles of 32 x 32 (expected: a sorted group's rows are counted together), three for each CU; 16-byte
@@ -114,6 +225,36 @@ void launch_skinny_row_gemm(const RowGemmArgs& a, hipStream_t s) {
   const int group_rows = a.perm && a.max_group_rows > 0 ? a.max_group_rows : a.M;
   const dim3 g((group_rows + SK_T - 1) / SK_T, a.heads * a.E * ((a.Nc + SK_T - 1) / SK_T));
   skinny_row_gemm_kernel<<<g, 256, 0, s>>>(a);
+}
+
+static int sk_concat_vec(const RowGemmArgs& a) {
+  for (int vec = 8; vec >= 4; vec -= 4) {
+    auto al = [&](const void* p) { return ((uintptr_t)p % (2 * vec)) == 0; };
+    bool ok = a.K >= vec && a.Nc >= vec && a.K % vec == 0 && a.Nc % vec == 0 && a.lda % vec == 0 && a.sbk % vec == 0 && ((uintptr_t)a.C % 4) == 0 && a.ldc % 2 == 0;
+    for (int p = 0; ok && p < a.nseg; ++p) ok = al(a.segd[p].A) && al(a.segd[p].B);
+    if (ok) return vec;
+  }
+  return 0;
+}
+
+// One tile for each CU (8 of 1024 columns each: 256 tokens), two where a tile's reduction is short.  us, by expert sets with the sum of the
+// heads / here: d_model 1024, 4 heads of 128, 3 of 5 experts, 1 token 22.0 / 12.3, 128 24.1 / 18.1, 256 24.8 / 18.1, 384 24.6 / 25.8;
+// 2 of 8 experts, 256 tokens 31.1 / 22.1, 384 31.3 / 32.7; d_model 412, 2 heads of 76, 3 of 5 experts, 512 tokens (208 tiles) 21.9 / 11.3, 1024 (416)
+// 22.8 / 17.9, 1536 (624) 22.9 / 24.7; 20 dense heads of 80, 256 tokens 24.0 / 14.4.
+bool skinny_concat_supported(const RowGemmArgs& a) {
+  if (a.seg_mode != 3 || a.perm || a.heads != 1 || a.E != 1 || a.mode != STORE_T || a.sbn != 1 || a.M < 1 || a.gtab || a.seg_q) return false;
+  // (segment h * experts + e: expert e of head h, the head's read-out the same for all of them)
+  if (a.nseg < 1 || a.nseg > MAX_SEGD || a.gheads * a.experts != a.nseg) return false;
+  const long tiles = (long)((a.M + SK_T - 1) / SK_T) * ((a.Nc + SK_T - 1) / SK_T);
+  return tiles <= ((long)a.nseg * a.K <= 1024 ? 512 : 256) && sk_concat_vec(a) != 0;
+}
+
+void launch_skinny_concat(const RowGemmArgs& a, hipStream_t s) {
+  const dim3 g((a.M + SK_T - 1) / SK_T, (a.Nc + SK_T - 1) / SK_T);
+  if (sk_concat_vec(a) == 8)
+    skinny_concat_kernel<8><<<g, 512, 0, s>>>(a);
+  else
+    skinny_concat_kernel<4><<<g, 512, 0, s>>>(a);
 }
 
 }  // namespace sh

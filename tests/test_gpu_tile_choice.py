@@ -27,3 +27,28 @@ def _cfg(**over):
 ])
 def test_fp32_tiles(over, shared):
     run_case(_cfg(dtype="f32", **over), shared=shared, seed=211)
+
+
+@pytest.mark.parametrize("over, dense", [
+    # the output experts of a few rows: one row, remainders of rows, columns and 64 reduction indices, 8-byte pieces, more experts than a wave
+    # takes at a time, fewer pieces than waves, dense heads; 256 tiles and the next size
+    (dict(T=1, d_model=8, nheads=1, d_head=8, E=3, k=2), False),
+    (dict(T=33, d_model=72, nheads=2, d_head=24, E=3, k=2), False),
+    (dict(T=70, T_q=37, d_model=412, nheads=2, d_head=76, E=5, k=3), False),
+    (dict(T=100, d_model=1024, nheads=4, d_head=100, E=8, k=2), False),
+    (dict(T=65, d_model=128, nheads=4, d_head=64, E=13, k=4), False),
+    (dict(T=50, d_model=256, nheads=20, d_head=80, E=1, k=1), True),
+    (dict(T=256, d_model=1024, nheads=4, d_head=128, E=5, k=3), False),
+    (dict(T=257, d_model=1024, nheads=4, d_head=128, E=5, k=3), False),
+])
+def test_output_experts_of_a_few_rows(over, dense):
+    run_case(_cfg(**over), dense=dense, backward=False, seed=223)
+
+
+@pytest.mark.parametrize("over", [
+    dict(T=2100, d_model=64, nheads=16, d_head=128, E=2, k=1),      # dense queries and keys: 144 tiles of 256 x 256
+    dict(T=2100, d_model=4096, nheads=2, d_head=64, E=5, k=2),      # their input gradient: 144 such tiles
+    dict(T=2100, d_model=256, nheads=2, d_head=128, E=5, k=2),      # both: fewer than 128
+])
+def test_dense_projections_by_tile_count(over):
+    run_case(_cfg(**over), seed=227, check_inter=False)
