@@ -288,7 +288,7 @@ Layout make_layout(const sh_shape* s) {
       // each other, are dead in between: the score gradient takes their place if it fits.
       if (L.u == L.acc32 + align_up(N * dm * 4) && bytes <= align_up(N * dm * 4) + align_up(H * N * k * dh * esz))
         L.dst = L.acc32;
-      else if (bytes <= ((size_t)1 << 30))
+      else if (bytes <= ((size_t)1 << 30) && dh % 8 == 0)   // (other head widths only where it costs no room)
         L.dst = take(bytes);
     }
   }

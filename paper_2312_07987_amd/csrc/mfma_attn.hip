@@ -958,7 +958,7 @@ __global__ __launch_bounds__(256, 2) void mfma_attn_dq_ds_kernel(AttnBwdArgs a) 
 // kernel is already the smaller part there).
 bool attn_ds_dims(int T, int Tq, int dh, int causal, int* ld, long* per) {
   if (Tq <= 0) Tq = T;
-  if (dh < 64 || dh > 128 || dh % 8 != 0) return false;
+  if (dh < 64 || dh > 128 || dh % 4 != 0) return false;
   *ld = (Tq + 255) / 256 * 256;
   *per = ds_block_offset((T + 127) / 128, *ld, T - Tq, causal);
   return true;
@@ -1019,10 +1019,15 @@ static void launch_dh(const AttnArgs* f, const AttnBwdArgs* bw, hipStream_t s) {
         // 128-query tiles (half of d per wave) unless 256-query tiles already make three work-groups per CU
         constexpr bool can_split = (DH / 32) % 2 == 0;
         const long big = (long)((tq + 255) / 256) * bw->H * bw->B;
+        const bool v8 = attn_vec(bw->dh) == 8;
         if (can_split && big < 3 * 256) {
-          if constexpr (can_split) mfma_attn_dq_ds_kernel<DH, 8, 128><<<dim3(((tq + 127) / 128) * bw->H * bw->B), 256, 0, s>>>(*bw);
+          if constexpr (can_split) {
+            auto kern = v8 ? mfma_attn_dq_ds_kernel<DH, 8, 128> : mfma_attn_dq_ds_kernel<DH, 4, 128>;
+            kern<<<dim3(((tq + 127) / 128) * bw->H * bw->B), 256, 0, s>>>(*bw);
+          }
         } else {
-          mfma_attn_dq_ds_kernel<DH, 8, 256><<<dim3((unsigned)big), 256, 0, s>>>(*bw);
+          auto kern = v8 ? mfma_attn_dq_ds_kernel<DH, 8, 256> : mfma_attn_dq_ds_kernel<DH, 4, 256>;
+          kern<<<dim3((unsigned)big), 256, 0, s>>>(*bw);
         }
         return;
       }

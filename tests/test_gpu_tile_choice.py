@@ -52,3 +52,13 @@ def test_output_experts_of_a_few_rows(over, dense):
 ])
 def test_dense_projections_by_tile_count(over):
     run_case(_cfg(**over), seed=227, check_inter=False)
+
+
+@pytest.mark.parametrize("over", [
+    dict(B=2, T=300, d_model=128, nheads=2, d_head=100, E=4, k=2, rope=1),
+    dict(B=2, T=517, T_q=130, d_model=128, nheads=2, d_head=68, E=3, k=2),
+    dict(B=3, T=256, d_model=412, nheads=2, d_head=76, E=5, k=3, causal=0),
+])
+def test_query_gradient_from_kept_scores(over):
+    """Head widths that are multiples of four but not of eight: the score gradient is kept where it fits over dead buffers."""
+    run_case(_cfg(**over), seed=229)
