@@ -21,6 +21,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 
@@ -352,6 +353,165 @@ __global__ __launch_bounds__(256 * NG, (DH <= 128 && NG == 1) ? 2 : 1) void mfma
         }
       }
     if (g == 0) a.lse[((long)b * a.H + h) * Tq + q] = (m + log2f(l)) * 0.69314718055994530942f;
+  }
+}
+
+// ----------------------------------------------------------------------------------------
+// forward for at most 16 queries per sequence (decoding over a cached context): a work-group per (sequence, head), eight waves that
+// take every eighth piece of 32 keys and merge their (o, m, l) through LDS at the end.  16 x 16 x 32 products, lane = 16 g + r:
+//   S^T[key][query] = K Q^T     K straight from memory in operand order (16 rows of 64 contiguous bytes an instruction)
+//   O^T[d][query] += V^T P^T    a lane's scores of the piece's two key blocks (keys 4 g .. 4 g + 3 of each) are its operand as they
+//                               are; V goes through the wave's own LDS and is read with transposing loads in that key order
+// The next piece's loads are requested as soon as this one's registers are free and travel during the softmax and the second
+// product.  The kernel above gives such a sequence one tile of 128 queries and walks it
+// in trips of 64 or 128 keys between barriers.  One query over 1000 keys, 32 (sequence, head) pairs of width 128: 28.2 -> 17.4 us, over
+// 4000 keys 86 -> 44 us (2.2 us a round of 256 keys).  Bound by reading K and V through one CU.
+// ----------------------------------------------------------------------------------------
+template <int DH, int VEC>
+__global__ __launch_bounds__(512, 1) void mfma_attn_few_kernel(AttnArgs a) {
+  constexpr int W = 8, KP = 32;              // waves; keys of a piece
+  constexpr int NK = DH / 32, ND = DH / 16;  // reduction steps of the first product, 16-wide d blocks of the second
+  constexpr int LDV = DH + 16;               // rows 8 banks apart: the 16 rows of a transposing read fall on all banks twice
+  constexpr int CPR = DH / 8, NV = KP * CPR / 64;
+  __shared__ __attribute__((aligned(16))) unsigned short fsm[W * KP * LDV];   // a piece of V per wave, then its output in fp32
+  __shared__ float ms[W][16], ls[W][16];
+  static_assert(16 * (DH + 4) * 4 <= KP * LDV * 2, "a wave's output fits over its V piece");
+  const int T = a.T, dh = a.dh, Tq = a.Tq > 0 ? a.Tq : T, off = T - Tq;
+  const int b = blockIdx.x / a.H, h = blockIdx.x % a.H;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+  const long rs = (long)a.H * dh;
+  const unsigned short* Q = (const unsigned short*)a.Q + (long)b * Tq * rs + (long)h * dh;
+  const unsigned short* K = (const unsigned short*)a.K + (long)b * T * rs + (long)h * dh;
+  const unsigned short* V = (const unsigned short*)a.V + (long)b * T * rs + (long)h * dh;
+  unsigned short* const vl = fsm + wave * KP * LDV;
+  bf16x8 qf[NK];
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) qf[kk] = global_frag<VEC>(Q + (long)r * rs, kk * 32 + 8 * g, dh, r < Tq);
+
+  // eight elements of a row from column d on, zeros from dh on (clamped addresses, no test around a load)
+  auto row8 = [&](const unsigned short* row, int d) {
+    uint4 v;
+    if constexpr (VEC == 8) {
+      v = *(const uint4*)(row + min(d, dh - 8));
+    } else {
+      const uint2 lo = *(const uint2*)(row + min(d, dh - 4)), hi = *(const uint2*)(row + min(d + 4, dh - 4));
+      v = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
+    return v;
+  };
+  auto cut = [&](uint4 v, int d) {
+    if (DH == dh) return v;   // uniform
+    if (d >= dh) v.x = v.y = 0;
+    if (d + (VEC == 8 ? 0 : 4) >= dh) v.z = v.w = 0;
+    return v;
+  };
+  uint4 kf[2][NK], vf[NV];
+  auto load = [&](int k0) {   // (a key past the end repeats the last one, at probability zero)
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) kf[blk][kk] = row8(K + (long)min(k0 + 16 * blk + r, T - 1) * rs, kk * 32 + 8 * g);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = lane + 64 * i;
+      vf[i] = row8(V + (long)min(k0 + c / CPR, T - 1) * rs, c % CPR * 8);
+    }
+  };
+  f32x4 o[ND];
+#pragma unroll
+  for (int d = 0; d < ND; ++d) o[d] = f32x4{};
+  float m = -INFINITY, l = 0.f;
+  const float sc = a.scale * 1.44269504088896340736f;   // logits in log2 units
+  if (wave * KP < T) load(wave * KP);
+  for (int k0 = wave * KP; k0 < T; k0 += W * KP) {
+    f32x4 s[2];
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      s[blk] = f32x4{};
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk)
+        s[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cut(kf[blk][kk], kk * 32 + 8 * g)), qf[kk], s[blk], 0, 0, 0);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (the area is the wave's own, and a wave's LDS operations keep their order)
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = lane + 64 * i;
+      *(uint4*)(vl + (c / CPR) * LDV + c % CPR * 8) = cut(vf[i], c % CPR * 8);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (k0 + W * KP < T) load(k0 + W * KP);   // uniform
+    if (k0 + KP > T || (a.causal && k0 + KP - 1 > off)) {
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int key = k0 + 16 * blk + 4 * g + v;
+          if (key >= T || (a.causal && key > r + off)) s[blk][v] = -INFINITY;
+        }
+    }
+    float mt = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
+    mt = fmaxf(mt, __shfl_xor(mt, 32, 64)) * sc;   // sc > 0
+    const float mn = fmaxf(m, mt), mb = mn == -INFINITY ? 0.f : mn;   // (a piece wholly masked for the query)
+    const float alpha = __builtin_amdgcn_exp2f(m - mb);               // m = -inf: 0
+    m = mn;
+    float ps = 0.f;
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        s[blk][v] = __builtin_amdgcn_exp2f(fmaf(s[blk][v], sc, -mb));   // masked: 0
+        ps += s[blk][v];
+      }
+    l = l * alpha + ps;
+    const float p8[8] = {s[0][0], s[0][1], s[0][2], s[0][3], s[1][0], s[1][1], s[1][2], s[1][3]};
+    const bf16x8 pb = pack8(p8);
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+      o[d] *= alpha;
+      const unsigned short* p = vl + (4 * g + (r >> 2)) * LDV + d * 16 + (r & 3) * 4;
+      union {
+        s16x4 half[2];
+        bf16x8 v;
+      } u;
+      u.half[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, p));
+      u.half[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, p + 16 * LDV));
+      o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u.v, pb, o[d], 0, 0, 0);
+    }
+  }
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  constexpr int LDO = DH + 4;
+  float* const po = (float*)vl;
+#pragma unroll
+  for (int d = 0; d < ND; ++d) *(f32x4*)(po + r * LDO + d * 16 + 4 * g) = o[d];
+  if (g == 0) {
+    ms[wave][r] = m;
+    ls[wave][r] = l;
+  }
+  __syncthreads();
+  // two output columns a thread; a wave that saw no key has m = -inf and counts for nothing (some wave saw key 0)
+  for (int t = tid; t < Tq * (DH / 2); t += 512) {
+    const int q = t / (DH / 2), d = t % (DH / 2) * 2;
+    float mx = ms[0][q];
+#pragma unroll
+    for (int w = 1; w < W; ++w) mx = fmaxf(mx, ms[w][q]);
+    float lt = 0.f, x = 0.f, y = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const float f = __builtin_amdgcn_exp2f(ms[w][q] - mx);
+      const float2 v = *(const float2*)((const float*)(fsm + w * KP * LDV) + q * LDO + d);
+      lt += f * ls[w][q];
+      x += f * v.x;
+      y += f * v.y;
+    }
+    const float inv = 1.f / lt;
+    if (d < dh) *(unsigned*)((unsigned short*)a.O + ((long)b * Tq + q) * rs + (long)h * dh + d) = pack_bf16x2(x * inv, y * inv);
+    if (d == 0) a.lse[((long)b * a.H + h) * Tq + q] = (mx + log2f(lt)) * 0.69314718055994530942f;
   }
 }
 
@@ -980,6 +1140,21 @@ static void launch_dh(const AttnArgs* f, const AttnBwdArgs* bw, hipStream_t s) {
     // 640 keys 23.6 / 24.1 with 240, but 22.2 / 20.8 with 32).
     const int queries = f->Tq > 0 ? f->Tq : f->T;
     const int keys_from = DH > 96 ? 320 : 256, groups_to = DH > 96 && (f->T < 512 || queries < 128) ? 128 : 256;
+    // At most 16 queries per sequence: a work-group per (sequence, head) that reads only the rows there are, if these work-groups run in
+    // one round or have 256 keys each.  Tiles of 128 queries / this one, us: one query per sequence, heads of 128 over 1000 keys
+    // 28.2 / 17.4 with 32 work-groups, over 4000 86.4 / 44.3 with 16, over 64 7.9 / 7.0 with 32; in more than one round, of 76 over 1000
+    // keys 40.7 / 38.1 with 320, of 100 over 200 19.9 / 17.7 (16 queries 20.9 / 22.2) with 512, over 128 14.0 / 14.5 and over 64 9.7 / 11.2
+    // with 288: there two work-groups of the other kernel share a CU.
+    if constexpr (DH <= 128) {
+      if (queries <= 16 && ((int)g.x <= 256 || f->T >= 256)) {
+        const dim3 gf(f->H * f->B);
+        if (attn_vec(f->dh) == 8)
+          mfma_attn_few_kernel<DH, 8><<<gf, 512, 0, s>>>(*f);
+        else
+          mfma_attn_few_kernel<DH, 4><<<gf, 512, 0, s>>>(*f);
+        return;
+      }
+    }
     const bool split = DH <= 128 && DH >= 64 && (f->T >= 1024 || (f->T >= keys_from && (int)g.x <= groups_to));
     if constexpr (DH <= 128 && DH >= 64) {
       if (split) {

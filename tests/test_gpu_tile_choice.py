@@ -62,3 +62,22 @@ def test_dense_projections_by_tile_count(over):
 def test_query_gradient_from_kept_scores(over):
     """Head widths that are multiples of four but not of eight: the score gradient is kept where it fits over dead buffers."""
     run_case(_cfg(**over), seed=229)
+
+
+@pytest.mark.parametrize("over", [
+    # at most 16 queries per sequence: one and all queries of a block, fewer keys than waves have pieces, remainders of a piece and of a
+    # round of pieces, rows of 8 and 16 bytes, every width of the operands; no causal mask; all queries are the sequence
+    dict(T=33, T_q=1, d_model=64, nheads=3, d_head=8, E=2, k=1),
+    dict(T=300, T_q=16, d_model=72, nheads=2, d_head=36, E=3, k=2, rope=1),
+    dict(B=3, T=257, T_q=4, d_model=412, nheads=2, d_head=76, E=5, k=3),
+    dict(T=1055, T_q=15, d_model=128, nheads=2, d_head=100, E=4, k=2),
+    dict(B=2, T=640, T_q=16, d_model=64, nheads=2, d_head=128, E=2, k=1, causal=0),
+    dict(B=9, T=16, d_model=128, nheads=2, d_head=64, E=4, k=2),
+    # the other kernel: the next number of queries, more work-groups than a round of few keys
+    dict(T=300, T_q=17, d_model=72, nheads=2, d_head=64, E=3, k=2),
+    dict(B=129, T=70, T_q=3, d_model=64, nheads=2, d_head=64, E=3, k=2),
+    dict(B=129, T=256, T_q=3, d_model=64, nheads=2, d_head=64, E=3, k=2),   # (and enough of them)
+])
+def test_attention_of_a_few_queries(over):
+    # (a single query of narrow heads: its router gradient is a few cancelling sums of 8 rounded terms, no measure of anything)
+    run_case(_cfg(**over), backward=over["d_head"] > 8, seed=233)
