@@ -10,8 +10,23 @@
 #include "common.h"
 #include "mfma_util.h"
 #include <cstdlib>
+#include <type_traits>
 
 namespace sh {
+
+// 16 bytes at a multiple of 8
+typedef unsigned half_piece __attribute__((ext_vector_type(4), aligned(8)));
+__device__ __forceinline__ uint4 second_half(uint4 v) { return make_uint4(v.z, v.w, 0, 0); }
+__device__ __forceinline__ uint2 second_half(uint2 v) { return v; }   // (pieces of 8 bytes have none)
+template <int VEC, bool HALF>
+__device__ __forceinline__ typename Chunk<VEC>::type load_piece(const unsigned short* p) {
+  if constexpr (HALF) {
+    const half_piece v = *(const half_piece*)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+  } else {
+    return *(const typename Chunk<VEC>::type*)p;
+  }
+}
 
 // ----------------------------------------------------------------------------------------
 // Row GEMM.  4 waves per work-group arranged WM x WN, each wave owns MI x NJ MFMA blocks of
@@ -49,8 +64,12 @@ typedef TileCfg<4, 1, 1, 3, 64, 1> CfgN96;      // 128 x 96, wave tile 32 x 96: 
 typedef TileCfg<2, 2, 2, 4, 64, 1, 2> CfgWide;     // 128 x 256, wave tile 64 x 128, two work-groups per CU
 typedef TileCfg<2, 2, 4, 2, 64, 1, 2> CfgMed;   // 256 x 128, wave tile 128 x 64, two work-groups per CU
 
-template <class Cfg, int VEC, bool BNT, int TAG, int SEG>
-__global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmArgs a) {
+// HALF: rows are multiples of 8 bytes only.  They are taken in pieces of 16 bytes all the same (a load wants no more than 4-byte
+// alignment): the last piece of a row of an odd number of half pieces is read 8 bytes early, so that nothing past the row is touched,
+// and moved into place on its way into LDS.
+template <class Cfg, int VEC, bool BNT, int TAG, int SEG, bool HALF = false>
+__global__ __launch_bounds__(256, HALF && SEG == 0 && Cfg::BN == 96 ? 4 : Cfg::MINB) void mfma_row_gemm_kernel(RowGemmArgs a) {
+  static_assert(!HALF || VEC == 8, "a half piece is 8 bytes");
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, MI = Cfg::MI, NJ = Cfg::NJ;
   constexpr int LDA = Cfg::LDA, LDB_NT = Cfg::LDB_NT, LDB_NN = Cfg::LDB_NN;
   typedef typename Chunk<VEC>::type chunk_t;
@@ -153,7 +172,7 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
   }
   long b_off[B_N];
   int b_kc[B_N], b_lds[B_N];
-  bool b_ok[B_N];
+  bool b_ok[B_N], b_half[B_N];
 #pragma unroll
   for (int i = 0; i < B_N; ++i) {
     int c = tid + i * 256;
@@ -161,6 +180,7 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
       constexpr int CPR = BK / VEC;
       int n = c / CPR, kc = (c % CPR) * VEC;
       b_ok[i] = n0 + n < Nc;
+      b_half[i] = false;
       b_off[i] = (long)(n0 + n) * a.sbn + kc;
       b_kc[i] = kc;
       b_lds[i] = n * LDB_NT + kc;
@@ -168,7 +188,8 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
       constexpr int CPR = BN / VEC;
       int kr = c / CPR, nc = (c % CPR) * VEC;
       b_ok[i] = n0 + nc < Nc;
-      b_off[i] = (long)kr * a.sbk + n0 + nc;
+      b_half[i] = HALF && n0 + nc + 8 > Nc;
+      b_off[i] = (long)kr * a.sbk + n0 + nc - (b_half[i] ? 4 : 0);
       b_kc[i] = kr;
       b_lds[i] = kr * LDB_NN + nc;
     }
@@ -177,10 +198,12 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
   chunk_t ra[A_N], rb[B_N];
   const int nks = (K + BK - 1) / BK;   // K steps per segment
   int staged_seg = 0;   // segment of the K step that sits in ra / rb
+  int staged_k0 = 0;    // and its first index
   auto load_global = [&](int it) {
     const int seg = SEG ? it / nks : 0;
     const int k0 = (SEG ? it % nks : it) * BK;
     staged_seg = seg;
+    staged_k0 = k0;
     const unsigned short* Ap = A;
     const unsigned short* Bp = B;
     if constexpr (SEG == 1) Bp = B + bseg[seg];
@@ -192,31 +215,45 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
 #pragma unroll
     for (int i = 0; i < A_N; ++i) {
       ra[i] = zero_chunk<VEC>();
-      if (a_off[i] >= 0 && k0 + a_kc[i] < K) ra[i] = *(const chunk_t*)(Ap + a_off[i] + k0);
+      if (a_off[i] >= 0 && k0 + a_kc[i] < K) ra[i] = load_piece<VEC, HALF>(Ap + a_off[i] + (HALF && k0 + a_kc[i] + 8 > K ? k0 - 4 : k0));
     }
 #pragma unroll
     for (int i = 0; i < B_N; ++i) {
       rb[i] = zero_chunk<VEC>();
       if (b_ok[i] && k0 + b_kc[i] < K) {
         if constexpr (BNT)
-          rb[i] = *(const chunk_t*)(Bp + b_off[i] + k0);
+          rb[i] = load_piece<VEC, HALF>(Bp + b_off[i] + (HALF && k0 + b_kc[i] + 8 > K ? k0 - 4 : k0));
         else
-          rb[i] = *(const chunk_t*)(Bp + b_off[i] + (long)k0 * a.sbk);
+          rb[i] = load_piece<VEC, HALF>(Bp + b_off[i] + (long)k0 * a.sbk);
       }
     }
   };
   auto store_lds = [&](int stage) {
     unsigned short* As = smem + stage * Cfg::STAGE_ELEMS;
     unsigned short* Bs = As + Cfg::A_ELEMS;
+    auto put = [&](auto ends) __attribute__((always_inline)) {   // ends: the step holds the half pieces at the end of a row of k
 #pragma unroll
-    for (int i = 0; i < A_N; ++i) {
-      // expert-set mode: the gate is applied here, not at the load, so that the load stays in
-      // flight while the previous step is multiplied
-      if constexpr (SEG == 1) ra[i] = scale_chunk(ra[i], gsc[(a_lds[i] / LDA) * 8 + staged_seg]);
-      *(chunk_t*)(&As[a_lds[i]]) = ra[i];
+      for (int i = 0; i < A_N; ++i) {
+        chunk_t v = ra[i];
+        if constexpr (decltype(ends)::value) v = staged_k0 + a_kc[i] + 8 > K ? second_half(v) : v;
+        // expert-set mode: the gate is applied here, not at the load, so that the load stays in
+        // flight while the previous step is multiplied
+        if constexpr (SEG == 1) v = scale_chunk(v, gsc[(a_lds[i] / LDA) * 8 + staged_seg]);
+        *(chunk_t*)(&As[a_lds[i]]) = v;
+      }
+#pragma unroll
+      for (int i = 0; i < B_N; ++i) {
+        chunk_t v = rb[i];
+        if constexpr (HALF && BNT && decltype(ends)::value) v = staged_k0 + b_kc[i] + 8 > K ? second_half(v) : v;
+        if constexpr (HALF && !BNT) v = b_half[i] ? second_half(v) : v;
+        *(chunk_t*)(&Bs[b_lds[i]]) = v;
+      }
+    };
+    if constexpr (HALF) {
+      if ((K & 4) && staged_k0 + BK > K)   // uniform
+        return put(std::true_type());
     }
-#pragma unroll
-    for (int i = 0; i < B_N; ++i) *(chunk_t*)(&Bs[b_lds[i]]) = rb[i];
+    put(std::false_type());
   };
 
   const int wm = (wave / Cfg::WN) * (MI * 32), wn = (wave % Cfg::WN) * (NJ * 32);
@@ -293,7 +330,16 @@ __global__ __launch_bounds__(256, Cfg::MINB) void mfma_row_gemm_kernel(RowGemmAr
         const int id = ids[wm + i * 32 + lr];
         if (id < 0 || n0 + wn + cc >= Nc) continue;
         const long crow = (long)div_by(id, inv_cdiv) * a.ldc + (long)hh * a.c_hoff;
-        *(chunk_t*)((unsigned short*)Cb + crow + n0 + wn + cc) = *(const chunk_t*)(&Cs[lr * LDC + cc]);
+        unsigned short* o = (unsigned short*)Cb + crow + n0 + wn + cc;
+        if constexpr (HALF) {
+          const uint4 v = *(const uint4*)(&Cs[lr * LDC + cc]);
+          if (n0 + wn + cc + 8 > Nc)
+            *(uint2*)o = make_uint2(v.x, v.y);
+          else
+            *(half_piece*)o = half_piece{v.x, v.y, v.z, v.w};
+        } else {
+          *(chunk_t*)o = *(const chunk_t*)(&Cs[lr * LDC + cc]);
+        }
       }
     }
     return;
@@ -353,7 +399,7 @@ bool mfma_row_gemm_supported(const RowGemmArgs& a) {
   return row_gemm_vec(a) != 0;
 }
 
-template <class Cfg, int VEC, bool BNT, int TAG, int SEG>
+template <class Cfg, int VEC, bool BNT, int TAG, int SEG, bool HALF = false>
 static void launch_cfg(const RowGemmArgs& a, hipStream_t s) {
   const int ncol = (a.Nc + Cfg::BN - 1) / Cfg::BN;
   dim3 g;
@@ -365,7 +411,7 @@ static void launch_cfg(const RowGemmArgs& a, hipStream_t s) {
     g = dim3(grid_windows((group_rows + Cfg::BM - 1) / Cfg::BM, a.heads * a.E * ncol));
   }
   const size_t lds = Cfg::lds_bytes(SEG == 1);
-  auto kern = mfma_row_gemm_kernel<Cfg, VEC, BNT, TAG, SEG>;
+  auto kern = mfma_row_gemm_kernel<Cfg, VEC, BNT, TAG, SEG, HALF>;
   if (lds > 64 * 1024) {
     static bool raised = false;   // per instantiation
     if (!raised) {
@@ -407,23 +453,23 @@ static void launch_tagged(const RowGemmArgs& a, hipStream_t s) {
   }
 }
 
-template <class Cfg, int VEC, bool BNT>
+template <class Cfg, int VEC, bool BNT, bool HALF>
 static void launch_generic_cfg(const RowGemmArgs& a, hipStream_t s) {
   if (a.seg_mode == 1)
-    launch_cfg<Cfg, VEC, BNT, TAG_GENERIC, 1>(a, s);
+    launch_cfg<Cfg, VEC, BNT, TAG_GENERIC, 1, HALF>(a, s);
   else if (a.seg_mode == 2)
-    launch_cfg<Cfg, VEC, BNT, TAG_GENERIC, 2>(a, s);
+    launch_cfg<Cfg, VEC, BNT, TAG_GENERIC, 2, HALF>(a, s);
   else
-    launch_cfg<Cfg, VEC, BNT, TAG_GENERIC, 0>(a, s);
+    launch_cfg<Cfg, VEC, BNT, TAG_GENERIC, 0, HALF>(a, s);
 }
-template <int VEC, bool BNT>
+template <int VEC, bool BNT, bool HALF>
 static void launch_generic(const RowGemmArgs& a, hipStream_t s) {
   if (a.K > 64 && a.K <= 80)
-    launch_generic_cfg<CfgSmall80, VEC, BNT>(a, s);
+    launch_generic_cfg<CfgSmall80, VEC, BNT, HALF>(a, s);
   else if (a.Nc > 64 && a.Nc <= 96)
-    launch_generic_cfg<CfgN96, VEC, BNT>(a, s);
+    launch_generic_cfg<CfgN96, VEC, BNT, HALF>(a, s);
   else
-    launch_generic_cfg<CfgSmall, VEC, BNT>(a, s);
+    launch_generic_cfg<CfgSmall, VEC, BNT, HALF>(a, s);
 }
 
 // At most 128 tiles of 256 x 256: their 512 tiles of 128 x 128 (two for each CU) are faster than one work-group on every other CU.  Dense
@@ -450,7 +496,7 @@ void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s) {
         case TAG_V_DGRAD * 4 + 1: return launch_tagged<true, TAG_V_DGRAD, 1>(a, s);
         case TAG_QK_DGRAD * 4 + 0: return launch_tagged<true, TAG_QK_DGRAD, 0>(a, s);
         case TAG_QK_DGRAD * 4 + 2: return launch_tagged<true, TAG_QK_DGRAD, 2>(a, s);
-        default: return launch_generic<8, true>(a, s);
+        default: return launch_generic<8, true, false>(a, s);
       }
     } else {
       switch (key) {
@@ -458,13 +504,20 @@ void launch_mfma_row_gemm(const RowGemmArgs& a, hipStream_t s) {
         case TAG_V_EXPERTS * 4 + 0: return launch_tagged<false, TAG_V_EXPERTS, 0>(a, s);
         case TAG_O_EXPERTS * 4 + 0: return launch_tagged<false, TAG_O_EXPERTS, 0>(a, s);
         case TAG_O_EXPERTS * 4 + 1: return launch_tagged<false, TAG_O_EXPERTS, 1>(a, s);
-        default: return launch_generic<8, false>(a, s);
+        default: return launch_generic<8, false, false>(a, s);
       }
     }
   }
-  if (nt)
-    return launch_generic<4, true>(a, s);
-  return launch_generic<4, false>(a, s);
+  // Rows of whole 8 bytes only: in pieces of 16 bytes, which take half the loads and fewer registers (three work-groups per CU instead of
+  // two), where a launch fills the chip; with one work-group per CU a step waits for its last piece, and a piece of 8 bytes is there
+  // sooner.  8 / 16 bytes, us, by tiles of 128 rows.  Expert sets: 2 heads of 76, d_model 412, 160 tiles 17.5 / 15.8, 1000 40.7 / 35.9; 4
+  // heads of 100, d_model 1024, 64 tiles 16.0 / 16.4 and 15.9 / 15.3, 256 21.8 / 18.7, 1024 41.2 / 31.3, 6016 158 / 113.  Other rows of
+  // one segment: 252 tiles 25.6 / 26.4, 256 26.2 / 27.0, 376 18.5 / 17.2, 500 34.2 / 30.9, 1500 88.0 / 72.3.  The concatenated reduction
+  // of the query / key gradient: 252 30.5 / 32.8, 500 21.0 / 23.6 and 37.3 / 38.1, 752 31.5 / 30.6, 1000 77.9 / 70.3, 1504 115 / 91.
+  const long tiles = (long)((a.M + 127) / 128) * a.heads * ((a.Nc + 127) / 128);
+  const bool half = a.K >= 8 && (nt || a.Nc >= 8) && (a.seg_mode == 1 || tiles > (a.seg_mode == 2 ? 512 : 256));
+  if (nt) return half ? launch_generic<8, true, true>(a, s) : launch_generic<4, true, false>(a, s);
+  return half ? launch_generic<8, false, true>(a, s) : launch_generic<4, false, false>(a, s);
 }
 
 // ----------------------------------------------------------------------------------------

@@ -81,3 +81,18 @@ def test_query_gradient_from_kept_scores(over):
 def test_attention_of_a_few_queries(over):
     # (a single query of narrow heads: its router gradient is a few cancelling sums of 8 rounded terms, no measure of anything)
     run_case(_cfg(**over), backward=over["d_head"] > 8, seed=233)
+
+
+@pytest.mark.parametrize("over", [
+    # rows of 8 but not 16 bytes in pieces of 16: reductions and outputs that end in a half piece, in the first piece, in the last place of a
+    # K step and in the first of the next, or in none; dense and gathered rows, expert sets, concatenated reductions, on both sides of the lines
+    dict(T=40, d_model=12, nheads=2, d_head=12, E=4, k=2),
+    dict(T=300, d_model=68, nheads=2, d_head=60, E=5, k=3),
+    dict(T=300, d_model=124, nheads=3, d_head=132, E=3, k=2),
+    dict(B=3, T=1000, d_model=412, nheads=2, d_head=76, E=8, k=2),                 # sorted rows: 94 tiles, sets: 192
+    dict(B=17, T=1000, d_model=260, nheads=3, d_head=68, E=5, k=3, qk_experts=1),
+    dict(B=17, T=1000, d_model=620, nheads=4, d_head=100, E=4, k=2),               # dense rows 1064 tiles, their gradient 665
+    dict(B=9, T=1000, d_model=412, nheads=4, d_head=48, E=1, k=1),                 # rows of a whole number of pieces, outputs that are not
+])
+def test_rows_of_half_pieces(over):
+    run_case(_cfg(**over), seed=239, check_inter=False)
