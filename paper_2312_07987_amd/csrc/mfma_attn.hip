@@ -363,9 +363,9 @@ __global__ __launch_bounds__(256 * NG, (DH <= 128 && NG == 1) ? 2 : 1) void mfma
 //   O^T[d][query] += V^T P^T    a lane's scores of the piece's two key blocks (keys 4 g .. 4 g + 3 of each) are its operand as they
 //                               are; V goes through the wave's own LDS and is read with transposing loads in that key order
 // The next piece's loads are requested as soon as this one's registers are free and travel during the softmax and the second
-// product.  The kernel above gives such a sequence one tile of 128 queries and walks it
-// in trips of 64 or 128 keys between barriers.  One query over 1000 keys, 32 (sequence, head) pairs of width 128: 28.2 -> 17.4 us, over
-// 4000 keys 86 -> 44 us (2.2 us a round of 256 keys).  Bound by reading K and V through one CU.
+// product.  The kernel above gives such a sequence one tile of 128 queries and walks it in trips of 64 or 128 keys between barriers.
+// One query over 1000 keys, 32 (sequence, head) pairs of width 128: 28.2 -> 17.4 us, over 4000 keys 86 -> 44 us (2.2 us a round of 256
+// keys).  Bound by reading K and V through one CU.
 // ----------------------------------------------------------------------------------------
 template <int DH, int VEC>
 __global__ __launch_bounds__(512, 1) void mfma_attn_few_kernel(AttnArgs a) {

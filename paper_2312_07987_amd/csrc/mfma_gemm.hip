@@ -66,7 +66,8 @@ typedef TileCfg<2, 2, 4, 2, 64, 1, 2> CfgMed;   // 256 x 128, wave tile 128 x 64
 
 // HALF: rows are multiples of 8 bytes only.  They are taken in pieces of 16 bytes all the same (a load wants no more than 4-byte
 // alignment): the last piece of a row of an odd number of half pieces is read 8 bytes early, so that nothing past the row is touched,
-// and moved into place on its way into LDS.
+// and moved into place on its way into LDS.  (96 columns of one segment: held to 128 registers, four work-groups per CU; 750 tiles of
+// a 412-wide reduction 28.7 -> 25.2 us.)
 template <class Cfg, int VEC, bool BNT, int TAG, int SEG, bool HALF = false>
 __global__ __launch_bounds__(256, HALF && SEG == 0 && Cfg::BN == 96 ? 4 : Cfg::MINB) void mfma_row_gemm_kernel(RowGemmArgs a) {
   static_assert(!HALF || VEC == 8, "a half piece is 8 bytes");
