@@ -14,20 +14,6 @@
 
 namespace sh {
 
-// 16 bytes at a multiple of 8
-typedef unsigned half_piece __attribute__((ext_vector_type(4), aligned(8)));
-__device__ __forceinline__ uint4 second_half(uint4 v) { return make_uint4(v.z, v.w, 0, 0); }
-__device__ __forceinline__ uint2 second_half(uint2 v) { return v; }   // (pieces of 8 bytes have none)
-template <int VEC, bool HALF>
-__device__ __forceinline__ typename Chunk<VEC>::type load_piece(const unsigned short* p) {
-  if constexpr (HALF) {
-    const half_piece v = *(const half_piece*)p;
-    return make_uint4(v.x, v.y, v.z, v.w);
-  } else {
-    return *(const typename Chunk<VEC>::type*)p;
-  }
-}
-
 // ----------------------------------------------------------------------------------------
 // Row GEMM.  4 waves per work-group arranged WM x WN, each wave owns MI x NJ MFMA blocks of
 // 32 x 32.  Two shapes of use:

@@ -85,7 +85,8 @@ def test_attention_of_a_few_queries(over):
 
 @pytest.mark.parametrize("over", [
     # rows of 8 but not 16 bytes in pieces of 16: reductions and outputs that end in a half piece, in the first piece, in the last place of a
-    # K step and in the first of the next, or in none; dense and gathered rows, expert sets, concatenated reductions, on both sides of the lines
+    # K step and in the first of the next, or in none; dense and gathered rows, expert sets, concatenated reductions, weight gradients, on both sides of
+    # the lines
     dict(T=40, d_model=12, nheads=2, d_head=12, E=4, k=2),
     dict(T=300, d_model=68, nheads=2, d_head=60, E=5, k=3),
     dict(T=300, d_model=124, nheads=3, d_head=132, E=3, k=2),
