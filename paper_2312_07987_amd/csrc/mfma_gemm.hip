@@ -54,7 +54,7 @@ typedef TileCfg<2, 2, 4, 2, 64, 1, 2> CfgMed;   // 256 x 128, wave tile 128 x 64
 // alignment): the last piece of a row of an odd number of half pieces is read 8 bytes early, so that nothing past the row is touched,
 // and moved into place on its way into LDS.  (96 columns of one segment: held to 128 registers, four work-groups per CU; 750 tiles of
 // a 412-wide reduction 28.7 -> 25.2 us.)
-template <class Cfg, int VEC, bool BNT, int TAG, int SEG, bool HALF = false>
+template <class Cfg, int VEC, bool HALF, bool BNT, int TAG, int SEG>
 __global__ __launch_bounds__(256, HALF && SEG == 0 && Cfg::BN == 96 ? 4 : Cfg::MINB) void mfma_row_gemm_kernel(RowGemmArgs a) {
   static_assert(!HALF || VEC == 8, "a half piece is 8 bytes");
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, MI = Cfg::MI, NJ = Cfg::NJ;
@@ -398,7 +398,7 @@ static void launch_cfg(const RowGemmArgs& a, hipStream_t s) {
     g = dim3(grid_windows((group_rows + Cfg::BM - 1) / Cfg::BM, a.heads * a.E * ncol));
   }
   const size_t lds = Cfg::lds_bytes(SEG == 1);
-  auto kern = mfma_row_gemm_kernel<Cfg, VEC, BNT, TAG, SEG, HALF>;
+  auto kern = mfma_row_gemm_kernel<Cfg, VEC, HALF, BNT, TAG, SEG>;
   if (lds > 64 * 1024) {
     static bool raised = false;   // per instantiation
     if (!raised) {
