@@ -689,16 +689,19 @@ __global__ __launch_bounds__(512, 4) void router_tile_kernel(RouterTileArgs a) {
     const double bound0 = 4.0 * 33 * 5.9604645e-8 * (double)(sqrtf(rs[t]) * 1.0001f) * (double)(sqrtf(wn) * 1.0001f);
     bool flag = false;
     if (E <= 8) {
-      // every pair in registers; decided: no other logit close to a selected one
+      // every pair in registers; decided: no other logit close to a selected one, and every logit finite (with a NaN the pairs are no
+      // order: 1, NaN, 2 gives every expert rank 1, and nothing would be written for rank 0)
       double v[8];
       int rank[8], near[8];
-      double top = 0.0;
+      double top = 0.0, finite = 0.0;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         v[e] = zi[min(e, E - 1)];
         top = fmax(top, fabs(v[e]));
+        finite = fma(v[e], 0.0, finite);   // stays 0, or a NaN from the first infinity or NaN on
         rank[e] = near[e] = 0;
       }
+      flag = finite != 0.0;   // (the second stage writes every place)
       const double gap = 2.0 * (bound0 + 1e-13 * (top + 1.0));
 #pragma unroll
       for (int e = 1; e < 8; ++e)
@@ -706,7 +709,7 @@ __global__ __launch_bounds__(512, 4) void router_tile_kernel(RouterTileArgs a) {
 #pragma unroll
           for (int f = 0; f < e; ++f) {
             const double d = v[e] - v[f];
-            const int c = !(fabs(d) > gap), later = d > 0.0;   // (a NaN counts as close)
+            const int c = !(fabs(d) > gap), later = d > 0.0;
             rank[f] += later;
             rank[e] += 1 - later;
             near[e] |= c;

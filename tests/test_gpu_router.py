@@ -60,3 +60,58 @@ def test_routing_tables(over, shared, ties):
             assert np.array_equal(perm[h], want[0]), (side, h)
             assert np.array_equal(r["offsets"]["SD".index(side)][h], want[1]), (side, h)
     assert np.isfinite(layer.outputs()).all()
+
+
+def _first_of_the_largest(z, nheads, k):
+    """k passes of "largest remaining logit, the lowest index on ties", where nothing is larger than a NaN that a pass begins with."""
+    N, E = z.shape[0], z.shape[1] // nheads
+    idx = np.zeros((nheads, N, k), np.int32)
+    for h in range(nheads):
+        for n in range(N):
+            left = list(range(E))
+            for j in range(k):
+                best = left[0]
+                for e in left[1:]:
+                    if z[n, h * E + e] > z[n, h * E + best]:
+                        best = e
+                left.remove(best)
+                idx[h, n, j] = best
+    return idx
+
+
+@pytest.mark.parametrize("E, k, columns, bias", [
+    (3, 1, (1,), {}),                                    # 1, NaN, 2: every expert goes before one other
+    (5, 1, (1,), {}),
+    (8, 2, (1, 4), {}),
+    (4, 2, (), {1: np.nan}),
+    (5, 3, (), {0: np.inf, 3: np.inf, 4: -np.inf}),      # equal infinities
+    (9, 2, (0, 5), {}),
+    (12, 3, (), {2: np.nan, 7: np.inf}),
+])
+def test_logits_that_are_not_finite(E, k, columns, bias):
+    """NaNs in a router's columns or bias, in tokens, infinities, logits that only fp32 cannot hold: every choice is still one of the
+    experts, that of the serial rule, and the permutation is one."""
+    from paper_2312_07987_amd.runner import DeviceLayer
+    cfg = dict(name="router", dtype="bf16", B=1, T=75, d_model=68, nheads=3 if E < 9 else 2, d_head=8, E=E, k=k, causal=1, bias0=0.0)
+    print("case", cfg, columns, bias, flush=True)
+    H = cfg["nheads"]
+    t = make_inputs(cfg, seed=47 + E)
+    t["x"], t["W_S"] = t["x"].copy(), t["W_S"].copy()
+    for c in columns:
+        t["W_S"][9, E + c] = np.nan
+    t["b_S"] = np.zeros(H * E, np.float32)
+    for c, v in bias.items():
+        t["b_S"][E + c] = v
+    t["x"][0, 40] = np.nan
+    t["x"][0, 41, ::2] = np.inf
+    t["x"][0, 42] *= np.float32(2.0 ** 126)   # the sum of its squares is past the largest fp32
+    layer = DeviceLayer(cfg, t)
+    layer.forward()
+    r = layer.routing()
+    with np.errstate(all="ignore"):
+        for side, W, b in ((0, "W_S", "b_S"), (1, "W_D", "b_D")):
+            want = _first_of_the_largest(orc.router_logits(t["x"][0].astype(np.float64), t[W], t[b]), H, k)
+            assert np.array_equal(r["idx"][side], want), side
+            for h in range(H):
+                perm, offsets = orc.routing_tables(want[h], E)[:2]
+                assert np.array_equal(r["perm"][side][h], perm) and np.array_equal(r["offsets"][side][h], offsets), (side, h)
