@@ -97,10 +97,11 @@ __global__ __launch_bounds__(256, 2) void skinny_row_gemm_kernel(RowGemmArgs a) 
 
 // ----------------------------------------------------------------------------------------
 // Output experts of calls of a few rows: y[n] = sum over every (head, expert) segment of gate * ctx[n, h] W_O[h, e] in one accumulator
-// (segment mode 3, gates from the top-k tables, 0 for an expert that a token did not select).  32 x 32 tiles, token-ordered rows, the
-// reduction shared out among the waves in pieces of a head and 64 indices.  By expert sets the same
+// (segment mode 3, gates from the top-k tables).  32 x 32 tiles, token-ordered rows, the reduction shared out among the waves in pieces
+// of a head and 64 indices.  A piece's product is an fp32 accumulator of its own that the gates multiply on its way into the sum: nothing
+// is rounded before the end, and what an expert gives a token that did not select it (an infinity, a NaN) is left out.  By expert sets the same
 // call was a launch of 128 x 128 tiles over the k selected experts of each head, a bf16 partial sum per head, and another launch to add
-// them.
+// them; by expert-sorted rows fp32 atomics, with launches to clear the accumulator and to cast it.
 // ----------------------------------------------------------------------------------------
 template <int VEC>
 __device__ __forceinline__ uint4 sk_load8(const unsigned short* row, int k, int end) {   // row[k .. k + 7], zeros from `end` on (end >= VEC)
@@ -117,21 +118,21 @@ template <int VEC>
 __global__ __launch_bounds__(512, 1) void skinny_concat_kernel(RowGemmArgs a) {
   constexpr int W = 8, UK = 64, EB = 5;
   __shared__ __attribute__((aligned(16))) unsigned short bs[W][UK * SK_T];   // then the partial sums [W][32][32] fp32
-  __shared__ float gts[SK_T * MAX_SEGD];   // the tile's dense gates [row][head * experts + expert]
+  __shared__ __attribute__((aligned(16))) float gts[MAX_SEGD * SK_T];   // the tile's gates [head * experts + expert][row], -1: not selected
   __shared__ SegDesc descs[MAX_SEGD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
   const int row0 = blockIdx.x * SK_T, n0 = blockIdx.y * SK_T;
   const int rows = min(a.M - row0, SK_T);
   if (tid < a.nseg) descs[tid] = a.segd[tid];
-  for (int t = tid; t < SK_T * MAX_SEGD; t += 512) gts[t] = 0.f;
+  for (int t = tid; t < a.nseg * SK_T; t += 512) gts[t] = a.gidx ? -1.f : 1.f;   // (no tables: every segment counts)
   __syncthreads();
   if (a.gidx) {
     for (int t = tid; t < SK_T * a.gheads * a.gk; t += 512) {
       const int row = t % SK_T, j = t / SK_T % a.gk, h = t / SK_T / a.gk;
       if (row < rows) {
         const long o = ((long)h * a.M + row0 + row) * a.gk + j;
-        gts[row * MAX_SEGD + h * a.experts + a.gidx[o]] = a.ggate[o];
+        gts[(h * a.experts + a.gidx[o]) * SK_T + row] = a.ggate[o];
       }
     }
     __syncthreads();
@@ -162,8 +163,9 @@ __global__ __launch_bounds__(512, 1) void skinny_concat_kernel(RowGemmArgs a) {
 #pragma unroll
     for (int u = 0; u < EB; ++u)
       if (u < ne) {
-        const int gcol = descs[h * E + e0 + u].gcol;
-        const float gt = gcol >= 0 ? gts[r * MAX_SEGD + gcol] : 1.f;
+        f32x16 prod;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) prod[q] = 0.f;
         wave_order();   // (the area is the wave's own and a wave's LDS operations keep their order)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -171,10 +173,14 @@ __global__ __launch_bounds__(512, 1) void skinny_concat_kernel(RowGemmArgs a) {
         wave_order();
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (k0 + 16 * i < a.K) {   // uniform
-            const uint4 f = gcol >= 0 ? scale_chunk(fa[i], gt) : fa[i];
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f), frag_transposed(bs[wave], SK_T, 16 * i + 8 * g, 0, lane), acc, 0, 0, 0);
-          }
+          if (k0 + 16 * i < a.K)   // uniform
+            prod = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[i]), frag_transposed(bs[wave], SK_T, 16 * i + 8 * g, 0, lane), prod, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 gt = *(const f32x4*)(&gts[(h * E + e0 + u) * SK_T + 8 * i + 4 * g]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[4 * i + q] = gt[q] < 0.f ? acc[4 * i + q] : fmaf(gt[q], prod[4 * i + q], acc[4 * i + q]);
+        }
       }
   }
   __syncthreads();
@@ -191,18 +197,6 @@ __global__ __launch_bounds__(512, 1) void skinny_concat_kernel(RowGemmArgs a) {
     s[0] = w ? s[0] + v.x : v.x;
     s[1] = w ? s[1] + v.y : v.y;
   }
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-    if (s[u] != s[u]) {
-      // (zero times an infinity or NaN of an expert that the token did not select: once more from the selected experts alone)
-      s[u] = 0.f;
-      for (int p = 0; p < a.nseg && s[u] == s[u]; ++p) {
-        const float gt = descs[p].gcol >= 0 ? gts[row * MAX_SEGD + descs[p].gcol] : 1.f;
-        if (gt == 0.f) continue;
-        const unsigned short *Ap = (const unsigned short*)descs[p].A + (long)(row0 + row) * a.lda, *Bp = (const unsigned short*)descs[p].B + n + u;
-        for (int k = 0; k < a.K; ++k) s[u] = fmaf(bf16_to_f32(f32_to_bf16(bf16_to_f32(Ap[k]) * gt)), bf16_to_f32(Bp[(long)k * a.sbk]), s[u]);
-      }
-    }
   *(unsigned*)((unsigned short*)a.C + (long)(row0 + row) * a.ldc + n) = pack_bf16x2(s[0], s[1]);
 }
 

@@ -113,6 +113,34 @@ def test_gates_scale_fp32_results_where_there_are_too_many_sets():
     assert {"fwd.y_cast", "bwd.v_dgrad"} <= got and "bwd.dx_gemm" not in got, got
 
 
+@pytest.mark.parametrize("over, dense", [
+    (dict(T=128, d_model=1024, nheads=4, d_head=128, E=10, k=5), False),     # 252 sets
+    (dict(T=101, d_model=412, nheads=2, d_head=76, E=5, k=3), False),        # rows that make no set tables
+    (dict(T=100, d_model=1024, nheads=4, d_head=128, E=5, k=3), False),      # sets
+    (dict(T=60, T_q=33, d_model=132, nheads=3, d_head=36, E=3, k=2), False),
+    (dict(T=50, d_model=256, nheads=4, d_head=80, E=1, k=1), True),
+])
+def test_output_experts_of_a_few_rows_round_once(over, dense):
+    """y from the layer's own read-outs and gates: gates on fp32 products, one fp32 sum over heads and experts, so the error is that of
+    rounding the result to bf16 and no more (fp32 sums add 1e-6; a rounding of gate x read-out alone would make it 1.4 times that)."""
+    cfg = _cfg(B=1, **over)
+    t = make_inputs(cfg, seed=113)
+    layer = _layer(cfg, t, dense)
+    assert not _steps(layer) & {"fwd.y_sum", "fwd.y_zero", "fwd.y_cast"}
+    ctx, r = layer.intermediates()["ctx"].astype(np.float64), layer.routing()
+    idx, gate = (r["idx_D"], r["gate_D"]) if "idx_D" in r else (r["idx"][1], r["gate"][1])
+    want = np.zeros((ctx.shape[0], cfg["d_model"]))
+    for h in range(cfg["nheads"]):
+        for j in range(cfg["k"]):
+            for e in range(cfg["E"]):
+                n = np.nonzero(idx[h, :, j] == e)[0]
+                want[n] += gate[h, n, j, None].astype(np.float64) * (ctx[n, h] @ t["W_O"][h, e].astype(np.float64))
+    rel = lambda v: float(np.sqrt(np.sum((v - want) ** 2) / np.sum(want ** 2)))
+    e, once = rel(layer.outputs().reshape(want.shape)), rel(round_to_bf16(want.astype(np.float32)))
+    print("  relative error %.3e, of the rounding alone %.3e" % (e, once), flush=True)
+    assert e < 1.05 * once
+
+
 def _poison_one(t, n, h, e, i, j):
     t[n] = t[n].copy()
     t[n][h, e, i, j] = np.inf
@@ -122,6 +150,8 @@ def _poison_one(t, n, h, e, i, j):
 @pytest.mark.parametrize("over, shared", [
     (dict(dtype="f32", B=2, T=70, d_model=50, nheads=2, d_head=20, E=4, k=2), False),
     (dict(dtype="f32", B=2, T=70, d_model=412, nheads=2, d_head=76, E=5, k=3, T_q=41), False),
+    (dict(B=1, T=70, d_model=412, nheads=2, d_head=76, E=5, k=3), False),                # a few rows, of 8 bytes
+    (dict(B=1, T=100, d_model=1024, nheads=4, d_head=128, E=5, k=3), False),             # ... and of 16
     (dict(B=5, T=1161, d_model=2048, nheads=2, d_head=64, E=3, k=2), False),             # a last tile of 173 rows
     (dict(B=5, T=1160, T_q=1000, d_model=2048, nheads=2, d_head=64, E=3, k=2), True),    # two token sets
     (dict(B=5, T=1161, d_model=2048, nheads=2, d_head=64, E=3, k=2, qk_experts=1), False),
