@@ -414,8 +414,8 @@ void launch_pp_row_gemm(const RowGemmArgs& a, hipStream_t s);
 // 32 x 32 tiles for launches of a few rows (mfma_skinny.hip); launch_mfma_row_gemm routes to it
 bool skinny_row_gemm_supported(const RowGemmArgs& a);
 void launch_skinny_row_gemm(const RowGemmArgs& a, hipStream_t s);
-// ... and segment mode 3 with the gates from the top-k tables
-bool skinny_concat_supported(const RowGemmArgs& a);
+// ... and segment mode 3 with the gates from the top-k tables; sets: the call could run by expert sets instead
+bool skinny_concat_supported(const RowGemmArgs& a, bool sets);
 void launch_skinny_concat(const RowGemmArgs& a, hipStream_t s);
 bool mfma_wgrad_supported(const WgradArgs& a);
 void launch_mfma_wgrad(const WgradArgs& a, hipStream_t s);

@@ -1036,7 +1036,7 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     a.nseg = H * E;
     for (int s_ = 0; s_ < H * E; ++s_)
       a.segd[s_] = {c.p<bf16_t>(c.L.ctx) + (size_t)(s_ / E) * dh, (const bf16_t*)W_O + (size_t)s_ * dh * dm, c.dense ? -1 : s_, 0, 0, 0};
-    if (skinny_concat_supported(a)) {
+    if (skinny_concat_supported(a, sets)) {
       prof_mark(c.st, "fwd.o_experts");
       launch_skinny_concat(a, c.st);
       y_done = true;

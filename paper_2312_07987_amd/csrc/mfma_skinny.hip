@@ -231,16 +231,26 @@ static int sk_concat_vec(const RowGemmArgs& a) {
   return 0;
 }
 
-// One tile for each CU (8 of 1024 columns each: 256 tokens), two where a tile's reduction is short.  us, by expert sets with the sum of the
-// heads / here: d_model 1024, 4 heads of 128, 3 of 5 experts, 1 token 22.0 / 12.3, 128 24.1 / 18.1, 256 24.8 / 18.1, 384 24.6 / 25.8;
-// 2 of 8 experts, 256 tokens 31.1 / 22.1, 384 31.3 / 32.7; d_model 412, 2 heads of 76, 3 of 5 experts, 512 tokens (208 tiles) 21.9 / 11.3, 1024 (416)
-// 22.8 / 17.9, 1536 (624) 22.9 / 24.7; 20 dense heads of 80, 256 tokens 24.0 / 14.4.
-bool skinny_concat_supported(const RowGemmArgs& a) {
+// One tile for each CU (8 of 1024 columns each: 256 tokens), two where a tile's reduction is short and there is more than one head.
+// Every expert is multiplied, selected or not, so there is a line in the pieces of a tile (of 64 indices), too.  us, the other path / here:
+//   `sets`, expert sets with the sum of the heads: d_model 1024, 4 heads of 128, 3 of 5 experts, 1 token 20.8 / 12.1, 256 23.7 / 18.2, 500
+//   24.5 / 25.5; 2 of 8, 256 tokens 30.1 / 23.5, 500 30.9 / 34.6; 1 of 8 (64 pieces, 8 needed), 16 tokens 17.3 / 19.3, 100 17.5 / 23.7; 2 heads, 1 of
+//   32, 16 tokens 18.0 / 34.4; d_model 412, 2 heads of 76, 3 of 5 experts, 500 tokens (208 tiles) 20.0 / 10.9, 1000 (416) 20.5 / 17.4, 1600
+//   (650) 21.2 / 24.1; 8 heads of 256, 4 of 8 (256 pieces), 1 token 34.3 / 60.3.
+//   One head has no sum: 1 of 64 experts of 128, 100 tokens 11.8 / 40.8; 1 of 5, 500 tokens (512 tiles) 10.5 / 13.9.
+//   Expert-sorted rows (more sets than the tables hold, or rows that make none) cost launches to clear and to cast, and more with every
+//   row: 4 heads of 128, 4 of 16 experts (128 pieces), 1 token 30.3 / 33.9, 16 54.4 / 33.7, 256 77.7 / 38.4.
+// Over 2401 shapes that lie on both sides of these lines, 21 that come here lose more than 2 per cent (the worst 4.2 us), 38 us in all
+// of 43760; without the lines in pieces 421 of them, 4517 us.
+bool skinny_concat_supported(const RowGemmArgs& a, bool sets) {
   if (a.seg_mode != 3 || a.perm || a.heads != 1 || a.E != 1 || a.mode != STORE_T || a.sbn != 1 || a.M < 1 || a.gtab || a.seg_q) return false;
   // (segment h * experts + e: expert e of head h, the head's read-out the same for all of them)
   if (a.nseg < 1 || a.nseg > MAX_SEGD || a.gheads * a.experts != a.nseg) return false;
   const long tiles = (long)((a.M + SK_T - 1) / SK_T) * ((a.Nc + SK_T - 1) / SK_T);
-  return tiles <= ((long)a.nseg * a.K <= 1024 ? 512 : 256) && sk_concat_vec(a) != 0;
+  if (tiles > ((long)a.nseg * a.K <= 1024 && !(sets && a.gheads == 1) ? 512 : 256) || sk_concat_vec(a) == 0) return false;
+  const int per = (a.K + 63) / 64, pieces = a.nseg * per, needed = a.gheads * a.gk * per;
+  if (!sets) return pieces <= 128 && pieces <= 64 + 4l * a.M;
+  return a.gheads == 1 ? pieces <= 4 * needed : pieces <= 112 && pieces <= 32 + 2 * needed;
 }
 
 void launch_skinny_concat(const RowGemmArgs& a, hipStream_t s) {
