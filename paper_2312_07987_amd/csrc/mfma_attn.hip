@@ -1140,13 +1140,16 @@ static void launch_dh(const AttnArgs* f, const AttnBwdArgs* bw, hipStream_t s) {
     // 640 keys 23.6 / 24.1 with 240, but 22.2 / 20.8 with 32).
     const int queries = f->Tq > 0 ? f->Tq : f->T;
     const int keys_from = DH > 96 ? 320 : 256, groups_to = DH > 96 && (f->T < 512 || queries < 128) ? 128 : 256;
-    // At most 16 queries per sequence: a work-group per (sequence, head) that reads only the rows there are, if these work-groups run in
-    // one round or have 256 keys each.  Tiles of 128 queries / this one, us: one query per sequence, heads of 128 over 1000 keys
-    // 28.2 / 17.4 with 32 work-groups, over 4000 86.4 / 44.3 with 16, over 64 7.9 / 7.0 with 32; in more than one round, of 76 over 1000
-    // keys 40.7 / 38.1 with 320, of 100 over 200 19.9 / 17.7 (16 queries 20.9 / 22.2) with 512, over 128 14.0 / 14.5 and over 64 9.7 / 11.2
-    // with 288: there two work-groups of the other kernel share a CU.
+    // At most 16 queries per sequence: a work-group per (sequence, head) that reads only the rows there are.  Tiles of 128 queries / this
+    // one, us.  Work-groups that run in one round: one query per sequence, heads of 128 over 1000 keys 28.2 / 17.4 with 32, over 4000 86.4 /
+    // 44.3 with 16, over 64 7.9 / 7.0 with 32.  In more than one round two work-groups of the other kernel share a CU.  From 1024 keys on
+    // it splits them over two wave groups and has the CU to itself: 512 work-groups of 128 over 1500 keys 0.86 of its time, 1024 of 76 over 3000 0.90.
+    // From 256 keys on heads of at most 96 with 16-byte rows (1024 of 96 over 256 keys and 16 queries 0.93, 1024 of 64 0.71), but not wider
+    // ones or 8-byte rows, at 16 queries (1024 of 112 over 256 34.4 / 37.1, 1024 of 128 over 512 77.5 / 82.9, 512 of 76 over 256 17.7 / 18.8).
+    // Fewer keys are mixed: 512 of 100 over 200 19.9 / 17.7 (16 queries 20.9 / 22.2), 288 over 128 14.0 / 14.5, over 64 9.7 / 11.2.
     if constexpr (DH <= 128) {
-      if (queries <= 16 && ((int)g.x <= 256 || f->T >= 256)) {
+      const bool narrow = DH <= 64 || (DH <= 96 && attn_vec(f->dh) == 8);
+      if (queries <= 16 && ((int)g.x <= 256 || f->T >= (narrow ? 256 : 1024))) {
         const dim3 gf(f->H * f->B);
         if (attn_vec(f->dh) == 8)
           mfma_attn_few_kernel<DH, 8><<<gf, 512, 0, s>>>(*f);

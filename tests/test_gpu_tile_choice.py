@@ -82,6 +82,8 @@ def test_query_gradient_from_kept_scores(over):
     dict(T=300, T_q=17, d_model=72, nheads=2, d_head=64, E=3, k=2),
     dict(B=129, T=70, T_q=3, d_model=64, nheads=2, d_head=64, E=3, k=2),
     dict(B=129, T=256, T_q=3, d_model=64, nheads=2, d_head=64, E=3, k=2),   # (and enough of them)
+    dict(B=129, T=300, T_q=16, d_model=64, nheads=2, d_head=76, E=3, k=2),
+    dict(B=65, T=1030, T_q=2, d_model=64, nheads=4, d_head=100, E=3, k=2),  # (and enough of them)
 ])
 def test_attention_of_a_few_queries(over):
     # (a single query of narrow heads: its router gradient is a few cancelling sums of 8 rounded terms, no measure of anything)
