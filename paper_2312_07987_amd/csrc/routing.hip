@@ -125,47 +125,6 @@ __global__ __launch_bounds__(256) void router_select_kernel(const T* __restrict_
   for (int c = tid; c < ncols; c += 256) cnt[((long)(side * H + h0) * E + c) * ncb + blockIdx.x] = cn[c];
 }
 
-// One block per (side, head).  blockcnt[sh][e][blk] (counts) -> in place: first position of
-// bin e for token block blk; offsets[sh][0..E].  One wave per bin, lanes over token blocks.
-__device__ __forceinline__ void scan_body(int* __restrict__ blockcnt, int* __restrict__ offsets, int E, int nblk) {
-  __shared__ int tot[129];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int e = wave; e < E; e += 4) {
-    int sum = 0;
-    for (int b = lane; b < nblk; b += 64) sum += blockcnt[(long)e * nblk + b];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if (lane == 0) tot[e] = sum;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int i = 0; i < E; ++i) {
-      int t = tot[i];
-      tot[i] = run;
-      run += t;
-    }
-    tot[E] = run;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i <= E; i += 256) offsets[i] = tot[i];
-  for (int e = wave; e < E; e += 4) {
-    int run = tot[e];
-    for (int b0 = 0; b0 < nblk; b0 += 64) {
-      const int b = b0 + lane;
-      const int v = b < nblk ? blockcnt[(long)e * nblk + b] : 0;
-      int inc = v;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        int u = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += u;
-      }
-      if (b < nblk) blockcnt[(long)e * nblk + b] = run + inc - v;
-      run += __shfl(inc, 63, 64);
-    }
-  }
-}
-
 // sum over the 16 lanes of a row (rotations inside the row)
 __device__ __forceinline__ int row_sum(int v) {
   v += __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, false);
@@ -174,39 +133,14 @@ __device__ __forceinline__ int row_sum(int v) {
   return v + __builtin_amdgcn_mov_dpp(v, 0x121, 0xf, 0xf, false);
 }
 
-// What scan_body would leave for this token block, computed by the block itself from the raw counts
-// cnt[bin][count block] (for tables small enough that every block can read them whole): sbase[bin] = first
-// position of bin `bin` for token block blockIdx.x, which holds the count blocks from blockIdx.x * per on; token block 0
-// also writes offsets[0..nbins].  16 lanes per bin, sixteen loads in flight.  Called by all RB threads; ends with a barrier.
-__device__ __forceinline__ void block_bases(const int* __restrict__ cnt, int* __restrict__ offsets, int nbins, int ncb, int per,
-                                            int* __restrict__ sbase /* LDS [2 * 128 + 1] */) {
-  const int first = blockIdx.x * per;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int* tot = sbase + 128;
-  for (int e0 = 0; e0 < nbins; e0 += RB / 16) {
-    const int e = e0 + (threadIdx.x >> 4);
-    const int* c = cnt + (long)min(e, nbins - 1) * ncb;
-    int all = 0, pre = 0;
-    for (int b0 = lane & 15; b0 - (lane & 15) < ncb; b0 += 256) {
-      int v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = c[min(b0 + 16 * u, ncb - 1)];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int b = b0 + 16 * u;
-        all += b < ncb ? v[u] : 0;
-        pre += b < first ? v[u] : 0;   // (first < ncb)
-      }
-    }
-    all = row_sum(all);
-    pre = row_sum(pre);
-    if ((lane & 15) == 0 && e < nbins) {
-      tot[e] = all;
-      sbase[e] = pre;
-    }
-  }
+// Starts of the bins in LDS: sbase[bin] becomes the first position of bin `bin` for token block blockIdx.x.
+//   in: sbase[bin] the bin's count in the token blocks before this one, sbase[128 + bin] in all.  Token block 0 also writes
+// offsets[0..nbins].  Called by all RB threads (at most 128 bins); barriers on both sides.
+__device__ __forceinline__ void add_bin_starts(int* __restrict__ offsets, int nbins, int* __restrict__ sbase /* LDS [2 * 128] */) {
+  const int* tot = sbase + 128;
+  const int lane = threadIdx.x & 63;
   __syncthreads();
-  if (wave == 0) {   // exclusive sum over the bins (at most 128)
+  if (threadIdx.x < 64) {   // exclusive sum over the bins
     const int v0 = lane < nbins ? tot[lane] : 0, v1 = lane + 64 < nbins ? tot[lane + 64] : 0;
     int p0 = v0, p1 = v1;
     for (int o = 1; o < 64 && o < nbins; o <<= 1) {
@@ -230,13 +164,57 @@ __device__ __forceinline__ void block_bases(const int* __restrict__ cnt, int* __
   __syncthreads();
 }
 
-// The waves' counts of a token block become their first positions.  base[e * stride]: the block's.  Called by all threads; barriers
+// The same from the raw counts cnt[bin][count block] (for tables small enough that every block can read them whole): this token block
+// holds the count blocks from blockIdx.x * per on.  16 lanes per bin, sixteen loads in flight.
+__device__ __forceinline__ void block_bases(const int* __restrict__ cnt, int* __restrict__ offsets, int nbins, int ncb, int per,
+                                            int* __restrict__ sbase) {
+  const int first = blockIdx.x * per;
+  const int lane = threadIdx.x & 63;
+  int* tot = sbase + 128;
+  for (int e0 = 0; e0 < nbins; e0 += RB / 16) {
+    const int e = e0 + (threadIdx.x >> 4);
+    const int* c = cnt + (long)min(e, nbins - 1) * ncb;
+    int all = 0, pre = 0;
+    for (int b0 = lane & 15; b0 - (lane & 15) < ncb; b0 += 256) {
+      int v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = c[min(b0 + 16 * u, ncb - 1)];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int b = b0 + 16 * u;
+        all += b < ncb ? v[u] : 0;
+        pre += b < first ? v[u] : 0;   // (first < ncb)
+      }
+    }
+    all = row_sum(all);
+    pre = row_sum(pre);
+    if ((lane & 15) == 0 && e < nbins) {
+      tot[e] = all;
+      sbase[e] = pre;
+    }
+  }
+  add_bin_starts(offsets, nbins, sbase);
+}
+
+// ... and from the sums that scan_kernel left
+__device__ __forceinline__ void stored_bases(const int* __restrict__ cnt, int* __restrict__ offsets, int nbins, int ncb, int per,
+                                             int* __restrict__ sbase) {
+  const int first = blockIdx.x * per;
+  for (int e = threadIdx.x; e < nbins; e += RB) {
+    const int* c = cnt + (long)e * ncb;
+    sbase[128 + e] = c[0];
+    sbase[e] = first ? c[first] : 0;
+  }
+  add_bin_starts(offsets, nbins, sbase);
+}
+
+// The waves' counts of a token block become their first positions.  base[e]: the block's.  Called by all threads; barriers
 // on both sides.
 template <int BINS>
-__device__ __forceinline__ void wave_bases(int (&wcnt)[RB / 64][BINS], const int* base, long stride, int nbins) {
+__device__ __forceinline__ void wave_bases(int (&wcnt)[RB / 64][BINS], const int* base, int nbins) {
   __syncthreads();
   for (int e = threadIdx.x; e < nbins; e += RB) {
-    int run = base[e * stride];
+    int run = base[e];
 #pragma unroll
     for (int w = 0; w < RB / 64; ++w) {
       const int v = wcnt[w][e];
@@ -988,18 +966,18 @@ struct SortArgs {
   int per;                     // count blocks per block of RB tokens
   int experts;                 // 0: the sets alone
 };
-// LOCAL: the block finds its first positions from the raw counts, else they are in the tables already (scan_kernel).  Everything a
-// block reads is requested before it waits: one trip to memory.
+// LOCAL: the block finds its first positions from the raw counts, else from their sums (scan_kernel).  Everything a block reads is requested before it
+// waits: one trip to memory.
 template <bool LOCAL>
 __device__ __forceinline__ void sort_body(const SortArgs& a) {
-  __shared__ int sb[2 * 128 + 1];
+  __shared__ int sb[2 * 128];
   __shared__ int wcnt[RB / 64][128];
   const int side = blockIdx.z % a.sides, sets = (int)blockIdx.z >= a.sides || !a.experts;
   const int h = blockIdx.y, N = a.N[side], ncb = a.ncb[side], first = blockIdx.x * a.per, k = a.k;
   if (first >= ncb) return;
   const long at = (long)side * a.H * a.N[0] + (long)h * N, sh_ = side * a.H + h;
   const int nbins = sets ? a.t.nsets : a.E;
-  int* c = (sets ? a.t.blockcnt : a.cnt) + ((long)side * a.H * a.ncb[0] + (long)h * ncb) * nbins;
+  const int* c = (sets ? a.t.blockcnt : a.cnt) + ((long)side * a.H * a.ncb[0] + (long)h * ncb) * nbins;
   int* offsets = sets ? a.t.setoff + sh_ * (nbins + 1) : a.offsets + sh_ * (nbins + 1);
   const int n = blockIdx.x * RB + threadIdx.x, nc = min(n, N - 1);
   const bool valid = n < N;
@@ -1011,7 +989,7 @@ __device__ __forceinline__ void sort_body(const SortArgs& a) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) gv[j] = a.t.gset[(at + nc) * k + min(j, k - 1)];
     for (int t = threadIdx.x; t < RB / 64 * 128; t += RB) (&wcnt[0][0])[t] = 0;
-    if constexpr (LOCAL) block_bases(c, offsets, nbins, ncb, a.per, sb);
+    LOCAL ? block_bases(c, offsets, nbins, ncb, a.per, sb) : stored_bases(c, offsets, nbins, ncb, a.per, sb);
     // the rank among the wave's tokens of the same set: the lanes whose set id agrees with one's own in every bit
     unsigned long long same = __ballot(valid);
     for (int bit = 0; (1 << bit) < nbins; ++bit) {
@@ -1019,9 +997,8 @@ __device__ __forceinline__ void sort_body(const SortArgs& a) {
       same &= (sid >> bit) & 1 ? bal : ~bal;
     }
     const int rk = __popcll(same & lt);
-    if constexpr (!LOCAL) __syncthreads();
     if (valid && rk == 0) wcnt[wave][sid] = __popcll(same);
-    wave_bases(wcnt, LOCAL ? sb : c + first, LOCAL ? 1 : ncb, nbins);
+    wave_bases(wcnt, sb, nbins);
     if (!valid) return;
     const int pos = rk + wcnt[wave][sid];
     a.t.setperm[at + pos] = n;
@@ -1033,7 +1010,7 @@ __device__ __forceinline__ void sort_body(const SortArgs& a) {
   int ej[8], rk[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) ej[j] = a.idx[(at + nc) * k + min(j, k - 1)];
-  if constexpr (LOCAL) block_bases(c, offsets, nbins, ncb, a.per, sb);
+  LOCAL ? block_bases(c, offsets, nbins, ncb, a.per, sb) : stored_bases(c, offsets, nbins, ncb, a.per, sb);
   unsigned long long sel = 0ull;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -1049,26 +1026,54 @@ __device__ __forceinline__ void sort_body(const SortArgs& a) {
       if (ej[j] == e) rk[j] = r;
     if (lane == 0) wcnt[wave][e] = __popcll(bal);
   }
-  wave_bases(wcnt, LOCAL ? sb : c + first, LOCAL ? 1 : ncb, nbins);
+  wave_bases(wcnt, sb, nbins);
 #pragma unroll
   for (int j = 0; j < 8; ++j)
     if (ej[j] >= 0) a.perm[at * k + rk[j] + wcnt[wave][ej[j]]] = n * k + j;
 }
 __global__ __launch_bounds__(RB) void scan_scatter_kernel(SortArgs a) { sort_body<true>(a); }
 __global__ __launch_bounds__(RB) void scatter_kernel(SortArgs a) { sort_body<false>(a); }
-// one block per (side, head) and table
+// Running sums of the counts of a bin, a wave per bin of either table: the count of every block becomes the sum of those before it.  The first place,
+// where that is 0, takes the sum of all.
+// (A work-group per (side, head) and table for all of its bins, 64 counts a step: router and sorts of 3 x 126 sets, 16384 tokens 245 -> 81 us, 104000
+// 1361 -> 333; 3 x 70 sets, 32768 tokens 261 -> 77; fp32, 64 experts, 65536 tokens 483 -> 161.)
 __global__ __launch_bounds__(256) void scan_kernel(SortArgs a) {
-  const int side = blockIdx.y, h = blockIdx.x, ncb = a.ncb[side], sets = blockIdx.z || !a.experts;
-  const long cat = (long)side * a.H * a.ncb[0] + (long)h * ncb, sh_ = side * a.H + h;
-  if (sets)
-    scan_body(a.t.blockcnt + cat * a.t.nsets, a.t.setoff + sh_ * (a.t.nsets + 1), a.t.nsets, ncb);
-  else
-    scan_body(a.cnt + cat * a.E, a.offsets + sh_ * (a.E + 1), a.E, ncb);
+  const int side = blockIdx.y, h = blockIdx.x, ncb = a.ncb[side], lane = threadIdx.x & 63;
+  const int bin = blockIdx.z * 4 + (threadIdx.x >> 6), ne = a.experts ? a.E : 0;
+  if (bin >= ne + a.t.nsets) return;
+  const long at = (long)side * a.H * a.ncb[0] + (long)h * ncb;
+  int* c = bin < ne ? a.cnt + at * a.E + (long)bin * ncb : a.t.blockcnt + at * a.t.nsets + (long)(bin - ne) * ncb;
+  int run = 0;
+  for (int b0 = 0; b0 < ncb; b0 += 64 * 16) {
+    const int b = b0 + lane * 16;
+    int v[16], sum = 0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = c[min(b + u, ncb - 1)];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) sum += b + u < ncb ? v[u] : 0;
+    int inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += t;
+    }
+    int pre = run + inc - sum;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (b + u < ncb && b + u > 0) c[b + u] = pre;
+      pre += v[u];
+    }
+    run += __shfl(inc, 63, 64);
+  }
+  if (lane == 0) c[0] = run;
 }
 
-// Tables of up to SCAN_MAX counts per (side, head) are scanned by every scatter block for itself, one launch instead of two.
+// Tables of up to SCAN_MAX counts per (side, head) are scanned by every scatter block for itself, one launch instead of two; what a block
+// reads then grows with the tokens, and all blocks' with their square.  Router and sorts, us, with the line at 2048 / 8192 / 16384 / 32768 counts: bf16,
+// 4 x 28 sets, 8192 tokens 30.4 / 27.1 / 27.2 / 27.2, 26000 58.2 / 58.0 / 57.6 / 63.7, 32768 67 / 67 / 67 / 74; 2 x 10 sets, 16384 35.5 / 31.5 /
+// 31.8 / 31.9, 32768 51.9 / 52.3 / 50.1 / 49.6; fp32, 2 x 16 experts, 32768 39.9 / 40.6 / 35.0 / 35.1.
 static void launch_sort(const SortArgs& a, hipStream_t s) {
-  constexpr long SCAN_MAX = 32768;
+  constexpr long SCAN_MAX = 16384;
   const int nmax = a.sides > 1 && a.N[1] > a.N[0] ? a.N[1] : a.N[0];
   const int tables = (a.experts ? 1 : 0) + (a.t.setid ? 1 : 0);
   const dim3 g(router_blocks(nmax), a.H, a.sides * tables);
@@ -1077,7 +1082,7 @@ static void launch_sort(const SortArgs& a, hipStream_t s) {
     scan_scatter_kernel<<<g, RB, 0, s>>>(a);
     return;
   }
-  scan_kernel<<<dim3(a.H, a.sides, tables), 256, 0, s>>>(a);
+  scan_kernel<<<dim3(a.H, a.sides, ((a.experts ? a.E : 0) + a.t.nsets + 3) / 4), 256, 0, s>>>(a);
   scatter_kernel<<<g, RB, 0, s>>>(a);
 }
 

@@ -246,12 +246,12 @@ def test_fp32_causal_queries_do_not_meet_what_lies_far_behind_them(d_head):
 
 
 def test_fp32_sort_tables_too_large_for_the_in_block_scan():
-    """The fp64 router's scan and scatter over a count table of 32-token blocks: 130 blocks of 64 experts."""
-    run_case(_cfg(dtype="f32", B=41, T=101, d_model=16, nheads=1, d_head=8, E=64, k=2), seed=139)
+    """The fp64 router's scan and scatter over a count table of 32-token blocks: 259 blocks of 64 experts, past what one block scans."""
+    run_case(_cfg(dtype="f32", B=82, T=101, d_model=16, nheads=1, d_head=8, E=64, k=2), seed=139)
 
 
-def test_bf16_two_token_sets_with_sort_tables_too_large_for_shared_launches():
-    """67 token blocks of 126 expert sets: each side is routed and sorted in launches of its own."""
+def test_bf16_two_token_sets_with_sort_tables_too_large_for_the_in_block_scan():
+    """533 blocks of 126 expert sets on one side and 22 on the other: both are summed in a launch of their own."""
     run_case(_cfg(B=34, T=501, T_q=20, d_model=64, nheads=1, d_head=32, E=9, k=4), seed=149)
 
 

@@ -1,7 +1,8 @@
 """The two-stage router of bf16 storage and the sorts behind it at the sizes where they change form: columns per router that are a
 multiple of four, even or odd (how the router's rows are laid out in LDS) and on both sides of 12, 16 and 20; more than eight
 experts (selection by passes); features that fill no K step, one trip or several; 8-byte rows of x; tokens that fill no
-tile of 32; count tables past what one block scans.  Indices, permutation and offsets are the float64 oracle's exactly; gates are
+tile of 32; count tables past what one block scans, and past what a
+wave sums in one step.  Indices, permutation and offsets are the float64 oracle's exactly; gates are
 sigmoids of logits summed in fp32 over 64 features at a time (2e-5 bounds that many times over at these sizes)."""
 import numpy as np
 import pytest
@@ -25,6 +26,9 @@ pytestmark = pytest.mark.gpu
     (dict(T=513, T_q=65, d_model=1024, nheads=4, E=5, k=3), False, True),
     (dict(T=100, T_q=1, d_model=412, nheads=2, E=5, k=3), True, False),
     (dict(B=5, T=8000, d_model=16, nheads=1, E=9, k=4), False, False),
+    (dict(B=3, T=43, d_model=16, nheads=2, E=9, k=4), False, True),          # a table that a block scans, of more than 64 bins
+    (dict(B=40, T=104, d_model=16, nheads=3, E=9, k=4), False, True),        # 130 blocks of 126 sets: the last size of those
+    (dict(B=41, T=102, d_model=16, nheads=3, E=9, k=4), True, False),        # and the next
 ])
 def test_routing_tables(over, shared, ties):
     from paper_2312_07987_amd.runner import DeviceLayer
