@@ -385,30 +385,43 @@ __device__ __forceinline__ void recheck_select(const unsigned short* __restrict_
       if (lane < E && rank < k) sel_out[rank] = (unsigned char)lane;
       return;
     }
-  } else if (lane < E) {
-    for (int f = 0; f < lane; ++f) close = close || !(fabs(z[lane] - z[f]) > reorder);
-  }
-  if (__ballot(close)) {   // the canonical sums, an expert per lane
-    const int e = min(lane, E - 1);
-    double acc = 0.0;
-    for (int i0 = 0; i0 < dm; i0 += 16) {
-      unsigned short xv[16], wv[16];
+  } else {   // a lane per expert
+    const double ze = z[min(lane, E - 1)];
+    int rank = 0;
+    for (int f0 = 0; f0 < E; f0 += 8) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const unsigned i = min(i0 + j, dm - 1);
-        xv[j] = xrow[i];
-        wv[j] = w[i * (unsigned)HE + e];
-      }
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const double next = fma(bf16_to_f64(xv[j]), bf16_to_f64(wv[j]), acc);
-        acc = i0 + j < dm ? next : acc;
+      for (int f = f0; f < f0 + 8; ++f) {
+        const double zf = z[min(f, E - 1)];
+        close = close || (f < E && f != lane && !(fabs(ze - zf) > reorder));
+        rank += f < E && zf > ze;
       }
     }
-    wave_order();
-    if (lane < E) z[lane] = acc + (bh ? (double)bh[lane] : 0.0);
-    wave_order();
+    close = close && lane < E;
+    if (!__ballot(close)) {
+      if (lane < E && rank < k) sel_out[rank] = (unsigned char)lane;
+      return;
+    }
   }
+  // the canonical sums, an expert per lane
+  const int e = min(lane, E - 1);
+  double acc = 0.0;
+  for (int i0 = 0; i0 < dm; i0 += 16) {
+    unsigned short xv[16], wv[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const unsigned i = min(i0 + j, dm - 1);
+      xv[j] = xrow[i];
+      wv[j] = w[i * (unsigned)HE + e];
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const double next = fma(bf16_to_f64(xv[j]), bf16_to_f64(wv[j]), acc);
+      acc = i0 + j < dm ? next : acc;
+    }
+  }
+  wave_order();
+  if (lane < E) z[lane] = acc + (bh ? (double)bh[lane] : 0.0);
+  wave_order();
   if (lane == 0) select_serial(z, sel_out, E, k);
 }
 
@@ -423,7 +436,7 @@ __global__ __launch_bounds__(512, 4) void router_tile_kernel(RouterTileArgs a) {
   __shared__ float gd[RT_TOK * 32];     // [token][H*E] dense gates
   __shared__ unsigned short flist[1024];
   __shared__ float rsp[8][32], wsp[8][32], rs[32], w2[32];
-  __shared__ double part[2][8][8];
+  __shared__ double part[2][8][32];
   __shared__ int nflag;
   const int H = a.H, E = a.E, k = a.k, HE = H * E, dm = a.dm;
   int side, tile;
@@ -729,73 +742,61 @@ __global__ __launch_bounds__(512, 4) void router_tile_kernel(RouterTileArgs a) {
   const int nf = nflag;
   if (nf) {
     // Second stage: the waves share an entry's K steps, the next wave in turn adds up their parts and selects while the others
-    // go on (two sets of parts, one barrier each).
+    // go on (two sets of parts, one barrier each).  A lane takes one of 8, 16 or 32 columns and every 8th, 4th or 2nd row, so the router's
+    // rows are staged once, however many experts there are.  (A lane per row with eight columns at a time, staged again for every eight: router
+    // and sorts, us, 16384 tokens of d_model 1024, 3 heads, 4 of 10 experts 121 -> 80, 1 head, 2 of 31 143 -> 82; 298 tokens of d_model 2048, 8 of 31 273 -> 117.)
     unsigned short* w2l = (unsigned short*)(zp + (32 * ZS + 1) / 2 * 2) + wave * (CB * 64 * 16);   // behind the logits
+    const int cbits = E <= 8 ? 3 : E <= 16 ? 4 : 5, nr = 1 << cbits, step = 64 >> cbits, r0 = lane >> cbits;
     int buf = 0;
-    for (int f = 0; f < nf; ++f) {
+    for (int f = 0; f < nf; ++f, buf ^= 1) {
       const int it = flist[f], h = it / RT_TOK, t = it % RT_TOK;
       const unsigned short* xrow = a.x + row_of(tok0 + t) * dm;
       double* zi = zp + t * ZS + h * E;
-      for (int e0 = 0; e0 < E; e0 += 8, buf ^= 1) {
-        double acc[8];
+      const int c = h * E + min(lane & (nr - 1), E - 1);
+      const unsigned short* wc = w2l + ((c >> 4) * 64 + r0) * 16 + (c & 15);
+      double acc = 0.0;
+      for (int kb = wave * 64; kb < dm; kb += 1024) {
+        uint2 wv[2][P];
+        unsigned short xv[2];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] = 0.0;
-        for (int kb = wave * 64; kb < dm; kb += 1024) {
-          uint2 wv[2][P];
-          unsigned short xv[2];
+        for (int s = 0; s < 2; ++s) {
+          const int k0 = kb + 512 * s;
 #pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            const int k0 = kb + 512 * s;
+          for (int i = 0; i < P; ++i) wv[s][i] = *(const uint2*)(W + min(k0 * HE + 4 * (lane + 64 * i), total - 4));
+          xv[s] = xrow[min(k0 + lane, dm - 1)];
+        }
 #pragma unroll
-            for (int i = 0; i < P; ++i) wv[s][i] = *(const uint2*)(W + min(k0 * HE + 4 * (lane + 64 * i), total - 4));
-            xv[s] = xrow[min(k0 + lane, dm - 1)];
-          }
+        for (int s = 0; s < 2; ++s) {
+          const int rows = dm - (kb + 512 * s);
+          if (rows <= 0) break;   // uniform
+          stage(w2l, wv[s]);
+          for (int j0 = 0; j0 < nr; j0 += 8) {   // rows r0, r0 + step, ...
 #pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            stage(w2l, wv[s]);
-            if (kb + 512 * s + lane < dm) {
-#pragma unroll
-              for (int u = 0; u < 8; ++u)
-                if (e0 + u < E) {
-                  const int c = h * E + e0 + u;
-                  acc[u] = fma(bf16_to_f64(xv[s]), bf16_to_f64(w2l[((c >> 4) * 64 + lane) * 16 + (c & 15)]), acc[u]);
-                }
+            for (int j = 0; j < 8; ++j) {
+              const int row = (j0 + j) * step;
+              const double next = fma(bf16_to_f64((unsigned short)__shfl((int)xv[s], r0 + row, 64)), bf16_to_f64(wc[row * 16]), acc);
+              acc = r0 + row < rows ? next : acc;
             }
           }
         }
-        // Sum over the lanes, half of the values handed to the other half of the lanes at each of the first steps: the tree over
-        // the lanes is the same for every value, whichever lanes end up with it.
-        int u0 = 0, d = 32;
+      }
+      // the same tree over the row groups for every column
+      for (int o = 32; o >= nr; o >>= 1) acc += __shfl_xor(acc, o, 64);
+      if (lane < E) part[buf][wave][lane] = acc;
+      __syncthreads();
+      if (wave == f % 8) {
+        if (lane < E) {
+          double v = part[buf][0][lane];
 #pragma unroll
-        for (int nv = 8; nv > 1; nv >>= 1, d >>= 1) {
-          const bool hi = lane & d;
-          u0 = 2 * u0 + hi;
-#pragma unroll
-          for (int i = 0; i < nv / 2; ++i) {
-            const double keep = hi ? acc[i + nv / 2] : acc[i], give = hi ? acc[i] : acc[i + nv / 2];
-            acc[i] = keep + __shfl_xor(give, d, 64);
-          }
+          for (int w = 1; w < 8; ++w) v += part[buf][w][lane];
+          zi[lane] = v + (b ? (double)b[h * E + lane] : 0.0);
         }
-#pragma unroll
-        for (int o = 4; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
-        if ((lane & 7) == 0) part[buf][wave][u0] = acc[0];
-        __syncthreads();
-        if (wave == f % 8) {
-          if (lane < 8 && e0 + lane < E) {
-            double v = part[buf][0][lane];
-#pragma unroll
-            for (int w = 1; w < 8; ++w) v += part[buf][w][lane];
-            zi[e0 + lane] = v + (b ? (double)b[h * E + e0 + lane] : 0.0);
-          }
-          if (e0 + 8 >= E) {
-            wave_order();
-            // twice d_model * 2^-53 * |x| * max|w|, doubled again for the rounding of the norms themselves
-            float wn = 0.f;
-            for (int e = 0; e < E; ++e) wn = fmaxf(wn, w2[h * E + e]);
-            const double reorder = 4.0 * (double)dm * 1.1102230246251565e-16 * (double)sqrtf(rs[t]) * (double)sqrtf(wn);
-            recheck_select(xrow, W + h * E, b ? b + h * E : nullptr, zi, sidx + it * k, dm, HE, E, k, lane, reorder);
-          }
-        }
+        wave_order();
+        // twice d_model * 2^-53 * |x| * max|w|, doubled again for the rounding of the norms themselves
+        float wn = 0.f;
+        for (int e = 0; e < E; ++e) wn = fmaxf(wn, w2[h * E + e]);
+        const double reorder = 4.0 * (double)dm * 1.1102230246251565e-16 * (double)sqrtf(rs[t]) * (double)sqrtf(wn);
+        recheck_select(xrow, W + h * E, b ? b + h * E : nullptr, zi, sidx + it * k, dm, HE, E, k, lane, reorder);
       }
     }
     __syncthreads();

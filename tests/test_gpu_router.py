@@ -23,6 +23,9 @@ pytestmark = pytest.mark.gpu
     (dict(T=64, d_model=2100, nheads=2, E=7, k=5), False, True),
     (dict(T=130, d_model=512, nheads=2, E=9, k=4), False, True),
     (dict(T=96, d_model=260, nheads=1, E=31, k=8), False, True),
+    (dict(T=70, d_model=1500, nheads=2, E=16, k=3), False, True),            # the second stage's 16 and 32 columns
+    (dict(T=50, d_model=2052, nheads=1, E=17, k=8), False, True),
+    (dict(T=40, d_model=520, nheads=1, E=32, k=8), True, False),
     (dict(T=513, T_q=65, d_model=1024, nheads=4, E=5, k=3), False, True),
     (dict(T=100, T_q=1, d_model=412, nheads=2, E=5, k=3), True, False),
     (dict(B=5, T=8000, d_model=16, nheads=1, E=9, k=4), False, False),
