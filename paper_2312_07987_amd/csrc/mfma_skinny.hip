@@ -114,9 +114,21 @@ __device__ __forceinline__ uint4 sk_load8(const unsigned short* row, int k, int 
   }
 }
 
+constexpr int SK_W = 8, SK_UK = 64, SK_EB = 5;   // waves; reduction indices and experts of a wave's item
+// A wave's item: a head, 64 of its reduction indices (`per` pieces), up to SK_EB of its experts (fewer where there would be idle waves): eb
+// experts, split items for all of them.
+struct SkItems {
+  int split, eb;
+};
+__host__ __device__ inline SkItems sk_items(int H, int E, int per) {
+  const int most = (E + SK_EB - 1) / SK_EB, wide = SK_W / (H * per) < E ? SK_W / (H * per) : E;
+  const int split = most > wide ? most : wide, eb = (E + split - 1) / split;
+  return {(E + eb - 1) / eb, eb};
+}
+
 template <int VEC>
 __global__ __launch_bounds__(512, 1) void skinny_concat_kernel(RowGemmArgs a) {
-  constexpr int W = 8, UK = 64, EB = 5;
+  constexpr int W = SK_W, UK = SK_UK, EB = SK_EB;
   __shared__ __attribute__((aligned(16))) unsigned short bs[W][UK * SK_T];   // then the partial sums [W][32][32] fp32
   __shared__ __attribute__((aligned(16))) float gts[MAX_SEGD * SK_T];   // the tile's gates [head * experts + expert][row], -1: not selected
   __shared__ SegDesc descs[MAX_SEGD];
@@ -137,12 +149,10 @@ __global__ __launch_bounds__(512, 1) void skinny_concat_kernel(RowGemmArgs a) {
     }
     __syncthreads();
   }
-  // A wave's item: a head, 64 of its reduction indices, up to EB of its experts (fewer where there would be idle waves).  The head's
-  // read-out is loaded once for its experts; everything of an item is requested before the wave waits.
+  // The head's read-out is loaded once for an item's experts; everything of an item is requested before the wave waits.
   const int H = a.gheads, E = a.experts, ups = (a.K + UK - 1) / UK;
-  int split = max((E + EB - 1) / EB, min(E, W / (H * ups)));
-  const int eb = (E + split - 1) / split;
-  split = (E + eb - 1) / eb;
+  const SkItems items = sk_items(H, E, ups);
+  const int split = items.split, eb = items.eb;
   const long arow = (long)(row0 + min(r, rows - 1)) * a.lda;   // (a row past the end repeats the last one; not stored)
   f32x16 acc;
 #pragma unroll
@@ -231,26 +241,30 @@ static int sk_concat_vec(const RowGemmArgs& a) {
   return 0;
 }
 
-// One tile for each CU (8 of 1024 columns each: 256 tokens), two where a tile's reduction is short and there is more than one head.
-// Every expert is multiplied, selected or not, so there is a line in the pieces of a tile (of 64 indices), too.  us, the other path / here:
-//   `sets`, expert sets with the sum of the heads: d_model 1024, 4 heads of 128, 3 of 5 experts, 1 token 20.8 / 12.1, 256 23.7 / 18.2, 500
-//   24.5 / 25.5; 2 of 8, 256 tokens 30.1 / 23.5, 500 30.9 / 34.6; 1 of 8 (64 pieces, 8 needed), 16 tokens 17.3 / 19.3, 100 17.5 / 23.7; 2 heads, 1 of
-//   32, 16 tokens 18.0 / 34.4; d_model 412, 2 heads of 76, 3 of 5 experts, 500 tokens (208 tiles) 20.0 / 10.9, 1000 (416) 20.5 / 17.4, 1600
-//   (650) 21.2 / 24.1; 8 heads of 256, 4 of 8 (256 pieces), 1 token 34.3 / 60.3.
-//   One head has no sum: 1 of 64 experts of 128, 100 tokens 11.8 / 40.8; 1 of 5, 500 tokens (512 tiles) 10.5 / 13.9.
-//   Expert-sorted rows (more sets than the tables hold, or rows that make none) cost launches to clear and to cast, and more with every
-//   row: 4 heads of 128, 4 of 16 experts (128 pieces), 1 token 30.3 / 33.9, 16 54.4 / 33.7, 256 77.7 / 38.4.
-// Over 2401 shapes that lie on both sides of these lines, 21 that come here lose more than 2 per cent (the worst 4.2 us), 38 us in all
-// of 43760; without the lines in pieces 421 of them, 4517 us.
+// Every expert is multiplied, selected or not, so the line compares what the two ways take, in us (the weights of both sums are fitted to
+// 6000 calls that ran both ways, 1 to 4096 rows of 64 to 2048 columns, 1 to 10 heads of 16 to 256, up to 64 experts):
+//   here: 0.8 for an expert that a wave multiplies, 2 for a round of 256 tiles;
+//   expert sets (`sets`): 3.1, with more than one head 5.6 for the sum of the heads, and 0.7 for 64 indices of a selected expert;
+//   expert-sorted rows (more sets than the tables hold, or rows that make none): 5.7 for the launches that clear and cast, 0.034 for a
+//   tile of 128 rows and columns (few rows are nearly all tiles of a few rows each).
+// The whole forward call, us, the other path / here.  Sets: 4 heads of 128, 5 of 5 experts, d_model 1024, 173 tokens 77.7 / 71.6; 2 heads of 96, 5 of 5,
+// d_model 412, 256 tokens 69.5 / 56.8; 10 heads of 96, 3 of 5, 6 tokens of 412 138.9 / 147.1; 2 heads of 160, 1 of 32, 58 tokens of 768
+// 189.7 / 217.1; one head of 128, 2 of 5, 119 tokens of 1024 45.6 / 42.9.  Sorted rows: 4 heads of 112, 8 of 16, 205 tokens of 1024 299.7 / 267.3,
+// but 8 heads of 256, 1 of 4, 17 tokens of 100 52.3 / 71.0; 2 heads of 76, 5 of 32, 40 tokens of 64 68.4 / 81.3.
+// Of 5000 other calls 47 that come here lose more than 2 per cent, 98 us in all, for 21000 us that the rest gain (a line in the products alone: one
+// in fifteen lost, 1887 us on the 6000).
 bool skinny_concat_supported(const RowGemmArgs& a, bool sets) {
   if (a.seg_mode != 3 || a.perm || a.heads != 1 || a.E != 1 || a.mode != STORE_T || a.sbn != 1 || a.M < 1 || a.gtab || a.seg_q) return false;
   // (segment h * experts + e: expert e of head h, the head's read-out the same for all of them)
   if (a.nseg < 1 || a.nseg > MAX_SEGD || a.gheads * a.experts != a.nseg) return false;
   const long tiles = (long)((a.M + SK_T - 1) / SK_T) * ((a.Nc + SK_T - 1) / SK_T);
-  if (tiles > ((long)a.nseg * a.K <= 1024 && !(sets && a.gheads == 1) ? 512 : 256) || sk_concat_vec(a) == 0) return false;
-  const int per = (a.K + 63) / 64, pieces = a.nseg * per, needed = a.gheads * a.gk * per;
-  if (!sets) return pieces <= 128 && pieces <= 64 + 4l * a.M;
-  return a.gheads == 1 ? pieces <= 4 * needed : pieces <= 112 && pieces <= 32 + 2 * needed;
+  if (tiles > 512 || sk_concat_vec(a) == 0) return false;
+  const int H = a.gheads, E = a.experts, per = (a.K + SK_UK - 1) / SK_UK;
+  const SkItems it = sk_items(H, E, per);
+  const long rounds = (tiles + 255) / 256, slots = (long)a.M * a.gk;
+  const double here = 0.8 * rounds * ((H * per * it.split + SK_W - 1) / SK_W) * it.eb + 2.0 * rounds + 0.5;
+  const double sorted_tiles = H * ((slots < E ? slots : E) + slots / 128.0) * ((a.Nc + 127) / 128);
+  return here <= (sets ? (H > 1 ? 5.6 : 3.1) + 0.7 * a.gk * per : 5.7 + 0.034 * sorted_tiles);
 }
 
 void launch_skinny_concat(const RowGemmArgs& a, hipStream_t s) {

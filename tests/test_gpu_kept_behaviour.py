@@ -141,6 +141,21 @@ def test_output_experts_of_a_few_rows_round_once(over, dense):
     assert e < 1.05 * once
 
 
+@pytest.mark.parametrize("over, step", [
+    (dict(T=17, d_model=100, nheads=8, d_head=256, E=4, k=1), "fwd.y_zero"),
+    (dict(T=40, d_model=64, nheads=2, d_head=76, E=32, k=5), "fwd.y_zero"),
+    (dict(T=6, d_model=412, nheads=10, d_head=96, E=5, k=3), "fwd.y_sum"),
+    (dict(T=17, d_model=256, nheads=4, d_head=128, E=8, k=1), "fwd.y_sum"),
+    (dict(T=100, d_model=1024, nheads=4, d_head=128, E=5, k=3), None),
+    (dict(T=205, d_model=1024, nheads=4, d_head=112, E=16, k=8), None),
+])
+def test_output_experts_of_a_few_rows_leave_short_calls_to_the_other_paths(over, step):
+    """Every expert is multiplied there: calls with many experts for those a token selects, or of narrow models, were slower."""
+    cfg = _cfg(B=1, **over)
+    got = _steps(_layer(cfg, make_inputs(cfg, seed=117)))
+    assert got & {"fwd.y_sum", "fwd.y_zero"} == ({step} if step else set()), got
+
+
 def _poison_one(t, n, h, e, i, j):
     t[n] = t[n].copy()
     t[n][h, e, i, j] = np.inf

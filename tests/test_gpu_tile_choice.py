@@ -45,6 +45,11 @@ def test_fp32_tiles(over, shared):
     (dict(T=40, d_model=256, nheads=1, d_head=64, E=5, k=1), False),
     (dict(T=1, d_model=256, nheads=4, d_head=128, E=16, k=4), False),
     (dict(T=16, d_model=256, nheads=4, d_head=128, E=16, k=4), False),
+    # ... and on narrow models, whose other path is short; 512 tiles and the next size
+    (dict(T=17, d_model=100, nheads=8, d_head=256, E=4, k=1), False),
+    (dict(T=40, d_model=64, nheads=2, d_head=76, E=32, k=5), False),
+    (dict(T=1024, d_model=512, nheads=1, d_head=16, E=3, k=3), False),
+    (dict(T=1025, d_model=512, nheads=1, d_head=16, E=3, k=3), False),
 ])
 def test_output_experts_of_a_few_rows(over, dense):
     run_case(_cfg(**over), dense=dense, backward=False, seed=223)
