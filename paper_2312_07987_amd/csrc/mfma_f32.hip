@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256) void f32_row_gemm_kernel(RowGemmArgs a) {
 // The line, launches of 128 tiles of 64 rows: a training step with the small tiles up to 0 / 32 / 128 / 256 of them, us: toy layer (d_model 64, 2
 // heads of 32) over 128 tokens 91 / 71 / 70 / 70; 47M layer over 128 tokens 212 / 121 / 121 / 121, 512 tokens 235 / 224 / 160 / 159, 2048 tokens
 // 268 / 268 / 264 / 296; 262M layer over 128 tokens 468 / 303 / 272 / 272, 512 tokens 549 / 549 / 483 / 498.
-// ----------------------------------------------------------------------------------------
+// A second line, small_tiles_pay(), where the small tiles are many and their reduction is short, or their scalar loads run along the columns of B.
 static constexpr int F32_SMALL_TILES = 128;
 static constexpr int FSM_M = 16, FSM_N = 32, FSM_W = 8, FSM_U = 4;
 
@@ -486,12 +486,24 @@ static void launch_f32_small(const RowGemmArgs& a, hipStream_t s) {
     a.sbk == 1 ? f32_small_gemm_kernel<VEC, true, false><<<g, 64 * FSM_W, 0, s>>>(a) : f32_small_gemm_kernel<VEC, false, false><<<g, 64 * FSM_W, 0, s>>>(a);
 }
 
+// A work-group costs as much as 190 of its reduction indices before it begins, and a launch of large tiles little more than its
+// reduction.  One launch, us, large tiles / small ones, work-groups of the latter and K: 1500 sorted rows of 4 heads of 48 7.4 / 12.2 (772, K 128),
+// 1874 of 3 heads of 42 8.8 / 15.1 (717, 128), but 1107 rows of 4 heads of 76 18.7 / 11.3 (840, 412).  Rows of B along the
+// reduction that cannot be read 16 bytes at a time are 32 scattered lines an instruction: 2018 sorted rows of 3 heads of 36 32.7 / 51.5 (777, 1030), 155 of
+// 10 heads of 128 33.7 / 52.0 (500, 1030).  Of 3964 launches up to the first line 172 that come here are slower by more than 3 per cent, 322 us in all, and
+// the others 60000 us faster; by the first line alone 245 were slower, 670 us.
+static bool small_tiles_pay(const RowGemmArgs& a, bool v4) {
+  const long wgs = (long)((a.M + FSM_M - 1) / FSM_M + (a.perm ? a.E / 2 : 0)) * ((a.Nc + FSM_N - 1) / FSM_N) * a.heads;
+  const long K = a.seg_mode == 3 ? (long)(a.nseg - a.seg_own) * a.K + (a.seg_own ? (long)a.seg_own * a.segd[a.nseg - 1].klen : 0) : a.K;
+  return !v4 && a.sbk == 1 ? wgs * (190 + K) <= 520 * (30 + K) : wgs * (190 + K) <= 1400 * (40 + K);
+}
+
 void launch_f32_row_gemm(const RowGemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.Nc <= 0) return;
   const bool v4 = f32_vec4(a);
   const int nj = f32_nj(a.Nc);
   const long tiles = (long)((a.M + FBM - 1) / FBM + (a.perm ? a.E / 2 : 0)) * ((a.Nc + 16 * nj - 1) / (16 * nj)) * a.heads;
-  if (tiles <= F32_SMALL_TILES) return v4 ? launch_f32_small<4>(a, s) : launch_f32_small<1>(a, s);
+  if (tiles <= F32_SMALL_TILES && small_tiles_pay(a, v4)) return v4 ? launch_f32_small<4>(a, s) : launch_f32_small<1>(a, s);
   switch (f32_nj(a.Nc) * 2 + (v4 ? 1 : 0)) {
     case 5: return launch_f32_rg<2, 4>(a, s);
     case 4: return launch_f32_rg<2, 1>(a, s);

@@ -24,6 +24,9 @@ def _cfg(**over):
     # 64-row tiles
     (dict(T=1300, d_model=410, nheads=2, d_head=42, E=5, k=3), False),
     (dict(T=1400, T_q=1300, d_model=412, nheads=2, d_head=76, E=5, k=3), True),
+    # few of those, but many small tiles: a short reduction; 4-byte loads along the reduction
+    (dict(T=1040, d_model=128, nheads=4, d_head=76, E=1, k=1), False),
+    (dict(T=400, d_model=410, nheads=3, d_head=36, E=5, k=3), False),
 ])
 def test_fp32_tiles(over, shared):
     run_case(_cfg(dtype="f32", **over), shared=shared, seed=211)
