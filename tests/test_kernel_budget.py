@@ -77,3 +77,28 @@ def test_ping_pong_gemm_budgets(tmp_path):
     assert len(kernels) >= 6
     for k in kernels:
         assert t[k][0] <= 256 and t[k][1] == 0, (k, t[k])
+
+
+def test_router_budgets(tmp_path):
+    # two work-groups of eight waves per CU: 128 registers.  Static LDS, and the largest dynamic part of the instances (20
+    # columns and two steps), within the 64 KB that a launch gets without asking
+    t = kernel_table("routing.hip", tmp_path)
+    tiles = [k for k in t if "router_tile_kernel<" in k]
+    assert len(tiles) >= 14
+    for k in tiles:
+        assert t[k][0] <= 128 and t[k][1] == 0, (k, t[k])
+    text = open(os.path.join(str(tmp_path), "routing.hip.s")).read()
+    static = [int(v) for v in re.findall(r"\.amdhsa_kernel \S*router_tile_kernel\S*\s+\.amdhsa_group_segment_fixed_size (\d+)", text)]
+    assert len(static) == len(tiles) and max(static) + 43008 <= 65536, static
+
+
+@pytest.mark.parametrize("source, kernel, count, registers", [
+    ("mfma_attn.hip", "mfma_attn_few_kernel<", 8, 256),        # eight waves, one work-group per CU
+    ("mfma_skinny.hip", "skinny_concat_kernel<", 2, 256),
+    ("mfma_f32.hip", "f32_small_gemm_kernel<", 8, 128),        # two work-groups of eight waves
+])
+def test_small_call_budgets(tmp_path, source, kernel, count, registers):
+    t = {k: v for k, v in kernel_table(source, tmp_path).items() if kernel in k}
+    assert len(t) >= count
+    for k, (vgpr, scratch) in t.items():
+        assert vgpr <= registers and scratch == 0, (k, vgpr, scratch)
