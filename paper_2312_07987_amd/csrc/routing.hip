@@ -1139,16 +1139,8 @@ template <int VEC, int S, int P, int CB>
 static void launch_router_tiles(const RouterTileArgs& t, int blocks, hipStream_t s) {
   const size_t ZS = (t.H * t.E) | 1, wl = CB * 64 * 16 * 2, sums = (S * 32 * ZS * 4 + 15) / 16 * 16;
   const size_t first = 8 * (wl > sums ? wl : sums), second = (32 * ZS + 1) / 2 * 2 * 8 + 8 * wl;   // (the logits, then the second stage's router rows)
-  const size_t lds = first > second ? first : second;   // at most 68 KB
-  auto kern = router_tile_kernel<VEC, S, P, CB>;
-  if (lds > 48 * 1024) {   // (with the static part beyond 64 KB)
-    static bool raised = false;   // per instantiation
-    if (!raised) {
-      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 68 * 1024);
-      raised = true;
-    }
-  }
-  kern<<<blocks + 1, 512, lds, s>>>(t);
+  const size_t lds = first > second ? first : second;   // at most 43008 bytes (20 columns, two steps), with the static part below 64 KB
+  router_tile_kernel<VEC, S, P, CB><<<blocks + 1, 512, lds, s>>>(t);
 }
 template <int VEC, int S>
 static void launch_router_tiles(const RouterTileArgs& t, int blocks, hipStream_t s) {
