@@ -23,7 +23,7 @@ namespace sh {
 //           work-groups per CU; dense rows.  The larger wave tile reads 0.75 KB of LDS per MFMA
 //           instead of 1 KB, and a K step of 64 takes whole 128-byte lines from every row (a step of
 //           32 with two stages moved half lines and measured 5 % slower).
-// LDS is dynamic: [stages][A tile | B tile] bf16, then row ids, row scales, segment offsets.
+// LDS is dynamic: [A tile | B tile] bf16, then row ids, row scales, segment offsets.
 // ----------------------------------------------------------------------------------------
 template <int WM_, int WN_, int MI_, int NJ_, int BK_, int STAGES_, int MINB_ = 1>
 struct TileCfg {
@@ -37,6 +37,7 @@ struct TileCfg {
   static constexpr int B_ELEMS = (BN * LDB_NT > BK * LDB_NN) ? BN * LDB_NT : BK * LDB_NN;
   static constexpr int STAGE_ELEMS = A_ELEMS + B_ELEMS;
   static constexpr int LDC = NJ * 32 + 8;   // staged output: 32 rows per wave at a time
+  static_assert(STAGES == 1, "the K loop has one operand stage; the next step waits in registers");
   static_assert(4 * 32 * LDC <= STAGES * STAGE_ELEMS, "output staging must fit in the operand tiles");
   static constexpr size_t lds_bytes(bool sets) {
     return (size_t)STAGES * STAGE_ELEMS * 2 + (size_t)BM * 4 + (size_t)BM * (sets ? 8 : 1) * 4 + 64;
