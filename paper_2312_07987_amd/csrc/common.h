@@ -267,7 +267,6 @@ struct RouterArgs {
   // if not NULL (and for as many sides), launch_router_hybrid also sorts the tokens by expert set,
   // sharing the passes of the expert sort; the caller then skips launch_set_sort
   const SetSortArgs* sets;
-  int* setcnt;            // [sides*H, nsets, router_count_blocks(N)] scratch for that
   // if not NULL (launch_router_hybrid): the dense gate table [sides][N][H*E] is written as well
   float* gtab;
   // launch_router_hybrid with sides == 2 and Nq > 0: side 1 routes the last Tq of every T rows of x, Nq in all, and copies them
@@ -307,7 +306,7 @@ struct SetSortArgs {
   int* setexp;         // [nsets, 8] the ascending experts of every set
   int* setperm;        // [sides, H, N] token ids sorted by set id (stable)
   int* setoff;         // [sides, H, nsets+1]
-  int* blockcnt;       // [sides*H, nsets, nblk] scratch
+  int* blockcnt;       // [sides*H, nsets, nblk] scratch; launch_router_hybrid: nblk = router_count_blocks(N)
   int N, H, k, E, nsets, sides;
 };
 void launch_set_sort(const SetSortArgs& a, hipStream_t s);

@@ -80,7 +80,7 @@ struct Layout {
   size_t gtab;                                                     // dense gate table [2][N][H*E] fp32 (gated-concatenation GEMMs)
   size_t wrt;                                                      // x^T dz of both routers [dm, dh] fp32 (fused with the Q/K weight gradient)
   size_t dR, wr3;                                                  // wide router dz rows [N, H*dh], routers packed [dm, dh]                 // expert-set path (bf16 only)
-  size_t rh, rh_bytes;                                             // routers packed for the backward pass; counts of the set sort (bf16 only)
+  size_t rh;                                                       // routers packed for the backward pass (bf16 only)
   size_t wpart;                                                    // per-chunk weight-gradient partial sums
   size_t wpart_floats = 0;                                         // ... their room
   size_t u, dctx, dQ, dK, dV, delta, dgate, dz;                    // backward scratch
@@ -230,6 +230,9 @@ Layout make_layout(const sh_shape* s) {
     L.setexp = take((size_t)MAX_SETS * 8 * 4, true);
     L.setperm = take(2 * H * N * 4, true);
     L.setoff = take(2 * H * (ns + 1) * 4, true);
+    // Counts of the tokens per set, in blocks of 256 (set histogram) or of 32 (two-stage router).  The latter are up to eight times as
+    // many and run on into the partial sums and the gate table behind them: the sums are written later, such shapes do not use the table,
+    // and its 8 bytes per token, head and expert alone hold the rest (up to 14 sets per expert; up to 32 tokens there is none).
     L.setcnt = take(2 * H * (size_t)router_blocks((int)N) * ns * 4);
     // partial sums of dx (y in the forward pass): one per head from the value experts, then either one
     // for the dense Q/K pair or one per head for each of the query and key experts, one for the routers
@@ -237,12 +240,10 @@ Layout make_layout(const sh_shape* s) {
   } else {
     L.setid = L.gset = L.gsort = L.setexp = L.setperm = L.setoff = L.setcnt = L.yh = 0;
   }
-  L.rh = L.rh_bytes = L.wpart = L.gtab = 0;
+  L.rh = L.wpart = L.gtab = 0;
   if (s->dtype == SH_BF16) {
     L.gtab = take(2 * N * H * E * 4, true);
-    // both routers padded to HEp columns, and as much again in whole slabs of 1024 features (what callers' workspaces are sized for)
-    L.rh_bytes = align_up(2 * dm * ((H * E + 7) / 8 * 8) * 2) + align_up(2 * H * E * 4) + align_up(2 * H * E * ((dm + 1023) / 1024 * 1024) * 2);
-    L.rh = take(L.rh_bytes);
+    L.rh = take(2 * dm * ((H * E + 7) / 8 * 8) * 2);   // both routers padded to HEp columns
   }
   if (s->dtype == SH_F32) {
     // The weight gradients of one backward call share a launch: room for the partial sums of their chunks, as far as it neither pushes
@@ -648,7 +649,8 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
   const bool gate_table = gated_shape(shape) && !c.dense;
   bool gtab_done = false;
   // the tables a path uses must have a place in the workspace layout (offset 0 is the top-k indices)
-  if ((tables && (c.L.setperm == 0 || c.L.setid == 0 || c.L.gsort == 0)) || ((gated || gate_table) && c.L.gtab == 0) || (sets && c.L.yh == 0))
+  if ((tables && (c.L.setperm == 0 || c.L.setid == 0 || c.L.gsort == 0)) || ((gated || gate_table) && c.L.gtab == 0) || (sets && c.L.yh == 0) ||
+      (tables && (size_t)2 * H * router_count_blocks(N) * count_sets(E, k) * 4 > c.L.rh - c.L.setcnt))
     return fail(SH_ERR_UNSUPPORTED, "switchhead_forward: internal error, the workspace layout lacks a table this shape's path uses");
   bool sets_sorted = false;
   SetSortArgs sa{};
@@ -669,13 +671,6 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     sa.nsets = count_sets(E, k);
     sa.sides = 2;
   }
-  // The two-stage router counts its tokens per set in blocks of 32.  The counts live until the scatter: in the scratch of the packed routers
-  // or, longer tables, where queries, keys, values, read-outs and value slots are written later (36 bytes or more per token and head
-  // of four or more columns, for at most 32 bytes of counts).
-  int* const setcnt = [&] {
-    const size_t need = tables ? (size_t)2 * H * router_count_blocks(N) * count_sets(E, k) * 4 : 0;
-    return need <= c.L.rh_bytes ? c.p<int>(c.L.rh) : need <= c.L.pV + (size_t)H * N * k * dh * 2 - c.L.Q ? c.p<int>(c.L.Q) : nullptr;
-  }();
   prof_mark(c.st, "fwd.router");
   const void* xq = x;   // the destination (query) tokens' rows of x
   if (c.rect) {
@@ -709,9 +704,8 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     rs.sides = 2;
     rs.bf16 = c.bf16;
     if (tables) rs.sets = &sa;
-    rs.setcnt = setcnt;
     if (gate_table) rs.gtab = c.p<float>(c.L.gtab);
-    const bool together = !c.dense && use_mfma(c) && router_hybrid_supported(rs) && setcnt;
+    const bool together = !c.dense && use_mfma(c) && router_hybrid_supported(rs);
     if (!together && hipMemcpy2DAsync(c.p<void>(c.L.xq), (size_t)c.Tq * rowb, (const char*)x + (size_t)(shape->T - c.Tq) * rowb,
                          (size_t)shape->T * rowb, (size_t)c.Tq * rowb, (size_t)shape->B, hipMemcpyDeviceToDevice,
                          c.st) != hipSuccess)
@@ -785,11 +779,10 @@ sh_status switchhead_forward(const sh_shape* shape, const void* x, const void* W
     ra.k = k;
     ra.sides = c.shared ? 1 : 2;
     ra.bf16 = c.bf16;
-    if (use_mfma(c) && router_hybrid_supported(ra) && setcnt) {
+    if (use_mfma(c) && router_hybrid_supported(ra)) {
       if (tables) {   // both sorts in the same launches
         sa.sides = ra.sides;
         ra.sets = &sa;
-        ra.setcnt = setcnt;
         sets_sorted = true;
       } else if (gate_table && !c.shared) {   // the router writes the dense gate table itself
         ra.gtab = c.p<float>(c.L.gtab);

@@ -1167,11 +1167,10 @@ void launch_router_hybrid(const RouterArgs& a, hipStream_t s) {
   t.gtab = a.gtab;
   if (a.sets) {
     d.t = *a.sets;
-    d.t.blockcnt = a.setcnt;
     t.setid = a.sets->setid;
     t.gset = a.sets->gset;
     t.setexp = a.sets->setexp;
-    t.setcnt = a.setcnt;
+    t.setcnt = a.sets->blockcnt;
     t.nsets = a.sets->nsets;
   }
   t.sides = a.sides;

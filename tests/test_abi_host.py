@@ -96,6 +96,12 @@ def test_fp32_scratch_of_backward_leaves_forward_its_built_in_workspace(lib, B, 
     assert 0 < binding.switchhead_workspace_bytes(binding.make_shape(B, T, *layer, 1, "f32")) <= binding.STATIC_WORKSPACE_BYTES
 
 
+def test_workspace_holds_no_whole_slabs_of_features(lib):
+    """Nothing keeps the routers' columns padded to 1024 features: a few features more take a few bytes more."""
+    a, b = (binding.switchhead_workspace_bytes(binding.make_shape(1, 1, dm, 4, 8, 8, 2, 1, "bf16")) for dm in (1024, 1028))
+    assert 0 < b - a < 32 << 10
+
+
 def test_fp32_partial_sums_at_most_double_the_workspace(lib):
     """Many experts, few tokens: the partial sums would be the gradients of every expert (430 MiB instead of 12)."""
     s = binding.make_shape(3, 94, 2048, 5, 76, 63, 2, 1, "f32", qk_experts=1)

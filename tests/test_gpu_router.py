@@ -29,6 +29,7 @@ pytestmark = pytest.mark.gpu
     (dict(T=513, T_q=65, d_model=1024, nheads=4, E=5, k=3), False, True),
     (dict(T=100, T_q=1, d_model=412, nheads=2, E=5, k=3), True, False),
     (dict(B=5, T=8000, d_model=16, nheads=1, E=9, k=4), False, False),
+    (dict(T=100, d_model=4, nheads=3, E=9, k=4), False, True),               # more counts than partial sums of the heads
     (dict(B=3, T=43, d_model=16, nheads=2, E=9, k=4), False, True),          # a table that a block scans, of more than 64 bins
     (dict(B=40, T=104, d_model=16, nheads=3, E=9, k=4), False, True),        # 130 blocks of 126 sets: the last size of those
     (dict(B=41, T=102, d_model=16, nheads=3, E=9, k=4), True, False),        # and the next
