@@ -113,8 +113,8 @@ struct RowGemmArgs {
   const float* gtab;
   int gld;
   int seg_q, seq_T, seq_Tq;
-  // ... the fp32 kernels and the bf16 one for a few rows take the gates from the top-k tables [head][token][gk] of `gheads` heads instead and keeps the
-  // tile's dense gates in LDS (column head * experts + expert)
+  // ... the fp32 kernels and the bf16 one for a few rows take the gates from the top-k tables [head][token][gk] of `gheads` heads instead and
+  // keep the tile's dense gates in LDS (segment head * experts + expert)
   const int* gidx;
   const float* ggate;
   int gk, gheads;

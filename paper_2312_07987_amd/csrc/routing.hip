@@ -291,10 +291,13 @@ void launch_copy_list(const CopyList& l, hipStream_t s) {
 // the router's rows, contiguous in memory, through the wave's own corner of LDS, from where transposing reads make the other
 // operand.  The norms of the bound are summed from the fragments (two products an instruction), the K steps' sums meet in LDS.
 // Bound by one trip to memory and the chain of short steps behind it (25000 cycles for a tile, two or four tiles on a CU at a time), for many
-// tokens by those tiles' vector instructions.  Router and sorts, us, against four launches (router packed and copied out as columns;
+// tokens by those tiles' vector instructions.  Router and sorts, us between events, against four launches (router packed and copied out as columns;
 // logits on 64 x 64 tiles of the row GEMM, 20 of 64 columns used, and a recheck of one entry per wave; histogram; scan and scatter):
-// d_model 1024, 2 x 20 columns, 100 tokens 46 -> 17, 6300 tokens 57 -> 31, 16384 tokens 56 -> 43; d_model 412, 2 x 10 columns, 16384
-// tokens 48 -> 31; 2 x 32 columns, 16384 tokens 63 -> 60; 8000 cached and 8 query rows, with the copy of the latter, 57 -> 24.
+// d_model 1024, 2 x 20 columns, 100 tokens 45 -> 21, 6300 tokens 54 -> 27, 16384 tokens 53 -> 40; d_model 412, 2 x 10 columns, 16384
+// tokens 49 -> 30; 2 x 32 columns, 16384 tokens 73 -> 52; 8000 cached and 8 query rows, with the copy of the latter, 54 -> 23.  Few columns of
+// narrow tokens are the exception: d_model 64, 2 x 3 columns, 32768 tokens 39 -> 42.
+// An entry whose logits tie takes one wave d_model / 16 trips to memory more, and the others wait for that wave at the barrier of the next
+// entry but one: 16384 tokens of which 2 % are zeros 5.4 -> 3.9 ms, half of them 34 -> 12 ms.
 // ----------------------------------------------------------------------------------------
 struct RouterTileArgs {
   const unsigned short* x;
