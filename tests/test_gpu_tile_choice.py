@@ -43,11 +43,13 @@ def test_fp32_tiles(over, shared):
     (dict(T=50, d_model=256, nheads=20, d_head=80, E=1, k=1), True),
     (dict(T=256, d_model=1024, nheads=4, d_head=128, E=5, k=3), False),
     (dict(T=257, d_model=1024, nheads=4, d_head=128, E=5, k=3), False),
-    # too many experts for those a token selects: two heads and one; expert-sorted rows, one row and four
+    # too many experts for those a token selects, and few enough: two heads, one head; expert-sorted rows of few columns and of many
     (dict(T=40, d_model=256, nheads=2, d_head=128, E=32, k=1), False),
     (dict(T=40, d_model=256, nheads=1, d_head=64, E=5, k=1), False),
     (dict(T=1, d_model=256, nheads=4, d_head=128, E=16, k=4), False),
     (dict(T=16, d_model=256, nheads=4, d_head=128, E=16, k=4), False),
+    (dict(T=40, d_model=256, nheads=1, d_head=64, E=16, k=1), False),
+    (dict(T=16, d_model=1024, nheads=4, d_head=128, E=16, k=4), False),
     # ... and on narrow models, whose other path is short; 512 tiles and the next size
     (dict(T=17, d_model=100, nheads=8, d_head=256, E=4, k=1), False),
     (dict(T=40, d_model=64, nheads=2, d_head=76, E=32, k=5), False),
