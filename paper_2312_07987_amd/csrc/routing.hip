@@ -294,8 +294,7 @@ void launch_copy_list(const CopyList& l, hipStream_t s) {
 // tokens by those tiles' vector instructions.  Router and sorts, us between events, against four launches (router packed and copied out as columns;
 // logits on 64 x 64 tiles of the row GEMM, 20 of 64 columns used, and a recheck of one entry per wave; histogram; scan and scatter):
 // d_model 1024, 2 x 20 columns, 100 tokens 45 -> 21, 6300 tokens 54 -> 27, 16384 tokens 53 -> 40; d_model 412, 2 x 10 columns, 16384
-// tokens 49 -> 30; 2 x 32 columns, 16384 tokens 73 -> 52; 8000 cached and 8 query rows, with the copy of the latter, 54 -> 23.  Few columns of
-// narrow tokens are the exception: d_model 64, 2 x 3 columns, 32768 tokens 39 -> 42.
+// tokens 49 -> 30; 2 x 32 columns, 16384 tokens 73 -> 52; 8000 cached and 8 query rows, with the copy of the latter, 54 -> 23.
 // An entry whose logits tie takes one wave d_model / 16 trips to memory more, and the others wait for that wave at the barrier of the next
 // entry but one: 16384 tokens of which 2 % are zeros 5.4 -> 3.9 ms, half of them 34 -> 12 ms.
 // ----------------------------------------------------------------------------------------
@@ -429,9 +428,9 @@ __device__ __forceinline__ void recheck_select(const unsigned short* __restrict_
 }
 
 // VEC: bf16 elements of x per load (d_model a multiple of 8 or of 4).  S: K steps of a wave per trip (2: one trip, d_model at most 1024).  P: 8-byte pieces of a K step's
-// router rows per lane (16 * H*E pieces).  CB: blocks of 16 logit columns.
-template <int VEC, int S, int P, int CB>
-__global__ __launch_bounds__(512, 4) void router_tile_kernel(RouterTileArgs a) {
+// router rows per lane (16 * H*E pieces).  CB: blocks of 16 logit columns.  WG: work-groups per CU.
+template <int VEC, int S, int P, int CB, int WG>
+__global__ __launch_bounds__(512, 2 * WG) void router_tile_kernel(RouterTileArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ int bt[32 * 8];            // binom_table
   __shared__ int cn[32], cns[384];      // counts of the tile's tokens per (head, expert) and per (head, set); H*E <= 32, at most 128 sets a head
@@ -1143,7 +1142,16 @@ static void launch_router_tiles(const RouterTileArgs& t, int blocks, hipStream_t
   const size_t ZS = (t.H * t.E) | 1, wl = CB * 64 * 16 * 2, sums = (S * 32 * ZS * 4 + 15) / 16 * 16;
   const size_t first = 8 * (wl > sums ? wl : sums), second = (32 * ZS + 1) / 2 * 2 * 8 + 8 * wl;   // (the logits, then the second stage's router rows)
   const size_t lds = first > second ? first : second;   // at most 43008 bytes (20 columns, two steps), with the static part below 64 KB
-  router_tile_kernel<VEC, S, P, CB><<<blocks + 1, 512, lds, s>>>(t);
+  if constexpr (S == 1 && CB == 1) {
+    // More than two tiles for each CU: three at a time, in 80 registers (six or seven spilled).  Forward calls, us, two / three: d_model 64, 2 x 2
+    // columns, 8192 tokens (512 tiles) 44.3 / 44.4, 10240 49.5 / 47.4, 32768 63.9 / 59.8; d_model 412, 2 x 10 columns, 8192 78.4 /
+    // 78.6, 10240 89.6 / 85.8, 16384 112.4 / 109.9, 32768 177.4 / 170.4.  Two steps a trip lose: d_model 1024, 2 x 10 columns, 32768 277 / 281.
+    if (blocks > 512) {
+      router_tile_kernel<VEC, S, P, CB, 3><<<blocks + 1, 512, lds, s>>>(t);
+      return;
+    }
+  }
+  router_tile_kernel<VEC, S, P, CB, 2><<<blocks + 1, 512, lds, s>>>(t);
 }
 template <int VEC, int S>
 static void launch_router_tiles(const RouterTileArgs& t, int blocks, hipStream_t s) {

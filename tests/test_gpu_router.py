@@ -29,6 +29,9 @@ pytestmark = pytest.mark.gpu
     (dict(T=513, T_q=65, d_model=1024, nheads=4, E=5, k=3), False, True),
     (dict(T=100, T_q=1, d_model=412, nheads=2, E=5, k=3), True, False),
     (dict(B=5, T=8000, d_model=16, nheads=1, E=9, k=4), False, False),
+    (dict(B=3, T=3000, d_model=64, nheads=4, E=4, k=2), False, True),        # more than two tiles for each CU
+    (dict(B=3, T=3000, d_model=20, nheads=4, E=4, k=2), True, False),
+    (dict(B=3, T=2740, T_q=2733, d_model=36, nheads=2, E=5, k=3), False, False),
     (dict(T=100, d_model=4, nheads=3, E=9, k=4), False, True),               # more counts than partial sums of the heads
     (dict(B=3, T=43, d_model=16, nheads=2, E=9, k=4), False, True),          # a table that a block scans, of more than 64 bins
     (dict(B=40, T=104, d_model=16, nheads=3, E=9, k=4), False, True),        # 130 blocks of 126 sets: the last size of those

@@ -80,13 +80,14 @@ def test_ping_pong_gemm_budgets(tmp_path):
 
 
 def test_router_budgets(tmp_path):
-    # two work-groups of eight waves per CU: 128 registers.  Static LDS, and the largest dynamic part of the instances (20
+    # two work-groups of eight waves per CU: 128 registers; or three: 80, with a few spilled outside the products.  Static LDS, and the largest dynamic part of the instances (20
     # columns and two steps), within the 64 KB that a launch gets without asking
     t = kernel_table("routing.hip", tmp_path)
     tiles = [k for k in t if "router_tile_kernel<" in k]
-    assert len(tiles) >= 14
+    assert len(tiles) >= 18
     for k in tiles:
-        assert t[k][0] <= 128 and t[k][1] == 0, (k, t[k])
+        three = ", 3>(" in k
+        assert t[k][0] <= (80 if three else 128) and t[k][1] <= (32 if three else 0), (k, t[k])
     text = open(os.path.join(str(tmp_path), "routing.hip.s")).read()
     static = [int(v) for v in re.findall(r"\.amdhsa_kernel \S*router_tile_kernel\S*\s+\.amdhsa_group_segment_fixed_size (\d+)", text)]
     assert len(static) == len(tiles) and max(static) + 43008 <= 65536, static
