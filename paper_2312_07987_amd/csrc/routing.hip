@@ -1071,17 +1071,20 @@ __global__ __launch_bounds__(256) void scan_kernel(SortArgs a) {
   if (lane == 0) c[0] = run;
 }
 
-// Tables of up to SCAN_MAX counts per (side, head) are scanned by every scatter block for itself, one launch instead of two; what a block
-// reads then grows with the tokens, and all blocks' with their square.  Router and sorts, us, with the line at 2048 / 8192 / 16384 / 32768 counts: bf16,
-// 4 x 28 sets, 8192 tokens 30.4 / 27.1 / 27.2 / 27.2, 26000 58.2 / 58.0 / 57.6 / 63.7, 32768 67 / 67 / 67 / 74; 2 x 10 sets, 16384 35.5 / 31.5 /
-// 31.8 / 31.9, 32768 51.9 / 52.3 / 50.1 / 49.6; fp32, 2 x 16 experts, 32768 39.9 / 40.6 / 35.0 / 35.1.
+// Short tables are scanned by every scatter block for itself, one launch instead of two.  A block takes a trip to memory for 256 counts of
+// 16 bins, one after the other, and all blocks' trips share the caches: both sums have a line.  Router and sorts, us, by every block / scanned first: bf16,
+// 16 to 64 features, two sides, 2 sets, one head, 49152 tokens (6 trips, 768 blocks) 41.7 / 44.2, 65536 (8, 1024) 53.4 / 53.7, 131072 107 / 94; 3 heads, 24576
+// (3, 1152) 29.4 / 30.8, 32768 (4, 1536) 37.8 / 36.8, 131072 172 / 103; 3 x 10 sets, 24576 39.4 / 40.0, 32768 47.0 / 45.8; 3 x 28 sets, 16384 (4, 768)
+// 34.1 / 35.4, 24576 (6, 1152) 47.9 / 46.6; 70 sets, 8192 (5, 128) 24.0 / 24.8, 12288 (10, 192) 27.8 / 26.0; 126 sets, 2048 (8, 32)
+// 28.2 / 26.6; fp32, 2 x 16 experts, 49152 (6, 768) 46.0 / 49.0, 65536 (8, 1024) 59.1 / 59.6; 2 x 64, 8192 (4, 128) 65.6 / 66.2, 16384 (8, 256) 90.4 / 90.7.
 static void launch_sort(const SortArgs& a, hipStream_t s) {
-  constexpr long SCAN_MAX = 16384;
   const int nmax = a.sides > 1 && a.N[1] > a.N[0] ? a.N[1] : a.N[0];
   const int tables = (a.experts ? 1 : 0) + (a.t.setid ? 1 : 0);
   const dim3 g(router_blocks(nmax), a.H, a.sides * tables);
   const long bins = a.t.setid && a.t.nsets > a.E ? a.t.nsets : a.E;
-  if (a.ncb[0] * bins <= SCAN_MAX) {
+  const int ncb = a.sides > 1 && a.ncb[1] > a.ncb[0] ? a.ncb[1] : a.ncb[0];
+  const long trips = (bins + 15) / 16 * ((ncb + 255) / 256), blocks = (long)g.x * g.y * g.z;
+  if (trips <= 7 && trips * blocks <= 5500) {
     scan_scatter_kernel<<<g, RB, 0, s>>>(a);
     return;
   }

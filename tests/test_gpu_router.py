@@ -33,9 +33,13 @@ pytestmark = pytest.mark.gpu
     (dict(B=3, T=3000, d_model=20, nheads=4, E=4, k=2), True, False),
     (dict(B=3, T=2740, T_q=2733, d_model=36, nheads=2, E=5, k=3), False, False),
     (dict(T=100, d_model=4, nheads=3, E=9, k=4), False, True),               # more counts than partial sums of the heads
-    (dict(B=3, T=43, d_model=16, nheads=2, E=9, k=4), False, True),          # a table that a block scans, of more than 64 bins
-    (dict(B=40, T=104, d_model=16, nheads=3, E=9, k=4), False, True),        # 130 blocks of 126 sets: the last size of those
-    (dict(B=41, T=102, d_model=16, nheads=3, E=9, k=4), True, False),        # and the next
+    (dict(B=3, T=43, d_model=16, nheads=2, E=9, k=4), False, True),          # short tables of 126 sets: summed in a launch of their own
+    (dict(B=40, T=104, d_model=16, nheads=3, E=9, k=4), False, True),
+    (dict(B=41, T=102, d_model=16, nheads=3, E=9, k=4), True, False),
+    (dict(B=64, T=128, d_model=16, nheads=1, E=8, k=4), False, True),        # 256 blocks of 70 sets: the last size that a block scans
+    (dict(B=11, T=745, d_model=16, nheads=1, E=8, k=4), True, False),        # and the next, 257
+    (dict(B=9, T=3072, d_model=16, nheads=3, E=2, k=1), False, True),        # four trips of 1296 blocks: scanned by every one
+    (dict(B=10, T=2940, d_model=16, nheads=3, E=2, k=1), False, True),       # ... of 1380: not
 ])
 def test_routing_tables(over, shared, ties):
     from paper_2312_07987_amd.runner import DeviceLayer
